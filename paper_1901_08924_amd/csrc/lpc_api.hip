@@ -372,7 +372,7 @@ lpc_status exchange_and_prox(lpc_ctx *c, StreamKey key, float *w, bool want_clip
   if (c->quant && c->cfg.scheme != LPC_SCHEME_A) {
     // schemes (b), (c): delta = max_i delta_i for every worker, integer sum at the receiver
     LPC_TRY_HIP(launch_share_delta(c, c->cfg.N, nullptr, st));
-    LPC_TRY_HIP(launch_quantize(c, s.U, key, s.packed, s.delta, s.n_clipped, st));
+    LPC_TRY_HIP(launch_quantize(c, s.U, key, s.packed, s.delta, want_clip_counts ? s.n_clipped : nullptr, st));
     LPC_TRY_HIP(launch_dequantize_shared(c, s.packed, s.delta, c->cfg.scheme == LPC_SCHEME_C, key, s.u_avg, st));
     LPC_TRY_HIP(launch_prox(c, w, s.u_avg, s.mu, c->cfg.eta, st));
   } else if (c->quant) {
@@ -572,12 +572,13 @@ lpc_status lpc_exchange(lpc_ctx *ctx, const float *U, uint32_t epoch, uint32_t i
   const StreamKey key = key_of(ctx, epoch, iter);
   if (fused_exchange_supported(ctx)) {
     int32_t slots = 0;
-    LPC_TRY_HIP(launch_vector_stats(ctx, U, ctx->d_pad, 0, ctx->cfg.N, nullptr, kStatsPartial, &slots, st));
+    if (!own_statistics(ctx))
+      LPC_TRY_HIP(launch_vector_stats(ctx, U, ctx->d_pad, 0, ctx->cfg.N, nullptr, kStatsPartial, &slots, st));
     LPC_TRY_HIP(launch_fused_exchange(ctx, U, slots, key, packed, delta_out, nullptr, 0.0f, nullptr, u_avg, st));
     return LPC_OK;
   }
   LPC_TRY_HIP(launch_vector_stats(ctx, U, ctx->d_pad, 0, ctx->cfg.N, nullptr, kStatsFinal, nullptr, st));
-  LPC_TRY_HIP(launch_quantize(ctx, U, key, packed, delta_out, ctx->s.n_clipped, st));
+  LPC_TRY_HIP(launch_quantize(ctx, U, key, packed, delta_out, nullptr, st));  // nobody reads the clip counts
   LPC_TRY_HIP(launch_dequantize_avg(ctx, packed, delta_out, u_avg, st));
   return LPC_OK;
 }
@@ -656,12 +657,12 @@ lpc_status lpc_exchange_static(int64_t d, int32_t N, int32_t bits, int32_t clip_
   const StreamKey key = key_of(&c, epoch, iter);
   if (fused_exchange_supported(&c)) {
     int32_t slots = 0;
-    LPC_TRY_HIP(launch_vector_stats(&c, U, c.d_pad, 0, N, nullptr, kStatsPartial, &slots, st));
+    if (!own_statistics(&c)) LPC_TRY_HIP(launch_vector_stats(&c, U, c.d_pad, 0, N, nullptr, kStatsPartial, &slots, st));
     LPC_TRY_HIP(launch_fused_exchange(&c, U, slots, key, packed, delta_out, nullptr, 0.0f, nullptr, u_avg, st));
     return LPC_OK;
   }
   LPC_TRY_HIP(launch_vector_stats(&c, U, c.d_pad, 0, N, nullptr, kStatsFinal, nullptr, st));
-  LPC_TRY_HIP(launch_quantize(&c, U, key, packed, delta_out, s.n_clipped, st));
+  LPC_TRY_HIP(launch_quantize(&c, U, key, packed, delta_out, nullptr, st));
   LPC_TRY_HIP(launch_dequantize_avg(&c, packed, delta_out, u_avg, st));
   return LPC_OK;
 }
@@ -945,10 +946,10 @@ lpc_status lpc_epoch(lpc_ctx *ctx, float *w_snap, float *y, float *z, uint32_t e
       ProfScope ps(c, LPC_PROF_EXCHANGE, st);
       if (c->quant && g.scheme != LPC_SCHEME_A) {
         LPC_TRY_HIP(launch_share_delta(c, g.N, nullptr, st));
-        LPC_TRY_HIP(launch_quantize(c, s.U, key, s.packed, s.delta, s.n_clipped, st));
+        LPC_TRY_HIP(launch_quantize(c, s.U, key, s.packed, s.delta, tracing ? s.n_clipped : nullptr, st));
         LPC_TRY_HIP(launch_dequantize_shared(c, s.packed, s.delta, g.scheme == LPC_SCHEME_C, key, s.u_avg, st));
       } else if (c->quant) {
-        LPC_TRY_HIP(launch_quantize(c, s.U, key, s.packed, s.delta, s.n_clipped, st));
+        LPC_TRY_HIP(launch_quantize(c, s.U, key, s.packed, s.delta, tracing ? s.n_clipped : nullptr, st));
         LPC_TRY_HIP(launch_dequantize_avg(c, s.packed, s.delta, s.u_avg, st));
       } else {
         LPC_TRY_HIP(launch_plain_avg(c, s.U, s.u_avg, st));

@@ -321,6 +321,7 @@ bool fused_iter_supported(const lpc_ctx *c);
 int64_t fused_iter_slot_words(const lpc_ctx *c);
 hipError_t launch_fused_iter_reset(const lpc_ctx *c, hipStream_t st);
 hipError_t launch_fused_iter(const lpc_ctx *c, StreamKey key, uint32_t *packed, float *delta_out, const float *mu,
+bool own_statistics(const lpc_ctx *c);  // launch_fused_exchange without statistic partials (nslots = 0)
                              float step, float *w, const AlpcStep *al, hipStream_t st);
 hipError_t launch_fused_exchange(const lpc_ctx *c, const float *U, int32_t nslots, StreamKey key, uint32_t *packed,
                                  float *delta_out, const float *mu, float step, float *w, float *u_avg_out,

@@ -1078,6 +1078,7 @@ constexpr int kFusedCoords = 128;
 // iterations/s on the d = 4096, N = 8 workload and -1.9 % on d = 8192, N = 16; 1024 threads -3.3 % and -1.0 %
 constexpr int kFusedThreads = 512;
 constexpr int kFusedMaxN = 64;
+constexpr int64_t kOwnChunks = 8;  // see own_statistics()
 
 struct FusedArgs {
   const float *U;
@@ -1173,6 +1174,45 @@ __device__ __forceinline__ void warm_next_rows(const FusedArgs &a, int ntiles) {
   if (sink == -1.2345678e-38f) *a.warm_sink = sink;
 }
 
+// Statistics of one vector by one wavefront, with the bits that vector_stats_kernel and the fold of its partials give:
+// 1024-coordinate chunks (at most 64), lane l standing for threads l, l+64, l+128, l+192 of the chunk's workgroup, whose
+// four wavefronts are added in order; lane k keeps chunk k, and the butterflies over the lanes are the fold.
+__device__ __forceinline__ void vector_statistics(const float *__restrict__ u, int64_t d, int lane, double &am,
+                                                  double &s, double &s2, double &b) {
+  am = 0.0; s = 0.0; s2 = 0.0; b = 0.0;
+  for (int32_t k = 0; (int64_t)k * 1024 < d; ++k) {
+    const float *uc = u + (int64_t)k * 1024;
+    const int32_t len = d - (int64_t)k * 1024 < 1024 ? (int32_t)(d - (int64_t)k * 1024) : 1024, n4 = len / 4;
+    float4 t[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      t[q] = lane + 64 * q < n4 ? *reinterpret_cast<const float4 *>(uc + 4 * (lane + 64 * q))
+                                : make_float4(0.f, 0.f, 0.f, 0.f);
+    const float last = lane < len - 4 * n4 ? uc[4 * n4 + lane] : 0.0f;
+    double c_am = 0.0, c_s = 0.0, c_s2 = 0.0, c_b = 0.0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      double sum = 0.0, sumsq = 0.0;
+      float fmx = 0.0f;
+      uint32_t nbad = 0;
+      auto take = [&](float x) {
+        const bool fin = isfinite(x);
+        const float y = fin ? x : 0.0f;
+        nbad += fin ? 0u : 1u;
+        fmx = fmaxf(fmx, fabsf(y)); sum += (double)y; sumsq += (double)y * (double)y;
+      };
+      take(t[q].x); take(t[q].y); take(t[q].z); take(t[q].w);
+      if (q == 0) take(last);
+      c_am = fmax(c_am, (double)wave_max(fmx)); c_s += wave_sum(sum); c_s2 += wave_sum(sumsq);
+      c_b += (double)wave_sum(nbad);
+    }
+    if (lane == k) { am = c_am; s = c_s; s2 = c_s2; b = c_b; }
+  }
+}
+
+// OWN: the statistics are taken here, by every workgroup from all of U, instead of read as partials that an earlier
+// launch left (where U is so small that this is less than a launch: see own_statistics()).
+template <bool OWN>
 __global__ __launch_bounds__(kFusedThreads) void fused_exchange_kernel(FusedArgs a) {
   touch_kernel_arguments<(int)(sizeof(FusedArgs))>();
   constexpr int GROUPS = kFusedThreads / 32, NW = kFusedThreads / 64;  // 32-lane groups (a worker each per round), wavefronts
@@ -1220,7 +1260,13 @@ __global__ __launch_bounds__(kFusedThreads) void fused_exchange_kernel(FusedArgs
     double am[4], s[4], s2[4], b[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) { am[q] = 0.0; s[q] = 0.0; s2[q] = 0.0; b[q] = 0.0; }
-    for (int32_t k = lane; k < a.nslots; k += 64) {
+    if constexpr (OWN) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (i0 + NW * q < a.N)
+          vector_statistics(a.U + (int64_t)(i0 + NW * q) * a.d_pad, a.d, lane, am[q], s[q], s2[q], b[q]);
+    }
+    for (int32_t k = lane; !OWN && k < a.nslots; k += 64) {
       double2 lo[4], hi[4];
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
@@ -2180,7 +2226,8 @@ hipError_t launch_fused_exchange(const lpc_ctx *c, const float *U, int32_t nslot
   prox_consts(c, step > 0.0f ? step : 1.0f, &a.thr, &a.shrink);
   const int extra = w != nullptr ? warm_setup(c, key, false, &a) : 0;
   const dim3 grid((unsigned)((c->d_pad + kFusedCoords - 1) / kFusedCoords + extra));
-  LPC_LAUNCH_TIMED(fused_exchange_kernel, grid, dim3(kFusedThreads), st, a);
+  if (nslots == 0) LPC_LAUNCH_TIMED(fused_exchange_kernel<true>, grid, dim3(kFusedThreads), st, a);
+  else LPC_LAUNCH_TIMED(fused_exchange_kernel<false>, grid, dim3(kFusedThreads), st, a);
   return hipGetLastError();
 }
 
@@ -2189,6 +2236,12 @@ hipError_t launch_fused_exchange_alpc(const lpc_ctx *c, const float *U, int32_t 
   FusedArgs a{};
   a.U = U; a.d = c->d; a.d_pad = c->d_pad; a.W = c->W;
   a.N = c->cfg.N; a.bits = c->cfg.bits; a.nslots = nslots; a.stat_slots = c->stat_slots;
+// Whether the exchange of vectors that no launch has taken statistics of takes them itself (nslots = 0 above).  Every
+// workgroup then reads all N vectors, one 1024-coordinate chunk per wavefront and step, and the launch of
+// vector_stats_kernel is saved: calls back to back 9.8 -> 7.7 us with up to eight chunks (one step: N = 8, d = 1024),
+// 9.8 -> 9.5 / 10.4 us with sixteen, 9.8 -> 11.0 us with 32.
+bool own_statistics(const lpc_ctx *c) { return (int64_t)c->cfg.N * ((c->d + 1023) / 1024) <= kOwnChunks; }
+
   a.stat_part = c->s.stat_part; a.qs = spec_of(c); a.key = key;
   a.packed = packed; a.delta_out = delta_out; a.stats = c->s.stats; a.flags = c->s.flags;
   a.mu = al.mu; a.do_alpc = 1;
@@ -2200,7 +2253,7 @@ hipError_t launch_fused_exchange_alpc(const lpc_ctx *c, const float *U, int32_t 
   prox_consts(c, al.alpha, &a.thr_z, &a.shrink_z);
   const int extra = warm_setup(c, key, true, &a);
   const dim3 grid((unsigned)((c->d_pad + kFusedCoords - 1) / kFusedCoords + extra));
-  LPC_LAUNCH_TIMED(fused_exchange_kernel, grid, dim3(kFusedThreads), st, a);
+  LPC_LAUNCH_TIMED(fused_exchange_kernel<false>, grid, dim3(kFusedThreads), st, a);
   return hipGetLastError();
 }
 
@@ -2246,7 +2299,7 @@ hipError_t launch_cols_exchange(const lpc_ctx *c, const float *U, StreamKey key,
   } else {
     a.dots.rows_per_wg = 0; a.dots.nvec = 0; a.dots.B = 1; a.dots.C = tiles;
   }
-  LPC_LAUNCH_TIMED(fused_exchange_kernel, dim3((unsigned)(tiles * a.dots_R)), dim3(kFusedThreads), st, a);
+  LPC_LAUNCH_TIMED(fused_exchange_kernel<false>, dim3((unsigned)(tiles * a.dots_R)), dim3(kFusedThreads), st, a);
   return hipGetLastError();
 }
 
