@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cmath>
+#include <condition_variable>
 #include <cstring>
 #include <mutex>
 #include <new>
@@ -54,6 +55,61 @@ struct ProfScope {
   }
 };
 
+// A few words of host memory that a kernel writes and the host polls: a result that a call returns needs no copy from
+// the device (a launch of its own and a staging buffer) and no wait for the stream, whose notice of the end takes longer
+// than the word.  One page for the process, allocated at the first use and kept; a call holds one slot while it runs,
+// and waits for one if 64 calls of other threads hold them all.
+class HostSlot {
+  static constexpr int kSlots = 64, kWords = kHostSlotWords;
+  static std::mutex &mu() { static std::mutex m; return m; }
+  static std::condition_variable &freed() { static std::condition_variable v; return v; }
+  static unsigned long long *page, used;
+  int slot = -1;
+
+ public:
+  HostSlot() {
+    std::unique_lock<std::mutex> lock(mu());
+    if (!page) {
+      void *p = nullptr;
+      if (hipHostMalloc(&p, kSlots * kWords * sizeof(*page), hipHostMallocPortable | hipHostMallocMapped) != hipSuccess)
+        return;
+      page = static_cast<unsigned long long *>(p);
+    }
+    freed().wait(lock, [] { return used != ~0ull; });
+    slot = __builtin_ctzll(~used);
+    used |= 1ull << slot;
+    __atomic_store_n(words() + kWords - 1, 0ull, __ATOMIC_RELAXED);
+  }
+  // until the kernel that was given words() has handed them over; asks the stream now and then, so that a launch that
+  // failed ends the wait
+  hipError_t wait(hipStream_t st) const {
+    unsigned long long *flag = words() + kWords - 1;
+    for (uint32_t k = 1;; ++k) {
+      if (__atomic_load_n(flag, __ATOMIC_ACQUIRE)) return hipSuccess;
+      if (k % 4096 == 0) {
+        const hipError_t e = hipStreamQuery(st);
+        if (e == hipSuccess) return __atomic_load_n(flag, __ATOMIC_ACQUIRE) ? hipSuccess : hipErrorUnknown;
+        if (e != hipErrorNotReady) return e;
+      }
+#if defined(__x86_64__)
+      __builtin_ia32_pause();
+#endif
+    }
+  }
+  ~HostSlot() {
+    if (slot < 0) return;
+    {
+      std::lock_guard<std::mutex> lock(mu());
+      used &= ~(1ull << slot);
+    }
+    freed().notify_one();
+  }
+  HostSlot(const HostSlot &) = delete;
+  HostSlot &operator=(const HostSlot &) = delete;
+  unsigned long long *words() const { return slot < 0 ? nullptr : page + slot * kWords; }
+};
+unsigned long long *HostSlot::page = nullptr, HostSlot::used = 0;
+
 // Computes sizes; when base != nullptr also assigns the scratch pointers.
 size_t layout(lpc_ctx *c, char *base) {
   size_t off = 0;
@@ -83,11 +139,9 @@ size_t layout(lpc_ctx *c, char *base) {
   s.f_scalar = (double *)take(sizeof(double));
   s.clip_total = (unsigned long long *)take(sizeof(unsigned long long));
   {
-    const size_t syms = c->quant ? (size_t)1 << c->cfg.bits : 1, segs = (size_t)(c->d_pad / 32);
+    const size_t syms = c->quant ? (size_t)1 << c->cfg.bits : 1;
     s.huff_table = (HuffEntry *)take(syms * sizeof(HuffEntry));
-    s.huff_seg_bits = (uint32_t *)take((c->quant ? segs : 1) * sizeof(uint32_t));
-    s.huff_off = (unsigned long long *)take((c->quant ? segs : 1) * sizeof(unsigned long long));
-    s.huff_meta = (unsigned long long *)take(2 * sizeof(unsigned long long));
+    s.huff_wg_bits = (uint32_t *)take((c->quant ? (size_t)huffman_wgs(c->d) : 1) * sizeof(uint32_t));
   }
   s.csr_tail = (float *)take((c->csr ? (size_t)c->d_pad : 4) * sizeof(float));
   s.csc_ptr = (int32_t *)take((c->csr ? (size_t)c->d + 4 : 4) * sizeof(int32_t));
@@ -229,8 +283,9 @@ StreamKey key_of(const lpc_ctx *c, uint32_t epoch, uint32_t iter) {
   } while (0)
 
 // Alg. 1 step 4 into (mu, z), all on `st`
+// (parts_only: the loss stays as the pass's partials in part_loss, for a caller that folds them itself)
 lpc_status full_grad_impl(lpc_ctx *c, const float *w, float *mu, float *z, double *f_out, int64_t n_rows,
-                          hipStream_t st) {
+                          hipStream_t st, bool parts_only = false) {
   if (!c->grad_ok) return LPC_EUNSUPPORTED;
   hipError_t e;
   {
@@ -240,11 +295,12 @@ lpc_status full_grad_impl(lpc_ctx *c, const float *w, float *mu, float *z, doubl
                : launch_dense_full_grad(c, w, z, f_out != nullptr, n_rows, st);
   }
   if (e != hipSuccess) return LPC_EDEVICE;
+  if (parts_only && !mu) return LPC_OK;
   ProfScope ps(c, LPC_PROF_FULL_FOLD, st);
   // dense: every column comes from the fold; CSR: the privatised head columns do
   const int64_t cols = c->csr ? csr_head_columns(c->d) : c->d;
   e = launch_finish_full_grad(c, c->full_grad_wgs, cols, (float)(1.0 / (double)n_rows), mu, f_out,
-                              f_out != nullptr, st);
+                              f_out != nullptr && !parts_only, st);
   return dev(e);
 }
 
@@ -1044,10 +1100,16 @@ lpc_status lpc_clip_sweep(lpc_ctx *ctx, const float *w0, int32_t n_clip, const f
 lpc_status lpc_objective(lpc_ctx *ctx, const float *w, double *P_out_host, void *stream) {
   if (!ctx || !w || !P_out_host) return LPC_ENULL;
   hipStream_t st = as_stream(stream);
-  LPC_TRY(full_grad_impl(ctx, w, nullptr, nullptr, ctx->s.f_scalar, ctx->n, st));
-  LPC_TRY_HIP(launch_objective_reg(ctx, w, ctx->s.f_scalar, st));
-  LPC_TRY_HIP(hipMemcpyAsync(P_out_host, ctx->s.f_scalar, sizeof(double), hipMemcpyDeviceToHost, st));
-  LPC_TRY_HIP(hipStreamSynchronize(st));
+  HostSlot out;
+  if (!out.words()) return LPC_EDEVICE;
+  // linear models leave one loss partial per workgroup of the pass, the perceptron its loss as one number
+  LPC_TRY(full_grad_impl(ctx, w, nullptr, nullptr, ctx->s.f_scalar, ctx->n, st, !ctx->mlp));
+  LPC_TRY_HIP(launch_objective_reg(ctx, w, st));
+  LPC_TRY_HIP(launch_fold_result(ctx, result_groups(ctx), ctx->s.part_loss, ctx->mlp ? 0 : ctx->full_grad_wgs,
+                                 (double)(float)(1.0 / (double)ctx->n), ctx->s.f_scalar,
+                                 reinterpret_cast<double *>(out.words()), st));
+  LPC_TRY_HIP(out.wait(st));
+  std::memcpy(P_out_host, out.words(), sizeof(double));
   return LPC_OK;
 }
 
@@ -1055,11 +1117,15 @@ lpc_status lpc_gradient_mapping(lpc_ctx *ctx, const float *w, float eta, double 
   if (!ctx || !w || !gm2_out_host) return LPC_ENULL;
   if (!(eta > 0.0f)) return LPC_EINVAL;
   hipStream_t st = as_stream(stream);
+  HostSlot out;
+  if (!out.words()) return LPC_EDEVICE;
   float *grad = ctx->s.u_avg;   // free outside an epoch
   LPC_TRY(full_grad_impl(ctx, w, grad, nullptr, nullptr, ctx->n, st));
-  LPC_TRY_HIP(launch_gradient_mapping(ctx, w, grad, (double)eta, ctx->s.f_scalar, st));
-  LPC_TRY_HIP(hipMemcpyAsync(gm2_out_host, ctx->s.f_scalar, sizeof(double), hipMemcpyDeviceToHost, st));
-  LPC_TRY_HIP(hipStreamSynchronize(st));
+  LPC_TRY_HIP(launch_gradient_mapping(ctx, w, grad, (double)eta, st));
+  LPC_TRY_HIP(launch_fold_result(ctx, result_groups(ctx), nullptr, 0, 0.0, nullptr,
+                                 reinterpret_cast<double *>(out.words()), st));
+  LPC_TRY_HIP(out.wait(st));
+  std::memcpy(gm2_out_host, out.words(), sizeof(double));
   return LPC_OK;
 }
 
@@ -1078,19 +1144,16 @@ lpc_status lpc_huffman_encode(lpc_ctx *ctx, const uint32_t *packed, const int32_
   const int32_t nsym = 1 << ctx->cfg.bits;
   std::vector<HuffEntry> table((size_t)nsym);
   if (huffman_canonical_table(lens_host, nsym, table.data()) != 0) return LPC_EINVAL;
-  LPC_TRY_HIP(hipMemcpyAsync(ctx->s.huff_table, table.data(), sizeof(HuffEntry) * (size_t)nsym, hipMemcpyHostToDevice,
-                             st));
-  LPC_TRY_HIP(launch_huffman_measure(ctx, packed, st));
-  unsigned long long meta[2] = {0, 0};
-  LPC_TRY_HIP(hipMemcpyAsync(meta, ctx->s.huff_meta, sizeof(meta), hipMemcpyDeviceToHost, st));
-  LPC_TRY_HIP(hipStreamSynchronize(st));  // also: the table has left the host vector
-  if (meta[1]) return LPC_EINVAL;         // a coordinate whose symbol has no codeword
-  *total_bits_out_host = meta[0];
-  const int64_t need = (int64_t)((meta[0] + 31) / 32);
-  if (need > capacity_words) return LPC_ESHAPE;
-  if (need == 0) return LPC_OK;
-  LPC_TRY_HIP(launch_huffman_emit(ctx, packed, out_words, need, st));
-  return LPC_OK;
+  if (nsym > 256)  // shorter tables travel in the kernels' arguments
+    LPC_TRY_HIP(hipMemcpyAsync(ctx->s.huff_table, table.data(), sizeof(HuffEntry) * (size_t)nsym,
+                               hipMemcpyHostToDevice, st));
+  HostSlot meta;
+  if (!meta.words()) return LPC_EDEVICE;
+  LPC_TRY_HIP(launch_huffman(ctx, packed, table.data(), ctx->s.huff_table, out_words, capacity_words, meta.words(), st));
+  LPC_TRY_HIP(meta.wait(st));  // also: the table has left the host vector
+  if (meta.words()[1]) return LPC_EINVAL;  // a coordinate whose symbol has no codeword
+  *total_bits_out_host = meta.words()[0];
+  return (int64_t)((meta.words()[0] + 31) / 32) > capacity_words ? LPC_ESHAPE : LPC_OK;
 }
 
 lpc_status lpc_take_device_flags(lpc_ctx *ctx, void *stream) {

@@ -64,6 +64,15 @@ __device__ __forceinline__ void touch_kernel_arguments() {
   asm volatile("" ::"s"(seen));
 }
 
+// The last word of a host slot (lpc_api.hip) is set once the words before it are in host memory: the host, which polls
+// it, may go on although the launch has not ended.
+template <class T>
+__device__ __forceinline__ void hand_over(T *slot) {
+  static_assert(sizeof(T) == 8, "slots are arrays of 64-bit words");
+  __hip_atomic_store(reinterpret_cast<unsigned long long *>(slot) + kHostSlotWords - 1, 1ull, __ATOMIC_RELEASE,
+                     __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // ---- wavefront (64 lanes) reductions: every lane ends with the same bits ----
 // Lanes exchange values with data-parallel-primitive moves inside their row of 16 (no trip through the
 // LDS crossbar): after xor-1, xor-2, half-mirror and mirror steps every lane of a row holds the row's

@@ -18,21 +18,34 @@ namespace lpc {
 
 namespace {
 
-// |G_eta(w)|^2 with G_eta(w) = (w - prox_{eta h}(w - eta*grad))/eta, one workgroup, fixed summation order.
+// partial[g] = workgroup g's share of |G_eta(w)|^2, G_eta(w) = (w - prox_{eta h}(w - eta*grad))/eta: coordinates
+// g*1024 + tid, then in steps of 1024*gridDim.x, four in flight per thread; fp64, fixed order.  (One workgroup for
+// all of d took 58 us on 150,001 coordinates, its threads walking 147 coordinates and fp64 divisions one by one.)
 __global__ __launch_bounds__(1024) void gradient_mapping_kernel(const float *__restrict__ w,
                                                                 const float *__restrict__ grad, int64_t d, double eta,
-                                                                double l1, double l2, double *__restrict__ out) {
+                                                                double l1, double l2, double *__restrict__ partial) {
   __shared__ double red[16];
   const int tid = threadIdx.x;
-  const double thr = eta * l1, shrink = 1.0 / (1.0 + eta * l2);
+  const int64_t stride = (int64_t)gridDim.x * 1024;
+  const double thr = eta * l1, shrink = 1.0 / (1.0 + eta * l2), inv = 1.0 / eta;
   double a = 0.0;
-  for (int64_t j = tid; j < d; j += 1024) {
-    const double x = (double)w[j];
-    const double p = x - eta * (double)grad[j];
-    const double mag = fabs(p) - thr;
-    const double px = mag > 0.0 ? copysign(mag, p) * shrink : 0.0;
-    const double g = (x - px) / eta;
-    a += g * g;
+  for (int64_t j = (int64_t)blockIdx.x * 1024 + tid; j < d; j += 4 * stride) {
+    float wv[4], gv[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const bool in = j + q * stride < d;
+      wv[q] = in ? w[j + q * stride] : 0.0f;
+      gv[q] = in ? grad[j + q * stride] : 0.0f;  // zeros map to zero
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const double x = (double)wv[q];
+      const double p = x - eta * (double)gv[q];
+      const double mag = fabs(p) - thr;
+      const double px = mag > 0.0 ? copysign(mag, p) * shrink : 0.0;
+      const double g = (x - px) * inv;
+      a += g * g;
+    }
   }
   a = wave_sum(a);
   if ((tid & 63) == 0) red[tid >> 6] = a;
@@ -40,7 +53,7 @@ __global__ __launch_bounds__(1024) void gradient_mapping_kernel(const float *__r
   if (tid == 0) {
     double t = 0.0;
     for (int k = 0; k < 16; ++k) t += red[k];
-    *out = t;
+    partial[blockIdx.x] = t;
   }
 }
 
@@ -57,161 +70,271 @@ __global__ void zero_u64_kernel(unsigned long long *__restrict__ dst, int64_t n)
   if (i < n) dst[i] = 0ull;
 }
 
-// counts[code + 2^(b-1)] += 1 for the first d coordinates of one packed message.  A thread takes one
-// 32-coordinate segment (b words).  Up to kLdsBins bins are privatised per workgroup.
+// The B words of one 32-coordinate segment and its symbols (bin index = code + 2^(B-1)).  B is a template parameter so
+// that a field's word and shift are constants and the words stay in registers.
+template <int B>
+struct Segment {
+  uint32_t w[B];
+  __device__ __forceinline__ void load(const uint32_t *__restrict__ seg) {
+    if constexpr (B % 4 == 0) {
+#pragma unroll
+      for (int i = 0; i < B; i += 4) {
+        const uint4 t = *reinterpret_cast<const uint4 *>(seg + i);
+        w[i] = t.x; w[i + 1] = t.y; w[i + 2] = t.z; w[i + 3] = t.w;
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < B; ++i) w[i] = seg[i];
+    }
+  }
+  template <int J>
+  __device__ __forceinline__ uint32_t symbol() const {
+    constexpr int off = J * B, wi = off >> 5, sh = off & 31;
+    constexpr uint32_t mask = (1u << B) - 1u, bias = 1u << (B - 1);
+    uint32_t f = w[wi] >> sh;
+    if constexpr (sh + B > 32) f |= w[wi + 1] << (32 - sh);
+    // two's complement field -> bin index: adding 2^(B-1) modulo 2^B maps -2^(B-1).. to 0..
+    return ((f & mask) + bias) & mask;
+  }
+};
+// f(symbol) for the first cnt (of 32) coordinates of a segment, in order; whole segments without a check per coordinate
+template <int B, bool WHOLE, int J, class F>
+__device__ __forceinline__ void for_symbols_from(const Segment<B> &s, int cnt, F &f) {
+  if constexpr (J < 32) {
+    if (WHOLE || J < cnt) f(s.template symbol<J>());
+    for_symbols_from<B, WHOLE, J + 1>(s, cnt, f);
+  }
+}
+template <int B, class F>
+__device__ __forceinline__ void for_symbols(const Segment<B> &s, int cnt, F f) {
+  if (cnt == 32) for_symbols_from<B, true, 0>(s, cnt, f);
+  else for_symbols_from<B, false, 0>(s, cnt, f);
+}
+
+// counts[symbol] += 1 for the first d coordinates of one packed message, one 32-coordinate segment per thread and step.
+// Up to 8192 bins are counted in LDS.  The codes of a message are close to normal: with 16 bins most of a wavefront
+// asks for the same few counters, and additions to one LDS address are taken one after the other.  Up to 256 bins
+// (B <= 8) therefore have 32 copies, one per LDS bank: lane l uses copy l % 32 of its bin, so a wavefront's additions
+// hit distinct banks.  4.2 M coordinates, B = 4: 13.7 us with one copy, 6.2 us with 32.
+constexpr int kHistCopies = 32;
 constexpr int kLdsBins = 8192;
 
-__global__ __launch_bounds__(256) void code_histogram_kernel(const uint32_t *__restrict__ words, int64_t d, int32_t b,
+template <int B>
+__global__ __launch_bounds__(256) void code_histogram_kernel(const uint32_t *__restrict__ words, int64_t d,
                                                              unsigned long long *__restrict__ counts) {
-  __shared__ uint32_t bins[kLdsBins];
-  const int nbins = 1 << b;
-  const bool priv = nbins <= kLdsBins;
-  if (priv) {
-    for (int k = threadIdx.x; k < nbins; k += 256) bins[k] = 0u;
+  constexpr int kBins = 1 << B;
+  constexpr bool kCopied = kBins * kHistCopies <= kLdsBins, kLds = kBins <= kLdsBins;
+  constexpr int kSize = kCopied ? kBins * kHistCopies : (kLds ? kBins : 1);
+  __shared__ uint32_t bins[kSize];
+  const int tid = threadIdx.x;
+  if constexpr (kLds) {
+    for (int k = tid; k < kSize; k += 256) bins[k] = 0u;
     __syncthreads();
   }
   const int64_t segs = (d + 31) / 32;
-  const uint32_t mask = (1u << b) - 1u, bias = 1u << (b - 1);
-  for (int64_t s = (int64_t)blockIdx.x * 256 + threadIdx.x; s < segs; s += (int64_t)gridDim.x * 256) {
-    const uint32_t *seg = words + s * b;
+  for (int64_t s = (int64_t)blockIdx.x * 256 + tid; s < segs; s += (int64_t)gridDim.x * 256) {
+    Segment<B> seg;
+    seg.load(words + s * B);
     const int64_t left = d - s * 32;
-    const int cnt = left < 32 ? (int)left : 32;
-    for (int j = 0; j < cnt; ++j) {
-      const int off = j * b, wi = off >> 5, sh = off & 31;
-      uint32_t f = seg[wi] >> sh;
-      if (sh + b > 32) f |= seg[wi + 1] << (32 - sh);   // wi+1 < b here: the last field ends at bit 32*b
-      // two's complement field -> bin index: adding 2^(b-1) modulo 2^b maps -2^(b-1).. to 0..
-      const uint32_t bin = ((f & mask) + bias) & mask;
-      if (priv) atomicAdd(&bins[bin], 1u);
+    for_symbols<B>(seg, left < 32 ? (int)left : 32, [&](uint32_t bin) {
+      if constexpr (kCopied) atomicAdd(&bins[bin * kHistCopies + (tid & (kHistCopies - 1))], 1u);
+      else if constexpr (kLds) atomicAdd(&bins[bin], 1u);
       else atomicAdd(&counts[bin], 1ull);
-    }
+    });
   }
-  if (priv) {
+  if constexpr (kLds) {
     __syncthreads();
-    for (int k = threadIdx.x; k < nbins; k += 256)
-      if (bins[k]) atomicAdd(&counts[k], (unsigned long long)bins[k]);
+    for (int k = tid; k < kBins; k += 256) {
+      uint32_t t = 0u;
+      if constexpr (kCopied) {
+        for (int r = 0; r < kHistCopies; ++r) t += bins[k * kHistCopies + ((r + k) & (kHistCopies - 1))];
+      } else {
+        t = bins[k];
+      }
+      if (t) atomicAdd(&counts[k], (unsigned long long)t);
+    }
   }
 }
 
 }  // namespace
 
-hipError_t launch_gradient_mapping(const lpc_ctx *c, const float *w, const float *grad, double eta, double *out,
-                                   hipStream_t st) {
-  hipLaunchKernelGGL(gradient_mapping_kernel, dim3(1), dim3(1024), 0, st, w, grad, c->d, eta,
-                     (double)c->prob.lambda1, (double)c->prob.lambda2, out);
+hipError_t launch_gradient_mapping(const lpc_ctx *c, const float *w, const float *grad, double eta, hipStream_t st) {
+  hipLaunchKernelGGL(gradient_mapping_kernel, dim3((unsigned)result_groups(c)), dim3(1024), 0, st, w, grad, c->d, eta,
+                     (double)c->prob.lambda1, (double)c->prob.lambda2, c->s.stat_part);
   return hipGetLastError();
 }
 
 namespace {
 
-// symbol (bin index) of coordinate j of a 32-coordinate segment
-__device__ __forceinline__ uint32_t segment_symbol(const uint32_t *seg, int j, int b, uint32_t mask, uint32_t bias) {
-  const int off = j * b, wi = off >> 5, sh = off & 31;
-  uint32_t f = seg[wi] >> sh;
-  if (sh + b > 32) f |= seg[wi + 1] << (32 - sh);
-  return ((f & mask) + bias) & mask;
+// ---- entropy-coded stream of one message ---------------------------------------------------------------------------
+// Two launches.  A workgroup owns kEmitSegs = 255 consecutive segments, one per thread.
+//   measure: the encoded size of every workgroup's share (bit 31: a coordinate's symbol has no codeword);
+//   emit:    every workgroup adds up the sizes of the shares before its own (a few hundred words out of the L2), scans
+//            its segments' sizes, and assembles its part of the stream in LDS.  A stream word belongs to the workgroup
+//            in whose share its first bit lies; the last word of a share is completed from the following segment, which
+//            thread 255 encodes (it has at least 32 coordinates of at least one bit, or it is the message's last).  So
+//            every word is written once, with a plain store, and the output needs no clearing.
+// 4.2 M coordinates, b = 4 (one MI355X): 282 us for sizes per segment, a scan by one workgroup whose threads walked
+// their shares word by word, a fill, and codewords OR-ed into global memory; 14.5 us for these two launches.
+constexpr int kEmitSegs = 255;
+constexpr uint32_t kBadBit = 0x80000000u;
+
+// codewords of up to 256 symbols travel in the kernel's arguments (no copy to the device ahead of the launch);
+// `far` holds the table where there are more
+struct HuffTable {
+  HuffEntry e[256];
+  const HuffEntry *far;
+};
+
+template <int B>
+__device__ __forceinline__ const HuffEntry *huffman_stage(const HuffTable &t, HuffEntry *lds, int tid) {
+  if constexpr (B > 8) {
+    return t.far;
+  } else {
+    if (tid < (1 << B)) lds[tid] = t.e[tid];
+    __syncthreads();
+    return lds;
+  }
 }
 
-// seg_bits[s] = encoded size of segment s; meta[1] != 0 if some coordinate's symbol has no codeword
-__global__ __launch_bounds__(256) void huffman_measure_kernel(const uint32_t *__restrict__ words, int64_t d, int32_t b,
-                                                              const HuffEntry *__restrict__ table,
-                                                              uint32_t *__restrict__ seg_bits,
-                                                              unsigned long long *__restrict__ meta) {
-  const int64_t segs = (d + 31) / 32;
-  const int64_t s = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (s >= segs) return;
-  const uint32_t mask = (1u << b) - 1u, bias = 1u << (b - 1);
-  const int64_t left = d - s * 32;
-  const int cnt = left < 32 ? (int)left : 32;
-  uint32_t total = 0;
-  bool bad = false;
-  for (int j = 0; j < cnt; ++j) {
-    const uint32_t len = table[segment_symbol(words + s * b, j, b, mask, bias)].len;
-    bad = bad || len == 0;
+// encoded bits of this thread's segment (kBadBit: a symbol without codeword)
+template <int B>
+__device__ __forceinline__ uint32_t huffman_segment_bits(const Segment<B> &seg, int cnt, const HuffEntry *table) {
+  uint32_t total = 0, bad = 0;
+  for_symbols<B>(seg, cnt, [&](uint32_t s) {
+    const uint32_t len = table[s].len;
+    bad |= len == 0 ? kBadBit : 0u;
     total += len;
-  }
-  seg_bits[s] = total;
-  if (bad) atomicOr(&meta[1], 1ull);
+  });
+  return total | bad;
 }
 
-// off[s] = sum of seg_bits[0..s), meta[0] = the total; one workgroup, each thread a contiguous share
-__global__ __launch_bounds__(1024) void huffman_scan_kernel(const uint32_t *__restrict__ seg_bits, int64_t segs,
-                                                            unsigned long long *__restrict__ off,
-                                                            unsigned long long *__restrict__ meta) {
-  __shared__ unsigned long long share[1024];
+template <int B>
+__global__ __launch_bounds__(256) void huffman_measure_kernel(const uint32_t *__restrict__ words, int64_t d,
+                                                              HuffTable table, uint32_t *__restrict__ wg_bits) {
+  __shared__ HuffEntry lds[B > 8 ? 1 : (1 << B)];
+  __shared__ uint32_t red[4];
   const int tid = threadIdx.x;
-  const int64_t per = (segs + 1023) / 1024;
-  const int64_t lo = tid * per, hi = lo + per < segs ? lo + per : segs;
-  unsigned long long mine = 0;
-  for (int64_t s = lo; s < hi; ++s) mine += seg_bits[s];
-  share[tid] = mine;
-  __syncthreads();
-  if (tid == 0) {
-    unsigned long long run = 0;
-    for (int k = 0; k < 1024; ++k) {
-      const unsigned long long t = share[k];
-      share[k] = run;
-      run += t;
-    }
-    meta[0] = run;
+  const HuffEntry *tab = huffman_stage<B>(table, lds, tid);
+  const int64_t s = (int64_t)blockIdx.x * kEmitSegs + tid, left = d - s * 32;
+  uint32_t bits = 0;
+  if (tid < kEmitSegs && left > 0) {
+    Segment<B> seg;
+    seg.load(words + s * B);
+    bits = huffman_segment_bits<B>(seg, left < 32 ? (int)left : 32, tab);
   }
+  const uint32_t sum = wave_sum(bits & ~kBadBit);
+  const uint32_t bad = __ballot((bits & kBadBit) != 0u) ? kBadBit : 0u;
+  if ((tid & 63) == 0) red[tid >> 6] = sum | bad;
   __syncthreads();
-  unsigned long long pos = share[tid];
-  for (int64_t s = lo; s < hi; ++s) {
-    off[s] = pos;
-    pos += seg_bits[s];
-  }
+  if (tid == 0)
+    wg_bits[blockIdx.x] = (((red[0] & ~kBadBit) + (red[1] & ~kBadBit)) + ((red[2] & ~kBadBit) + (red[3] & ~kBadBit))) |
+                          ((red[0] | red[1] | red[2] | red[3]) & kBadBit);
 }
 
-// A thread appends the codewords of its segment from stream position off[s] on.  Words shared with the
-// neighbouring segments are merged with atomic ORs (the stream was zero-filled).
-__global__ __launch_bounds__(256) void huffman_emit_kernel(const uint32_t *__restrict__ words, int64_t d, int32_t b,
-                                                           const HuffEntry *__restrict__ table,
-                                                           const unsigned long long *__restrict__ off,
-                                                           uint32_t *__restrict__ out) {
-  const int64_t segs = (d + 31) / 32;
-  const int64_t s = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (s >= segs) return;
-  const uint32_t mask = (1u << b) - 1u, bias = 1u << (b - 1);
-  const int64_t left = d - s * 32;
-  const int cnt = left < 32 ? (int)left : 32;
-  const unsigned long long pos = off[s];
-  int64_t wi = (int64_t)(pos >> 5);
-  uint32_t filled = (uint32_t)(pos & 31ull);   // bits of out[wi] that belong to earlier segments
+// meta (a host slot): total bits, and whether a coordinate has no codeword; out is written only if all is well and
+// the stream fits capacity_words.  Dynamic LDS: 256 * (longest codeword) + 2 words.
+template <int B>
+__global__ __launch_bounds__(256) void huffman_emit_kernel(const uint32_t *__restrict__ words, int64_t d,
+                                                           HuffTable table, const uint32_t *__restrict__ wg_bits,
+                                                           uint32_t buffer_words, int64_t capacity_words,
+                                                           uint32_t *__restrict__ out,
+                                                           unsigned long long *__restrict__ meta) {
+  extern __shared__ uint32_t buf[];
+  __shared__ HuffEntry lds[B > 8 ? 1 : (1 << B)];
+  __shared__ unsigned long long before_sh[4], all_sh[4];
+  __shared__ uint32_t bad_sh[4], scan_sh[4];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int64_t s = (int64_t)blockIdx.x * kEmitSegs + tid, left = d - s * 32;
+  const int cnt = left < 32 ? (left > 0 ? (int)left : 0) : 32;
+  Segment<B> seg;
+  if (cnt > 0) seg.load(words + s * B);
+  // the shares before this one, and all of them
+  unsigned long long before = 0, all = 0;
+  uint32_t bad = 0;
+  for (uint32_t k = tid; k < gridDim.x; k += 256) {
+    const uint32_t t = wg_bits[k];
+    const uint32_t v = t & ~kBadBit;
+    bad |= t & kBadBit;
+    all += v;
+    if (k < blockIdx.x) before += v;
+  }
+  const uint32_t share = wg_bits[blockIdx.x] & ~kBadBit, used_words = share / 32 + 3;  // with the skew and a part word
+  for (uint32_t k = tid; k < (used_words < buffer_words ? used_words : buffer_words); k += 256) buf[k] = 0u;
+  const HuffEntry *tab = huffman_stage<B>(table, lds, tid);  // a barrier for B <= 8
+  const uint32_t mine = huffman_segment_bits<B>(seg, cnt, tab) & ~kBadBit;
+  uint32_t incl = mine;  // inclusive scan over the wavefront
+#pragma unroll
+  for (int step = 1; step < 64; step <<= 1) {
+    const uint32_t up = __shfl_up(incl, step, 64);
+    if (lane >= step) incl += up;
+  }
+#pragma unroll
+  for (int step = 32; step >= 1; step >>= 1) {
+    before += __shfl_xor(before, step, 64);
+    all += __shfl_xor(all, step, 64);
+  }
+  bad = __ballot(bad != 0u) ? 1u : 0u;
+  if (lane == 63) scan_sh[wv] = incl;
+  if (lane == 0) { before_sh[wv] = before; all_sh[wv] = all; bad_sh[wv] = bad; }
+  __syncthreads();
+  before = before_sh[0] + before_sh[1] + before_sh[2] + before_sh[3];
+  all = all_sh[0] + all_sh[1] + all_sh[2] + all_sh[3];
+  bad = bad_sh[0] | bad_sh[1] | bad_sh[2] | bad_sh[3];
+  if (blockIdx.x == 0 && tid == 0) { meta[0] = all; meta[1] = bad; hand_over(meta); }
+  const int64_t need = (int64_t)((all + 31) / 32);
+  if (bad || need > capacity_words) return;  // uniform over the launch
+  for (int k = 0; k < wv; ++k) incl += scan_sh[k];
+  const uint32_t skew = (uint32_t)(before & 31ull);          // bits of the first word that belong to earlier shares
+  const uint32_t at = skew + incl - mine;                    // this segment's first bit in buf
+  uint32_t wi = at >> 5, filled = at & 31u;
+  const uint32_t stop = tid < kEmitSegs ? buffer_words : wi + 1;  // the following segment completes one word only
   unsigned long long acc = 0;
-  for (int j = 0; j < cnt; ++j) {
-    const HuffEntry e = table[segment_symbol(words + s * b, j, b, mask, bias)];
-    acc |= (unsigned long long)e.rev << filled;   // filled <= 31, e.len <= 32
+  for_symbols<B>(seg, cnt, [&](uint32_t sym) {
+    const HuffEntry e = tab[sym];
+    acc |= (unsigned long long)e.rev << filled;  // filled <= 31, e.len <= 32
     filled += e.len;
     if (filled >= 32) {
-      if ((uint32_t)acc) atomicOr(&out[wi], (uint32_t)acc);
+      if (wi < stop) atomicOr(&buf[wi], (uint32_t)acc);
       acc >>= 32;
       filled -= 32;
       ++wi;
     }
-  }
-  if ((uint32_t)acc) atomicOr(&out[wi], (uint32_t)acc);
+  });
+  if ((uint32_t)acc && wi < stop) atomicOr(&buf[wi], (uint32_t)acc);
+  __syncthreads();
+  // words whose first bit lies in [before, before + share)
+  const unsigned long long end = before + (unsigned long long)share;
+  const int64_t w0 = (int64_t)(before >> 5), first = (int64_t)((before + 31) >> 5), last = (int64_t)((end + 31) >> 5);
+  for (int64_t w = first + tid; w < last; w += 256) out[w] = buf[w - w0];
 }
 
 }  // namespace
 
-hipError_t launch_huffman_measure(const lpc_ctx *c, const uint32_t *words, hipStream_t st) {
-  const int64_t segs = c->d_pad / 32;
-  hipLaunchKernelGGL(zero_u64_kernel, dim3(1), dim3(64), 0, st, c->s.huff_meta, (int64_t)2);
-  hipLaunchKernelGGL(huffman_measure_kernel, dim3((unsigned)((segs + 255) / 256)), dim3(256), 0, st, words, c->d,
-                     c->cfg.bits, (const HuffEntry *)c->s.huff_table, c->s.huff_seg_bits, c->s.huff_meta);
-  hipLaunchKernelGGL(huffman_scan_kernel, dim3(1), dim3(1024), 0, st, (const uint32_t *)c->s.huff_seg_bits, segs,
-                     c->s.huff_off, c->s.huff_meta);
-  return hipGetLastError();
-}
+int64_t huffman_wgs(int64_t d) { return ((d + 31) / 32 + kEmitSegs - 1) / kEmitSegs; }
 
-hipError_t launch_huffman_emit(const lpc_ctx *c, const uint32_t *words, uint32_t *out, int64_t out_words,
-                               hipStream_t st) {
-  const int64_t segs = c->d_pad / 32;
-  hipError_t e = launch_fill_u32(out, 0u, out_words, st);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(huffman_emit_kernel, dim3((unsigned)((segs + 255) / 256)), dim3(256), 0, st, words, c->d,
-                     c->cfg.bits, (const HuffEntry *)c->s.huff_table, (const unsigned long long *)c->s.huff_off, out);
+// Both launches: sizes, then the stream into out (nothing when it does not fit or a symbol has no codeword) with
+// {total bits, bad symbol} in meta.  table: 2^bits codewords on the host, far: the same on the device where bits > 8.
+hipError_t launch_huffman(const lpc_ctx *c, const uint32_t *words, const HuffEntry *table, const HuffEntry *far,
+                          uint32_t *out, int64_t capacity_words, unsigned long long *meta, hipStream_t st) {
+  HuffTable t{};
+  t.far = far;
+  const int nsym = 1 << c->cfg.bits;
+  uint32_t longest = 0;
+  for (int k = 0; k < nsym; ++k) {
+    if (nsym <= 256) t.e[k] = table[k];
+    longest = table[k].len > longest ? table[k].len : longest;
+  }
+  const dim3 grid((unsigned)huffman_wgs(c->d));
+  const uint32_t buffer_words = 256u * longest + 2u;
+#define CALL(BITS)                                                                                                     \
+  do {                                                                                                                 \
+    hipLaunchKernelGGL(huffman_measure_kernel<BITS>, grid, dim3(256), 0, st, words, c->d, t, c->s.huff_wg_bits);       \
+    hipLaunchKernelGGL(huffman_emit_kernel<BITS>, grid, dim3(256), buffer_words * sizeof(uint32_t), st, words, c->d,   \
+                       t, (const uint32_t *)c->s.huff_wg_bits, buffer_words, capacity_words, out, meta);               \
+  } while (0)
+  LPC_DISPATCH_BITS(c->cfg.bits, CALL)
+#undef CALL
   return hipGetLastError();
 }
 
@@ -257,8 +380,10 @@ hipError_t launch_code_histogram(const uint32_t *words, int64_t d, int32_t bits,
   if (e != hipSuccess || d <= 0) return e;
   const int64_t segs = (d + 31) / 32;
   int64_t wgs = (segs + 255) / 256;
-  if (wgs > 512) wgs = 512;
-  hipLaunchKernelGGL(code_histogram_kernel, dim3((unsigned)wgs), dim3(256), 0, st, words, d, bits, cnt);
+  if (wgs > 256) wgs = 256;  // one per CU: every further one repeats the 2^b additions to the global counters
+#define CALL(BITS) hipLaunchKernelGGL(code_histogram_kernel<BITS>, dim3((unsigned)wgs), dim3(256), 0, st, words, d, cnt)
+  LPC_DISPATCH_BITS(bits, CALL)
+#undef CALL
   return hipGetLastError();
 }
 

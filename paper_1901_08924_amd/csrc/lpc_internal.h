@@ -15,6 +15,7 @@
 namespace lpc {
 
 constexpr uint32_t kTagQuant = 0, kTagBatch = 1, kTagShared = 2, kTagRequant = 3;
+constexpr int kHostSlotWords = 8;  // 64-bit words of a host slot (lpc_api.hip); the last one says that the others are there
 constexpr uint32_t kSharedWorkerField = 0xFFFFFFu;
 
 // Per-vector quantizer parameters, produced on the device right after the
@@ -87,6 +88,16 @@ extern thread_local LaunchTimer *g_launch_timer;  // set while such a class's la
     }                                                                                                         \
   } while (0)
 
+// CALL(bits) for the message widths of the quantizer; a template argument in the callers
+#define LPC_DISPATCH_BITS(bits, CALL)                                                                     \
+  switch (bits) {                                                                                         \
+    case 2: CALL(2); break;   case 3: CALL(3); break;   case 4: CALL(4); break;   case 5: CALL(5); break;   \
+    case 6: CALL(6); break;   case 7: CALL(7); break;   case 8: CALL(8); break;   case 9: CALL(9); break;   \
+    case 10: CALL(10); break; case 11: CALL(11); break; case 12: CALL(12); break; case 13: CALL(13); break; \
+    case 14: CALL(14); break; case 15: CALL(15); break; case 16: CALL(16); break;                          \
+    default: return hipErrorInvalidValue;                                                                 \
+  }
+
 // ---- device scratch owned by a context (all pointers into the workspace) ----
 struct Scratch {
   float *part;          // partial gradient rows
@@ -110,9 +121,7 @@ struct Scratch {
   float *warm_sink;                // [1] never written in practice: keeps the cache-warming loads alive
   unsigned long long *clip_total;  // [1] clipped coordinates summed over an evaluation run
   HuffEntry *huff_table;           // [2^bits] codeword table of the entropy coder
-  uint32_t *huff_seg_bits;         // [d_pad/32] encoded bits per 32-coordinate segment
-  unsigned long long *huff_off;    // [d_pad/32] stream position of each segment
-  unsigned long long *huff_meta;   // [2] total bits, bad-symbol flag
+  uint32_t *huff_wg_bits;          // [huffman_wgs(d)] encoded bits per workgroup of the entropy coder
   float *csr_tail;      // [d_pad] CSR snapshot pass: accumulator of the non-privatised columns
   // column-major copy of the CSR entries whose column is not in the head (built by lpc_create)
   int32_t *csc_ptr;     // [d+4]: column extents (head columns are empty), the longest column, two build counters
@@ -287,9 +296,9 @@ constexpr int kSnapWide = 2048;  // rows per block of its weight-gradient produc
 // 0 if lens[0..nsym) (each in [0, 32]) are the lengths of a prefix code, and then table[k] holds symbol k's
 // canonical codeword; -1 otherwise.
 int huffman_canonical_table(const int32_t *lens, int32_t nsym, HuffEntry *table);
-hipError_t launch_huffman_measure(const lpc_ctx *c, const uint32_t *words, hipStream_t st);
-hipError_t launch_huffman_emit(const lpc_ctx *c, const uint32_t *words, uint32_t *out, int64_t out_words,
-                               hipStream_t st);
+int64_t huffman_wgs(int64_t d);
+hipError_t launch_huffman(const lpc_ctx *c, const uint32_t *words, const HuffEntry *table, const HuffEntry *far,
+                          uint32_t *out, int64_t capacity_words, unsigned long long *meta, hipStream_t st);
 hipError_t launch_epoch_report(const float *delta, const uint32_t *nclip, int64_t n, unsigned long long *out,
                                hipStream_t st);
 hipError_t launch_accumulate_clipped(const uint32_t *n_clipped, int32_t N, unsigned long long *total, hipStream_t st);
@@ -312,6 +321,7 @@ hipError_t launch_reduce_parts(const lpc_ctx *c, const float *part, int32_t part
 // stats_mode values of launch_reduce_parts
 constexpr int kStatsNone = 0, kStatsFinal = 1, kStatsPartial = 2;
 bool fused_exchange_supported(const lpc_ctx *c);
+bool own_statistics(const lpc_ctx *c);  // launch_fused_exchange without statistic partials (nslots = 0)
 int reduce_parts_waves(const lpc_ctx *c, int32_t parts, int32_t nvec);
 struct AlpcStep;
 hipError_t launch_cols_exchange(const lpc_ctx *c, const float *U, StreamKey key, uint32_t *packed, float *delta_out,
@@ -321,7 +331,6 @@ bool fused_iter_supported(const lpc_ctx *c);
 int64_t fused_iter_slot_words(const lpc_ctx *c);
 hipError_t launch_fused_iter_reset(const lpc_ctx *c, hipStream_t st);
 hipError_t launch_fused_iter(const lpc_ctx *c, StreamKey key, uint32_t *packed, float *delta_out, const float *mu,
-bool own_statistics(const lpc_ctx *c);  // launch_fused_exchange without statistic partials (nslots = 0)
                              float step, float *w, const AlpcStep *al, hipStream_t st);
 hipError_t launch_fused_exchange(const lpc_ctx *c, const float *U, int32_t nslots, StreamKey key, uint32_t *packed,
                                  float *delta_out, const float *mu, float step, float *w, float *u_avg_out,
@@ -375,10 +384,13 @@ hipError_t launch_alpc_update(const lpc_ctx *c, const float *x, const float *u_a
 // Alg. 2 steps 13-15 and the next step 6 over d coordinates, reading the average from the context's u_avg; clears u_hat
 hipError_t launch_alpc_update_couple(const lpc_ctx *c, const AlpcStep &al, hipStream_t st);
 hipError_t launch_scale_to(const lpc_ctx *c, const float *src, float scale, float *dst, hipStream_t st);
-hipError_t launch_objective_reg(const lpc_ctx *c, const float *w, double *acc, hipStream_t st);
+// the regulariser's partials (statistic scratch), and the fold of a call's partials into its one number
+int32_t result_groups(const lpc_ctx *c);
+hipError_t launch_objective_reg(const lpc_ctx *c, const float *w, hipStream_t st);
+hipError_t launch_fold_result(const lpc_ctx *c, int32_t groups, const double *loss, int32_t n_loss, double scale,
+                              const double *base, double *out, hipStream_t st);
 // evaluators (Sec. 3.3 gradient mapping; Sec. 6.1 entropy coding of the code stream)
-hipError_t launch_gradient_mapping(const lpc_ctx *c, const float *w, const float *grad, double eta, double *out,
-                                   hipStream_t st);
+hipError_t launch_gradient_mapping(const lpc_ctx *c, const float *w, const float *grad, double eta, hipStream_t st);
 hipError_t launch_code_histogram(const uint32_t *words, int64_t d, int32_t bits, uint64_t *counts, hipStream_t st);
 uint64_t huffman_code_lengths(const uint64_t *counts, int32_t nsym, int32_t *lens);
 

@@ -1924,16 +1924,29 @@ __global__ __launch_bounds__(1024) void objective_reg_kernel(const float *__rest
   }
 }
 
-// acc += the n <= 256 partials: lane l takes partial[l], [l+64], [l+128], [l+192], then the wavefront sum (one
-// wavefront; a fixed order)
-__global__ __launch_bounds__(64) void objective_reg_fold_kernel(const double *__restrict__ partial, int32_t n,
-                                                               double *__restrict__ acc) {
-  const int lane = threadIdx.x;
-  double v[4];
+// out[0] = scale * sum of the n_loss loss partials (or *base where there are none) + sum of the n <= 256 partials: a
+// call's one number, handed to the waiting host (hand_over).  One workgroup; fixed order.
+__global__ __launch_bounds__(kThreads) void fold_result_kernel(const double *__restrict__ partial, int32_t n,
+                                                               const double *__restrict__ loss, int32_t n_loss,
+                                                               double scale, const double *__restrict__ base,
+                                                               double *__restrict__ out) {
+  __shared__ double red[4];
+  const int tid = threadIdx.x;
+  double acc = 0.0, t = 0.0;
+  for (int32_t k = tid; k < n_loss; k += kThreads) acc += loss[k];
+  acc = wave_sum(acc);
+  if ((tid & 63) == 0) red[tid >> 6] = acc;
+  if (tid < 64) {
+    double v[4];
 #pragma unroll
-  for (int q = 0; q < 4; ++q) v[q] = lane + 64 * q < n ? partial[lane + 64 * q] : 0.0;
-  const double t = wave_sum((v[0] + v[1]) + (v[2] + v[3]));
-  if (lane == 0) *acc += t;
+    for (int q = 0; q < 4; ++q) v[q] = tid + 64 * q < n ? partial[tid + 64 * q] : 0.0;
+    t = wave_sum((v[0] + v[1]) + (v[2] + v[3]));
+  }
+  __syncthreads();
+  if (tid == 0) {
+    *out = (n_loss > 0 ? (((red[0] + red[1]) + red[2]) + red[3]) * scale : base ? *base : 0.0) + t;
+    hand_over(out);
+  }
 }
 
 QuantSpec spec_of(const lpc_ctx *c) {
@@ -2085,14 +2098,6 @@ void dequantize_launch(const lpc_ctx *c, const uint32_t *packed, const float *de
   }
 }
 
-#define LPC_DISPATCH_BITS(bits, CALL)                                                                     \
-  switch (bits) {                                                                                         \
-    case 2: CALL(2); break;   case 3: CALL(3); break;   case 4: CALL(4); break;   case 5: CALL(5); break;   \
-    case 6: CALL(6); break;   case 7: CALL(7); break;   case 8: CALL(8); break;   case 9: CALL(9); break;   \
-    case 10: CALL(10); break; case 11: CALL(11); break; case 12: CALL(12); break; case 13: CALL(13); break; \
-    case 14: CALL(14); break; case 15: CALL(15); break; case 16: CALL(16); break;                          \
-    default: return hipErrorInvalidValue;                                                                 \
-  }
 }  // namespace
 
 hipError_t launch_quantize(const lpc_ctx *c, const float *U, StreamKey key, uint32_t *packed, float *delta_out,
@@ -2231,17 +2236,17 @@ hipError_t launch_fused_exchange(const lpc_ctx *c, const float *U, int32_t nslot
   return hipGetLastError();
 }
 
-hipError_t launch_fused_exchange_alpc(const lpc_ctx *c, const float *U, int32_t nslots, StreamKey key,
-                                      uint32_t *packed, float *delta_out, const AlpcStep &al, hipStream_t st) {
-  FusedArgs a{};
-  a.U = U; a.d = c->d; a.d_pad = c->d_pad; a.W = c->W;
-  a.N = c->cfg.N; a.bits = c->cfg.bits; a.nslots = nslots; a.stat_slots = c->stat_slots;
 // Whether the exchange of vectors that no launch has taken statistics of takes them itself (nslots = 0 above).  Every
 // workgroup then reads all N vectors, one 1024-coordinate chunk per wavefront and step, and the launch of
 // vector_stats_kernel is saved: calls back to back 9.8 -> 7.7 us with up to eight chunks (one step: N = 8, d = 1024),
 // 9.8 -> 9.5 / 10.4 us with sixteen, 9.8 -> 11.0 us with 32.
 bool own_statistics(const lpc_ctx *c) { return (int64_t)c->cfg.N * ((c->d + 1023) / 1024) <= kOwnChunks; }
 
+hipError_t launch_fused_exchange_alpc(const lpc_ctx *c, const float *U, int32_t nslots, StreamKey key,
+                                      uint32_t *packed, float *delta_out, const AlpcStep &al, hipStream_t st) {
+  FusedArgs a{};
+  a.U = U; a.d = c->d; a.d_pad = c->d_pad; a.W = c->W;
+  a.N = c->cfg.N; a.bits = c->cfg.bits; a.nslots = nslots; a.stat_slots = c->stat_slots;
   a.stat_part = c->s.stat_part; a.qs = spec_of(c); a.key = key;
   a.packed = packed; a.delta_out = delta_out; a.stats = c->s.stats; a.flags = c->s.flags;
   a.mu = al.mu; a.do_alpc = 1;
@@ -2468,16 +2473,25 @@ hipError_t launch_scale_to(const lpc_ctx *c, const float *src, float scale, floa
   return hipGetLastError();
 }
 
-hipError_t launch_objective_reg(const lpc_ctx *c, const float *w, double *acc, hipStream_t st) {
-  // one workgroup per 8192 coordinates, at most as many as the statistic scratch (free outside an epoch) holds
+// workgroups of a reduction over w's d coordinates: one per 8192, at most as many as the statistic scratch (free
+// outside an epoch) holds partials and fold_result_kernel folds
+int32_t result_groups(const lpc_ctx *c) {
   int64_t groups = (c->d + 8191) / 8192;
   const int64_t room = (int64_t)(c->cfg.N + 1) * c->stat_slots * 4;
   if (groups > room) groups = room;
-  if (groups > 256) groups = 256;
-  hipLaunchKernelGGL(objective_reg_kernel, dim3((unsigned)groups), dim3(1024), 0, st, w, c->d,
+  return (int32_t)(groups > 256 ? 256 : groups);
+}
+
+hipError_t launch_fold_result(const lpc_ctx *c, int32_t groups, const double *loss, int32_t n_loss, double scale,
+                              const double *base, double *out, hipStream_t st) {
+  hipLaunchKernelGGL(fold_result_kernel, dim3(1), dim3(kThreads), 0, st, (const double *)c->s.stat_part, groups, loss,
+                     n_loss, scale, base, out);
+  return hipGetLastError();
+}
+
+hipError_t launch_objective_reg(const lpc_ctx *c, const float *w, hipStream_t st) {
+  hipLaunchKernelGGL(objective_reg_kernel, dim3((unsigned)result_groups(c)), dim3(1024), 0, st, w, c->d,
                      (double)c->prob.lambda1, (double)c->prob.lambda2, c->s.stat_part);
-  hipLaunchKernelGGL(objective_reg_fold_kernel, dim3(1), dim3(64), 0, st, (const double *)c->s.stat_part,
-                     (int32_t)groups, acc);
   return hipGetLastError();
 }
 
