@@ -28,7 +28,8 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBPS = 8000.0        # MI355X HBM3E, published peak
-MFMA_FP32_PEAK_TFLOPS = 157.3  # MI355X dense fp32 matrix peak
+# dense fp32 products as the contraction kernels take them: six bf16 products each (lpc_gemm.hip), 2.5 PFLOP/s of those
+MFMA_FP32_PEAK_TFLOPS = 2500.0 / 6.0
 
 KERNEL_NAMES = {
     "full_rows": "snapshot pass (lpc_full_grad): rows kernel(s)",

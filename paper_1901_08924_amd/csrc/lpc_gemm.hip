@@ -1,112 +1,142 @@
-// fp32 matrix-core GEMM for the MLP instance of eq. (1) (gfx950).
+// fp32 GEMM on the matrix cores for the MLP instance of eq. (1) (gfx950).
 //
 //   C[m][n] (+)= alpha * sum_{segments} sum_k opA(m,k) * opB(k,n)   (+ bias[n], ReLU, ReLU-mask)
 //
-// The only dense contractions of the hot path are the MLP's layer products, so
-// this is where MFMA is used: v_mfma_f32_32x32x2_f32, fp32 in, fp32 accumulate.
-// A workgroup of 4 wavefronts owns a 128x64 tile of C; each wavefront owns a
-// 64x32 part = 2x1 MFMA tiles (32 accumulator registers).  (128x128 tiles, 64
-// accumulator registers per lane, were measured no faster on any product here,
-// 4096^3 included: their 164 registers allow three workgroups per CU, not four.)
-// The K loop runs
-// in slabs of 16: the next slab is fetched from global memory into registers
-// while the current one is consumed from LDS (stored k-major so that the 32
-// lanes of an MFMA operand read consecutive words).  Operands may be given
-// transposed (weight gradients A'D and data gradients D W' need it) and the K
-// range may consist of two segments with their own base pointers (the
-// difference of two weight gradients is one contraction over stacked rows).
+// The only dense contractions of the hot path are the MLP's layer products, so this is where MFMA is used.  Inputs,
+// accumulation and results are fp32, and so is the precision, but the products are taken on the bf16 matrix
+// instructions: the fp32 ones (v_mfma_f32_32x32x2_f32) run at 157 TFLOP/s, the bf16 ones at sixteen times that.  Every
+// operand is cut, while it is staged, into three bf16 numbers that add up to it exactly,
+//
+//   x = h + m + l,   h = bf16(x), m = bf16(x - h), l = x - h - m      (8 + 8 + 8 bits, each rounded to nearest),
+//
+// and x*y is taken as hh' + hm' + mh' + mm' + hl' + lh': six products, each exact in fp32, added up in fp32.  What is
+// left out, ml' + lm' + ll', is below 2^-24 |xy| (|m| <= 2^-8 |x|, |l| <= 2^-16 |x|, rounded to nearest, so of either
+// sign): less than the rounding of one fp32 addition of the sum.  Measured against fp64 (2-norm of the error over that of
+// the result, operands N(0,1)): K = 1024 / 2048 / 3072: 4.9e-7 / 7.0e-7 / 8.6e-7, where the
+// fp32 matrix instructions gave 5.7e-7 / 8.1e-7 / 9.9e-7; all operands positive: 3.4e-7 / 4.5e-7 / 4.7e-7 against
+// 4.9e-7 / 7.0e-7 / 7.4e-7 (a bf16 instruction adds sixteen products before it rounds, an fp32 one two).  (An infinite operand gives NaN where fp32 gives an infinity or NaN.)
+//
+// Two kernels share the epilogue's options:
+//   gemm_tile_kernel: 128 x TN tiles of C through LDS, for products with enough tiles to occupy the chip;
+//   gemm_small_kernel: 32 x 32 tiles whose wavefronts split K between them, for the others.
+// Operands may be given transposed (weight gradients A'D and data gradients D W' need it) and the K range may consist
+// of two segments with their own base pointers (the difference of two weight gradients is one contraction over stacked
+// rows).
 #include <hip/hip_runtime.h>
 
 #include "lpc_device.h"
 #include "lpc_internal.h"
+#include <type_traits>
 
 namespace lpc {
 
 namespace {
 
-#ifndef LPC_GEMM_BK
-#define LPC_GEMM_BK 16
-#endif
-constexpr int BM = 128, BN = 64, BK = LPC_GEMM_BK;
-constexpr int LDT = BM + 4;  // LDS row pitch (floats)
+constexpr int BM = 128, BK = 32;
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
-// element (r, c) of a row-major matrix with leading dimension ld, zero outside [0,R)x[0,C)
-__device__ __forceinline__ float guarded(const float *p, int64_t ld, int r, int c, int R, int C) {
-  return (r < R && c < C) ? p[(int64_t)r * ld + c] : 0.0f;
-}
+// a NaN stays one: it has to reach u^i, whose statistics report it
+__device__ __forceinline__ float relu(float v) { return v < 0.0f ? 0.0f : v; }
 
-// Fetch this thread's share of a TILE x BK operand slab into registers, as TILE*BK/1024 groups of four.
-//   TRANS == false: the operand is stored [mn][k] (k contiguous).  Group h of thread t: row t/(BK/4) +
-//                   h*(1024/BK), columns k0 + 4*(t % (BK/4)) .. +3.
-//   TRANS == true : the operand is stored [k][mn] (mn contiguous).  Group h of thread t: row k0 +
-//                   t/(TILE/4) + h*(1024/TILE), columns 4*(t % (TILE/4)) .. +3.
-// FULL: the whole slab lies inside the operand and is 16-byte aligned (the launcher checks): plain vector
-// loads with no branches between them, so all of a slab's loads are in flight together.
-template <bool TRANS, int TILE, bool FULL>
-__device__ __forceinline__ void fetch_slab(const float *__restrict__ p, int64_t ld, int mn0, int k0, int MN, int K,
-                                           bool vec_ok, int tid, float (&r)[TILE * BK / 256]) {
-  constexpr int G = TILE * BK / 1024;
-#pragma unroll
-  for (int h = 0; h < G; ++h) {
-    int row, col, R, C;
-    if (!TRANS) { row = mn0 + tid / (BK / 4) + h * (1024 / BK); col = k0 + 4 * (tid % (BK / 4)); R = MN; C = K; }
-    else { row = k0 + tid / (TILE / 4) + h * (1024 / TILE); col = mn0 + 4 * (tid % (TILE / 4)); R = K; C = MN; }
-    if constexpr (FULL) {
-      const float4 v = *reinterpret_cast<const float4 *>(p + (int64_t)row * ld + col);
-      r[4 * h + 0] = v.x; r[4 * h + 1] = v.y; r[4 * h + 2] = v.z; r[4 * h + 3] = v.w;
-    } else if (vec_ok && row < R && col + 3 < C) {
-      const float4 v = *reinterpret_cast<const float4 *>(p + (int64_t)row * ld + col);
-      r[4 * h + 0] = v.x; r[4 * h + 1] = v.y; r[4 * h + 2] = v.z; r[4 * h + 3] = v.w;
-    } else {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) r[4 * h + i] = guarded(p, ld, row, col + i, R, C);
-    }
-  }
-}
-
-// The same shares for whole tiles (FULL), slab after slab: the thread's address is set up once per segment and
-// then moved by pointer steps, so no product is formed per load.  fetch() reads the next slab, in order.
-template <bool TRANS, int TILE>
-struct SlabWalker {
-  const float *p;
-  int64_t hstep, kstep;
-  __device__ __forceinline__ void init(const float *base, int64_t ld, int mn0, int tid) {
-    if (!TRANS) {
-      p = base + (int64_t)(mn0 + tid / (BK / 4)) * ld + 4 * (tid % (BK / 4));
-      hstep = (int64_t)(1024 / BK) * ld;
-      kstep = BK;
-    } else {
-      p = base + (int64_t)(tid / (TILE / 4)) * ld + mn0 + 4 * (tid % (TILE / 4));
-      hstep = (int64_t)(1024 / TILE) * ld;
-      kstep = (int64_t)BK * ld;
-    }
-  }
-  __device__ __forceinline__ void fetch(float (&r)[TILE * BK / 256]) {
-    constexpr int G = TILE * BK / 1024;
-#pragma unroll
-    for (int h = 0; h < G; ++h) {
-      const float4 v = *reinterpret_cast<const float4 *>(p + h * hstep);
-      r[4 * h + 0] = v.x; r[4 * h + 1] = v.y; r[4 * h + 2] = v.z; r[4 * h + 3] = v.w;
-    }
-    p += kstep;
-  }
+// The three bf16 parts of eight consecutive k of one row (or column): s.p[0] = h, s.p[1] = m, s.p[2] = l.
+struct Split {
+  uint4 p[3];
 };
+__device__ __forceinline__ uint32_t bf16_pair(float a, float b) {
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector((floatx2){a, b}, bf16x2));
+}
+__device__ __forceinline__ Split split8(const float (&x)[8]) {
+  uint32_t w[3][4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    float a = x[2 * i], b = x[2 * i + 1];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      const uint32_t t = bf16_pair(a, b);
+      w[q][i] = t;
+      if (q < 2) {
+        a -= __builtin_bit_cast(float, t << 16);
+        b -= __builtin_bit_cast(float, t & 0xFFFF0000u);
+      }
+    }
+  }
+  Split s;
+#pragma unroll
+  for (int q = 0; q < 3; ++q) s.p[q] = make_uint4(w[q][0], w[q][1], w[q][2], w[q][3]);
+  return s;
+}
+// the six products, the smallest first
+constexpr int kParts = 6;
+constexpr int kPartA[kParts] = {0, 2, 1, 0, 1, 0}, kPartB[kParts] = {2, 0, 1, 1, 0, 0};
+__device__ __forceinline__ floatx16 mfma(uint4 a, uint4 b, floatx16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
 
-// Store the registers k-major into an LDS slab T[k][mn].
-template <bool TRANS, int TILE>
-__device__ __forceinline__ void stash_slab(float (*T)[LDT], int tid, const float (&r)[TILE * BK / 256]) {
-  constexpr int G = TILE * BK / 1024;
+// Eight consecutive k of row / column mn of an operand, zero outside [0, MN) x [0, K).  k0 is the first k of the eight.
+//   TRANS == false: stored [mn][k] (k contiguous);  TRANS == true : stored [k][mn].
+// Plain addresses, for operands of any extent: loads outside are redirected inside and their values dropped.
+template <bool TRANS>
+__device__ __forceinline__ void fetch8_far(const float *__restrict__ p, int64_t ld, int mn, int k0, int MN, int K,
+                                           float (&r)[8]) {
+  const int c = mn < MN ? mn : MN - 1;
 #pragma unroll
-  for (int h = 0; h < G; ++h) {
-    if (!TRANS) {
-      const int mn = tid / (BK / 4) + h * (1024 / BK), k = 4 * (tid % (BK / 4));
+  for (int i = 0; i < 8; ++i) {
+    const int k = k0 + i < K ? k0 + i : K - 1;
+    const float v = TRANS ? p[(int64_t)k * ld + c] : p[(int64_t)c * ld + k];
+    r[i] = mn < MN && k0 + i < K ? v : 0.0f;
+  }
+}
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const float *p, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p), 0, (int)bytes, 0x00027000);
+}
+__device__ __forceinline__ float buffer_float(__amdgpu_buffer_rsrc_t rs, uint32_t offset, uint32_t scalar_offset = 0) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, offset, scalar_offset, 0));
+}
+// eight floats at `offset`, two 16-byte loads (rows need not start on 16 bytes)
+__device__ __forceinline__ void buffer_float8(__amdgpu_buffer_rsrc_t rs, uint32_t offset, uint32_t scalar_offset,
+                                              float (&r)[8]) {
+  typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+  const u4 a = __builtin_amdgcn_raw_buffer_load_b128(rs, offset, scalar_offset, 0),
+           b = __builtin_amdgcn_raw_buffer_load_b128(rs, offset + 16u, scalar_offset, 0);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) T[k + i][mn] = r[4 * h + i];
+  for (int i = 0; i < 4; ++i) {
+    const uint32_t x = a[i], y = b[i];  // (a bit cast of the vector's element itself reads element 0)
+    r[i] = __builtin_bit_cast(float, x);
+    r[4 + i] = __builtin_bit_cast(float, y);
+  }
+}
+constexpr uint32_t kOutside = 0x80000000u;  // an offset past every buffer (they are below 2^31 bytes): such a load gives 0
+
+// The same through a buffer that ends where the operand does: a load past the end gives zero, so a row, column or k
+// outside costs an offset and no branch.  mn0 / k0: the tile's first row (column) and the slab's first k, the same for
+// the whole wavefront; mn / kq: this lane's within them.  Needs 128 rows of ld floats to span less than 2^31 bytes.
+template <bool TRANS>
+__device__ __forceinline__ void fetch8(const float *__restrict__ p, int64_t ld, int mn0, int mn, int k0, int kq, int MN,
+                                       int K, float (&r)[8]) {
+  const uint32_t ld4 = (uint32_t)ld * 4u;
+  const bool in = mn0 + mn < MN;
+  if constexpr (TRANS) {
+    const int rows = K - k0 < 32 ? K - k0 : 32;
+    const __amdgpu_buffer_rsrc_t rs =
+        buffer_of(p + (int64_t)k0 * ld + mn0, (uint32_t)(rows - 1) * ld4 + (uint32_t)(MN - mn0) * 4u);
+    const uint32_t v = in ? (uint32_t)kq * ld4 + (uint32_t)mn * 4u : kOutside;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) r[i] = buffer_float(rs, v + (uint32_t)i * ld4);
+  } else {
+    const int rows = MN - mn0 < 128 ? MN - mn0 : 128;
+    const __amdgpu_buffer_rsrc_t rs =
+        buffer_of(p + (int64_t)mn0 * ld + k0, (uint32_t)(rows - 1) * ld4 + (uint32_t)(K - k0) * 4u);
+    const uint32_t v = (uint32_t)mn * ld4 + (uint32_t)kq * 4u;
+    if (k0 + 32 <= K) {  // uniform
+      buffer_float8(rs, in ? v : kOutside, 0, r);
     } else {
-      const int k = tid / (TILE / 4) + h * (1024 / TILE), mn = 4 * (tid % (TILE / 4));
-      *reinterpret_cast<float4 *>(&T[k][mn]) = make_float4(r[4 * h], r[4 * h + 1], r[4 * h + 2], r[4 * h + 3]);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) r[i] = buffer_float(rs, in && k0 + kq + i < K ? v + 4u * i : kOutside);
     }
   }
 }
@@ -140,7 +170,7 @@ __device__ __forceinline__ void store_tile_as(const GemmArgs &g, const floatx16 
         if (!FULL && row0 + dr >= g.M) continue;
         float *cp = crow + dr * ldc;
         float val = g.alpha * acc[i][j][v] + bias;
-        if (RELU) val = val > 0.0f ? val : 0.0f;
+        if (RELU) val = relu(val);
         if (MASK) val = mrow[dr * ldc] > 0.0f ? val : 0.0f;
         if (ACC) val += *cp;
         *cp = val;
@@ -162,17 +192,17 @@ template <int TN, bool FULL>
 __device__ __forceinline__ void store_tile(const GemmArgs &g, const floatx16 (&acc)[2][TN / 64], int m0, int n0,
                                            int64_t bz, int lane, int wm, int wn, float &fmx, float &ssum, float &ssq,
                                            float &sbad) {
-  const bool bias = g.bias != nullptr, relu = g.relu != 0, mask = g.relu_mask != nullptr, accu = g.accumulate != 0,
+  const bool bias = g.bias != nullptr, relu_on = g.relu != 0, mask = g.relu_mask != nullptr, accu = g.accumulate != 0,
              stat = g.stat_part != nullptr;
-  if (bias && relu && !mask && !accu && !stat)          // forward layer
+  if (bias && relu_on && !mask && !accu && !stat)          // forward layer
     store_tile_as<TN, FULL, true, true, false, false, false>(g, acc, m0, n0, bz, lane, wm, wn, fmx, ssum, ssq, sbad);
-  else if (!bias && !relu && mask && !accu && !stat)    // data gradient
+  else if (!bias && !relu_on && mask && !accu && !stat)    // data gradient
     store_tile_as<TN, FULL, false, false, true, false, false>(g, acc, m0, n0, bz, lane, wm, wn, fmx, ssum, ssq, sbad);
-  else if (!bias && !relu && !mask && !accu && stat)    // a worker's weight gradient, with its statistics
+  else if (!bias && !relu_on && !mask && !accu && stat)    // a worker's weight gradient, with its statistics
     store_tile_as<TN, FULL, false, false, false, false, true>(g, acc, m0, n0, bz, lane, wm, wn, fmx, ssum, ssq, sbad);
-  else if (!bias && !relu && !mask && !stat && accu)    // snapshot weight gradient, accumulating
+  else if (!bias && !relu_on && !mask && !stat && accu)    // snapshot weight gradient, accumulating
     store_tile_as<TN, FULL, false, false, false, true, false>(g, acc, m0, n0, bz, lane, wm, wn, fmx, ssum, ssq, sbad);
-  else if (!bias && !relu && !mask && !stat)            // snapshot weight gradient, first chunk or block
+  else if (!bias && !relu_on && !mask && !stat)            // snapshot weight gradient, first chunk or block
     store_tile_as<TN, FULL, false, false, false, false, false>(g, acc, m0, n0, bz, lane, wm, wn, fmx, ssum, ssq, sbad);
   else {
     // general: every option decided per element
@@ -192,7 +222,7 @@ __device__ __forceinline__ void store_tile(const GemmArgs &g, const floatx16 (&a
           if (row >= g.M) continue;
           const int64_t off = (int64_t)row * g.ldc + col;
           float val = g.alpha * acc[i][j][v] + bv;
-          if (relu) val = val > 0.0f ? val : 0.0f;
+          if (relu_on) val = relu(val);
           if (mk) val = mk[off] > 0.0f ? val : 0.0f;
           if (accu) val += C[off];
           C[off] = val;
@@ -211,6 +241,7 @@ __device__ __forceinline__ void store_tile(const GemmArgs &g, const floatx16 (&a
 
 // The tile's statistics: wavefront reductions, then the wavefronts in order through `red` (LDS, 4 doubles per
 // wavefront, not in use by anyone else); slot `tile` of batch item bz receives them.  Contains a barrier.
+template <int NW = 4>
 __device__ __forceinline__ void tile_statistics(const GemmArgs &g, double *red, int tid, int64_t bz, int64_t tile,
                                                 float fmx, double ssum, double ssq, double sbad) {
   const int lane = tid & 63, wave = tid >> 6;
@@ -219,23 +250,91 @@ __device__ __forceinline__ void tile_statistics(const GemmArgs &g, double *red, 
   __syncthreads();
   if (tid == 0) {
     double a_t = 0.0, s_t = 0.0, q_t = 0.0, b_t = 0.0;
-    for (int k = 0; k < 4; ++k) { a_t = fmax(a_t, red[k * 4]); s_t += red[k * 4 + 1]; q_t += red[k * 4 + 2]; b_t += red[k * 4 + 3]; }
+    for (int k = 0; k < NW; ++k) { a_t = fmax(a_t, red[k * 4]); s_t += red[k * 4 + 1]; q_t += red[k * 4 + 2]; b_t += red[k * 4 + 3]; }
     double *p = g.stat_part + bz * g.stat_batch_stride + ((int64_t)g.stat_slot0 + tile) * 4;
     p[0] = a_t; p[1] = s_t; p[2] = q_t; p[3] = b_t;
   }
 }
 
-// TN = 64: 128x64 tile, each wavefront 64x32 (2x1 MFMA tiles); the code is also valid for TN = 128 (2x2).
+// one element of C through all options of the launch
+__device__ __forceinline__ float skinny_store(const GemmArgs &g, float *C, int64_t bz, int row, int col, float acc) {
+  const int64_t off = (int64_t)row * g.ldc + col;
+  float val = g.alpha * acc + (g.bias ? g.bias[bz * g.strideBias + col] : 0.0f);
+  if (g.relu) val = relu(val);
+  if (g.relu_mask) val = g.relu_mask[off + (C - g.C)] > 0.0f ? val : 0.0f;
+  if (g.accumulate) val += C[off];
+  C[off] = val;
+  return val;
+}
+
+// The same eight values for whole tiles, slab after slab (BK = 32 k each), with next to no address arithmetic: buffer
+// loads take a scalar base that moves with the slab, a scalar offset per row and the thread's own offset.  (Every address
+// is inside the operand; the launcher checks that a tile's span fits the 31-bit offsets.)
+template <bool TRANS>
+struct TileWalker {
+  const float *base[2];
+  int64_t step[2];
+  uint32_t voff[2], row[2];
+  // q: which eight of a slab's 32 k are this thread's; uniform over the wavefront where TRANS
+  __device__ __forceinline__ void init(int s, const float *p, int64_t ld, int mn0, int mn, int q) {
+    row[s] = (uint32_t)ld * 4u;
+    if constexpr (TRANS) {
+      base[s] = p + mn0 + (int64_t)(8 * q) * ld;
+      voff[s] = (uint32_t)mn * 4u;
+      step[s] = (int64_t)BK * ld;
+    } else {
+      base[s] = p + (int64_t)mn0 * ld;
+      voff[s] = (uint32_t)mn * row[s] + (uint32_t)q * 32u;
+      step[s] = BK;
+    }
+  }
+  // h: 64 rows / columns further on
+  __device__ __forceinline__ void fetch(int s, int slab, int h, float (&r)[8]) const {
+    const __amdgpu_buffer_rsrc_t rs = buffer_of((s ? base[1] : base[0]) + slab * (s ? step[1] : step[0]), 0x7FFFFFFFu);
+    const uint32_t v = s ? voff[1] : voff[0], ld4 = s ? row[1] : row[0];
+    if constexpr (TRANS) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) r[i] = buffer_float(rs, v + 256u * h, i * ld4);
+    } else {
+      buffer_float8(rs, v, 64u * h * ld4, r);
+    }
+  }
+};
+
+// The tile kernel.  A workgroup of four wavefronts owns a 128 x TN tile of C, each wavefront 64 x TN/2 of it (2 x TN/64
+// matrix-core tiles of 32 x 32).  K is walked in slabs of 32: the next slab's fp32 values wait in registers while the
+// current one, split, is consumed from LDS; the thread that fetched eight consecutive k of a row splits them and stores
+// 16 bytes per part.  A row's four 16-byte units are rotated by (row / 4) % 4, so that the sixteen lanes of a pass read
+// (same k, consecutive rows) and write distinct banks.  One LDS buffer (48 KB for TN = 128): two workgroups per CU cover
+// each other's splitting and barriers; a slab is 48 matrix instructions per wavefront against 24 16-byte LDS reads and
+// about 170 vector instructions for the splitting.  4096 x 4096 x 4096: 691 us = 199 TFLOP/s (fp32 instructions: 1015 us).
+// What bounds it: at full load the chip's power (1.6 to 1.9 PFLOP/s of bf16 products without any memory traffic, a sixth
+// of which is 270 to 310 TFLOP/s here), then the LDS writes and the loads of the slabs.
+// The order in which a workgroup walks K: tiles further down start four slabs further on.  Rows are often a multiple of
+// 4 KB apart, so that all rows of a slab, and the slabs that the workgroups of a die walk in step, lie in one or two
+// channels of the L2; the rotation spreads them (4096 x 1024 x 3072: 161 -> 146 us).
+__device__ __forceinline__ int rotated(int slab, int nslab, uint32_t tile) {
+  const int at = slab + (int)((4u * tile) % (uint32_t)nslab);
+  return at >= nslab ? at - nslab : at;
+}
+
+__device__ __forceinline__ int unit_of(int mn, int q) {
+  return mn * 4 + (q ^ ((mn >> 2) & 3));
+}
+
 template <bool TA, bool TB, int TN, bool FULL>
-__global__ __launch_bounds__(256) void gemm_mfma_kernel(GemmArgs g) {
+__global__ __launch_bounds__(256, 2) void gemm_tile_kernel(GemmArgs g) {
   touch_kernel_arguments<(int)(sizeof(GemmArgs))>();
   constexpr int NJ = TN / 64;
-  __shared__ __attribute__((aligned(16))) float As[2][BK][LDT];
-  __shared__ __attribute__((aligned(16))) float Bs[2][BK][LDT];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  __shared__ uint4 As[3][BM * 4];
+  __shared__ uint4 Bs[3][TN * 4];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = (wave >> 1) * 64, wn = (wave & 1) * (TN / 2);
   const int m0 = blockIdx.y * BM, n0 = blockIdx.x * TN;
   const int64_t bz = blockIdx.z;
+  // this thread's rows of a slab (mn, mn + 64, ...) and which eight of its 32 k
+  const int a_mn = TA ? lane : tid >> 2, a_q = TA ? wave : tid & 3;
+  const int b_mn = !TB ? lane : tid >> 2, b_q = !TB ? wave : tid & 3;
 
   floatx16 acc[2][NJ];
 #pragma unroll
@@ -245,182 +344,350 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(GemmArgs g) {
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
 
-  // Two register sets per operand: while slab t is consumed from LDS, slab t+1 waits in registers and slab t+2
-  // is in flight, so a slab's loads have two slabs' worth of matrix-unit time to arrive.
-  float ra[2][BM * BK / 256], rb[2][TN * BK / 256];
-  auto consume = [&](int cur) {
-    // the wavefront that has its operands in LDS goes first: +0.5 % on the MLP workload, back to back
+  const int nslab = (g.K + BK - 1) / BK, total = nslab * g.nseg;
+  float ra[2][8], rb[NJ][8];
+  TileWalker<TA> wa;
+  TileWalker<!TB> wb;
+  if constexpr (FULL) {
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      wa.init(s, g.A[s] + bz * g.strideA[s], g.lda[s], m0, a_mn, a_q);
+      wb.init(s, g.B[s] + bz * g.strideB[s], g.ldb[s], n0, b_mn, b_q);
+    }
+  }
+  auto fetch = [&](int at) {
+    const int s = at < nslab ? 0 : 1;
+    const int slab = rotated(s ? at - nslab : at, nslab, blockIdx.y);
+    if constexpr (FULL) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) wa.fetch(s, slab, h, ra[h]);
+#pragma unroll
+      for (int h = 0; h < NJ; ++h) wb.fetch(s, slab, h, rb[h]);
+    } else {
+      const float *A = (s ? g.A[1] : g.A[0]) + bz * (s ? g.strideA[1] : g.strideA[0]);
+      const float *B = (s ? g.B[1] : g.B[0]) + bz * (s ? g.strideB[1] : g.strideB[0]);
+      const int64_t lda = s ? g.lda[1] : g.lda[0], ldb = s ? g.ldb[1] : g.ldb[0];
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        fetch8<TA>(A, lda, m0, a_mn + 64 * h, slab * BK, 8 * a_q, g.M, g.K, ra[h]);
+#pragma unroll
+      for (int h = 0; h < NJ; ++h)
+        fetch8<!TB>(B, ldb, n0, b_mn + 64 * h, slab * BK, 8 * b_q, g.N, g.K, rb[h]);
+    }
+  };
+  fetch(0);
+  for (int at = 0; at < total; ++at) {
+    __syncthreads();  // the previous slab has been consumed
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const Split t = split8(ra[h]);
+#pragma unroll
+      for (int q = 0; q < 3; ++q) As[q][unit_of(a_mn + 64 * h, a_q)] = t.p[q];
+    }
+#pragma unroll
+    for (int h = 0; h < NJ; ++h) {
+      const Split t = split8(rb[h]);
+#pragma unroll
+      for (int q = 0; q < 3; ++q) Bs[q][unit_of(b_mn + 64 * h, b_q)] = t.p[q];
+    }
+    if (at + 1 < total) fetch(at + 1);
+    __syncthreads();
     __builtin_amdgcn_s_setprio(1);
 #pragma unroll
-    for (int kk = 0; kk < BK; kk += 2) {
-      const int kr = kk + (lane >> 5), c = lane & 31;
-      const float a0 = As[cur][kr][wm + c], a1 = As[cur][kr][wm + 32 + c];
-      const float b0 = Bs[cur][kr][wn + c];
-      acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b0, acc[0][0], 0, 0, 0);
-      acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b0, acc[1][0], 0, 0, 0);
-      if constexpr (NJ == 2) {
-        const float b1 = Bs[cur][kr][wn + 32 + c];
-        acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b1, acc[0][1], 0, 0, 0);
-        acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b1, acc[1][1], 0, 0, 0);
-      }
+    for (int step = 0; step < 2; ++step) {
+      const int q = 2 * step + (lane >> 5);
+      uint4 a[2][3], b[NJ][3];
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int p = 0; p < 3; ++p) a[i][p] = As[p][unit_of(wm + 32 * i + (lane & 31), q)];
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int p = 0; p < 3; ++p) b[j][p] = Bs[p][unit_of(wn + 32 * j + (lane & 31), q)];
+#pragma unroll
+      for (int t = 0; t < kParts; ++t)
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int j = 0; j < NJ; ++j) acc[i][j] = mfma(a[i][kPartA[t]], b[j][kPartB[t]], acc[i][j]);
     }
     __builtin_amdgcn_s_setprio(0);
-  };
-  for (int s = 0; s < g.nseg; ++s) {
-    const float *A = g.A[s] + bz * g.strideA[s];
-    const float *B = g.B[s] + bz * g.strideB[s];
-    const int64_t lda = g.lda[s], ldb = g.ldb[s];
-    const bool va = (lda % 4 == 0) && (((uintptr_t)A & 15u) == 0);
-    const bool vb = (ldb % 4 == 0) && (((uintptr_t)B & 15u) == 0);
-    const int K = g.K;
-    const int nslab = (K + BK - 1) / BK;
-    SlabWalker<TA, BM> wa;
-    SlabWalker<!TB, TN> wb;
-    if constexpr (FULL) {
-      wa.init(A, lda, m0, tid);
-      wb.init(B, ldb, n0, tid);
-    }
-    // slab `at` into register set P (whole tiles: the walkers deliver the slabs in order, `at` is implied)
-#define LPC_GEMM_FETCH(P, at)                                                          \
-    if constexpr (FULL) {                                                              \
-      wa.fetch(ra[(P)]);                                                               \
-      wb.fetch(rb[(P)]);                                                               \
-    } else {                                                                           \
-      fetch_slab<TA, BM, false>(A, lda, m0, (at)*BK, g.M, K, va, tid, ra[(P)]);        \
-      fetch_slab<!TB, TN, false>(B, ldb, n0, (at)*BK, g.N, K, vb, tid, rb[(P)]);       \
-    }
-    LPC_GEMM_FETCH(0, 0)
-    if (nslab > 1) { LPC_GEMM_FETCH(1, 1) }
-    __syncthreads();  // the previous segment's last slab has been consumed
-    stash_slab<TA, BM>(As[0], tid, ra[0]);
-    stash_slab<!TB, TN>(Bs[0], tid, rb[0]);
-    __syncthreads();
-    // step p of a pair handles slab t+p, which sits in LDS buffer p; registers [1-p] hold slab t+p+1 and
-    // registers [p] are free for slab t+p+2
-#define LPC_GEMM_STEP(P)                                                                        \
-    {                                                                                           \
-      const int slab = t + (P);                                                                 \
-      if (slab + 2 < nslab) { LPC_GEMM_FETCH((P), slab + 2) }                                   \
-      consume((P));                                                                             \
-      if (slab + 1 < nslab) {                                                                   \
-        stash_slab<TA, BM>(As[1 - (P)], tid, ra[1 - (P)]);                                      \
-        stash_slab<!TB, TN>(Bs[1 - (P)], tid, rb[1 - (P)]);                                     \
-      }                                                                                         \
-      __syncthreads();                                                                          \
-    }
-    for (int t = 0; t < nslab; t += 2) {
-      LPC_GEMM_STEP(0)
-      if (t + 1 < nslab) LPC_GEMM_STEP(1)
-    }
-#undef LPC_GEMM_STEP
-#undef LPC_GEMM_FETCH
   }
 
   float fmx = 0.0f, ssum = 0.0f, ssq = 0.0f, sbad = 0.0f;
   store_tile<TN, FULL>(g, acc, m0, n0, bz, lane, wm, wn, fmx, ssum, ssq, sbad);
-  // LDS is free for the statistics: the K loop ended with a barrier
-  if (g.stat_part)
-    tile_statistics(g, reinterpret_cast<double *>(&As[0][0][0]), tid, bz,
-                    (int64_t)blockIdx.y * gridDim.x + blockIdx.x, fmx, ssum, ssq, sbad);
+  if (g.stat_part) {
+    __syncthreads();  // LDS has been read; the statistics may have it
+    tile_statistics(g, reinterpret_cast<double *>(&As[0][0]), tid, bz, (int64_t)blockIdx.y * gridDim.x + blockIdx.x,
+                    fmx, ssum, ssq, sbad);
+  }
 }
 
-// Whole 128x64 tiles with EIGHT wavefronts (one 32x32 matrix-core tile each) instead of four: for products
-// with only one or two tiles per CU this doubles the wavefronts per SIMD, so that one wavefront's operand
-// staging and barrier waits are covered by another's matrix instructions.  Whole tiles only (the launcher
-// checks); 512 threads fetch a slab with one 16-byte load each for A and (the first 256) for B.
-template <bool TA, bool TB>
-__global__ __launch_bounds__(512) void gemm_mfma8_kernel(GemmArgs g) {
+// The same 128 x 128 tile by EIGHT wavefronts, for products with one such tile per CU: two groups of four, each group
+// taking one of a slab's two 16-deep steps on the whole tile (the groups' sums are added through LDS at the end).  Two
+// LDS buffers and one barrier per slab; between barriers one group splits the next slab first and then multiplies, the
+// other multiplies first, so that on every SIMD one wavefront's splitting runs beside the other's matrix instructions.
+// 4096 x 1024 x 3072: 146 us = 176 TFLOP/s (four wavefronts per tile: 205 us, 128 x 64 tiles: 187 us, the fp32
+// instructions: 235 us); without the splitting 140, without the loads 121, without both and the LDS writes 91.
+template <bool TA, bool TB, bool FULL>
+__global__ __launch_bounds__(512, 1) void gemm_pair_kernel(GemmArgs g) {
   touch_kernel_arguments<(int)(sizeof(GemmArgs))>();
-  static_assert(BK == 16, "thread-to-slab mapping below is for 16-deep slabs");
-  __shared__ __attribute__((aligned(16))) float As[2][BK][LDT];
-  __shared__ __attribute__((aligned(16))) float Bs[2][BK][LDT];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
-  const int m0 = blockIdx.y * BM, n0 = blockIdx.x * 64;
+  __shared__ uint4 smem[2][2][3][BM * 4];
+  auto &As = smem[0];
+  auto &Bs = smem[1];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int group = wave >> 2, w4 = wave & 3;
+  const int wm = (w4 >> 1) * 64, wn = (w4 & 1) * 64;
+  const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BM;
   const int64_t bz = blockIdx.z;
-  floatx16 acc;
+  // this thread's row of a slab (of 128) and which eight of its 32 k
+  const int a_mn = TA ? lane + 64 * group : tid >> 2, a_q = TA ? w4 : tid & 3;
+  const int b_mn = !TB ? lane + 64 * group : tid >> 2, b_q = !TB ? w4 : tid & 3;
+
+  floatx16 acc[2][2];
 #pragma unroll
-  for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
-  // slab element owned by this thread: A stored [m][k] -> row tid/4, k 4*(tid%4); stored [k][m] -> k tid/32,
-  // m 4*(tid%32).  B (threads 0..255) stored [n][k] -> row tid/4, k 4*(tid%4); stored [k][n] -> k tid/16, n 4*(tid%16).
-  const int a_r = TA ? (tid >> 5) : (tid >> 2), a_c = TA ? 4 * (tid & 31) : 4 * (tid & 3);
-  const int b_r = TB ? (tid >> 2) : (tid >> 4), b_c = TB ? 4 * (tid & 3) : 4 * (tid & 15);
-  const bool b_thread = tid < 256;
-  float4 ra0, ra1, rb0, rb1;  // two register sets (named, so that they stay in registers)
-  ra0 = ra1 = rb0 = rb1 = make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int s = 0; s < g.nseg; ++s) {
-    const float *A = g.A[s] + bz * g.strideA[s];
-    const float *B = g.B[s] + bz * g.strideB[s];
-    const int64_t lda = g.lda[s], ldb = g.ldb[s];
-    const int nslab = g.K / BK;
-    // address of this thread's element of slab 0; consecutive slabs are 16 k apart
-    const float *pa = TA ? A + (int64_t)a_r * lda + m0 + a_c : A + (int64_t)(m0 + a_r) * lda + a_c;
-    const float *pb = TB ? B + (int64_t)(n0 + b_r) * ldb + b_c : B + (int64_t)b_r * ldb + n0 + b_c;
-    const int64_t sa = TA ? (int64_t)BK * lda : BK, sb = TB ? BK : (int64_t)BK * ldb;
-#define LPC_GEMM8_FETCH(SLAB, RA, RB)                                              \
-    {                                                                              \
-      RA = *reinterpret_cast<const float4 *>(pa + (SLAB) * sa);                    \
-      if (b_thread) RB = *reinterpret_cast<const float4 *>(pb + (SLAB) * sb);      \
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
+
+  const int nslab = (g.K + BK - 1) / BK, total = nslab * g.nseg;
+  float ra0[8], rb0[8], ra1[8], rb1[8];
+  TileWalker<TA> wa;
+  TileWalker<!TB> wb;
+  if constexpr (FULL) {
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      wa.init(s, g.A[s] + bz * g.strideA[s], g.lda[s], m0, a_mn, a_q);
+      wb.init(s, g.B[s] + bz * g.strideB[s], g.ldb[s], n0, b_mn, b_q);
     }
-#define LPC_GEMM8_STASH(BUF, RA, RB)                                               \
-    {                                                                              \
-      if (TA) {                                                                    \
-        *reinterpret_cast<float4 *>(&As[BUF][a_r][a_c]) = RA;                      \
-      } else {                                                                     \
-        As[BUF][a_c + 0][a_r] = RA.x; As[BUF][a_c + 1][a_r] = RA.y;                \
-        As[BUF][a_c + 2][a_r] = RA.z; As[BUF][a_c + 3][a_r] = RA.w;                \
-      }                                                                            \
-      if (b_thread) {                                                              \
-        if (!TB) {                                                                 \
-          *reinterpret_cast<float4 *>(&Bs[BUF][b_r][b_c]) = RB;                    \
-        } else {                                                                   \
-          Bs[BUF][b_c + 0][b_r] = RB.x; Bs[BUF][b_c + 1][b_r] = RB.y;              \
-          Bs[BUF][b_c + 2][b_r] = RB.z; Bs[BUF][b_c + 3][b_r] = RB.w;              \
-        }                                                                          \
-      }                                                                            \
+  }
+  auto fetch = [&](int at, float (&ra)[8], float (&rb)[8]) {
+    at = at < total ? at : total - 1;  // past the end: a repeated load that nobody uses
+    const int s = at < nslab ? 0 : 1;
+    const int slab = rotated(s ? at - nslab : at, nslab, blockIdx.y);
+    if constexpr (FULL) {
+      wa.fetch(s, slab, 0, ra);
+      wb.fetch(s, slab, 0, rb);
+    } else {
+      fetch8<TA>((s ? g.A[1] : g.A[0]) + bz * (s ? g.strideA[1] : g.strideA[0]), s ? g.lda[1] : g.lda[0], m0, a_mn,
+                 slab * BK, 8 * a_q, g.M, g.K, ra);
+      fetch8<!TB>((s ? g.B[1] : g.B[0]) + bz * (s ? g.strideB[1] : g.strideB[0]), s ? g.ldb[1] : g.ldb[0], n0, b_mn,
+                  slab * BK, 8 * b_q, g.N, g.K, rb);
     }
-#define LPC_GEMM8_CONSUME(BUF)                                                                               \
-    _Pragma("unroll") for (int kk = 0; kk < BK; kk += 2) {                                                   \
-      const int kr = kk + (lane >> 5), c = lane & 31;                                                        \
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(As[BUF][kr][wm + c], Bs[BUF][kr][wn + c], acc, 0, 0, 0);    \
-    }
-    LPC_GEMM8_FETCH(0, ra0, rb0)
-    if (nslab > 1) LPC_GEMM8_FETCH(1, ra1, rb1)
-    __syncthreads();  // the previous segment's last slab has been consumed
-    LPC_GEMM8_STASH(0, ra0, rb0)
-    __syncthreads();
-    // as in the four-wavefront kernel: an even slab t sits in LDS buffer 0 while slab t+1 waits in register
-    // set 1 and slab t+2 is requested into set 0; for the odd slab the roles are swapped
-    for (int t = 0; t < nslab; t += 2) {
-      if (t + 2 < nslab) LPC_GEMM8_FETCH(t + 2, ra0, rb0)
-      LPC_GEMM8_CONSUME(0)
-      if (t + 1 < nslab) LPC_GEMM8_STASH(1, ra1, rb1)
+  };
+  auto stash = [&](int buf, const float (&ra)[8], const float (&rb)[8]) {
+    const Split x = split8(ra), y = split8(rb);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) As[buf][q][unit_of(a_mn, a_q)] = x.p[q];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) Bs[buf][q][unit_of(b_mn, b_q)] = y.p[q];
+  };
+  uint4 a[2][3], b[2][3];  // operands of this group's step
+  auto take = [&](int buf) {
+    const int q = 2 * group + (lane >> 5);
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int p = 2; p >= 0; --p) {
+        a[i][p] = As[buf][p][unit_of(wm + 32 * i + (lane & 31), q)];
+        b[i][p] = Bs[buf][p][unit_of(wn + 32 * i + (lane & 31), q)];
+      }
+    __builtin_amdgcn_sched_barrier(0);  // requested here, whatever follows
+  };
+  auto multiply = [&]() {
+#pragma unroll
+    for (int t = 0; t < kParts; ++t)
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = mfma(a[i][kPartA[t]], b[j][kPartB[t]], acc[i][j]);
+  };
+  fetch(0, ra0, rb0);
+  fetch(1, ra1, rb1);
+  stash(0, ra0, rb0);
+  fetch(2, ra0, rb0);
+  __syncthreads();
+  // slab t sits in buffer t % 2; slab t + 1 waits in registers, t + 2 is on its way.  The groups have a loop each: with
+  // one loop and a branch around the order, values still on their way were copied where the branches met.
+  auto loop = [&](auto first_splits) {
+    constexpr bool kSplitFirst = decltype(first_splits)::value;
+    auto step = [&](int t, int buf, float (&ra)[8], float (&rb)[8]) {
+      take(buf);
+      if constexpr (!kSplitFirst) multiply();
+      stash(1 - buf, ra, rb);
+      fetch(t + 3, ra, rb);
+      if constexpr (kSplitFirst) multiply();
       __syncthreads();
-      if (t + 1 < nslab) {
-        if (t + 3 < nslab) LPC_GEMM8_FETCH(t + 3, ra1, rb1)
-        LPC_GEMM8_CONSUME(1)
-        if (t + 2 < nslab) LPC_GEMM8_STASH(0, ra0, rb0)
-        __syncthreads();
+    };
+    int t = 0;
+    for (; t + 1 < total; t += 2) {
+      step(t, 0, ra1, rb1);
+      step(t + 1, 1, ra0, rb0);
+    }
+    if (t < total) {
+      take(0);
+      multiply();
+    }
+  };
+  if (group == 0) loop(std::integral_constant<bool, true>{});
+  else loop(std::integral_constant<bool, false>{});
+  __syncthreads();
+  // the second group hands its sums over, 32 KB at a time would do; the buffers hold all 64 KB
+  float *hand = reinterpret_cast<float *>(&As[0][0][0]) + w4 * 64 * 64;  // As and Bs: 96 KB, [wave][64 values][64 lanes]
+  if (group == 1) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) hand[((i * 2 + j) * 16 + v) * 64 + lane] = acc[i][j][v];
+  }
+  __syncthreads();
+  float fmx = 0.0f, ssum = 0.0f, ssq = 0.0f, sbad = 0.0f;
+  if (group == 0) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[i][j][v] += hand[((i * 2 + j) * 16 + v) * 64 + lane];
+    store_tile<128, FULL>(g, acc, m0, n0, bz, lane, wm, wn, fmx, ssum, ssq, sbad);
+  }
+  if (g.stat_part) {
+    __syncthreads();
+    tile_statistics<8>(g, reinterpret_cast<double *>(&As[0][0][0]), tid, bz,
+                       (int64_t)blockIdx.y * gridDim.x + blockIdx.x, fmx, ssum, ssq, sbad);
+  }
+}
+
+// The small kernel.  A workgroup owns a T x T tile of C (T = 32 or 64) and its NW wavefronts take the 16-deep steps of
+// K (of both segments) in turn, each straight from memory into the operand layout of the matrix instruction (lane l: row
+// or column l % 32, k 8*(l / 32) .. +7), DEPTH steps ahead; the NW partial tiles are added in wavefront order through LDS.
+// For products with too few tiles to occupy the chip, whose K loop would be a chain of trips to memory: 300 x 391 x
+// 777 12 us (64 us in 128 x 64 tiles on the fp32 instructions), 777 x 391 x 5003 transposed 59 us (588 us).
+// FAR: operands whose rows are too far apart for fetch8.
+template <bool TA, bool TB, int T, int NW, bool FAR = false>
+__global__ __launch_bounds__(64 * NW) void gemm_small_kernel(GemmArgs g) {
+  touch_kernel_arguments<(int)(sizeof(GemmArgs))>();
+  constexpr int I = T / 32, DEPTH = T == 32 ? 4 : 2;
+  __shared__ float part[NW][32][32];  // one 32 x 32 part of the tile at a time
+  __shared__ double red[4 * NW];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int m0 = blockIdx.y * T, n0 = blockIdx.x * T;
+  const int64_t bz = blockIdx.z;
+  const int steps = (g.K + 15) / 16, total = steps * g.nseg;
+  const int mn = lane & 31, kq = 8 * (lane >> 5);
+  floatx16 acc[I][I];
+#pragma unroll
+  for (int i = 0; i < I; ++i)
+#pragma unroll
+    for (int j = 0; j < I; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
+  float ra[DEPTH][I][8], rb[DEPTH][I][8];
+  auto fetch = [&](int at, float (&a)[I][8], float (&b)[I][8]) {
+    at = at < total ? at : total - 1;  // past the end: a repeated load that nobody uses
+    const bool first = at < steps;     // no indexing of the argument arrays by a run-time value
+    const int k0 = (first ? at : at - steps) * 16;
+    const float *A = (first ? g.A[0] : g.A[1]) + bz * (first ? g.strideA[0] : g.strideA[1]);
+    const float *B = (first ? g.B[0] : g.B[1]) + bz * (first ? g.strideB[0] : g.strideB[1]);
+#pragma unroll
+    for (int i = 0; i < I; ++i) {
+      const int64_t lda = first ? g.lda[0] : g.lda[1], ldb = first ? g.ldb[0] : g.ldb[1];
+      if constexpr (FAR) {
+        fetch8_far<TA>(A, lda, m0 + mn + 32 * i, k0 + kq, g.M, g.K, a[i]);
+        fetch8_far<!TB>(B, ldb, n0 + mn + 32 * i, k0 + kq, g.N, g.K, b[i]);
+      } else {
+        fetch8<TA>(A, lda, m0, mn + 32 * i, k0, kq, g.M, g.K, a[i]);
+        fetch8<!TB>(B, ldb, n0, mn + 32 * i, k0, kq, g.N, g.K, b[i]);
       }
     }
-#undef LPC_GEMM8_FETCH
-#undef LPC_GEMM8_STASH
-#undef LPC_GEMM8_CONSUME
-  }
-  float *C = g.C + bz * g.strideC;
-  const float *mask = g.relu_mask ? g.relu_mask + bz * g.strideC : nullptr;
-  const int col = n0 + wn + (lane & 31);
-  const float bias = g.bias ? g.bias[bz * g.strideBias + col] : 0.0f;
+  };
 #pragma unroll
-  for (int v = 0; v < 16; ++v) {
-    const int row = m0 + wm + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-    const int64_t off = (int64_t)row * g.ldc + col;
-    float val = g.alpha * acc[v] + bias;
-    if (g.relu) val = val > 0.0f ? val : 0.0f;
-    if (mask) val = mask[off] > 0.0f ? val : 0.0f;
-    if (g.accumulate) val += C[off];
-    C[off] = val;
+  for (int d = 0; d < DEPTH; ++d) fetch(wave + d * NW, ra[d], rb[d]);
+  for (int at = wave; at < total; at += DEPTH * NW) {
+#pragma unroll
+    for (int d = 0; d < DEPTH; ++d) {
+      if (at + d * NW < total) {  // uniform over the wavefront
+        Split x[I], y[I];
+#pragma unroll
+        for (int i = 0; i < I; ++i) {
+          x[i] = split8(ra[d][i]);
+          y[i] = split8(rb[d][i]);
+        }
+        fetch(at + (d + DEPTH) * NW, ra[d], rb[d]);
+#pragma unroll
+        for (int t = 0; t < kParts; ++t)
+#pragma unroll
+          for (int i = 0; i < I; ++i)
+#pragma unroll
+            for (int j = 0; j < I; ++j) acc[i][j] = mfma(x[i].p[kPartA[t]], y[j].p[kPartB[t]], acc[i][j]);
+      }
+    }
   }
+  float fmx = 0.0f;
+  double ssum = 0.0, ssq = 0.0, sbad = 0.0;
+#pragma unroll
+  for (int i = 0; i < I; ++i) {
+#pragma unroll
+    for (int j = 0; j < I; ++j) {
+      if (i + j > 0) __syncthreads();
+#pragma unroll
+      for (int v = 0; v < 16; ++v) part[wave][8 * (v >> 2) + 4 * (lane >> 5) + (v & 3)][lane & 31] = acc[i][j][v];
+      __syncthreads();
+#pragma unroll
+      for (int c = 0; c < 1024 / (64 * NW); ++c) {  // element e: row e / 32, column e % 32
+        const int e = c * 64 * NW + tid, row = m0 + 32 * i + (e >> 5), col = n0 + 32 * j + (e & 31);
+        float t = part[0][e >> 5][e & 31];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) t += part[w][e >> 5][e & 31];
+        if (row < g.M && col < g.N) {
+          const float val = skinny_store(g, g.C + bz * g.strideC, bz, row, col, t);
+          if (isfinite(val)) {
+            fmx = fmaxf(fmx, fabsf(val)); ssum += (double)val; ssq += (double)val * (double)val;
+          } else {
+            sbad += 1.0;
+          }
+        }
+      }
+    }
+  }
+  if (g.stat_part)  // uniform
+    tile_statistics<NW>(g, red, tid, bz, (int64_t)blockIdx.y * gridDim.x + blockIdx.x, fmx, ssum, ssq, sbad);
+}
+
+// Which kernel and tile a product takes, from its sizes alone (the number of statistic partials follows from it).
+// Single products on one MI355X, us (128 x 128 tile / 128 x 64 / 128 x 128 by eight wavefronts / 32 x 32 by four / 64 x
+// 64 by eight; tiles of 128 x 128 in brackets), which the lines below are drawn from:
+//   4096 x 4096 x 4096 [1024]     691 / 787 / 702 / 2540 / -       many tiles per CU: they cover each other
+//   4096 x 1024 x 1024 [256]       69 /  60 /  51 /  149 / 97      about one tile per CU: eight wavefronts on it
+//   8192 x  640 x   64 [320]     10.5 / 9.8 /  16 /   24 / 25      a short K: what surrounds the loop counts
+//   4662 x  391 x   50 [148]      9.6 / 7.8 /  11 /   12 / 12
+//   1024 x 1024 x 1024 [64]        59 /  39 /  38 /   41 / 25      few tiles: K is split between wavefronts
+//    700 x 1000 x 2048 [48]       121 /  86 /  80 /   52 / 35
+//    600 x  391 x  777 [20]        52 /  37 /  36 /   13 / 16
+//   2048 x  512 x  512 B' [64]     29 /  20 /  20 /   49 / 29      (both operands k-contiguous: the small kernel's
+//   1000 x  896 x  896 B' [56]     55 /  40 /  39 /   61 / 35       loads touch a line per lane)
+struct Plan {
+  int tile_m, tile_n;
+  int waves;  // 0: the tile kernel, 1: its eight-wavefront form, else the small kernel with that many
+  bool far = false;  // rows too far apart for 31-bit offsets within a tile
+};
+Plan plan_of(const GemmArgs &g) {
+  const auto tiles = [&](int tm, int tn) {
+    return (int64_t)((g.M + tm - 1) / tm) * ((g.N + tn - 1) / tn) * g.batch;
+  };
+  for (int s = 0; s < g.nseg; ++s)
+    if (g.lda[s] >= (1 << 22) || g.ldb[s] >= (1 << 22)) return {32, 32, 4, true};
+  const int64_t k = (int64_t)g.K * g.nseg, t128 = tiles(128, 128), t64 = tiles(64, 64);
+  if (t128 >= 640) return {128, 128, 0};
+  if (k <= 160 && tiles(128, 64) >= 200) return {128, 64, 0};
+  if (t128 >= 150 || (t128 >= 60 && k <= 640 && !g.transA && g.transB)) return {128, 128, 1};
+  if (k > 160 && t64 >= 100) return {64, 64, 8};
+  return {32, 32, 4};
 }
 
 // ---- outputs with at most 16 columns (the last layer of the MLP) -------------------------------------
@@ -428,16 +695,6 @@ __global__ __launch_bounds__(512) void gemm_mfma8_kernel(GemmArgs g) {
 // so these products run on the vector units with B (at most K x 16) staged in LDS.
 constexpr int kSkinnyN = 16;
 constexpr int kSkinnyLdsFloats = 16384;  // 64 KB
-
-__device__ __forceinline__ float skinny_store(const GemmArgs &g, float *C, int64_t bz, int row, int col, float acc) {
-  const int64_t off = (int64_t)row * g.ldc + col;
-  float val = g.alpha * acc + (g.bias ? g.bias[bz * g.strideBias + col] : 0.0f);
-  if (g.relu) val = val > 0.0f ? val : 0.0f;
-  if (g.relu_mask) val = g.relu_mask[off + (C - g.C)] > 0.0f ? val : 0.0f;
-  if (g.accumulate) val += C[off];
-  C[off] = val;
-  return val;
-}
 
 // C = A*B, A [M][K] row-major.  A wavefront takes one row of A at a time (16 rows per workgroup): its lanes
 // split K in groups of four, read B transposed from LDS (Bt[c][k], k contiguous) and close each of the N dot
@@ -586,7 +843,8 @@ __global__ __launch_bounds__(256) void gemm_skinny_tn_kernel(GemmArgs g, int kc)
 bool gemm_takes_matrix_cores(const GemmArgs &g) { return !(g.N <= kSkinnyN && !g.transB && g.M >= 64); }
 
 int gemm_tiles(const GemmArgs &g) {
-  return ((g.N + BN - 1) / BN) * ((g.M + BM - 1) / BM);
+  const Plan p = plan_of(g);
+  return ((g.N + p.tile_n - 1) / p.tile_n) * ((g.M + p.tile_m - 1) / p.tile_m);
 }
 
 // whether launch_gemm takes gemm_skinny_tn_short_kernel, which can leave statistic partials like the matrix-core
@@ -703,30 +961,33 @@ hipError_t launch_gemm(const GemmArgs &g, hipStream_t st) {
     }
     return hipGetLastError();
   }
-  constexpr int tn = BN;
-  const dim3 grid((unsigned)((g.N + tn - 1) / tn), (unsigned)((g.M + BM - 1) / BM), (unsigned)g.batch);
-  // whole tiles and slabs, 16-byte aligned rows: the branch-free fetch
-  bool full = g.M % BM == 0 && g.N % tn == 0 && g.K % BK == 0;
-  for (int s = 0; s < g.nseg; ++s)
-    full = full && g.lda[s] % 4 == 0 && g.ldb[s] % 4 == 0 && ((uintptr_t)g.A[s] & 15u) == 0 &&
-           ((uintptr_t)g.B[s] & 15u) == 0 && g.strideA[s] % 4 == 0 && g.strideB[s] % 4 == 0;
-#define LPC_GEMM_LAUNCH2(TA_, TB_, FULL_) \
-  hipLaunchKernelGGL((gemm_mfma_kernel<TA_, TB_, BN, FULL_>), grid, dim3(256), 0, st, g)
-  // at most one whole tile per CU: eight wavefronts per tile (measured: 6-30 % faster there, no gain
-  // once two four-wavefront workgroups share a CU)
-  const bool eight = full && (int64_t)grid.x * grid.y * grid.z <= 256 && !g.stat_part;
-#define LPC_GEMM_LAUNCH(TA_, TB_)                                                                   \
-  do {                                                                                              \
-    if (eight) hipLaunchKernelGGL((gemm_mfma8_kernel<TA_, TB_>), grid, dim3(512), 0, st, g);        \
-    else if (full) LPC_GEMM_LAUNCH2(TA_, TB_, true);                                                \
-    else LPC_GEMM_LAUNCH2(TA_, TB_, false);                                                         \
+  const Plan p = plan_of(g);
+  const dim3 grid((unsigned)((g.N + p.tile_n - 1) / p.tile_n), (unsigned)((g.M + p.tile_m - 1) / p.tile_m),
+                  (unsigned)g.batch);
+  const bool full = g.M % BM == 0 && g.N % p.tile_n == 0 && g.K % BK == 0;  // whole tiles and slabs: no checks
+#define LPC_GEMM_TILE(KERNEL_, THREADS_, ...)                                                                   \
+  do {                                                                                                        \
+    if (full) hipLaunchKernelGGL((KERNEL_<__VA_ARGS__, true>), grid, dim3(THREADS_), 0, st, g);               \
+    else hipLaunchKernelGGL((KERNEL_<__VA_ARGS__, false>), grid, dim3(THREADS_), 0, st, g);                   \
+  } while (0)
+#define LPC_GEMM_SMALL(TA_, TB_, T_, NW_) \
+  hipLaunchKernelGGL((gemm_small_kernel<TA_, TB_, T_, NW_>), grid, dim3(64 * NW_), 0, st, g)
+#define LPC_GEMM_LAUNCH(TA_, TB_)                                                                             \
+  do {                                                                                                        \
+    if (p.far) hipLaunchKernelGGL((gemm_small_kernel<TA_, TB_, 32, 4, true>), grid, dim3(256), 0, st, g);     \
+    else if (p.waves == 0 && p.tile_n == 128) LPC_GEMM_TILE(gemm_tile_kernel, 256, TA_, TB_, 128);                 \
+    else if (p.waves == 0) LPC_GEMM_TILE(gemm_tile_kernel, 256, TA_, TB_, 64);                                \
+    else if (p.waves == 1) LPC_GEMM_TILE(gemm_pair_kernel, 512, TA_, TB_);                                    \
+    else if (p.tile_m == 64) LPC_GEMM_SMALL(TA_, TB_, 64, 8);                                                 \
+    else LPC_GEMM_SMALL(TA_, TB_, 32, 4);                                                                     \
   } while (0)
   if (!g.transA && !g.transB) LPC_GEMM_LAUNCH(false, false);
   else if (!g.transA && g.transB) LPC_GEMM_LAUNCH(false, true);
   else if (g.transA && !g.transB) LPC_GEMM_LAUNCH(true, false);
   else LPC_GEMM_LAUNCH(true, true);
 #undef LPC_GEMM_LAUNCH
-#undef LPC_GEMM_LAUNCH2
+#undef LPC_GEMM_TILE
+#undef LPC_GEMM_SMALL
   return hipGetLastError();
 }
 

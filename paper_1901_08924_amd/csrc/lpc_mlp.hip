@@ -47,22 +47,30 @@ __global__ void gather_rows_kernel(const float *__restrict__ X, int64_t ldx, con
   if (threadIdx.x == 0) yb[r] = y[src];
 }
 
-// delta = sign * (softmax(logits) - onehot(label)); optionally the row's loss
-__global__ void softmax_delta_kernel(const float *__restrict__ logits, const float *__restrict__ labels, int rows,
-                                     int classes, float sign, float *__restrict__ delta,
-                                     double *__restrict__ row_loss) {
-  const int r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= rows) return;
-  const float *z = logits + (int64_t)r * classes;
-  float mx = z[0];
-  for (int c = 1; c < classes; ++c) mx = fmaxf(mx, z[c]);
-  float sum = 0.0f;
-  for (int c = 0; c < classes; ++c) sum += expf(z[c] - mx);
+// delta = sign * (softmax(logits) - onehot(label)) for both parameter sets (blockIdx.y; set 1 = the snapshot, sign -1);
+// optionally the row's loss (set 0).  A wavefront takes one row, its lanes the classes.  (A thread per row walked its
+// classes three times through memory, a launch per set: 300 rows of 33 classes 2 x 14.5 us, 2.4 us for the one launch.)
+__global__ __launch_bounds__(256) void softmax_delta_kernel(const float *__restrict__ logits,
+                                                            const float *__restrict__ labels, int rows, int classes,
+                                                            int64_t set_stride, float *__restrict__ delta,
+                                                            double *__restrict__ row_loss) {
+  const int lane = threadIdx.x & 63, r = blockIdx.x * 4 + (threadIdx.x >> 6), set = blockIdx.y;
+  if (r >= rows) return;  // whole wavefronts
+  const float sign = set == 0 ? 1.0f : -1.0f;
+  const int64_t off = (int64_t)set * set_stride + (int64_t)r * classes;
+  const float *z = logits + off;
   const int label = (int)labels[r];
+  const float first = lane < classes ? z[lane] : -INFINITY;  // the lane's first class stays in a register
+  float mx = first;
+  for (int c = lane + 64; c < classes; c += 64) mx = fmaxf(mx, z[c]);
+  mx = wave_max(mx);
+  float sum = lane < classes ? expf(first - mx) : 0.0f;
+  for (int c = lane + 64; c < classes; c += 64) sum += expf(z[c] - mx);
+  sum = wave_sum(sum);
   const float inv = 1.0f / sum;
-  for (int c = 0; c < classes; ++c)
-    delta[(int64_t)r * classes + c] = sign * (expf(z[c] - mx) * inv - (c == label ? 1.0f : 0.0f));
-  if (row_loss) row_loss[r] = (double)(logf(sum) + mx - z[label]);
+  for (int c = lane; c < classes; c += 64)
+    delta[off + c] = sign * (expf((c == lane ? first : z[c]) - mx) * inv - (c == label ? 1.0f : 0.0f));
+  if (set == 0 && row_loss && lane == 0) row_loss[r] = (double)(logf(sum) + mx - z[label]);
 }
 
 // The last layer as one launch per pass: logits = a*W + b, softmax cross-entropy delta, and the delta handed
@@ -448,10 +456,9 @@ hipError_t backward_data(const Net &nn, const float *W, int64_t wstride, int nse
                        dim3(64 * kLastRows / kRowsPerWave), lds, st, g);
     first = nn.L - 2;
   } else {
-    for (int set = 0; set < nsets; ++set)
-      hipLaunchKernelGGL(softmax_delta_kernel, dim3((unsigned)((rows + 127) / 128)), dim3(128), 0, st,
-                         (const float *)nn.act(nn.L, set), labels, rows, classes, set == 0 ? 1.0f : -1.0f,
-                         nn.del(nn.L, set), set == 0 ? row_loss : nullptr);
+    hipLaunchKernelGGL(softmax_delta_kernel, dim3((unsigned)((rows + 3) / 4), (unsigned)nsets), dim3(256), 0, st,
+                       (const float *)nn.act(nn.L, 0), labels, rows, classes, nn.rows_cap * classes, nn.del(nn.L, 0),
+                       row_loss);
   }
   for (int l = first; l >= 1; --l) {
     GemmArgs g{};

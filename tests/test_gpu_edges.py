@@ -1,0 +1,99 @@
+"""Kernels at the sizes where they can go wrong: edges of tiles, remainders, both sides of a dispatch's lines."""
+import numpy as np
+import pytest
+
+import lpc_synth
+from oracle import lpco
+from _common import gpu_context, to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+def _gemm(A, B, tA, tB):
+    import torch
+    from paper_1901_08924_amd import lpc
+    M, K = (A.shape[1], A.shape[0]) if tA else A.shape
+    N = B.shape[0] if tB else B.shape[1]
+    C = torch.full((M, N), float("nan"), device="cuda")
+    rc = lpc.lib.lpc_debug_gemm(A.data_ptr(), B.data_ptr(), C.data_ptr(), M, N, K, A.shape[1], B.shape[1], N, tA, tB,
+                                1.0, None, 0, 0, torch.cuda.current_stream().cuda_stream)
+    assert rc == 0
+    return C.cpu().numpy()
+
+
+# one product of each kernel (32 x 32, 64 x 64, 128 x 64, 128 x 128 by four and by eight wavefronts), with and without
+# remainders in every direction
+GEMMS = [(1, 17, 1), (33, 31, 15), (32, 32, 16), (31, 65, 33), (70, 700, 17), (640, 660, 161), (641, 1000, 479),
+         (1025, 1601, 7), (2048, 1920, 33), (1920, 1281, 161), (1921, 1280, 193), (2048, 1280, 256), (4096, 2560, 32),
+         (3201, 3330, 35)]
+
+
+@pytest.mark.parametrize("M,N,K", GEMMS)
+@pytest.mark.parametrize("tA,tB", [(0, 0), (0, 1), (1, 0), (1, 1)])
+def test_products_hold_fp32_precision_at_every_tile_edge(M, N, K, tA, tB):
+    import torch
+    rng = np.random.default_rng(M * 7 + N * 3 + K)
+    A, B = rng.standard_normal((M, K), dtype=np.float32), rng.standard_normal((K, N), dtype=np.float32)
+    A *= np.exp2(rng.integers(-20, 20, (M, 1))).astype(np.float32)      # rows of very different size
+    ref = A.astype(np.float64) @ B.astype(np.float64)
+    got = _gemm(to_dev(A.T.copy() if tA else A), to_dev(B.T.copy() if tB else B), tA, tB)
+    bound = np.abs(A).astype(np.float64) @ np.abs(B).astype(np.float64)
+    assert (np.abs(got - ref) / bound).max() < 1e-6 and np.isfinite(got).all()
+
+
+@pytest.mark.parametrize("M,N,K", [(40, 33, 70), (700, 700, 200), (2048, 1280, 256), (8192, 640, 64)])
+def test_products_use_all_24_bits_of_their_operands(M, N, K):
+    """Integers of up to 24 bits times +-1 with few terms per sum: every result is exact or a part was dropped."""
+    rng = np.random.default_rng(K)
+    A = rng.integers(-(1 << 24) + 1, 1 << 24, (M, K)).astype(np.float32)
+    B = np.zeros((K, N), np.float32)
+    B[rng.integers(0, K, N), np.arange(N)] = rng.choice((-1.0, 1.0), N)
+    got = _gemm(to_dev(A), to_dev(B), 0, 0)
+    assert np.array_equal(got, A.astype(np.float64) @ B.astype(np.float64))
+
+
+@pytest.mark.parametrize("d,N", [(1, 8), (1023, 8), (1024, 8), (1025, 4), (1025, 5), (4097, 1), (8192, 1), (8193, 1)])
+def test_exchange_takes_the_same_statistics_itself(d, N):
+    """Short vectors' exchange derives its statistics in its own launch: the outputs of the separate calls, bit for bit,
+    in c*sigma mode too (whose sums depend on their order)."""
+    import torch
+    sp = lpc_synth.make("c1", n=64, d=d, N=N, B=1, bits=3, seed=3)
+    ctx = gpu_context(sp, bits=3, clip_mode=lpco.CLIP_CSIGMA, clip=1.5)
+    U = to_dev(lpc_synth.gaussian_u(N, d, seed=d + N))
+    outs = []
+    for separate in (False, True):
+        packed = torch.empty(N, ctx.W, dtype=torch.int32, device="cuda")
+        delta, avg = torch.empty(N, device="cuda"), torch.empty(d, device="cuda")
+        if separate:
+            stats = torch.empty(N, 4, dtype=torch.float64, device="cuda")
+            ctx.vector_stats(U, N, stats)
+            ctx.quantize_clip(U, stats, None, 1, 2, packed, delta)
+            ctx.dequantize_avg(packed, delta, avg)
+        else:
+            ctx.exchange(U, 1, 2, packed, delta, avg)
+        outs.append([t.cpu().numpy() for t in (packed, delta, avg)])
+    for a, b in zip(*outs):
+        assert np.array_equal(a, b)
+    ctx.close()
+
+
+# a workgroup of the entropy coder owns 255 segments of 32 coordinates
+@pytest.mark.parametrize("d,bits,scale", [(8159, 3, 1.0), (8160, 3, 1.0), (8161, 2, 1e-3), (16321, 4, 1.0), (24481, 5, 0.05),
+                                          (40000, 9, 1.0)])
+def test_entropy_coded_stream_across_workgroups(d, bits, scale):
+    import torch
+    from paper_1901_08924_amd import lpc
+    sp = lpc_synth.make("c1", n=64, d=d, N=1, B=1, bits=bits, seed=4)
+    ctx = gpu_context(sp, bits=bits, clip_mode=lpco.CLIP_LAMBDA, clip=1.0, m=1)
+    U = lpc_synth.gaussian_u(1, d, seed=d, scale=scale)
+    U[0, 0] = 1.0                                   # small scales: nearly every code is 0, one bit per symbol
+    packed_o, _, _, _ = lpco.quantize_clip(U, d, bits, lpco.CLIP_LAMBDA, 1.0, seed=4)
+    packed = to_dev(packed_o.view(np.int32))[0]
+    counts = ctx.code_histogram(packed)
+    assert np.array_equal(counts.cpu().numpy().astype(np.uint64), lpco.code_histogram(packed_o[0], d, bits))
+    total, lens = lpc.huffman_bits(counts.tolist())
+    stream, got = ctx.huffman_encode(packed, lens, (total + 31) // 32)
+    ref, ref_total = lpco.huffman_encode(packed_o[0], d, bits, np.array(lens, np.int32))
+    assert got == ref_total == total
+    assert np.array_equal(stream.cpu().numpy().view(np.uint32), ref)
+    ctx.close()
