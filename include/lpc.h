@@ -199,7 +199,7 @@ lpc_status lpc_prox_step(lpc_ctx *ctx, float *w, const float *u_avg, const float
  * them equal to x~^0).  epoch = s selects the random streams and Alg. 3's schedule. */
 lpc_status lpc_epoch(lpc_ctx *ctx, float *w_snap, float *y, float *z, uint32_t epoch, void *stream);
 
-/* P(w) of eq. (1) over all n rows, returned to the HOST (synchronises the stream). */
+/* P(w) of eq. (1) over all n rows, returned to the HOST (waits for the stream to get there). */
 lpc_status lpc_objective(lpc_ctx *ctx, const float *w, double *P_out_host, void *stream);
 
 /* Reads and clears the context's device-side flags (synchronises the stream):
@@ -211,7 +211,7 @@ lpc_status lpc_take_device_flags(lpc_ctx *ctx, void *stream);
 /* ---- evaluators (outside the timed path) --------------------------------------------------
  * |G_eta(w)|^2 with G_eta(w) = (w - prox_{eta*h}(w - eta*grad f(w)))/eta, the convergence metric
  * of Sec. 3.3 (Theorems 1 and 2 bound its expectation), over all n rows; fp64 accumulation.
- * w: device, d floats.  Returned to the HOST (synchronises the stream).  Uses the context's
+ * w: device, d floats.  Returned to the HOST (waits for the stream to get there).  Uses the context's
  * scratch; the snapshot state kept by lpc_epoch is not touched.  eta > 0 else LPC_EINVAL. */
 lpc_status lpc_gradient_mapping(lpc_ctx *ctx, const float *w, float eta, double *gm2_out_host, void *stream);
 
@@ -290,8 +290,8 @@ lpc_status lpc_huffman_bits(const uint64_t *counts_host, int32_t nsym, int32_t *
  * lpc_huffman_bits (0 = symbol without codeword).  *total_bits_out_host receives the stream length.
  * LPC_EINVAL: quantization off, lengths that are no prefix code, or a coordinate whose symbol has length
  * 0.  LPC_ESHAPE: the stream needs more than capacity_words words (total_bits_out_host is still set, so
- * capacity_words = 0 asks for the size only).  Uses the context's scratch; synchronises the stream once,
- * the emitting launches are left in flight. */
+ * capacity_words = 0 asks for the size only).  Uses the context's scratch; waits once
+ * for the stream to get to the size, the emitting launches are left in flight. */
 lpc_status lpc_huffman_encode(lpc_ctx *ctx, const uint32_t *packed, const int32_t *lens_host, uint32_t *out_words,
                               int64_t capacity_words, uint64_t *total_bits_out_host, void *stream);
 
@@ -337,8 +337,11 @@ lpc_status lpc_debug_gemm(const float *A, const float *B, float *C, int32_t M, i
 /* ---- tuning and test aid (no passage of the paper) -----------------------------------------
  * Form and launch shape of the inner iteration on small dense problems (d_pad <= 16384, N <= 64).
  *   LPC_TUNE_ITER_FORM:
- *     0 (default): three launches: the workers' rows (whole rows per workgroup, partial gradient rows out), their
- *       fold, the exchange.
+ *     not set: form 0; on narrow problems (d <= 1024 and a batch that fits the registers of one workgroup, every scheme,
+ *       with or without quantization; not while the stream is being captured) all m inner iterations in one cooperative
+ *       launch with a workgroup per worker, whose waits LPC_TUNE_SPIN_LIMIT bounds as it does form 3's.
+ *     0: three launches: the workers' rows (whole rows per workgroup, partial gradient rows out), their fold, the
+ *       exchange.
  *     1: two launches: the workers' rows, then fold + exchange in one launch whose workgroups wait, for a bounded
  *       number of polls, for each other's statistics.
  *     2: two launches with nothing but the launch boundary between them.  The workers' pass runs in 128-column
@@ -359,8 +362,8 @@ lpc_status lpc_debug_gemm(const float *A, const float *B, float *C, int32_t M, i
  *     their u^i differ in the last bits.  Every form gives the same bits from run to run.
  *   LPC_TUNE_ITER_TILE: form 1: coordinates per workgroup of the second launch, 64 or 128;
  *   LPC_TUNE_ITER_THREADS: form 1: its threads per workgroup, 256 or 512;
- *   LPC_TUNE_SPIN_LIMIT: form 1: polls before a workgroup gives up waiting (it then finishes normally with what it
- *     has and lpc_take_device_flags reports LPC_EDEVICE); 0 makes every wait give up at once (tests of that path).
+ *   LPC_TUNE_SPIN_LIMIT: form 1 (for the others see there): polls before a workgroup gives up waiting (it then finishes
+ *     normally with what it has and lpc_take_device_flags reports LPC_EDEVICE); 0 makes every wait give up at once (tests of that path).
  * LPC_EINVAL for an unknown key or value, LPC_EUNSUPPORTED where the context cannot run the form. */
 typedef enum {
   LPC_TUNE_ITER_FORM = 0,

@@ -22,6 +22,11 @@ inline size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 inline lpc_status dev(hipError_t e) { return e == hipSuccess ? LPC_OK : LPC_EDEVICE; }
 inline hipStream_t as_stream(void *s) { return (hipStream_t)s; }
 
+bool capturing(hipStream_t st) {
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  return hipStreamIsCapturing(st, &status) == hipSuccess && status != hipStreamCaptureStatusNone;
+}
+
 bool is_csr(const lpc_problem &p) { return p.X == nullptr; }
 
 // Optional timing of kernel classes with HIP events on the launch stream (benchmarks only; the
@@ -170,6 +175,13 @@ size_t layout(lpc_ctx *c, char *base) {
   s.res_wbuf = (float *)take((c->res_capable ? resident_wbuf_floats(c) : 4) * sizeof(float));
   s.res_ctl = (uint32_t *)take((c->res_capable ? resident_ctl_words() : 4) * sizeof(uint32_t));
   s.res_trace = (unsigned long long *)take((c->res_capable ? (size_t)c->cfg.m * 16 : 1) * sizeof(unsigned long long));
+  {
+    const ClusterScratch cs = c->cluster_capable ? cluster_scratch(c) : ClusterScratch{1, 1, 1};
+    s.cl_msg = (unsigned long long *)take(cs.msg * sizeof(unsigned long long));
+    s.cl_vec = (unsigned long long *)take(cs.vec * sizeof(unsigned long long));
+    s.cl_scale = (unsigned long long *)take(cs.scale * sizeof(unsigned long long));
+    s.cl_ctl = (uint32_t *)take(16 * sizeof(uint32_t));
+  }
   s.iter_slots = (unsigned long long *)take((c->iter2_capable ? (size_t)fused_iter_slot_words(c) : 1) * sizeof(unsigned long long));
   if (c->mlp) {
     s.mlp_xb = (float *)take((size_t)c->mlp_rows * c->mlp_dims[0] * sizeof(float));
@@ -255,11 +267,12 @@ lpc_status fill_ctx(lpc_ctx *c, const lpc_problem *p, const lpc_config *cfg) {
   c->iter2_capable = fused_iter_supported(c);
   c->cols_capable = fused_exchange_supported(c) && dense_cols_supported(c);
   c->res_capable = resident_supported(c);
+  c->cluster_capable = cluster_supported(c);
   // measured on MI355X (inner iterations/s, forms 0 / 1 / 2): d = 4096, N = 8, B = 64: 59.9 k / 50.6 k / 47.6 k;
   // d = 8192, N = 16 (+ shared batch), B = 64: 32.3 k / - / 20.2 k.  Form 1 pays about 3 us per trip of the statistics
   // through device-scope atomics; form 2 pays for reading the sampled rows a second time in 512-byte slices (its
   // exchange launch takes 13.4 / 29.3 us against 6.3 / 8.7 us).  Three launches stay the default.
-  c->iter_form = 0;
+  c->iter_form = -1;  // not chosen: form 0, or the narrow problems' loop
   return LPC_OK;
 }
 
@@ -470,6 +483,14 @@ lpc_status lpc_create(lpc_ctx **ctx_out, const lpc_problem *problem, const lpc_c
       (c->mlp && launch_mlp_clear_padding(c, nullptr) != hipSuccess) || hipStreamSynchronize(nullptr) != hipSuccess) {
     delete c;
     return LPC_EDEVICE;
+  }
+  if (c->cluster_capable) {  // the same for the narrow problems' loop
+    const size_t words = ((char *)(c->s.cl_ctl + 16) - (char *)c->s.cl_msg) / sizeof(uint32_t);
+    if (launch_fill_u32(reinterpret_cast<uint32_t *>(c->s.cl_msg), 0u, (int64_t)words, nullptr) != hipSuccess ||
+        hipStreamSynchronize(nullptr) != hipSuccess) {
+      delete c;
+      return LPC_EDEVICE;
+    }
   }
   if (c->res_capable) {
     // the resident loop's tagged words: no tag of a launch is zero, so zeroed words never pass for written ones
@@ -736,11 +757,44 @@ lpc_status lpc_epoch(lpc_ctx *ctx, float *w_snap, float *y, float *z, uint32_t e
   Scratch &s = c->s;
   hipStream_t st = as_stream(stream);
   const lpc_config &g = c->cfg;
-  // evaluation runs take the unfused launches, whose quantizer reports the clip counts
+  // evaluation runs take the unfused launches, whose quantizer reports the clip counts, or a launch per iteration of the
+  // narrow problems' loop
   const bool tracing = c->trace_delta || c->trace_nclip || c->count_clipped || c->trace_coded_host;
   // communication step 1
   LPC_TRY(full_grad_impl(c, w_snap, s.mu, s.z_snap, nullptr, c->n_full, st));
   const float *zs = (c->n_full == c->n) ? s.z_snap : nullptr;  // margins cached only when every row was visited
+  if (c->cluster_capable && c->iter_form < 0 && !capturing(st)) {
+    // narrow problems: all m inner iterations in one launch, which starts from the snapshot and leaves the next one.
+    // (Not where the stream is being captured: a replay would repeat the launch's tags.)
+    ResidentStep rs{};
+    rs.z_snap = zs; rs.mu = s.mu; rs.key = key_of(c, epoch, 0); rs.theta = 1.0f; rs.step = g.eta;
+    double wsum = 1.0;
+    if (g.algo != LPC_ALGO_LPC) {
+      if (!y || !z) return LPC_ENULL;
+      if (!aligned(y, 16) || !aligned(z, 16)) return LPC_ESHAPE;
+      AlpcParams ap;
+      LPC_TRY(alpc_params(c, epoch, &ap));
+      rs.alpc = true; rs.y = y; rs.z = z; rs.step_y = (float)(1.0 / (4.0 * (double)g.L));
+      rs.alpha = ap.alpha; rs.tau1 = ap.tau1; rs.tau2 = ap.tau2; rs.theta = ap.theta;
+      wsum = 0.0;
+      double weight = 1.0;
+      for (int32_t t = 0; t < g.m; ++t) { wsum += weight; weight *= (double)ap.theta; }
+    }
+    rs.tag0 = c->res_tag;
+    c->res_tag += (uint32_t)g.m + 1u;
+    if (!tracing) {
+      ProfScope ps(c, LPC_PROF_RESIDENT, st);
+      return dev(launch_cluster_epoch(c, rs, w_snap, 1.0 / wsum, 0, g.m, 1.0, nullptr, st));
+    }
+    double weight = 1.0;
+    for (int32_t t = 0; t < g.m; ++t) {
+      if (c->quant) LPC_TRY_HIP(launch_fill_u32(s.n_clipped, 0u, g.N, st));
+      LPC_TRY_HIP(launch_cluster_epoch(c, rs, w_snap, 1.0 / wsum, t, t + 1, weight, c->quant ? s.n_clipped : nullptr, st));
+      LPC_TRY(record_iteration(c, t, st));
+      weight *= (double)rs.theta;
+    }
+    return LPC_OK;
+  }
   if (g.algo == LPC_ALGO_LPC) {
     LPC_TRY_HIP(launch_copy(s.w, w_snap, c->d, st));  // x_0 = x~
     const bool fused = fused_exchange_supported(c) && g.scheme == LPC_SCHEME_A && !tracing;

@@ -143,6 +143,8 @@ struct Scratch {
   float *res_wbuf;      // [8][d_pad] words: the iterate, one copy per die
   uint32_t *res_ctl;    // tickets, barrier counters, flags, abort word
   unsigned long long *res_trace;  // [m][16] time stamps of the resident loop's phases (lpc_resident_trace)
+  unsigned long long *cl_msg, *cl_vec, *cl_scale;  // lpc_cluster.hip: tagged words (cluster_scratch() says how many)
+  uint32_t *cl_ctl;     // [16]
   unsigned long long *iter_slots;  // two sets of [tiles][N][4] statistics exchanged between the workgroups of the
                                    // two-launch inner iteration (all ones = empty)
   uint32_t *touched;    // [N][bitmap_words] sparse inner iteration: one bit per 32-coordinate segment of u^i
@@ -184,14 +186,15 @@ struct lpc_ctx {
   int32_t stat_slots;     // statistic partials per vector
   int32_t cus;            // compute units of the device (256 on MI355X)
   int32_t fold_slices;    // slices of the two-level fold of the snapshot pass's partial rows
-  // form of the small-d dense inner iteration (lpc_tune): 0 = rows, fold, exchange (three launches); 1 = rows,
+  // form of the small-d dense inner iteration (lpc_tune): -1 = not chosen (form 0, or lpc_cluster.hip); 0 = rows, fold, exchange (three launches); 1 = rows,
   // then fold + exchange in one launch whose workgroups wait for each other's statistics; 2 = column tiles fed by
   // partial dot products, then the exchange, which also leaves the next iteration's partial dots (two launches);
   // 3 = all m iterations in one resident launch (lpc_resident.hip)
-  int32_t iter_form = 0;
+  int32_t iter_form = -1;
   bool at_snapshot = false;    // set by lpc_epoch while it issues t = 0 of Alg. 1, where x_0 is the snapshot itself
   bool iter2_capable = false;  // the context's scratch holds what form 1 needs
   bool cols_capable = false;   // ... what form 2 needs
+  bool cluster_capable = false;  // the inner loop fits lpc_cluster.hip
   bool res_capable = false;    // ... what form 3 (the resident inner loop) needs
   bool res_trace_on = false;   // the next resident launches leave their phase time stamps
   uint32_t res_tag = 0;        // tags handed to resident launches so far (each launch takes m + 1)
@@ -260,6 +263,18 @@ size_t resident_stat_doubles(const lpc_ctx *c);
 size_t resident_wbuf_floats(const lpc_ctx *c);
 size_t resident_ctl_words();
 hipError_t launch_resident_epoch(const lpc_ctx *c, const ResidentStep &rs, hipStream_t st);
+
+// The inner loop of narrow problems in one launch (lpc_cluster.hip); rs.w, rs.ysum are not used.  snap_scale: 1 / the sum
+// of the weights of Alg. 2 step 15.  w_snap: the snapshot, in and out.
+struct ClusterScratch {
+  size_t msg, vec, scale;  // 64-bit words
+};
+bool cluster_supported(const lpc_ctx *c);
+ClusterScratch cluster_scratch(const lpc_ctx *c);
+// Iterations t0 .. t1 - 1 of the m; `weight` is that of iteration t0 (Alg. 2 step 15), what lies between two launches
+// of one loop is left in s.w and s.ysum.  n_clipped (or null) is added to.
+hipError_t launch_cluster_epoch(const lpc_ctx *c, const ResidentStep &rs, float *w_snap, double snap_scale, int32_t t0,
+                                int32_t t1, double weight, uint32_t *n_clipped, hipStream_t st);
 
 // CSR GLM passes (lpc_csr.hip)
 int csr_head_columns(int64_t d);

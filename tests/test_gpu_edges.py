@@ -4,7 +4,7 @@ import pytest
 
 import lpc_synth
 from oracle import lpco
-from _common import gpu_context, to_dev
+from _common import gpu_context, oracle_config, oracle_problem, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -96,4 +96,53 @@ def test_entropy_coded_stream_across_workgroups(d, bits, scale):
     ref, ref_total = lpco.huffman_encode(packed_o[0], d, bits, np.array(lens, np.int32))
     assert got == ref_total == total
     assert np.array_equal(stream.cpu().numpy().view(np.uint32), ref)
+    ctx.close()
+
+
+@pytest.mark.parametrize("d,N,B,over", [
+    (1, 2, 3, {}), (31, 3, 5, dict(bits=32)), (32, 1, 1, {}), (33, 4, 16, dict(scheme=lpco.SCHEME_B)),
+    (64, 16, 4, {}), (64, 5, 9, dict(scheme=lpco.SCHEME_C, bits=3)), (65, 8, 64, dict(clip_mode=1, clip=2.0)),
+    (127, 16, 8, dict(algo=lpco.ALGO_ALPC_GC)), (128, 3, 7, dict(bits=8)), (129, 2, 70, dict(bits=5)),
+    (256, 40, 4, dict(scheme=lpco.SCHEME_B, algo=lpco.ALGO_ALPC_GC)), (257, 5, 64, dict(bits=32, algo=lpco.ALGO_ALPC_GC)),
+    (500, 2, 1, dict(scheme=lpco.SCHEME_C)), (512, 6, 65, dict(clip_mode=1, clip=1.0, algo=lpco.ALGO_ALPC_SC)),
+    (1000, 7, 32, dict(bits=7)), (1024, 4, 17, dict(algo=lpco.ALGO_ALPC_GC)), (1024, 63, 2, dict(bits=32)),
+    (1024, 2, 33, {}), (1025, 2, 4, {})])
+def test_narrow_epochs_in_one_launch(d, N, B, over):
+    """Alg. 1-3 on narrow dense data, both sides of every line of the one-launch form: coordinates of w, y and z as the
+    oracle's (up to a few flipped rounding decisions), the same bits from run to run."""
+    over = dict(dict(bits=4, scheme=lpco.SCHEME_A, algo=lpco.ALGO_LPC, clip_mode=0, clip=0.9, m=5, tau2=0.5, L=2.0, N=N, B=B,
+                     sigma=1e-2 if over.get("algo") == lpco.ALGO_ALPC_SC else 0.0), **over)
+    sp = lpc_synth.make("c2" if d % 2 else "c4", n=2048, d=d, N=N, B=B, seed=d)
+    runs = []
+    for _ in range(2):
+        ctx = gpu_context(sp, **over)
+        w, y, z = to_dev(sp.w0), to_dev(sp.w0), to_dev(sp.w0)
+        for s in range(3):
+            ctx.epoch(w, s, y, z)
+        assert ctx.take_device_flags() == 0
+        ctx.close()
+        runs.append([t.cpu().numpy() for t in (w, y, z)])
+    p, _k = oracle_problem(sp)
+    cfg = oracle_config(sp, **over)
+    w, y, z = sp.w0.copy(), sp.w0.copy(), sp.w0.copy()
+    for s in range(3):
+        lpco.epoch(p, cfg, w, s, y, z)
+    for got, want, again in zip(runs[0], (w, y, z), runs[1]):
+        scale = max(np.abs(want).max(), 1e-12)
+        assert (np.abs(got - want) > 2e-5 * scale).mean() <= 1e-2 and np.abs(got - want).max() <= 0.05 * scale
+        assert np.array_equal(got, again)
+
+
+def test_narrow_epoch_that_gives_up_waiting_says_so():
+    from paper_1901_08924_amd import lpc
+    sp = lpc_synth.make("c2", n=2048, d=512, N=4, B=16)
+    ctx = gpu_context(sp, m=4)
+    ctx.tune(lpc.TUNE_SPIN_LIMIT, 0)
+    w = to_dev(sp.w0)
+    ctx.epoch(w, 0)
+    assert ctx.take_device_flags() == lpc.EDEVICE
+    ctx.tune(lpc.TUNE_SPIN_LIMIT, 1 << 15)
+    w = to_dev(sp.w0)
+    ctx.epoch(w, 0)
+    assert ctx.take_device_flags() == 0
     ctx.close()
