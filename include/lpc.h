@@ -339,7 +339,9 @@ lpc_status lpc_debug_gemm(const float *A, const float *B, float *C, int32_t M, i
  *   LPC_TUNE_ITER_FORM:
  *     not set: form 0; on narrow problems (d <= 1024 and a batch that fits the registers of one workgroup, every scheme,
  *       with or without quantization; not while the stream is being captured) all m inner iterations in one cooperative
- *       launch with a workgroup per worker, whose waits LPC_TUNE_SPIN_LIMIT bounds as it does form 3's.
+ *       launch with a workgroup per worker, whose waits LPC_TUNE_SPIN_LIMIT bounds as it does form 3's; on wide problems
+ *       (d <= 24576, B <= 64, b <= 8 or quantization off, as far as the workers' column blocks fit the compute units)
+ *       likewise with a group of workgroups per worker.
  *     0: three launches: the workers' rows (whole rows per workgroup, partial gradient rows out), their fold, the
  *       exchange.
  *     1: two launches: the workers' rows, then fold + exchange in one launch whose workgroups wait, for a bounded

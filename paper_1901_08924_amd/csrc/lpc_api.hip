@@ -176,7 +176,11 @@ size_t layout(lpc_ctx *c, char *base) {
   s.res_ctl = (uint32_t *)take((c->res_capable ? resident_ctl_words() : 4) * sizeof(uint32_t));
   s.res_trace = (unsigned long long *)take((c->res_capable ? (size_t)c->cfg.m * 16 : 1) * sizeof(unsigned long long));
   {
-    const ClusterScratch cs = c->cluster_capable ? cluster_scratch(c) : ClusterScratch{1, 1, 1};
+    ClusterScratch cs = c->cluster_capable ? cluster_scratch(c) : ClusterScratch{1, 1, 1};
+    if (c->columns_capable) {
+      const ColumnScratch w = columns_scratch(c);
+      cs.msg = w.marg + w.stats + w.scale + w.msg + w.vec;
+    }
     s.cl_msg = (unsigned long long *)take(cs.msg * sizeof(unsigned long long));
     s.cl_vec = (unsigned long long *)take(cs.vec * sizeof(unsigned long long));
     s.cl_scale = (unsigned long long *)take(cs.scale * sizeof(unsigned long long));
@@ -268,11 +272,12 @@ lpc_status fill_ctx(lpc_ctx *c, const lpc_problem *p, const lpc_config *cfg) {
   c->cols_capable = fused_exchange_supported(c) && dense_cols_supported(c);
   c->res_capable = resident_supported(c);
   c->cluster_capable = cluster_supported(c);
+  c->columns_capable = !c->cluster_capable && columns_supported(c);
   // measured on MI355X (inner iterations/s, forms 0 / 1 / 2): d = 4096, N = 8, B = 64: 59.9 k / 50.6 k / 47.6 k;
   // d = 8192, N = 16 (+ shared batch), B = 64: 32.3 k / - / 20.2 k.  Form 1 pays about 3 us per trip of the statistics
   // through device-scope atomics; form 2 pays for reading the sampled rows a second time in 512-byte slices (its
   // exchange launch takes 13.4 / 29.3 us against 6.3 / 8.7 us).  Three launches stay the default.
-  c->iter_form = -1;  // not chosen: form 0, or the narrow problems' loop
+  c->iter_form = -1;  // not chosen: form 0, or the inner loop in one launch (lpc_cluster.hip, lpc_columns.hip)
   return LPC_OK;
 }
 
@@ -484,7 +489,7 @@ lpc_status lpc_create(lpc_ctx **ctx_out, const lpc_problem *problem, const lpc_c
     delete c;
     return LPC_EDEVICE;
   }
-  if (c->cluster_capable) {  // the same for the narrow problems' loop
+  if (c->cluster_capable || c->columns_capable) {  // the same for the loops in one launch
     const size_t words = ((char *)(c->s.cl_ctl + 16) - (char *)c->s.cl_msg) / sizeof(uint32_t);
     if (launch_fill_u32(reinterpret_cast<uint32_t *>(c->s.cl_msg), 0u, (int64_t)words, nullptr) != hipSuccess ||
         hipStreamSynchronize(nullptr) != hipSuccess) {
@@ -763,8 +768,8 @@ lpc_status lpc_epoch(lpc_ctx *ctx, float *w_snap, float *y, float *z, uint32_t e
   // communication step 1
   LPC_TRY(full_grad_impl(c, w_snap, s.mu, s.z_snap, nullptr, c->n_full, st));
   const float *zs = (c->n_full == c->n) ? s.z_snap : nullptr;  // margins cached only when every row was visited
-  if (c->cluster_capable && c->iter_form < 0 && !capturing(st)) {
-    // narrow problems: all m inner iterations in one launch, which starts from the snapshot and leaves the next one.
+  if ((c->cluster_capable || c->columns_capable) && c->iter_form < 0 && !capturing(st)) {
+    // all m inner iterations in one launch, which starts from the snapshot and leaves the next one.
     // (Not where the stream is being captured: a replay would repeat the launch's tags.)
     ResidentStep rs{};
     rs.z_snap = zs; rs.mu = s.mu; rs.key = key_of(c, epoch, 0); rs.theta = 1.0f; rs.step = g.eta;
@@ -782,14 +787,18 @@ lpc_status lpc_epoch(lpc_ctx *ctx, float *w_snap, float *y, float *z, uint32_t e
     }
     rs.tag0 = c->res_tag;
     c->res_tag += (uint32_t)g.m + 1u;
+    auto launch = [&](int32_t t0, int32_t t1, double weight, uint32_t *n_clipped) {
+      return c->cluster_capable ? launch_cluster_epoch(c, rs, w_snap, 1.0 / wsum, t0, t1, weight, n_clipped, st)
+                                : launch_columns_epoch(c, rs, w_snap, 1.0 / wsum, t0, t1, weight, tracing, n_clipped, st);
+    };
     if (!tracing) {
       ProfScope ps(c, LPC_PROF_RESIDENT, st);
-      return dev(launch_cluster_epoch(c, rs, w_snap, 1.0 / wsum, 0, g.m, 1.0, nullptr, st));
+      return dev(launch(0, g.m, 1.0, nullptr));
     }
     double weight = 1.0;
     for (int32_t t = 0; t < g.m; ++t) {
       if (c->quant) LPC_TRY_HIP(launch_fill_u32(s.n_clipped, 0u, g.N, st));
-      LPC_TRY_HIP(launch_cluster_epoch(c, rs, w_snap, 1.0 / wsum, t, t + 1, weight, c->quant ? s.n_clipped : nullptr, st));
+      LPC_TRY_HIP(launch(t, t + 1, weight, c->quant ? s.n_clipped : nullptr));
       LPC_TRY(record_iteration(c, t, st));
       weight *= (double)rs.theta;
     }

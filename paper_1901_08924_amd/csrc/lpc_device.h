@@ -276,4 +276,42 @@ __device__ __forceinline__ void tile_dots_finish(const DotsArgs &a, const float 
   }
 }
 
+// ---- tagged words: (value, tag) pairs that cross between workgroups of one launch (lpc_cluster.hip, lpc_columns.hip)
+typedef unsigned long long u64;
+
+__device__ __forceinline__ u64 ld_word(const u64 *p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void st_word(u64 *p, uint32_t v, uint32_t tag) {
+  __hip_atomic_store(p, (u64)v | ((u64)tag << 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The value of a tagged word, once it is there.  Gives up (ok = false) after `limit` polls or when another workgroup has.
+__device__ __forceinline__ uint32_t wait_word(const u64 *p, uint32_t tag, uint32_t limit, const uint32_t *gave_up,
+                                              uint32_t launch_tag, bool &ok) {
+  for (uint32_t k = 0; k < limit; ++k) {
+    const u64 v = ld_word(p);
+    if ((uint32_t)(v >> 32) == tag) return (uint32_t)v;
+    if ((k & 63u) == 63u &&
+        __hip_atomic_load(gave_up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == launch_tag)
+      break;
+  }
+  ok = false;
+  return 0u;
+}
+
+// Sums of four values over the wavefront: lane l gets the sum of v[l & 3] (a fixed order).  A step hands one of a pair of
+// values to the neighbour and takes the neighbour's share of the other, so four sums cost little more than one.
+__device__ __forceinline__ float sum4(const float (&v)[4], int lane) {
+  const bool o1 = lane & 1, o2 = lane & 2;
+  const float a = (o1 ? v[1] : v[0]) + dpp_move<kDppXor1>(o1 ? v[0] : v[1]);
+  const float b = (o1 ? v[3] : v[2]) + dpp_move<kDppXor1>(o1 ? v[2] : v[3]);
+  float s = (o2 ? b : a) + dpp_move<kDppXor2>(o2 ? a : b);
+  s += dpp_move<0x124>(s);  // row_ror:4, row_ror:8: the lanes of a row of 16 that hold the same sum
+  s += dpp_move<0x128>(s);
+  s += __shfl_xor(s, 16, 64);
+  s += __shfl_xor(s, 32, 64);
+  return s;
+}
+
 }  // namespace lpc

@@ -186,7 +186,8 @@ struct lpc_ctx {
   int32_t stat_slots;     // statistic partials per vector
   int32_t cus;            // compute units of the device (256 on MI355X)
   int32_t fold_slices;    // slices of the two-level fold of the snapshot pass's partial rows
-  // form of the small-d dense inner iteration (lpc_tune): -1 = not chosen (form 0, or lpc_cluster.hip); 0 = rows, fold, exchange (three launches); 1 = rows,
+  // form of the small-d dense inner iteration (lpc_tune): -1 = not chosen (form 0, or lpc_cluster.hip,
+  // lpc_columns.hip); 0 = rows, fold, exchange (three launches); 1 = rows,
   // then fold + exchange in one launch whose workgroups wait for each other's statistics; 2 = column tiles fed by
   // partial dot products, then the exchange, which also leaves the next iteration's partial dots (two launches);
   // 3 = all m iterations in one resident launch (lpc_resident.hip)
@@ -195,6 +196,7 @@ struct lpc_ctx {
   bool iter2_capable = false;  // the context's scratch holds what form 1 needs
   bool cols_capable = false;   // ... what form 2 needs
   bool cluster_capable = false;  // the inner loop fits lpc_cluster.hip
+  bool columns_capable = false;  // ... or lpc_columns.hip
   bool res_capable = false;    // ... what form 3 (the resident inner loop) needs
   bool res_trace_on = false;   // the next resident launches leave their phase time stamps
   uint32_t res_tag = 0;        // tags handed to resident launches so far (each launch takes m + 1)
@@ -275,6 +277,16 @@ ClusterScratch cluster_scratch(const lpc_ctx *c);
 // of one loop is left in s.w and s.ysum.  n_clipped (or null) is added to.
 hipError_t launch_cluster_epoch(const lpc_ctx *c, const ResidentStep &rs, float *w_snap, double snap_scale, int32_t t0,
                                 int32_t t1, double weight, uint32_t *n_clipped, hipStream_t st);
+
+// The same of wide problems, workgroups by blocks of columns (lpc_columns.hip); `traced`: the messages are left in s.packed
+// and s.delta.  The words lie one after another from s.cl_msg.
+struct ColumnScratch {
+  size_t marg, stats, scale, msg, vec;  // 64-bit words
+};
+bool columns_supported(const lpc_ctx *c);
+ColumnScratch columns_scratch(const lpc_ctx *c);
+hipError_t launch_columns_epoch(const lpc_ctx *c, const ResidentStep &rs, float *w_snap, double snap_scale, int32_t t0,
+                                int32_t t1, double weight, bool traced, uint32_t *n_clipped, hipStream_t st);
 
 // CSR GLM passes (lpc_csr.hip)
 int csr_head_columns(int64_t d);

@@ -67,7 +67,6 @@ constexpr int kCtlWords = kCtlAbort + 32;
 // dynamic LDS: more than half of a compute unit's, so that no two of these workgroups share one
 constexpr size_t kResLds = 84 * 1024;
 
-typedef unsigned long long u64;
 
 struct ResArgs {
   const float *X;

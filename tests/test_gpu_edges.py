@@ -99,17 +99,7 @@ def test_entropy_coded_stream_across_workgroups(d, bits, scale):
     ctx.close()
 
 
-@pytest.mark.parametrize("d,N,B,over", [
-    (1, 2, 3, {}), (31, 3, 5, dict(bits=32)), (32, 1, 1, {}), (33, 4, 16, dict(scheme=lpco.SCHEME_B)),
-    (64, 16, 4, {}), (64, 5, 9, dict(scheme=lpco.SCHEME_C, bits=3)), (65, 8, 64, dict(clip_mode=1, clip=2.0)),
-    (127, 16, 8, dict(algo=lpco.ALGO_ALPC_GC)), (128, 3, 7, dict(bits=8)), (129, 2, 70, dict(bits=5)),
-    (256, 40, 4, dict(scheme=lpco.SCHEME_B, algo=lpco.ALGO_ALPC_GC)), (257, 5, 64, dict(bits=32, algo=lpco.ALGO_ALPC_GC)),
-    (500, 2, 1, dict(scheme=lpco.SCHEME_C)), (512, 6, 65, dict(clip_mode=1, clip=1.0, algo=lpco.ALGO_ALPC_SC)),
-    (1000, 7, 32, dict(bits=7)), (1024, 4, 17, dict(algo=lpco.ALGO_ALPC_GC)), (1024, 63, 2, dict(bits=32)),
-    (1024, 2, 33, {}), (1025, 2, 4, {})])
-def test_narrow_epochs_in_one_launch(d, N, B, over):
-    """Alg. 1-3 on narrow dense data, both sides of every line of the one-launch form: coordinates of w, y and z as the
-    oracle's (up to a few flipped rounding decisions), the same bits from run to run."""
+def _epochs_as_the_oracle(d, N, B, over):
     over = dict(dict(bits=4, scheme=lpco.SCHEME_A, algo=lpco.ALGO_LPC, clip_mode=0, clip=0.9, m=5, tau2=0.5, L=2.0, N=N, B=B,
                      sigma=1e-2 if over.get("algo") == lpco.ALGO_ALPC_SC else 0.0), **over)
     sp = lpc_synth.make("c2" if d % 2 else "c4", n=2048, d=d, N=N, B=B, seed=d)
@@ -133,9 +123,41 @@ def test_narrow_epochs_in_one_launch(d, N, B, over):
         assert np.array_equal(got, again)
 
 
-def test_narrow_epoch_that_gives_up_waiting_says_so():
+@pytest.mark.parametrize("d,N,B,over", [
+    (1, 2, 3, {}), (31, 3, 5, dict(bits=32)), (32, 1, 1, {}), (33, 4, 16, dict(scheme=lpco.SCHEME_B)),
+    (64, 16, 4, {}), (64, 5, 9, dict(scheme=lpco.SCHEME_C, bits=3)), (65, 8, 64, dict(clip_mode=1, clip=2.0)),
+    (127, 16, 8, dict(algo=lpco.ALGO_ALPC_GC)), (128, 3, 7, dict(bits=8)), (129, 2, 70, dict(bits=5)),
+    (256, 40, 4, dict(scheme=lpco.SCHEME_B, algo=lpco.ALGO_ALPC_GC)), (257, 5, 64, dict(bits=32, algo=lpco.ALGO_ALPC_GC)),
+    (500, 2, 1, dict(scheme=lpco.SCHEME_C)), (512, 6, 65, dict(clip_mode=1, clip=1.0, algo=lpco.ALGO_ALPC_SC)),
+    (1000, 7, 32, dict(bits=7)), (1024, 4, 17, dict(algo=lpco.ALGO_ALPC_GC)), (1024, 63, 2, dict(bits=32)),
+    (1024, 2, 33, {}), (1025, 2, 4, {})])
+def test_narrow_epochs_in_one_launch(d, N, B, over):
+    """Alg. 1-3 on narrow dense data, both sides of every line of the one-launch form: coordinates of w, y and z as the
+    oracle's (up to a few flipped rounding decisions), the same bits from run to run."""
+    _epochs_as_the_oracle(d, N, B, over)
+
+
+# column blocks of 128 to 768 columns, groups of 2 to 32 workgroups, the shared batch's group on a die of its own or spread
+# over what the workers leave; batches of 64 rows are the largest, the last three take the separate launches
+@pytest.mark.parametrize("d,N,B,over", [
+    (1025, 2, 1, {}), (1100, 8, 64, dict(clip_mode=1, clip=2.0)), (1281, 16, 33, dict(algo=lpco.ALGO_ALPC_GC)),
+    (1500, 63, 2, dict(bits=5)), (1536, 9, 7, dict(algo=lpco.ALGO_ALPC_SC)), (2049, 5, 8, dict(scheme=lpco.SCHEME_B)),
+    (2049, 16, 63, dict(scheme=lpco.SCHEME_C, bits=3)), (4096, 8, 64, {}), (4097, 3, 9, dict(bits=32)),
+    (4099, 24, 17, dict(bits=8, algo=lpco.ALGO_ALPC_GC)), (8188, 15, 5, dict(bits=32, algo=lpco.ALGO_ALPC_GC)),
+    (8192, 16, 64, dict(bits=3, clip_mode=1, clip=2.0, algo=lpco.ALGO_ALPC_GC)),
+    (12292, 4, 16, dict(bits=7, scheme=lpco.SCHEME_B, algo=lpco.ALGO_ALPC_GC)),
+    (16388, 8, 10, dict(clip_mode=1, clip=1.0, scheme=lpco.SCHEME_B)), (20000, 8, 64, dict(bits=6)), (24576, 1, 2, {}),
+    (24580, 2, 4, {}), (1100, 2, 65, {}), (1100, 3, 4, dict(bits=9))])
+def test_wide_epochs_in_one_launch(d, N, B, over):
+    """The same by blocks of columns (d > 1024).  L, as the method asks, bounds the squared norms of the rows (1 for the odd
+    widths' rows, about d +- 6 sqrt(d) for the others'): steps of 1/L do not grow a difference in the last bit."""
+    _epochs_as_the_oracle(d, N, B, dict(over, L=2.0 if d % 2 else d + 8.0 * d ** 0.5))
+
+
+@pytest.mark.parametrize("d", [512, 4096])
+def test_epoch_in_one_launch_that_gives_up_waiting_says_so(d):
     from paper_1901_08924_amd import lpc
-    sp = lpc_synth.make("c2", n=2048, d=512, N=4, B=16)
+    sp = lpc_synth.make("c2", n=2048, d=d, N=4, B=16)
     ctx = gpu_context(sp, m=4)
     ctx.tune(lpc.TUNE_SPIN_LIMIT, 0)
     w = to_dev(sp.w0)
