@@ -19,12 +19,17 @@
 // The launch is cooperative: all workgroups are resident together; waits are bounded by LPC_TUNE_SPIN_LIMIT (the first
 // iteration's by 256 times as much: other work on the GPU may hold compute units), a workgroup that gives up says so to the
 // others, and lpc_take_device_flags reports LPC_EDEVICE.
-// What bounds an iteration is the chain of dependent trips (d = 4096, N = 8, B = 64, us: margins 0.9 + 1.6 for the words,
-// gradient 1.0, statistics 0.7 + 1.3, codes 0.6, their words across the dies 4.0, update 0.5).
+// What bounds an iteration: at d = 4096, N = 8, B = 64 the chain of dependent trips (7.0 us: margins 0.8 + 1.2 for the
+// words, gradient 0.4, statistics 0.7 + 1.0, codes 0.5, their words across the dies 1.5, update 0.4); at d = 20000 the rows
+// (41 MB in 10 us, paced) and that memory rests while margins are formed.
 // Measured on MI355X, snapshot pass (n = 16384) and 128 iterations, separate launches -> this kernel, us per iteration:
-//   d = 1500, N = 2, B = 16: 13.6 -> 5.2    d = 1500, N = 16, B = 64: 16.0 -> 9.1    d = 4096, N = 8, B = 64: 16.2 -> 10.8
-//   d = 12000, N = 16, B = 40: 30.3 -> 16.8    d = 20000, N = 8, B = 64: 29.0 -> 17.7    d = 20000, N = 2, B = 8: 19.1 -> 11.2
-//   d = 8192, N = 16, B = 64: Alg. 3 21.3 -> 16.6, scheme (b) 34.7 -> 17.4
+//   d = 1500, N = 2, B = 16: 13.6 -> 4.6    d = 1500, N = 16, B = 64: 16.0 -> 7.2    d = 4096, N = 8, B = 64: 16.2 -> 7.3
+//   d = 12000, N = 16, B = 40: 30.3 -> 14.0    d = 20000, N = 8, B = 64: 29.0 -> 15.5    d = 20000, N = 2, B = 8: 19.1 -> 9.2
+//   d = 8192, N = 16, B = 64: Alg. 3 21.3 -> 12.8, scheme (b) 34.7 -> 13.7
+// Steps that paid: all words of a wait requested together (waiting for them one after another: field words 3.4 us instead
+// of 1.5), rows requested after the barrier and paced (21 % at d = 12000), blocks of 256 instead of 128 columns at d = 4096
+// (25 %), the random words drawn while the rows' wavefronts work.  Rows of t + 2 touched ahead to have them in the L2: 10 %
+// slower, the touches queue with the words.
 #include <hip/hip_runtime.h>
 
 #include "lpc_device.h"
@@ -59,6 +64,9 @@ struct ColumnArgs {
   double theta, weight;
 };
 
+// the operand of s_waitcnt that waits until at most n vector loads are on their way
+constexpr int vmcnt_only(int n) { return n > 63 ? 0xcf7f : (n & 15) | (7 << 4) | (15 << 8) | ((n >> 4) << 14); }
+
 enum : int { kPlain = 0, kOwnScale = 1, kSharedScale = 2 };  // as in lpc_cluster.hip
 
 // K: 64-column chunks of a block; Q: the messages; ALPC: Alg. 2 and 3.
@@ -79,6 +87,11 @@ __global__ __launch_bounds__(kCoThreads) void column_epoch_kernel(ColumnArgs a) 
   }
   touch_kernel_arguments<(int)(sizeof(ColumnArgs))>();
   constexpr int C = 64 * K, RG = kColRows / 4;
+  // Rows that a wavefront has on their way.  The service wavefronts' words queue behind them in the compute unit: with all
+  // eight requested at once a trip of the statistics takes 4 to 5 us.  us per iteration with 1, 2, 4, 8 on their way:
+  // d = 4096, N = 8 (K = 4): 7.3, 7.4, 7.5, 7.8; d = 1500, N = 2, B = 16: 4.8, 4.6, 4.6, 5.1; d = 12000, N = 12 (K = 12):
+  // 14.5, 15.3, 17.9, 18.2
+  constexpr int kFlight = K <= 4 ? 2 : 1;
   __shared__ __attribute__((aligned(16))) float xs[C], part[kColRowWaves][C];
   __shared__ uint32_t rid[2][64], own[C / 2];
   __shared__ float ysh[2][64], ssh[2][64];
@@ -135,6 +148,15 @@ __global__ __launch_bounds__(kCoThreads) void column_epoch_kernel(ColumnArgs a) 
   }
   __syncthreads();
 
+  // `loads` requests all the words that a thread waits for and says whether they are there; one trip for all of them
+  auto poll = [&](uint32_t limit, bool &ok, auto loads) {
+    if (!ok) return;
+    for (uint32_t k = 0; k < limit; ++k) {
+      if (loads()) return;
+      if ((k & 63u) == 63u && __hip_atomic_load(a.ctl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == a.tag0 + 1u) break;
+    }
+    ok = false;
+  };
   bool gave_up = false;
   if (!service) {
     float x[kColRows][K];
@@ -148,6 +170,11 @@ __global__ __launch_bounds__(kCoThreads) void column_epoch_kernel(ColumnArgs a) 
 #pragma unroll
         for (int k = 0; k < K; ++k)
           x[i][k] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, 4u * lane + 256u * k, 0, 0));
+        if (i + 1 < kColRows && i + 1 >= kFlight) {  // at most kFlight rows on their way
+          __builtin_amdgcn_sched_barrier(0);
+          __builtin_amdgcn_s_waitcnt(vmcnt_only(K * (kFlight - 1)));
+          __builtin_amdgcn_sched_barrier(0);
+        }
       }
     };
     request(a.it0);
@@ -184,25 +211,28 @@ __global__ __launch_bounds__(kCoThreads) void column_epoch_kernel(ColumnArgs a) 
           st_word(ex + (int64_t)(q * a.G + g) * 4 + lane, __builtin_bit_cast(uint32_t, z), tag);
       }
       float coef[RG];
+      u64 f[RG][2];
+      {
+        const bool in0 = (lane >> 2) < a.G, in1 = (lane >> 2) + 16 < a.G;  // G <= 32
+        poll(limit, ok, [&] {
+          bool all = true;
+#pragma unroll
+          for (int q = 0; q < RG; ++q) {
+            const u64 *from = ex + (int64_t)q * a.G * 4 + lane;
+            f[q][0] = row_live[q] && in0 ? ld_word(from) : (u64)tag << 32;
+            f[q][1] = row_live[q] && in1 ? ld_word(from + 64) : (u64)tag << 32;
+          }
+#pragma unroll
+          for (int q = 0; q < RG; ++q) all = all && (uint32_t)(f[q][0] >> 32) == tag && (uint32_t)(f[q][1] >> 32) == tag;
+          return all;
+        });
+      }
 #pragma unroll
       for (int q = 0; q < RG; ++q) {
-        const u64 *from = ex + (int64_t)q * a.G * 4 + lane;
-        const int b0 = lane >> 2, b1 = b0 + 16;  // G <= 32
-        float z = 0.0f;
-        if (row_live[q] && b0 < a.G) {
-          const u64 f0 = ld_word(from), f1 = b1 < a.G ? ld_word(from + 64) : 0ull;
-          z = __builtin_bit_cast(float, (uint32_t)(f0 >> 32) == tag
-                                            ? (uint32_t)f0
-                                            : wait_word(from, tag, limit, a.ctl, a.tag0 + 1u, ok));
-          if (b1 < a.G)
-            z += __builtin_bit_cast(float, (uint32_t)(f1 >> 32) == tag || !ok
-                                               ? (uint32_t)f1
-                                               : wait_word(from + 64, tag, limit, a.ctl, a.tag0 + 1u, ok));
-        }
+        float z = __builtin_bit_cast(float, (uint32_t)f[q][0]) + __builtin_bit_cast(float, (uint32_t)f[q][1]);
         z += dpp_move<0x124>(z);  // row_ror:4, row_ror:8: the lanes of a row of 16 that hold the same batch position
         z += dpp_move<0x128>(z);
-        z += __shfl_xor(z, 16, 64);
-        z += __shfl_xor(z, 32, 64);
+        z = rows_sum(z);
         // (x_0 of Alg. 1 is the snapshot: its differences are exactly zero)
         const float diff = loss_slope(a.loss, z, yr[q]) - sr[q];
         coef[q] = row_live[q] && (ALPC || t > 0) ? diff : 0.0f;
@@ -219,8 +249,8 @@ __global__ __launch_bounds__(kCoThreads) void column_epoch_kernel(ColumnArgs a) 
       }
 #pragma unroll
       for (int k = 0; k < K; ++k) part[wave][lane + 64 * k] = acc[k];
-      if (t + 1 < a.it1) request(t + 1);  // they arrive while this iteration goes on
       __syncthreads();
+      if (t + 1 < a.it1) request(t + 1);  // they arrive while this iteration goes on
       __syncthreads();
       if (fail_sh[par] != 0u) { gave_up = true; break; }  // uniform: written before the barrier, next at t + 2
     }
@@ -237,17 +267,14 @@ __global__ __launch_bounds__(kCoThreads) void column_epoch_kernel(ColumnArgs a) 
       k.iter = (uint32_t)t;
       rnd = stream_block(k, kTagQuant, (uint32_t)v, (uint32_t)(j >> 2));
     };
-    if (quantizes) random_words(a.it0);
     for (int t = a.it0; t < a.it1; ++t) {
       const int par = t & 1;
       const uint32_t tag = a.tag0 + (uint32_t)t + 1u;
       const uint32_t limit = t == a.it0 ? (a.spin_limit > 0xffffffu ? ~0u : a.spin_limit * 256u) : a.spin_limit;
       bool ok = true;
-      auto value = [&](u64 first, const u64 *p) {
-        if ((uint32_t)(first >> 32) == tag) return (uint32_t)first;
-        return ok ? wait_word(p, tag, limit, a.ctl, a.tag0 + 1u, ok) : 0u;
-      };
+      auto there = [&](u64 w) { return (uint32_t)(w >> 32) == tag; };
       u64 *out = a.msg + ((int64_t)par * a.G + g) * msg_block;
+      if (quantizes) random_words(t);  // while the rows' wavefronts are at work
       __syncthreads();
       // ---- u^i (columns past the problem's hold zeros) and its statistics
       float u4[4] = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -292,28 +319,44 @@ __global__ __launch_bounds__(kCoThreads) void column_epoch_kernel(ColumnArgs a) 
           float am = 0.0f;
           sum = sumsq = 0.0;
           for (int e = lane; e < n_part; e += 64) {
-            u64 first[5];
+            u64 h[5] = {};
+            poll(limit, ok, [&] {
+              bool all = true;
 #pragma unroll
-            for (int i = 0; i < 5; ++i) first[i] = i == 0 || csigma ? ld_word(st + i * n_part + e) : 0ull;
-            am = fmaxf(am, __builtin_bit_cast(float, value(first[0], st + e)));
+              for (int i = 0; i < 5; ++i)
+                if (i == 0 || csigma) h[i] = ld_word(st + i * n_part + e);
+#pragma unroll
+              for (int i = 0; i < 5; ++i) all = all && (there(h[i]) || (i > 0 && !csigma));
+              return all;
+            });
+            am = fmaxf(am, __builtin_bit_cast(float, (uint32_t)h[0]));
             if (csigma) {
-              uint32_t h[4];
-#pragma unroll
-              for (int i = 0; i < 4; ++i) h[i] = value(first[1 + i], st + (1 + i) * n_part + e);
-              sum += __builtin_bit_cast(double, (u64)h[0] | ((u64)h[1] << 32));
-              sumsq += __builtin_bit_cast(double, (u64)h[2] | ((u64)h[3] << 32));
+              sum += __builtin_bit_cast(double, (h[1] & 0xffffffffull) | (h[2] << 32));
+              sumsq += __builtin_bit_cast(double, (h[3] & 0xffffffffull) | (h[4] << 32));
             }
           }
           am = wave_max(am);
           if (csigma) { sum = wave_sum(sum); sumsq = wave_sum(sumsq); }
-          // Sec. 3.2, eq. (3)
-          QParams q = make_qparams(a.qs, (double)am, sum, sumsq, a.d);
+          // Sec. 3.2, eq. (3); the reciprocal is the correctly rounded one, as 1/double(delta) rounded to float is
+          QParams q{0.0f, 0.0f, 0.0f, 0.0f};
+          if (csigma) {
+            q = make_qparams(a.qs, (double)am, sum, sumsq, a.d);
+          } else {
+            q.thresh = a.qs.clip * am;
+            const float delta = q.thresh / hi_q, rd = 1.0f / delta;
+            const bool live = delta > 0.0f && isfinite(rd);
+            q.delta = live ? delta : 0.0f;
+            q.rdelta = live ? rd : 0.0f;
+          }
           if constexpr (Q == kSharedScale) {  // the largest of the N scale factors
             u64 *sc = a.scale_ex + ((int64_t)par * a.G + g) * a.N;
             if (q_c == 0) st_word(sc + v, __builtin_bit_cast(uint32_t, q.delta), tag);
             float dmax = 0.0f;
-            for (int i = lane; i < a.N; i += 64)
-              dmax = fmaxf(dmax, __builtin_bit_cast(float, value(ld_word(sc + i), sc + i)));
+            if (lane < a.N) {  // N <= 64
+              u64 w = 0;
+              poll(limit, ok, [&] { w = ld_word(sc + lane); return there(w); });
+              dmax = __builtin_bit_cast(float, (uint32_t)w);
+            }
             dmax = wave_max(dmax);
             const float rd = 1.0f / dmax;
             const bool live = dmax > 0.0f && isfinite(rd);
@@ -361,40 +404,54 @@ __global__ __launch_bounds__(kCoThreads) void column_epoch_kernel(ColumnArgs a) 
           }
         }
       }
-      // ---- while the words travel: the random words of the next codes, the rows of t + 2
-      if (quantizes && t + 1 < a.it1) random_words(t + 1);
+      // ---- while the words travel: the rows of t + 2
       if (draws && t + 2 < a.it1) draw(t + 2);
       // ---- the receiver (eq. (4), or the integer sums of schemes (b), (c))
-      if (holds) {
+      if (256 * q_w < C) {  // whole wavefronts: a lane without columns reads the first ones' words
+        const int q_r = holds ? q_c : 0;
         float avg[4] = {0.0f, 0.0f, 0.0f, 0.0f};
         if constexpr (Q == kPlain) {
-          for (int i = 0; i < a.N; ++i) {
-            const u64 *p = out + (int64_t)i * C + q_c;
-            u64 first[4];
+          for (int i0 = 0; i0 < a.N; i0 += 2) {
+            const u64 *p = out + (int64_t)i0 * C + q_r;
+            const int64_t next = i0 + 1 < a.N ? C : 0;
+            u64 f[8] = {};
+            poll(limit, ok, [&] {
+              bool all = true;
 #pragma unroll
-            for (int c = 0; c < 4; ++c) first[c] = ld_word(p + c);
+              for (int c = 0; c < 8; ++c) f[c] = ld_word(p + (c & 3) + (c < 4 ? 0 : next));
 #pragma unroll
-            for (int c = 0; c < 4; ++c) avg[c] += __builtin_bit_cast(float, value(first[c], p + c));
+              for (int c = 0; c < 8; ++c) all = all && there(f[c]);
+              return all;
+            });
+#pragma unroll
+            for (int c = 0; c < 4; ++c) avg[c] += __builtin_bit_cast(float, (uint32_t)f[c]);
+            if (next) {
+#pragma unroll
+              for (int c = 0; c < 4; ++c) avg[c] += __builtin_bit_cast(float, (uint32_t)f[4 + c]);
+            }
           }
 #pragma unroll
           for (int c = 0; c < 4; ++c) avg[c] *= inv_n;
         } else {
           int32_t isum[4] = {0, 0, 0, 0};
-          float delta = 0.0f;
-          const u64 *p = out + (q_c >> 2), *pd = out + (int64_t)a.N * C;
+          const u64 *p = out + (q_r >> 2), *pd = out + (int64_t)a.N * C;
+          u64 fd = 0;  // a lane holds a worker's scale factor (N <= 64)
           for (int i0 = 0; i0 < a.N; i0 += 8) {
-            u64 first[8], fd[8];
+            u64 f[8] = {};
+            poll(limit, ok, [&] {
+              bool all = true;
+              if (i0 == 0) fd = ld_word(pd + (lane < a.N ? lane : 0));
 #pragma unroll
-            for (int r = 0; r < 8; ++r) {
-              const int i = i0 + r < a.N ? i0 + r : a.N - 1;
-              first[r] = ld_word(p + (int64_t)i * C);
-              fd[r] = Q == kOwnScale || i == 0 ? ld_word(pd + i) : 0ull;
-            }
+              for (int r = 0; r < 8; ++r) f[r] = ld_word(p + (int64_t)(i0 + r < a.N ? i0 + r : a.N - 1) * C);
+#pragma unroll
+              for (int r = 0; r < 8; ++r) all = all && there(f[r]);
+              return all && there(fd);
+            });
 #pragma unroll
             for (int r = 0; r < 8; ++r) {
               if (i0 + r < a.N) {
-                const uint32_t field = value(first[r], p + (int64_t)(i0 + r) * C);
-                if (Q == kOwnScale || i0 + r == 0) delta = __builtin_bit_cast(float, value(fd[r], pd + i0 + r));
+                const uint32_t field = (uint32_t)f[r];
+                const float delta = read_lane(__builtin_bit_cast(float, (uint32_t)fd), i0 + r);
 #pragma unroll
                 for (int c = 0; c < 4; ++c) {
                   const int32_t code = (int32_t)((field >> (c * a.bits)) << (32 - a.bits)) >> (32 - a.bits);
@@ -404,6 +461,7 @@ __global__ __launch_bounds__(kCoThreads) void column_epoch_kernel(ColumnArgs a) 
               }
             }
           }
+          const float delta = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane((int)(uint32_t)fd));
 #pragma unroll
           for (int c = 0; c < 4; ++c) {
             if constexpr (Q == kOwnScale) {
@@ -425,12 +483,18 @@ __global__ __launch_bounds__(kCoThreads) void column_epoch_kernel(ColumnArgs a) 
         }
         float uh[4] = {0.0f, 0.0f, 0.0f, 0.0f};
         if constexpr (ALPC) {
-          const u64 *p = a.vec + ((int64_t)par * a.G + g) * C + q_c;
-          u64 first[4];
+          const u64 *p = a.vec + ((int64_t)par * a.G + g) * C + q_r;
+          u64 f[4] = {};
+          poll(limit, ok, [&] {
+            bool all = true;
 #pragma unroll
-          for (int c = 0; c < 4; ++c) first[c] = ld_word(p + c);
+            for (int c = 0; c < 4; ++c) f[c] = ld_word(p + c);
 #pragma unroll
-          for (int c = 0; c < 4; ++c) uh[c] = __builtin_bit_cast(float, value(first[c], p + c));
+            for (int c = 0; c < 4; ++c) all = all && there(f[c]);
+            return all;
+          });
+#pragma unroll
+          for (int c = 0; c < 4; ++c) uh[c] = __builtin_bit_cast(float, (uint32_t)f[c]);
         }
         // ---- the update
 #pragma unroll
@@ -446,7 +510,7 @@ __global__ __launch_bounds__(kCoThreads) void column_epoch_kernel(ColumnArgs a) 
             x4[c] = prox_scalar(x4[c], avg[c] + mu4[c], a.step, a.thr, a.shrink);
           }
         }
-        *reinterpret_cast<float4 *>(&xs[q_c]) = make_float4(x4[0], x4[1], x4[2], x4[3]);
+        if (holds) *reinterpret_cast<float4 *>(&xs[q_c]) = make_float4(x4[0], x4[1], x4[2], x4[3]);
       }
       if constexpr (ALPC) weight *= a.theta;
       if (!ok) fail_sh[par] = 1u;
@@ -486,20 +550,22 @@ struct Shape {
 };
 
 // The launch for a context, or k = 0 where the kernel does not apply: the batch must fit the registers of the row
-// wavefronts (64 rows), four codes a word (b <= 8), and the groups the dies.  The narrowest block that fits: more
-// workgroups share the rows and the words to read grow slower than that.
+// wavefronts (64 rows), four codes a word (b <= 8), and the groups the dies.
+// Few workgroups wait for fewer words, many have fewer rows to fetch.  Up to 16 workgroups per group and 24 per die the
+// narrowest block is the fastest (us per iteration by K = 4, 6, 8, 10, 12: d = 4096, N = 8, B = 64: 7.6, 8.3, 8.3, -, -;
+// d = 5000, N = 16, B = 30: -, 8.4, 7.9, 8.1, 8.2), beyond that the widest is (d = 8192, N = 8: 11.8, 10.5, 9.8, 9.8, 9.9; Alg. 3,
+// N = 16: -, -, -, 13.6, 12.8; d = 20000, N = 8: -, -, -, 16.5, 15.5; K = 2 lost everywhere: d = 4096: 10.2).
 Shape shape_of(const lpc_ctx *c) {
   Shape s{};
   if (c->csr || c->mlp || !c->grad_ok || c->n_full != c->n || c->n >= ((int64_t)1 << 31)) return s;
   if (c->cfg.B > kColRowWaves * kColRows || c->cfg.N > 64 || c->cfg.m < 1 || (c->quant && c->cfg.bits > 8)) return s;
-  if (c->d > 64 * 12 * 32) return s;
   const int N = c->cfg.N, alpc = c->cfg.algo != LPC_ALGO_LPC ? 1 : 0;
-  for (int k : {2, 4, 6, 8, 9, 10, 12}) {
+  for (int k : {4, 6, 8, 10, 12}) {
     const int G = (int)((c->d + 64 * k - 1) / (64 * k));
     const bool extra = alpc && N % kDies == 0;  // the shared batch's group spread over what the workers leave
     const int per_die = (N + (extra ? 0 : alpc) + kDies - 1) / kDies;
     const int slots = per_die * G + (extra ? (G + kDies - 1) / kDies : 0);
-    if (G > 32 || slots * kDies > c->cus) continue;
+    if (k < 12 ? G > 16 || slots > 24 : G > 32 || slots * kDies > c->cus) continue;
     s.k = k; s.G = G; s.per_die = per_die; s.slots = slots;
     return s;
   }
@@ -558,7 +624,7 @@ hipError_t launch_columns_epoch(const lpc_ctx *c, const ResidentStep &rs, float 
     fn = rs.alpc ? reinterpret_cast<const void *>(&column_epoch_kernel<K_, Q_, true>)            \
                  : reinterpret_cast<const void *>(&column_epoch_kernel<K_, Q_, false>);
 #define LPC_COLUMNS(K_) LPC_COLUMNS_Q(K_, kPlain) LPC_COLUMNS_Q(K_, kOwnScale) LPC_COLUMNS_Q(K_, kSharedScale)
-  LPC_COLUMNS(2) LPC_COLUMNS(4) LPC_COLUMNS(6) LPC_COLUMNS(8) LPC_COLUMNS(9) LPC_COLUMNS(10) LPC_COLUMNS(12)
+  LPC_COLUMNS(4) LPC_COLUMNS(6) LPC_COLUMNS(8) LPC_COLUMNS(10) LPC_COLUMNS(12)
 #undef LPC_COLUMNS
 #undef LPC_COLUMNS_Q
   if (!fn) return hipErrorInvalidValue;

@@ -300,6 +300,16 @@ __device__ __forceinline__ uint32_t wait_word(const u64 *p, uint32_t tag, uint32
   return 0u;
 }
 
+// The sum over the four rows of 16 lanes, in every lane: (row 0 + row 1) + (row 2 + row 3), without a trip through LDS
+__device__ __forceinline__ float rows_sum(float v) {
+  const uint32_t b = __builtin_bit_cast(uint32_t, v);
+  const auto p = __builtin_amdgcn_permlane16_swap(b, b, false, false);  // rows 0 0 2 2 and 1 1 3 3
+  const uint32_t h = __builtin_bit_cast(uint32_t, __builtin_bit_cast(float, (uint32_t)p[0]) +
+                                                      __builtin_bit_cast(float, (uint32_t)p[1]));
+  const auto q = __builtin_amdgcn_permlane32_swap(h, h, false, false);
+  return __builtin_bit_cast(float, (uint32_t)q[0]) + __builtin_bit_cast(float, (uint32_t)q[1]);
+}
+
 // Sums of four values over the wavefront: lane l gets the sum of v[l & 3] (a fixed order).  A step hands one of a pair of
 // values to the neighbour and takes the neighbour's share of the other, so four sums cost little more than one.
 __device__ __forceinline__ float sum4(const float (&v)[4], int lane) {
@@ -309,9 +319,7 @@ __device__ __forceinline__ float sum4(const float (&v)[4], int lane) {
   float s = (o2 ? b : a) + dpp_move<kDppXor2>(o2 ? a : b);
   s += dpp_move<0x124>(s);  // row_ror:4, row_ror:8: the lanes of a row of 16 that hold the same sum
   s += dpp_move<0x128>(s);
-  s += __shfl_xor(s, 16, 64);
-  s += __shfl_xor(s, 32, 64);
-  return s;
+  return rows_sum(s);
 }
 
 }  // namespace lpc
