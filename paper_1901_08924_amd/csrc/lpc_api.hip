@@ -272,7 +272,11 @@ lpc_status fill_ctx(lpc_ctx *c, const lpc_problem *p, const lpc_config *cfg) {
   c->cols_capable = fused_exchange_supported(c) && dense_cols_supported(c);
   c->res_capable = resident_supported(c);
   c->cluster_capable = cluster_supported(c);
-  c->columns_capable = !c->cluster_capable && columns_supported(c);
+  // us per iteration, lpc_cluster.hip / lpc_columns.hip: d = 300, N = 8, B = 64: 5.4 / 5.5; d = 260, N = 2, B = 9: 5.0 / 4.6;
+  // d = 512, N = 8, B = 64: 6.0 / 5.4; d = 700, N = 4, B = 20: 6.7 / 4.7; d = 1000, N = 16, B = 32: 9.5 / 5.9; up to d = 256
+  // a column block would hold all columns
+  c->columns_capable = (c->d > 256 || !c->cluster_capable) && columns_supported(c);
+  if (c->columns_capable) c->cluster_capable = false;
   // measured on MI355X (inner iterations/s, forms 0 / 1 / 2): d = 4096, N = 8, B = 64: 59.9 k / 50.6 k / 47.6 k;
   // d = 8192, N = 16 (+ shared batch), B = 64: 32.3 k / - / 20.2 k.  Form 1 pays about 3 us per trip of the statistics
   // through device-scope atomics; form 2 pays for reading the sampled rows a second time in 512-byte slices (its

@@ -1,5 +1,5 @@
-// The inner loop of an epoch (Alg. 1 steps 5-11; Alg. 2 steps 5-15) in one launch for narrow dense problems (d <= 1024,
-// a worker's batch small enough for the registers of one workgroup): a workgroup per worker, as in the paper, or one
+// The inner loop of an epoch (Alg. 1 steps 5-11; Alg. 2 steps 5-15) in one launch for narrow dense problems (d <= 256, or
+// d <= 1024 with more than 8 bits; a worker's batch small enough for the registers of one workgroup): a workgroup per worker, as in the paper, or one
 // workgroup for all of them where even that is more than the work needs.
 //
 // Such an iteration moves tens or hundreds of KB and takes a few thousand instructions; as three launches (rows, fold,

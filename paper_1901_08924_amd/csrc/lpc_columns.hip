@@ -1,4 +1,4 @@
-// The inner loop of an epoch (Alg. 1 steps 5-11; Alg. 2 steps 5-15) in one launch for wide dense problems: a worker is a
+// The inner loop of an epoch (Alg. 1 steps 5-11; Alg. 2 steps 5-15) in one launch for dense problems past d = 256: a worker is a
 // group of G workgroups, each with a block of C = 64 K columns of the worker's rows, of its u^i and of the iterate.
 //
 // As separate launches an iteration is 15 to 29 us (rows, fold, exchange; five launches past d = 16384) for 8 to 41 MB of
