@@ -882,12 +882,10 @@ lpc_status lpc_epoch(lpc_ctx *ctx, float *w_snap, float *y, float *z, uint32_t e
           LPC_TRY_HIP(launch_sparse_receive_prox(c, s.mu, g.eta, s.w, st));
         } else {
           // schemes (b), (c): one scale factor for all workers, integer sums at the receiver (and eq. (5) for (c));
-          // the receiver is the dense one, so the consumed words and the bitmap are cleared by fills
+          // the receiver is the dense one, so the consumed words and the bitmap are cleared by the update
           LPC_TRY_HIP(launch_sparse_quantize(c, key, true, st));
           LPC_TRY_HIP(launch_dequantize_shared(c, s.packed, s.delta, g.scheme == LPC_SCHEME_C, key, s.u_avg, st));
-          LPC_TRY_HIP(launch_prox(c, s.w, s.u_avg, s.mu, g.eta, st));
-          LPC_TRY_HIP(launch_fill_u32(s.packed, 0u, (int64_t)g.N * c->W, st));
-          LPC_TRY_HIP(launch_fill_u32(s.touched, 0u, (int64_t)g.N * c->bitmap_words, st));
+          LPC_TRY_HIP(launch_prox(c, s.w, s.u_avg, s.mu, g.eta, st, true));
         }
       } else if (two) {
         // two launches per inner iteration: rows; fold + exchange + prox
@@ -1050,10 +1048,8 @@ lpc_status lpc_epoch(lpc_ctx *ctx, float *w_snap, float *y, float *z, uint32_t e
       al.y = y; al.z = z; al.ysum = s.ysum; al.x_next = s.w;
       al.step_y = step_y; al.alpha = ap.alpha; al.weight = (float)weight; al.tau1 = ap.tau1; al.tau2 = ap.tau2;
       al.first = t == 0 ? 1 : 0;
+      // (the consumed words and all bitmaps, the shared batch's included, start the next iteration at zero)
       LPC_TRY_HIP(launch_alpc_update_couple(c, al, st));
-      // the consumed words and all bitmaps (the shared batch's included) start the next iteration at zero
-      LPC_TRY_HIP(launch_fill_u32(s.packed, 0u, (int64_t)g.N * c->W, st));
-      LPC_TRY_HIP(launch_fill_u32(s.touched, 0u, (int64_t)nvec * c->bitmap_words, st));
       wsum += weight;
       weight *= (double)ap.theta;
     }

@@ -1723,6 +1723,8 @@ __global__ __launch_bounds__(THREADS) void fused_iter_kernel(IterArgs ia) {
 // REQUANT the average is stochastically rounded once more onto dom(delta, b) (eq. (5)); it lies inside
 // the hull, so this second rounding is unbiased.
 
+constexpr int kSharedThreads = 64;
+
 // all vectors take the largest delta among them
 __global__ void share_delta_kernel(QParams *qp, int32_t nvec, QuantSpec qs, float *delta_out) {
   if (blockIdx.x != 0 || threadIdx.x != 0) return;
@@ -1733,75 +1735,71 @@ __global__ void share_delta_kernel(QParams *qp, int32_t nvec, QuantSpec qs, floa
   if (delta_out) delta_out[0] = q.delta;
 }
 
-template <int B>
-__device__ __forceinline__ void unpack_add(const uint32_t *__restrict__ src, int32_t (&acc)[32]) {
-  uint32_t words[B];
-#pragma unroll
-  for (int i = 0; i < B; ++i) words[i] = src[i];
-#pragma unroll
-  for (int c = 0; c < 32; ++c) {
-    const int p = c * B, wi = p >> 5, sh = p & 31;
-    uint32_t field = words[wi] >> sh;
-    if (sh + B > 32) field |= words[wi + 1] << (32 - sh);
-    acc[c] += (int32_t)(field << (32 - B)) >> (32 - B);
-  }
-}
-
+// A thread takes four coordinates (one block of random words, a 16-byte store): neighbouring threads share words, but
+// d = 150,001 makes 586 workgroups of 64 where a 32-coordinate segment per thread made 19 of 256.  Two workers are
+// requested together.  us a launch, segment per thread -> this: d = 150,001, N = 8, b = 4: 6.2 -> see the end of the line
 template <int B, bool REQUANT>
-__global__ __launch_bounds__(kThreads) void dequantize_shared_kernel(const uint32_t *__restrict__ packed, int64_t W,
-                                                                     const float *__restrict__ delta, int32_t N,
-                                                                     int64_t d, int64_t d_pad, StreamKey key,
-                                                                     float *__restrict__ u_avg) {
-  __shared__ __attribute__((aligned(16))) float tile[kThreads * kPitch];
-  const int tid = threadIdx.x;
-  const int64_t tile_base = (int64_t)blockIdx.x * kTileFloats;
-  const int64_t seg = tile_base / kSegFloats + tid;
-  if (seg * kSegFloats < d_pad) {
-    int32_t acc[32];
+__global__ __launch_bounds__(kSharedThreads) void dequantize_shared_kernel(const uint32_t *__restrict__ packed,
+                                                                           int64_t W, const float *__restrict__ delta,
+                                                                           int32_t N, int64_t d, StreamKey key,
+                                                                           float *__restrict__ u_avg) {
+  const int64_t q = (int64_t)blockIdx.x * kSharedThreads + threadIdx.x, j = 4 * q;
+  if (j >= d) return;
+  constexpr int kBits = 4 * B;                                         // of this thread's codes, in kSpan words
+  constexpr int kSpan = 32 % kBits == 0 ? 1 : (kBits == 64 ? 2 : (kBits <= 36 ? 2 : 3));
+  const int64_t wi = q * kBits >> 5;
+  const int sh = (int)(q * kBits & 31);
+  const uint32_t *src = packed + wi;
+  int64_t next[kSpan];                                                 // the last message ends with its last word
 #pragma unroll
-    for (int c = 0; c < 32; ++c) acc[c] = 0;
-    for (int32_t i = 0; i < N; ++i) unpack_add<B>(packed + (int64_t)i * W + seg * B, acc);
-    const float dl = delta[0];
-    const float inv_n = 1.0f / (float)N;
-    const float hi = (float)((1 << (B - 1)) - 1), lo = -(float)(1 << (B - 1));
+  for (int k = 0; k < kSpan; ++k) next[k] = wi + k < W ? k : W - 1 - wi;
+  int32_t acc[4] = {0, 0, 0, 0};
+  const float dl = delta[0];
+  auto add = [&](const uint32_t (&w)[kSpan]) {
+    uint64_t lo = w[0];
+    if (kSpan > 1) lo |= (uint64_t)w[kSpan > 1 ? 1 : 0] << 32;
+    uint64_t field = lo >> sh;
+    if (kSpan > 2 && sh) field |= (uint64_t)w[kSpan > 2 ? 2 : 0] << (64 - sh);
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      float out[4];
-      uint32_t rnd[4] = {0u, 0u, 0u, 0u};
-      if (REQUANT) {
-        const Philox4 blk = stream_block(key, kTagRequant, 0u, (uint32_t)(seg * 8 + k));
-        rnd[0] = blk.x; rnd[1] = blk.y; rnd[2] = blk.z; rnd[3] = blk.w;
-      }
+    for (int c = 0; c < 4; ++c) acc[c] += (int32_t)((uint32_t)(field >> (c * B)) << (32 - B)) >> (32 - B);
+  };
+  for (int32_t i0 = 0; i0 < N; i0 += 4) {
+    uint32_t w[4][kSpan];
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const float mean_code = (float)acc[4 * k + t] * inv_n;  // position of the average on the grid
-        if (!REQUANT) {
-          out[t] = dl * mean_code;
-        } else {
-          float s = mean_code * 1.0f;
-          s = fminf(fmaxf(s, lo), hi);
-          const float base = floorf(s);
-          const float frac = s - base;
-          const float unif = (float)(rnd[t] >> 8) * 0x1.0p-24f;
-          out[t] = dl * (float)((int32_t)base + ((unif < frac) ? 1 : 0));
-        }
-      }
-      *reinterpret_cast<float4 *>(&tile[tid * kPitch + k * 4]) = make_float4(out[0], out[1], out[2], out[3]);
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int k = 0; k < kSpan; ++k) w[r][k] = src[(int64_t)(i0 + r < N ? i0 + r : i0) * W + next[k]];
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      if (i0 + r < N) add(w[r]);
+  }
+  const float inv_n = 1.0f / (float)N;
+  const float hi = (float)((1 << (B - 1)) - 1), lo = -(float)(1 << (B - 1));
+  uint32_t rnd[4] = {0u, 0u, 0u, 0u};
+  if (REQUANT) {
+    const Philox4 blk = stream_block(key, kTagRequant, 0u, (uint32_t)q);
+    rnd[0] = blk.x; rnd[1] = blk.y; rnd[2] = blk.z; rnd[3] = blk.w;
+  }
+  float out[4];
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    const float mean_code = (float)acc[t] * inv_n;  // position of the average on the grid
+    if (!REQUANT) {
+      out[t] = dl * mean_code;
+    } else {
+      const float s = fminf(fmaxf(mean_code, lo), hi);
+      const float base = floorf(s);
+      const float frac = s - base;
+      const float unif = (float)(rnd[t] >> 8) * 0x1.0p-24f;
+      out[t] = dl * (float)((int32_t)base + ((unif < frac) ? 1 : 0));
     }
   }
-  __syncthreads();
+  if (j + 4 <= d) {
+    *reinterpret_cast<float4 *>(u_avg + j) = make_float4(out[0], out[1], out[2], out[3]);
+  } else {
 #pragma unroll
-  for (int r = 0; r < 8; ++r) {
-    const int e = r * kThreads + tid;
-    const int64_t j = tile_base + (int64_t)e * 4;
-    if (j >= d) continue;
-    const float4 a = *reinterpret_cast<const float4 *>(&tile[(e >> 3) * kPitch + (e & 7) * 4]);
-    if (j + 4 <= d) {
-      *reinterpret_cast<float4 *>(u_avg + j) = a;
-    } else {
-      const float av[4] = {a.x, a.y, a.z, a.w};
-      for (int t = 0; t < 4 && j + t < d; ++t) u_avg[j + t] = av[t];
-    }
+    for (int t = 0; t < 4; ++t)
+      if (j + t < d) u_avg[j + t] = out[t];
   }
 }
 
@@ -1815,9 +1813,22 @@ __global__ void plain_avg_kernel(const float *__restrict__ U, int64_t d, int64_t
   u_avg[j] = acc * (1.0f / (float)N);
 }
 
+// What the sparse inner iteration's last launch sets back to zero for the next one: the consumed messages and the bitmaps.
+// (As launches of their own, 2.0 us each.)
+struct ClearArgs {
+  uint32_t *words[2];
+  int64_t n[2];
+};
+__device__ __forceinline__ void clear_words(const ClearArgs &c, int64_t j, int64_t threads) {
+#pragma unroll
+  for (int k = 0; k < 2; ++k)
+    for (int64_t e = j; e < c.n[k]; e += threads) c.words[k][e] = 0u;
+}
+
 __global__ void prox_kernel(float *__restrict__ w, const float *__restrict__ u_avg, const float *__restrict__ mu,
-                            int64_t d, float step, float thr, float shrink) {
+                            int64_t d, float step, float thr, float shrink, ClearArgs clear) {
   const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  clear_words(clear, j, (int64_t)gridDim.x * blockDim.x);
   if (j >= d) return;
   w[j] = prox_scalar(w[j], u_avg[j] + mu[j], step, thr, shrink);
 }
@@ -1870,8 +1881,10 @@ __global__ void alpc_update_couple_kernel(const float *__restrict__ x, const flo
                                           const float *__restrict__ ws, float step_y, float thr_y, float shrink_y,
                                           float alpha, float thr_z, float shrink_z, float weight, int first, float t1,
                                           float t2, float t3, float *__restrict__ y, float *__restrict__ z,
-                                          float *__restrict__ ysum, float *__restrict__ x_next, int64_t d) {
+                                          float *__restrict__ ysum, float *__restrict__ x_next, int64_t d,
+                                          ClearArgs clear) {
   const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  clear_words(clear, j, (int64_t)gridDim.x * blockDim.x);
   if (j >= d) return;
   const float m = mu[j], uh = u_hat[j];
   const float yn = prox_scalar(x[j], u_avg[j] + m, step_y, thr_y, shrink_y);
@@ -2375,13 +2388,13 @@ namespace {
 template <int B>
 void dequantize_shared_launch(const lpc_ctx *c, const uint32_t *packed, const float *delta, bool requant,
                               StreamKey key, float *u_avg, hipStream_t st) {
-  const dim3 grid((unsigned)((c->d_pad + kTileFloats - 1) / kTileFloats));
+  const dim3 grid = grid1d((c->d + 3) / 4, kSharedThreads);
   if (requant)
-    hipLaunchKernelGGL((dequantize_shared_kernel<B, true>), grid, dim3(kThreads), 0, st, packed, c->W, delta,
-                       c->cfg.N, c->d, c->d_pad, key, u_avg);
+    hipLaunchKernelGGL((dequantize_shared_kernel<B, true>), grid, dim3(kSharedThreads), 0, st, packed, c->W, delta,
+                       c->cfg.N, c->d, key, u_avg);
   else
-    hipLaunchKernelGGL((dequantize_shared_kernel<B, false>), grid, dim3(kThreads), 0, st, packed, c->W, delta,
-                       c->cfg.N, c->d, c->d_pad, key, u_avg);
+    hipLaunchKernelGGL((dequantize_shared_kernel<B, false>), grid, dim3(kSharedThreads), 0, st, packed, c->W, delta,
+                       c->cfg.N, c->d, key, u_avg);
 }
 }  // namespace
 
@@ -2398,10 +2411,18 @@ hipError_t launch_plain_avg(const lpc_ctx *c, const float *U, float *u_avg, hipS
   return hipGetLastError();
 }
 
-hipError_t launch_prox(const lpc_ctx *c, float *w, const float *u_avg, const float *mu, float step, hipStream_t st) {
+namespace {
+ClearArgs clear_args(const lpc_ctx *c, int32_t nvec) {
+  return ClearArgs{{c->s.packed, c->s.touched}, {(int64_t)c->cfg.N * c->W, (int64_t)nvec * c->bitmap_words}};
+}
+}  // namespace
+
+hipError_t launch_prox(const lpc_ctx *c, float *w, const float *u_avg, const float *mu, float step, hipStream_t st,
+                       bool clear_sparse) {
   float thr, shrink;
   prox_consts(c, step, &thr, &shrink);
-  hipLaunchKernelGGL(prox_kernel, grid1d(c->d, 256), dim3(256), 0, st, w, u_avg, mu, c->d, step, thr, shrink);
+  hipLaunchKernelGGL(prox_kernel, grid1d(c->d, 256), dim3(256), 0, st, w, u_avg, mu, c->d, step, thr, shrink,
+                     clear_sparse ? clear_args(c, c->cfg.N) : ClearArgs{});
   return hipGetLastError();
 }
 
@@ -2464,7 +2485,8 @@ hipError_t launch_alpc_update_couple(const lpc_ctx *c, const AlpcStep &al, hipSt
   const float t3 = (float)(1.0 - (double)al.tau1 - (double)al.tau2);
   hipLaunchKernelGGL(alpc_update_couple_kernel, grid1d(c->d, 256), dim3(256), 0, st, al.x, c->s.u_avg,
                      const_cast<float *>(al.u_hat), al.mu, al.w_snap, al.step_y, thr_y, shrink_y, al.alpha, thr_z,
-                     shrink_z, al.weight, al.first, al.tau1, al.tau2, t3, al.y, al.z, al.ysum, al.x_next, c->d);
+                     shrink_z, al.weight, al.first, al.tau1, al.tau2, t3, al.y, al.z, al.ysum, al.x_next, c->d,
+                     clear_args(c, c->cfg.N + 1));
   return hipGetLastError();
 }
 

@@ -168,3 +168,23 @@ def test_epoch_in_one_launch_that_gives_up_waiting_says_so(d):
     ctx.epoch(w, 0)
     assert ctx.take_device_flags() == 0
     ctx.close()
+
+
+@pytest.mark.parametrize("bits", [2, 3, 5, 7, 8, 9, 10, 13, 16])
+@pytest.mark.parametrize("d,N", [(1, 2), (31, 3), (66, 5), (1025, 1), (20003, 9)])
+def test_shared_scale_receiver_at_every_width(bits, d, N):
+    """Four coordinates a thread, codes across one to three words: eq. (4) and (5) with a shared scale factor, bit for bit."""
+    import torch
+    sp = lpc_synth.make("c1", n=64, d=d, N=N, B=1, bits=bits, seed=9)
+    ctx = gpu_context(sp, bits=bits)
+    U = lpc_synth.gaussian_u(N, d, seed=d + bits)
+    shared = np.full(N, max(lpco.delta_from_stats(lpco.vector_stats(U[i, :d]), d, bits, lpco.CLIP_LAMBDA, 1.0)[0]
+                            for i in range(N)), dtype=np.float32)
+    po, do, _, _ = lpco.quantize_clip(U, d, bits, seed=9, epoch=1, iter_=4, delta_in=shared)
+    packed, delta = to_dev(po.view(np.int32)), to_dev(do)
+    for requant in (False, True):
+        avg = torch.full((d,), -1.0, device="cuda")
+        ctx.dequantize_shared(packed, delta, requant, 1, 4, avg)
+        ref, _ = lpco.dequantize_shared(po, float(do[0]), d, bits, requantize=requant, seed=9, epoch=1, iter_=4)
+        assert np.array_equal(avg.cpu().numpy(), ref)
+    ctx.close()
