@@ -177,7 +177,9 @@ __global__ __launch_bounds__(kClThreads) void cluster_epoch_kernel(ClusterArgs a
     const int par = t & 1;
     const uint32_t tag = a.tag0 + (uint32_t)t + 1u;
     bool ok = true;
-    auto wait = [&](const u64 *p) { return wait_word(p, tag, a.spin_limit, a.ctl, a.tag0 + 1u, ok); };
+    // (other work on the GPU may hold compute units from workgroups that have yet to start)
+    const uint32_t limit = t == a.it0 ? (a.spin_limit > 0xffffffu ? ~0u : a.spin_limit * 256u) : a.spin_limit;
+    auto wait = [&](const u64 *p) { return wait_word(p, tag, limit, a.ctl, a.tag0 + 1u, ok); };
     // ---- rows: margins, slopes, this wavefront's share of u
     {
       float w[K], acc[K], yr[RG], sr[RG];

@@ -28,8 +28,10 @@
 //   d = 8192, N = 16, B = 64: Alg. 3 21.3 -> 12.8, scheme (b) 34.7 -> 13.7
 // Steps that paid: all words of a wait requested together (waiting for them one after another: field words 3.4 us instead
 // of 1.5), rows requested after the barrier and paced (21 % at d = 12000), blocks of 256 instead of 128 columns at d = 4096
-// (25 %), the random words drawn while the rows' wavefronts work.  Rows of t + 2 touched ahead to have them in the L2: 10 %
-// slower, the touches queue with the words.
+// (25 %), the random words drawn while the rows' wavefronts work.  Steps that did not: rows
+// touched ahead (a load per 128-byte line, of t + 2 after the requests, or of t + 1 while margins form): 10 to 25 % slower at
+// K = 12, the memory system is busy with the rows alone; rows requested by halves 8 %, non-temporal loads 4 %, a pause
+// between the polls of a wait 0 to 4 % slower.
 #include <hip/hip_runtime.h>
 
 #include "lpc_device.h"

@@ -188,3 +188,34 @@ def test_shared_scale_receiver_at_every_width(bits, d, N):
         ref, _ = lpco.dequantize_shared(po, float(do[0]), d, bits, requantize=requant, seed=9, epoch=1, iter_=4)
         assert np.array_equal(avg.cpu().numpy(), ref)
     ctx.close()
+
+
+@pytest.mark.parametrize("d,N", [(90, 8), (4096, 8), (20000, 8)])
+def test_epochs_of_two_threads_on_two_streams(d, N):
+    """Two launches that each want most of the GPU's compute units: they take turns, and give what each gives alone."""
+    import threading
+    import torch
+    sp = lpc_synth.make("c2", n=2048, d=d, N=N, B=16, seed=d)
+
+    def run(out, k, stream):
+        with torch.cuda.stream(stream):
+            ctx = gpu_context(sp, m=16, seed=k)
+            w = to_dev(sp.w0)
+            for s in range(6):
+                ctx.epoch(w, s)
+            stream.synchronize()
+            out[k] = (w.cpu().numpy(), ctx.take_device_flags())
+            ctx.close()
+
+    alone, together = {}, {}
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    for k in range(2):
+        run(alone, k, streams[k])
+    threads = [threading.Thread(target=run, args=(together, k, streams[k])) for k in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for k in range(2):
+        assert alone[k][1] == together[k][1] == 0
+        assert np.array_equal(alone[k][0], together[k][0])
