@@ -500,51 +500,7 @@ __global__ __launch_bounds__(kThreads) void quantize_word_kernel(const float *__
 
 // ---------------------------------------------------------------------------
 // Receiver: unpack, eq. (4), optional fused proximal step.
-template <int B>
-__device__ __forceinline__ void load_words(const uint32_t *__restrict__ src, uint32_t (&words)[B]) {
-  if constexpr (B % 4 == 0) {
-#pragma unroll
-    for (int i = 0; i < B; i += 4) {
-      const uint4 t = *reinterpret_cast<const uint4 *>(src + i);
-      words[i] = t.x; words[i + 1] = t.y; words[i + 2] = t.z; words[i + 3] = t.w;
-    }
-  } else if constexpr (B % 2 == 0) {
-#pragma unroll
-    for (int i = 0; i < B; i += 2) {
-      const uint2 t = *reinterpret_cast<const uint2 *>(src + i);
-      words[i] = t.x; words[i + 1] = t.y;
-    }
-  } else {
-#pragma unroll
-    for (int i = 0; i < B; ++i) words[i] = src[i];
-  }
-}
-
 constexpr int kQuarterThreads = 128;
-
-// acc[c] = fma(delta, code_c, acc[c]) for the 32 codes of one segment; returns the OR of the words
-template <int B>
-__device__ __forceinline__ uint32_t accumulate_words(const uint32_t (&words)[B], float delta, float (&acc)[32]) {
-  uint32_t any = 0u;
-#pragma unroll
-  for (int i = 0; i < B; ++i) any |= words[i];
-#pragma unroll
-  for (int c = 0; c < 32; ++c) {
-    const int p = c * B, wi = p >> 5, sh = p & 31;
-    uint32_t field = words[wi] >> sh;
-    if (sh + B > 32) field |= words[wi + 1] << (32 - sh);
-    const int32_t code = (int32_t)(field << (32 - B)) >> (32 - B);  // sign-extend the B-bit field
-    acc[c] = __builtin_fmaf(delta, (float)code, acc[c]);
-  }
-  return any;
-}
-
-template <int B>
-__device__ __forceinline__ void unpack_accumulate(const uint32_t *__restrict__ src, float delta, float (&acc)[32]) {
-  uint32_t words[B];
-  load_words<B>(src, words);
-  accumulate_words<B>(words, delta, acc);
-}
 
 struct ProxArgs {
   const float *mu;
@@ -557,94 +513,105 @@ struct ProxArgs {
   int64_t bitmap_words;
 };
 
-// The receiver for the bit widths that do not divide a word.  TPB threads per workgroup (one segment each): 256
-// for long vectors, 64 when that would leave CUs without work
-template <int B, bool PROX, int TPB>
-__global__ __launch_bounds__(TPB) void dequantize_kernel(const uint32_t *packed, int64_t W,
-                                                              const float *__restrict__ delta, int32_t N, int64_t d,
-                                                              int64_t d_pad, float *__restrict__ u_avg, ProxArgs pa) {
-  __shared__ __attribute__((aligned(16))) float tile[TPB * kPitch];
-  const int tid = threadIdx.x;
-  const int64_t tile_base = (int64_t)blockIdx.x * (TPB * kSegFloats);
-  const int64_t seg = tile_base / kSegFloats + tid;
-  // the proximal step's operands are requested before the messages are unpacked (one round trip, not two)
-  float4 w_pre[8], mu_pre[8];
-  if constexpr (PROX) {
+// Four codes of B bits of one message: they lie in up to three words, of which a thread loads what it may need.
+template <int B>
+struct FourCodes {
+  static constexpr int kBits = 4 * B, kSpan = 32 % kBits == 0 ? 1 : (kBits <= 36 || kBits == 64 ? 2 : 3);
+  int64_t word;         // the first, of a message of W
+  int shift;
+  int64_t next[kSpan];  // from it; the last message ends with its last word
+  __device__ __forceinline__ FourCodes(int64_t q, int64_t W) : word(q * kBits >> 5), shift((int)(q * kBits & 31)) {
 #pragma unroll
-    for (int r = 0; r < 8; ++r) {
-      const int64_t j = tile_base + (int64_t)(r * TPB + tid) * 4;
-      w_pre[r] = mu_pre[r] = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (j + 4 <= d) {
-        mu_pre[r] = *reinterpret_cast<const float4 *>(pa.mu + j);
-        w_pre[r] = *reinterpret_cast<const float4 *>(pa.w + j);
-      }
-    }
+    for (int k = 0; k < kSpan; ++k) next[k] = word + k < W ? k : W - 1 - word;
   }
-  if (seg * kSegFloats < d_pad) {
-    float acc[32];
+  // the codes, the first at bit 0
+  __device__ __forceinline__ uint64_t field(const uint32_t (&w)[kSpan]) const {
+    uint64_t lo = w[0];
+    if constexpr (kSpan > 1) lo |= (uint64_t)w[1] << 32;
+    uint64_t f = lo >> shift;
+    if constexpr (kSpan > 2) f |= shift ? (uint64_t)w[2] << (64 - shift) : 0ull;
+    return f;
+  }
+  __device__ __forceinline__ static int32_t code(uint64_t f, int c) {
+    return (int32_t)((uint32_t)(f >> (c * B)) << (32 - B)) >> (32 - B);
+  }
+};
+
+// The receiver for the bit widths of which eight do not divide a word: four coordinates per thread, a 16-byte store, no
+// transposition through LDS; the threads of a segment's B words sit in one wavefront, and each load of a message is
+// issued for all of them before any of its words is set back to zero.  Against 32 coordinates per thread and a transposition
+// through LDS: perceptron with 359,056 parameters, N = 6, b = 8: epoch 3362 -> 3259 us (32 launches, 7.6 us each before);
+// whole exchanges are never slower (4.2 M coordinates, N = 16, b = 3, 6, 8; 30,000 and 300,000 coordinates).
+template <int B, bool PROX>
+__global__ __launch_bounds__(kQuarterThreads) void dequantize_four_kernel(const uint32_t *packed, int64_t W,
+                                                                          const float *__restrict__ delta, int32_t N,
+                                                                          int64_t d, float *__restrict__ u_avg,
+                                                                          ProxArgs pa) {
+  const int64_t q = (int64_t)blockIdx.x * kQuarterThreads + threadIdx.x, j = 4 * q;
+  if (j >= (d + 31) / 32 * 32) return;  // whole segments: words of padding are consumed too
+  typedef FourCodes<B> Four;
+  const Four four(q, W);
+  float4 w_pre = make_float4(0.f, 0.f, 0.f, 0.f), mu_pre = w_pre;
+  if (PROX && j + 4 <= d) {  // requested before the messages are unpacked
+    mu_pre = *reinterpret_cast<const float4 *>(pa.mu + j);
+    w_pre = *reinterpret_cast<const float4 *>(pa.w + j);
+  }
+  float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+  const uint32_t *src = packed + four.word;
+  constexpr int kInFlight = 8;
+  for (int32_t i0 = 0; i0 < N; i0 += kInFlight) {
+    uint32_t w[kInFlight][Four::kSpan];
 #pragma unroll
-    for (int c = 0; c < 32; ++c) acc[c] = 0.0f;
-    // several messages in flight at a time (as many as the word count lets the registers hold);
-    // accumulation stays in worker order
-    constexpr int kInFlight = B <= 2 ? 16 : (B <= 8 ? 8 : 4);  // measured for B = 4: 8 in flight 22.5 us, 16: 29.2, 4: 23.6
-    uint64_t nonzero = 0;
-    for (int32_t i0 = 0; i0 < N; i0 += kInFlight) {
-      uint32_t wds[kInFlight][B];
+    for (int r = 0; r < kInFlight; ++r)
 #pragma unroll
-      for (int q = 0; q < kInFlight; ++q) {
-        const int32_t i = i0 + q < N ? i0 + q : N - 1;  // past the end: a repeated load, ignored below
-        load_words<B>(packed + (int64_t)i * W + seg * B, wds[q]);
-      }
+      for (int k = 0; k < Four::kSpan; ++k) w[r][k] = src[(int64_t)(i0 + r < N ? i0 + r : i0) * W + four.next[k]];
 #pragma unroll
-      for (int q = 0; q < kInFlight; ++q) {
-        if (i0 + q < N) {
-          if (accumulate_words<B>(wds[q], delta[i0 + q], acc)) nonzero |= 1ull << ((i0 + q) & 63);
-        }
+    for (int r = 0; r < kInFlight; ++r) {
+      if (i0 + r < N) {
+        const float dl = delta[i0 + r];
+        const uint64_t f = four.field(w[r]);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) acc[c] = __builtin_fmaf(dl, (float)Four::code(f, c), acc[c]);
       }
     }
     if constexpr (PROX) {
       if (pa.rezero) {
-        while (nonzero) {
-          const int k = __builtin_ctzll(nonzero);
-          nonzero &= nonzero - 1;
-          uint32_t *z = pa.rezero + (int64_t)k * W + seg * B;
 #pragma unroll
-          for (int q = 0; q < B; ++q) z[q] = 0u;
+        for (int r = 0; r < kInFlight; ++r) {
+          if (i0 + r < N) {
+            // words that begin in this thread's codes (the first thread of a segment: its first word as well)
+            uint32_t *z = pa.rezero + (int64_t)(i0 + r) * W + four.word;
+#pragma unroll
+            for (int k = 0; k < Four::kSpan; ++k)
+              if (four.next[k] == k && 32 * k - four.shift >= 0 && 32 * k - four.shift < Four::kBits && w[r][k]) z[k] = 0u;
+          }
         }
-        // the 32 segments of one bitmap word belong to this wavefront, and no pass reads the bitmap here
-        if ((seg & 31) == 0)
-          for (int32_t k = 0; k < N; ++k) pa.touched[(int64_t)k * pa.bitmap_words + (seg >> 5)] = 0u;
       }
     }
-    const float inv_n = 1.0f / (float)N;
-#pragma unroll
-    for (int k = 0; k < 8; ++k)
-      *reinterpret_cast<float4 *>(&tile[tid * kPitch + k * 4]) =
-          make_float4(acc[4 * k] * inv_n, acc[4 * k + 1] * inv_n, acc[4 * k + 2] * inv_n, acc[4 * k + 3] * inv_n);
   }
-  __syncthreads();
+  if constexpr (PROX) {
+    if (pa.rezero && (q & 255) == 0)  // a bitmap word: 32 segments of eight threads
+      for (int32_t k = 0; k < N; ++k) pa.touched[(int64_t)k * pa.bitmap_words + (q >> 8)] = 0u;
+  }
+  const float inv_n = 1.0f / (float)N;
 #pragma unroll
-  for (int r = 0; r < 8; ++r) {
-    const int e = r * TPB + tid;
-    const int64_t j = tile_base + (int64_t)e * 4;
-    if (j >= d) continue;
-    const float4 a = *reinterpret_cast<const float4 *>(&tile[(e >> 3) * kPitch + (e & 7) * 4]);
-    const float av[4] = {a.x, a.y, a.z, a.w};
-    if (j + 4 <= d) {
-      if (u_avg) *reinterpret_cast<float4 *>(u_avg + j) = a;
-      if constexpr (PROX) {
-        const float4 m = mu_pre[r];
-        float4 w = w_pre[r];
-        w.x = prox_scalar(w.x, a.x + m.x, pa.step, pa.thr, pa.shrink);
-        w.y = prox_scalar(w.y, a.y + m.y, pa.step, pa.thr, pa.shrink);
-        w.z = prox_scalar(w.z, a.z + m.z, pa.step, pa.thr, pa.shrink);
-        w.w = prox_scalar(w.w, a.w + m.w, pa.step, pa.thr, pa.shrink);
-        *reinterpret_cast<float4 *>(pa.w + j) = w;
-      }
-    } else {
-      for (int t = 0; t < 4 && j + t < d; ++t) {
-        if (u_avg) u_avg[j + t] = av[t];
-        if constexpr (PROX) pa.w[j + t] = prox_scalar(pa.w[j + t], av[t] + pa.mu[j + t], pa.step, pa.thr, pa.shrink);
+  for (int c = 0; c < 4; ++c) acc[c] *= inv_n;
+  if (j + 4 <= d) {
+    if (u_avg) *reinterpret_cast<float4 *>(u_avg + j) = make_float4(acc[0], acc[1], acc[2], acc[3]);
+    if constexpr (PROX) {
+      float4 w = w_pre;
+      w.x = prox_scalar(w.x, acc[0] + mu_pre.x, pa.step, pa.thr, pa.shrink);
+      w.y = prox_scalar(w.y, acc[1] + mu_pre.y, pa.step, pa.thr, pa.shrink);
+      w.z = prox_scalar(w.z, acc[2] + mu_pre.z, pa.step, pa.thr, pa.shrink);
+      w.w = prox_scalar(w.w, acc[3] + mu_pre.w, pa.step, pa.thr, pa.shrink);
+      *reinterpret_cast<float4 *>(pa.w + j) = w;
+    }
+  } else {
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      if (j + t < d) {
+        if (u_avg) u_avg[j + t] = acc[t];
+        if constexpr (PROX) pa.w[j + t] = prox_scalar(pa.w[j + t], acc[t] + pa.mu[j + t], pa.step, pa.thr, pa.shrink);
       }
     }
   }
@@ -654,7 +621,7 @@ __global__ __launch_bounds__(TPB) void dequantize_kernel(const uint32_t *packed,
 // each message (8B divides 32).  Four times as many threads as one-segment-per-thread, each with a quarter
 // of the arithmetic between its loads and its stores, and a thread's eight results are contiguous, so no
 // transposition through LDS.  Accumulation order (worker 0 first) and every operation are those of
-// dequantize_kernel.  The threads that share a word sit in one wavefront and load it in one instruction,
+// dequantize_four_kernel.  The threads that share a word sit in one wavefront and load it in one instruction,
 // which has returned before the thread at bit 0 sets the word back to zero.
 template <int B, bool PROX>
 __global__ __launch_bounds__(kQuarterThreads) void dequantize_quarter_kernel(const uint32_t *packed, int64_t W,
@@ -1745,33 +1712,25 @@ __global__ __launch_bounds__(kSharedThreads) void dequantize_shared_kernel(const
                                                                            float *__restrict__ u_avg) {
   const int64_t q = (int64_t)blockIdx.x * kSharedThreads + threadIdx.x, j = 4 * q;
   if (j >= d) return;
-  constexpr int kBits = 4 * B;                                         // of this thread's codes, in kSpan words
-  constexpr int kSpan = 32 % kBits == 0 ? 1 : (kBits == 64 ? 2 : (kBits <= 36 ? 2 : 3));
-  const int64_t wi = q * kBits >> 5;
-  const int sh = (int)(q * kBits & 31);
-  const uint32_t *src = packed + wi;
-  int64_t next[kSpan];                                                 // the last message ends with its last word
-#pragma unroll
-  for (int k = 0; k < kSpan; ++k) next[k] = wi + k < W ? k : W - 1 - wi;
+  typedef FourCodes<B> Four;
+  const Four four(q, W);
+  const uint32_t *src = packed + four.word;
   int32_t acc[4] = {0, 0, 0, 0};
   const float dl = delta[0];
-  auto add = [&](const uint32_t (&w)[kSpan]) {
-    uint64_t lo = w[0];
-    if (kSpan > 1) lo |= (uint64_t)w[kSpan > 1 ? 1 : 0] << 32;
-    uint64_t field = lo >> sh;
-    if (kSpan > 2 && sh) field |= (uint64_t)w[kSpan > 2 ? 2 : 0] << (64 - sh);
-#pragma unroll
-    for (int c = 0; c < 4; ++c) acc[c] += (int32_t)((uint32_t)(field >> (c * B)) << (32 - B)) >> (32 - B);
-  };
   for (int32_t i0 = 0; i0 < N; i0 += 4) {
-    uint32_t w[4][kSpan];
+    uint32_t w[4][Four::kSpan];
 #pragma unroll
     for (int r = 0; r < 4; ++r)
 #pragma unroll
-      for (int k = 0; k < kSpan; ++k) w[r][k] = src[(int64_t)(i0 + r < N ? i0 + r : i0) * W + next[k]];
+      for (int k = 0; k < Four::kSpan; ++k) w[r][k] = src[(int64_t)(i0 + r < N ? i0 + r : i0) * W + four.next[k]];
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
-      if (i0 + r < N) add(w[r]);
+    for (int r = 0; r < 4; ++r) {
+      if (i0 + r < N) {
+        const uint64_t f = four.field(w[r]);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) acc[c] += Four::code(f, c);
+      }
+    }
   }
   const float inv_n = 1.0f / (float)N;
   const float hi = (float)((1 << (B - 1)) - 1), lo = -(float)(1 << (B - 1));
@@ -2099,15 +2058,8 @@ void dequantize_launch(const lpc_ctx *c, const uint32_t *packed, const float *de
                        dim3((unsigned)((threads + kQuarterThreads - 1) / kQuarterThreads)), dim3(kQuarterThreads), 0, st,
                        packed, c->W, delta, c->cfg.N, c->d, c->d_pad, u_avg, pa);
   } else {
-    const int64_t wide = (c->d_pad + kTileFloats - 1) / kTileFloats;
-    if (wide >= 2 * c->cus) {
-      hipLaunchKernelGGL((dequantize_kernel<B, PROX, kThreads>), dim3((unsigned)wide), dim3(kThreads), 0, st, packed,
-                         c->W, delta, c->cfg.N, c->d, c->d_pad, u_avg, pa);
-    } else {
-      const int64_t tile = 64 * kSegFloats;
-      hipLaunchKernelGGL((dequantize_kernel<B, PROX, 64>), dim3((unsigned)((c->d_pad + tile - 1) / tile)), dim3(64), 0,
-                         st, packed, c->W, delta, c->cfg.N, c->d, c->d_pad, u_avg, pa);
-    }
+    hipLaunchKernelGGL((dequantize_four_kernel<B, PROX>), grid1d(c->d_pad / 4, kQuarterThreads), dim3(kQuarterThreads),
+                       0, st, packed, c->W, delta, c->cfg.N, c->d, u_avg, pa);
   }
 }
 
