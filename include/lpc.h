@@ -46,7 +46,7 @@ typedef enum {
   LPC_ESHAPE = -3,      /* sizes / leading dimensions / alignment do not fit */
   LPC_EWORKSPACE = -4,  /* workspace missing, misaligned or too small */
   LPC_ENONFINITE = -5,  /* a vector handed to the quantizer held NaN/Inf (see lpc_take_device_flags) */
-  LPC_EDEVICE = -6,     /* a HIP call failed */
+  LPC_EDEVICE = -6,     /* a HIP call failed, or a launch gave up waiting for its own workgroups (lpc_epoch) */
   LPC_EUNSUPPORTED = -7 /* valid in the paper, not built here */
 } lpc_status;
 
@@ -196,16 +196,22 @@ lpc_status lpc_prox_step(lpc_ctx *ctx, float *w, const float *u_avg, const float
 /* One epoch of Alg. 1 (algo LPC; y, z ignored) or of Alg. 2 / Alg. 3:
  * snapshot gradient, m inner iterations, snapshot update.  w_snap: in x~^s, out
  * x~^(s+1).  y, z: ALPC-SVRG's auxiliary iterates, in/out (d floats each; start
- * them equal to x~^0).  epoch = s selects the random streams and Alg. 3's schedule. */
+ * them equal to x~^0).  epoch = s selects the random streams and Alg. 3's schedule.
+ * On dense data the inner loop may be one launch whose workgroups wait for each other (LPC_TUNE_ITER_FORM), for a
+ * bounded time.  Should that run out (they have to be on the GPU together, and another process may hold part of it),
+ * the epoch does not take place: w_snap, y and z keep what they held.  As this call only enqueues, the next ones that
+ * answer to the host say so: lpc_objective, lpc_gradient_mapping, lpc_clip_sweep, lpc_epoch_report, and lpc_epoch_traced
+ * where it sizes the messages, return LPC_EDEVICE until lpc_take_device_flags has been asked. */
 lpc_status lpc_epoch(lpc_ctx *ctx, float *w_snap, float *y, float *z, uint32_t epoch, void *stream);
 
-/* P(w) of eq. (1) over all n rows, returned to the HOST (waits for the stream to get there). */
+/* P(w) of eq. (1) over all n rows, returned to the HOST (waits for the stream to get there).  LPC_EDEVICE, with P(w)
+ * all the same, if an epoch since the last lpc_take_device_flags gave up. */
 lpc_status lpc_objective(lpc_ctx *ctx, const float *w, double *P_out_host, void *stream);
 
 /* Reads and clears the context's device-side flags (synchronises the stream):
  * returns LPC_ENONFINITE if any vector seen by the statistics pass since the last
- * call held a NaN or Inf; LPC_EDEVICE if a workgroup of the two-launch inner iteration gave up
- * waiting for the others (the iterates since then are not to be trusted); else LPC_OK. */
+ * call held a NaN or Inf; LPC_EDEVICE if a workgroup gave up waiting for the others: the epoch then did not take place,
+ * or, with LPC_TUNE_ITER_FORM 1 or 3, left iterates that are not to be trusted; else LPC_OK. */
 lpc_status lpc_take_device_flags(lpc_ctx *ctx, void *stream);
 
 /* ---- evaluators (outside the timed path) --------------------------------------------------

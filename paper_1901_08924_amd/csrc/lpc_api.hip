@@ -29,6 +29,9 @@ bool capturing(hipStream_t st) {
 
 bool is_csr(const lpc_problem &p) { return p.X == nullptr; }
 
+// flags[0], bit 1: a workgroup of a launch whose workgroups wait for each other gave up
+bool gave_up(unsigned long long flags) { return (flags & 2u) != 0; }
+
 // Optional timing of kernel classes with HIP events on the launch stream (benchmarks only; the
 // events cost a little pipeline time, so the hot path leaves this off).  single = the scope issues exactly ONE
 // kernel, through LPC_LAUNCH_TIMED: that launch then carries the two events itself (dispatch begin / end).
@@ -185,6 +188,9 @@ size_t layout(lpc_ctx *c, char *base) {
     s.cl_vec = (unsigned long long *)take(cs.vec * sizeof(unsigned long long));
     s.cl_scale = (unsigned long long *)take(cs.scale * sizeof(unsigned long long));
     s.cl_ctl = (uint32_t *)take(16 * sizeof(uint32_t));
+    const size_t held = (c->cluster_capable || c->columns_capable) && c->cfg.algo != LPC_ALGO_LPC ? (size_t)c->d : 4;
+    s.cl_y = (float *)take(held * sizeof(float));
+    s.cl_z = (float *)take(held * sizeof(float));
   }
   s.iter_slots = (unsigned long long *)take((c->iter2_capable ? (size_t)fused_iter_slot_words(c) : 1) * sizeof(unsigned long long));
   if (c->mlp) {
@@ -277,6 +283,7 @@ lpc_status fill_ctx(lpc_ctx *c, const lpc_problem *p, const lpc_config *cfg) {
   // a column block would hold all columns
   c->columns_capable = (c->d > 256 || !c->cluster_capable) && columns_supported(c);
   if (c->columns_capable) c->cluster_capable = false;
+  c->loop_waits = c->columns_capable || (c->cluster_capable && cluster_waits(c));
   // measured on MI355X (inner iterations/s, forms 0 / 1 / 2): d = 4096, N = 8, B = 64: 59.9 k / 50.6 k / 47.6 k;
   // d = 8192, N = 16 (+ shared batch), B = 64: 32.3 k / - / 20.2 k.  Form 1 pays about 3 us per trip of the statistics
   // through device-scope atomics; form 2 pays for reading the sampled rows a second time in 512-byte slices (its
@@ -776,7 +783,7 @@ lpc_status lpc_epoch(lpc_ctx *ctx, float *w_snap, float *y, float *z, uint32_t e
     // all m inner iterations in one launch, which starts from the snapshot and leaves the next one.
     // (Not where the stream is being captured: a replay would repeat the launch's tags.)
     ResidentStep rs{};
-    rs.z_snap = zs; rs.mu = s.mu; rs.key = key_of(c, epoch, 0); rs.theta = 1.0f; rs.step = g.eta;
+    rs.z_snap = zs; rs.mu = s.mu; rs.w_snap = w_snap; rs.key = key_of(c, epoch, 0); rs.theta = 1.0f; rs.step = g.eta;
     double wsum = 1.0;
     if (g.algo != LPC_ALGO_LPC) {
       if (!y || !z) return LPC_ENULL;
@@ -793,11 +800,14 @@ lpc_status lpc_epoch(lpc_ctx *ctx, float *w_snap, float *y, float *z, uint32_t e
     c->res_tag += (uint32_t)g.m + 1u;
     auto launch = [&](int32_t t0, int32_t t1, double weight, uint32_t *n_clipped) {
       return c->cluster_capable ? launch_cluster_epoch(c, rs, w_snap, 1.0 / wsum, t0, t1, weight, n_clipped, st)
-                                : launch_columns_epoch(c, rs, w_snap, 1.0 / wsum, t0, t1, weight, tracing, n_clipped, st);
+                                : launch_columns_epoch(c, rs, t0, t1, weight, tracing, n_clipped, st);
     };
+    // what the loop leaves becomes the caller's, unless a workgroup gave up waiting for the others
+    const bool commits = c->loop_waits;
     if (!tracing) {
       ProfScope ps(c, LPC_PROF_RESIDENT, st);
-      return dev(launch(0, g.m, 1.0, nullptr));
+      LPC_TRY_HIP(launch(0, g.m, 1.0, nullptr));
+      return commits ? dev(launch_commit_epoch(c, rs, 1.0 / wsum, w_snap, st)) : LPC_OK;
     }
     double weight = 1.0;
     for (int32_t t = 0; t < g.m; ++t) {
@@ -806,7 +816,7 @@ lpc_status lpc_epoch(lpc_ctx *ctx, float *w_snap, float *y, float *z, uint32_t e
       LPC_TRY(record_iteration(c, t, st));
       weight *= (double)rs.theta;
     }
-    return LPC_OK;
+    return commits ? dev(launch_commit_epoch(c, rs, 1.0 / wsum, w_snap, st)) : LPC_OK;
   }
   if (g.algo == LPC_ALGO_LPC) {
     LPC_TRY_HIP(launch_copy(s.w, w_snap, c->d, st));  // x_0 = x~
@@ -1097,6 +1107,12 @@ lpc_status lpc_epoch_traced(lpc_ctx *ctx, float *w_snap, float *y, float *z, uin
   ctx->trace_delta = nullptr;
   ctx->trace_nclip = nullptr;
   ctx->trace_coded_host = nullptr;
+  if (rc == LPC_OK && coded_bits_host) {  // the host has waited anyway
+    uint32_t flags = 0;
+    LPC_TRY_HIP(hipMemcpyAsync(&flags, ctx->s.flags, sizeof(flags), hipMemcpyDeviceToHost, as_stream(stream)));
+    LPC_TRY_HIP(hipStreamSynchronize(as_stream(stream)));
+    if (gave_up(flags)) return LPC_EDEVICE;
+  }
   return rc;
 }
 
@@ -1173,7 +1189,7 @@ lpc_status lpc_objective(lpc_ctx *ctx, const float *w, double *P_out_host, void 
                                  reinterpret_cast<double *>(out.words()), st));
   LPC_TRY_HIP(out.wait(st));
   std::memcpy(P_out_host, out.words(), sizeof(double));
-  return LPC_OK;
+  return gave_up(out.words()[1]) ? LPC_EDEVICE : LPC_OK;
 }
 
 lpc_status lpc_gradient_mapping(lpc_ctx *ctx, const float *w, float eta, double *gm2_out_host, void *stream) {
@@ -1189,7 +1205,7 @@ lpc_status lpc_gradient_mapping(lpc_ctx *ctx, const float *w, float eta, double 
                                  reinterpret_cast<double *>(out.words()), st));
   LPC_TRY_HIP(out.wait(st));
   std::memcpy(gm2_out_host, out.words(), sizeof(double));
-  return LPC_OK;
+  return gave_up(out.words()[1]) ? LPC_EDEVICE : LPC_OK;
 }
 
 lpc_status lpc_code_histogram(lpc_ctx *ctx, const uint32_t *packed, uint64_t *counts, void *stream) {
@@ -1226,7 +1242,7 @@ lpc_status lpc_take_device_flags(lpc_ctx *ctx, void *stream) {
   LPC_TRY_HIP(hipMemcpyAsync(flags, ctx->s.flags, sizeof(flags), hipMemcpyDeviceToHost, st));
   LPC_TRY_HIP(hipStreamSynchronize(st));
   LPC_TRY_HIP(launch_fill_u32(ctx->s.flags, 0u, 4, st));
-  if (flags[0] & 2u) return LPC_EDEVICE;  // a workgroup of the two-launch iteration gave up waiting for the others
+  if (gave_up(flags[0])) return LPC_EDEVICE;
   return (flags[0] & 1u) ? LPC_ENONFINITE : LPC_OK;
 }
 

@@ -17,7 +17,9 @@
 // neither flag nor fence stands between writer and reader.  Two sets of slots alternate: who writes iteration t + 2 has
 // read everybody's t + 1, which were written after their owners had read t.
 // The launch with several workgroups is cooperative, so that all are resident together; every wait is bounded by
-// LPC_TUNE_SPIN_LIMIT, a workgroup that gives up says so to the others, and lpc_take_device_flags reports LPC_EDEVICE.
+// LPC_TUNE_SPIN_LIMIT, a workgroup that gives up says so to the others, the epoch leaves the caller's vectors as they were
+// (launch_commit_epoch), and the calls that answer to the host report LPC_EDEVICE.  One workgroup waits for nobody and
+// writes the caller's vectors itself.
 // What bounds an iteration is the chain of dependent steps: rows 1.1 us, statistics 0.5 us, codes 0.5 us, messages there
 // and back 0.9 us, receiver and update 0.9 us (d = 90, N = 8, B = 64: 3.9 us; the words stay inside one die's L2).
 // Measured on MI355X, whole epochs, three launches per iteration -> this kernel, us per inner iteration:
@@ -42,19 +44,20 @@ constexpr int kClLds = 156 * 1024;  // dynamic LDS of a launch, at most
 struct ClusterArgs {
   const float *X;
   int64_t ldx, n;
-  const float *y, *z_snap, *mu;
-  float *w_snap, *yv, *zv, *x_mid, *ysum_mid;  // _mid: what a launch of less than the whole loop leaves for the next
+  const float *y, *z_snap, *mu, *w_snap, *yv, *zv;
+  const float *in;              // where it0 > 0: x (Alg. 2, 3: the weighted sum of y), as the launch before left it
+  float *out, *y_out, *z_out;
   uint32_t *packed;
   float *delta_out;
   uint32_t *n_clipped;        // per vector, or null: not counted
   uint32_t *flags, *ctl;      // ctl[0]: first tag of a launch that gave up
   u64 *msg, *vec, *scale_ex;  // [2][N][W + 1] (words, then the scale factor), [2][vectors in full precision][d], [2][N]
-  int32_t d, dp, W, N, nvec, nv, G, spread, B, m, it0, it1, bits, scheme, loss, alpc, rpw, wpv;
+  int32_t d, dp, W, N, nvec, nv, G, spread, B, it0, it1, bits, scheme, loss, rpw, wpv;
   uint32_t tag0, spin_limit, inv_w1;  // inv_w1: ceil(2^32 / (W + 1))
   QuantSpec qs;
   StreamKey key;
   float scale, step, thr, shrink;
-  float step_y, thr_y, shrink_y, alpha, thr_z, shrink_z, t1, t2, t3, snap_scale;
+  float step_y, thr_y, shrink_y, alpha, thr_z, shrink_z, t1, t2, t3, out_scale;
   double theta, weight;
 };
 
@@ -97,9 +100,9 @@ __global__ __launch_bounds__(kClThreads) void cluster_epoch_kernel(ClusterArgs a
   if (mine) {
     mu_j = a.mu[j];
     ws_j = a.w_snap[j];
-    x_j = !ALPC && a.it0 > 0 ? a.x_mid[j] : ws_j;
+    x_j = !ALPC && a.it0 > 0 ? a.in[j] : ws_j;
     if (ALPC) {
-      ysum_j = a.it0 > 0 ? a.ysum_mid[j] : 0.0f;
+      ysum_j = a.it0 > 0 ? a.in[j] : 0.0f;
       y_j = a.yv[j];
       z_j = a.zv[j];
       x_j = (a.t1 * z_j + a.t2 * ws_j) + a.t3 * y_j;
@@ -511,16 +514,12 @@ __global__ __launch_bounds__(kClThreads) void cluster_epoch_kernel(ClusterArgs a
     return;
   }
   if (g == 0 && mine) {
-    const bool whole = a.it1 == a.m;
     if (ALPC) {
-      a.yv[j] = y_j;
-      a.zv[j] = z_j;
-      if (whole) a.w_snap[j] = ysum_j * a.snap_scale;
-      else a.ysum_mid[j] = ysum_j;
-    } else if (whole) {
-      a.w_snap[j] = x_j;
+      a.y_out[j] = y_j;
+      a.z_out[j] = z_j;
+      a.out[j] = ysum_j * a.out_scale;
     } else {
-      a.x_mid[j] = x_j;
+      a.out[j] = x_j;
     }
   }
 }
@@ -565,6 +564,24 @@ Shape shape_of(const lpc_ctx *c) {
   return s;
 }
 
+// The next snapshot and Alg. 2's vectors, out of what the loop's last launch left, unless one of its launches gave up: then
+// the epoch has not taken place.  Only a launch of its own sees whether ALL workgroups came through; where the loop's
+// workgroups wrote the caller's vectors themselves, some could have written their columns and others not.
+__global__ __launch_bounds__(256) void commit_epoch_kernel(const uint32_t *__restrict__ ctl, uint32_t launch_tag, int32_t d,
+                                                           const float *__restrict__ from, float scale,
+                                                           float *__restrict__ w_snap, const float *__restrict__ y_from,
+                                                           float *__restrict__ y, const float *__restrict__ z_from,
+                                                           float *__restrict__ z) {
+  if (ctl[0] == launch_tag) return;
+  const int j = (int)(blockIdx.x * 256 + threadIdx.x);
+  if (j >= d) return;
+  w_snap[j] = y ? from[j] * scale : from[j];
+  if (y) {
+    y[j] = y_from[j];
+    z[j] = z_from[j];
+  }
+}
+
 }  // namespace
 
 bool cluster_supported(const lpc_ctx *c) { return shape_of(c).G > 0; }
@@ -578,18 +595,34 @@ ClusterScratch cluster_scratch(const lpc_ctx *c) {
   return s;
 }
 
+bool cluster_waits(const lpc_ctx *c) { return shape_of(c).G > 1; }
+
+hipError_t launch_commit_epoch(const lpc_ctx *c, const ResidentStep &rs, double snap_scale, float *w_snap,
+                               hipStream_t st) {
+  hipLaunchKernelGGL(commit_epoch_kernel, dim3((unsigned)((c->d + 255) / 256)), dim3(256), 0, st, c->s.cl_ctl,
+                     rs.tag0 + 1u, (int32_t)c->d, rs.alpc ? c->s.ysum : c->s.w, (float)snap_scale, w_snap, c->s.cl_y,
+                     rs.alpc ? rs.y : nullptr, c->s.cl_z, rs.alpc ? rs.z : nullptr);
+  return hipGetLastError();
+}
+
 hipError_t launch_cluster_epoch(const lpc_ctx *c, const ResidentStep &rs, float *w_snap, double snap_scale, int32_t t0,
                                 int32_t t1, double weight, uint32_t *n_clipped, hipStream_t st) {
   const Shape s = shape_of(c);
   ClusterArgs a{};
   a.X = c->prob.X; a.ldx = c->prob.ldx; a.n = c->n; a.y = c->prob.y; a.z_snap = rs.z_snap; a.mu = rs.mu;
-  a.w_snap = w_snap; a.yv = rs.y; a.zv = rs.z; a.packed = c->s.packed; a.delta_out = c->s.delta; a.flags = c->s.flags;
+  // one workgroup in a launch: nobody can give up, the caller's vectors are written in place
+  const bool alone = s.G == 1, last = alone && t1 == c->cfg.m;
+  a.w_snap = w_snap; a.yv = !alone && t0 > 0 ? c->s.cl_y : rs.y; a.zv = !alone && t0 > 0 ? c->s.cl_z : rs.z;
+  float *kept = rs.alpc ? c->s.ysum : c->s.w;
+  a.in = kept; a.out = last ? w_snap : kept; a.out_scale = last ? (float)snap_scale : 1.0f;
+  a.y_out = alone ? rs.y : c->s.cl_y; a.z_out = alone ? rs.z : c->s.cl_z;
+  a.packed = c->s.packed; a.delta_out = c->s.delta; a.flags = c->s.flags;
   a.ctl = c->s.cl_ctl; a.msg = c->s.cl_msg; a.vec = c->s.cl_vec; a.scale_ex = c->s.cl_scale;
-  a.x_mid = c->s.w; a.ysum_mid = c->s.ysum; a.it0 = t0; a.it1 = t1; a.weight = weight; a.n_clipped = n_clipped;
+  a.it0 = t0; a.it1 = t1; a.weight = weight; a.n_clipped = n_clipped;
   a.d = (int32_t)c->d; a.dp = (int32_t)c->d_pad; a.W = (int32_t)c->W; a.N = c->cfg.N;
   a.nvec = c->cfg.N + (rs.alpc ? 1 : 0); a.nv = s.nv; a.G = s.G; a.wpv = s.wpv; a.rpw = s.rpw;
-  a.B = c->cfg.B; a.m = c->cfg.m; a.bits = c->quant ? c->cfg.bits : 0; a.scheme = c->quant ? c->cfg.scheme : -1;
-  a.loss = c->prob.loss; a.alpc = rs.alpc ? 1 : 0;
+  a.B = c->cfg.B; a.bits = c->quant ? c->cfg.bits : 0; a.scheme = c->quant ? c->cfg.scheme : -1;
+  a.loss = c->prob.loss;
   a.tag0 = rs.tag0; a.spin_limit = c->spin_limit;
   a.inv_w1 = (uint32_t)((0x100000000ull + (uint64_t)a.W) / ((uint64_t)a.W + 1));
   a.qs.bits = c->cfg.bits; a.qs.clip_mode = c->cfg.clip_mode; a.qs.clip = c->cfg.clip; a.qs.enabled = 1;
@@ -603,7 +636,7 @@ hipError_t launch_cluster_epoch(const lpc_ctx *c, const ResidentStep &rs, float 
   a.step_y = rs.step_y; consts(rs.step_y, &a.thr_y, &a.shrink_y);
   a.alpha = rs.alpha; consts(rs.alpha, &a.thr_z, &a.shrink_z);
   a.t1 = rs.tau1; a.t2 = rs.tau2; a.t3 = (float)(1.0 - (double)rs.tau1 - (double)rs.tau2); a.theta = (double)rs.theta;
-  a.scale = (float)(1.0 / (double)c->cfg.B); a.snap_scale = (float)snap_scale;
+  a.scale = (float)(1.0 / (double)c->cfg.B);
   const void *fn = nullptr;
   const int q = !c->quant ? kPlain : (c->cfg.scheme == LPC_SCHEME_A ? kOwnScale : kSharedScale);
 #define LPC_CLUSTER_Q(K_, RW_, Q_)                                                                               \

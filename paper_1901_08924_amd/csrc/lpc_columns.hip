@@ -18,7 +18,8 @@
 // each of their readers wrote after it had read t, or after a barrier that its reading wavefront had passed.
 // The launch is cooperative: all workgroups are resident together; waits are bounded by LPC_TUNE_SPIN_LIMIT (the first
 // iteration's by 256 times as much: other work on the GPU may hold compute units), a workgroup that gives up says so to the
-// others, and lpc_take_device_flags reports LPC_EDEVICE.
+// others, the epoch leaves the caller's vectors as they were (launch_commit_epoch), and the calls that answer to the host
+// report LPC_EDEVICE.
 // What bounds an iteration: at d = 4096, N = 8, B = 64 the chain of dependent trips (7.0 us: margins 0.8 + 1.2 for the
 // words, gradient 0.4, statistics 0.7 + 1.0, codes 0.5, their words across the dies 1.5, update 0.4); at d = 20000 the rows
 // (41 MB in 10 us, paced) and that memory rests while margins are formed.
@@ -49,20 +50,20 @@ constexpr int kDies = 8;
 struct ColumnArgs {
   const float *X;
   int64_t ldx, n;
-  const float *y, *z_snap, *mu;
-  float *w_snap, *yv, *zv, *x_mid, *ysum_mid;  // _mid: what a launch of less than the whole loop leaves for the next
+  const float *y, *z_snap, *mu, *w_snap, *yv, *zv;
+  float *x_mid, *ysum_mid, *y_mid, *z_mid;     // what a launch leaves for the next one, or for launch_commit_epoch
   uint32_t *packed;                            // messages, or null: nobody reads them
   float *delta_out;
   uint32_t *n_clipped;                         // per vector, or null: not counted
   uint32_t *flags, *ctl;                       // ctl[0]: first tag of a launch that gave up
   // [2][nvec][row waves][G][8]; [2][N][G * S][5]; [2][G][N]; [2][G][N][C (+ N words of scale factors)]; [2][G][C]
   u64 *marg, *stats, *scale_ex, *msg, *vec;
-  int32_t d, W, N, nvec, G, per_die, B, m, it0, it1, bits, scheme, loss, rpw, S;
+  int32_t d, W, N, nvec, G, per_die, B, it0, it1, bits, scheme, loss, rpw, S;
   uint32_t tag0, spin_limit;
   QuantSpec qs;
   StreamKey key;
   float scale, step, thr, shrink;
-  float step_y, thr_y, shrink_y, alpha, thr_z, shrink_z, t1, t2, t3, snap_scale;
+  float step_y, thr_y, shrink_y, alpha, thr_z, shrink_z, t1, t2, t3;
   double theta, weight;
 };
 
@@ -528,17 +529,13 @@ __global__ __launch_bounds__(kCoThreads) void column_epoch_kernel(ColumnArgs a) 
     return;
   }
   if (v == 0 && holds) {
-    const bool whole = a.it1 == a.m;
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
       if (q_c + c < cols) {
         if (ALPC) {
-          a.yv[j + c] = y4[c];
-          a.zv[j + c] = z4[c];
-          if (whole) a.w_snap[j + c] = ysum4[c] * a.snap_scale;
-          else a.ysum_mid[j + c] = ysum4[c];
-        } else if (whole) {
-          a.w_snap[j + c] = x4[c];
+          a.y_mid[j + c] = y4[c];
+          a.z_mid[j + c] = z4[c];
+          a.ysum_mid[j + c] = ysum4[c];
         } else {
           a.x_mid[j + c] = x4[c];
         }
@@ -590,20 +587,20 @@ ColumnScratch columns_scratch(const lpc_ctx *c) {
   return w;
 }
 
-hipError_t launch_columns_epoch(const lpc_ctx *c, const ResidentStep &rs, float *w_snap, double snap_scale, int32_t t0,
-                                int32_t t1, double weight, bool traced, uint32_t *n_clipped, hipStream_t st) {
+hipError_t launch_columns_epoch(const lpc_ctx *c, const ResidentStep &rs, int32_t t0, int32_t t1, double weight,
+                                bool traced, uint32_t *n_clipped, hipStream_t st) {
   const Shape s = shape_of(c);
   ColumnArgs a{};
   a.X = c->prob.X; a.ldx = c->prob.ldx; a.n = c->n; a.y = c->prob.y; a.z_snap = rs.z_snap; a.mu = rs.mu;
-  a.w_snap = w_snap; a.yv = rs.y; a.zv = rs.z; a.flags = c->s.flags;
+  a.w_snap = rs.w_snap; a.yv = t0 > 0 ? c->s.cl_y : rs.y; a.zv = t0 > 0 ? c->s.cl_z : rs.z; a.flags = c->s.flags;
   a.packed = traced ? c->s.packed : nullptr; a.delta_out = c->s.delta; a.n_clipped = n_clipped;
   a.ctl = c->s.cl_ctl;
   const ColumnScratch w = columns_scratch(c);
   a.marg = c->s.cl_msg; a.stats = a.marg + w.marg; a.scale_ex = a.stats + w.stats; a.msg = a.scale_ex + w.scale;
   a.vec = a.msg + w.msg;
-  a.x_mid = c->s.w; a.ysum_mid = c->s.ysum; a.it0 = t0; a.it1 = t1; a.weight = weight;
+  a.x_mid = c->s.w; a.ysum_mid = c->s.ysum; a.y_mid = c->s.cl_y; a.z_mid = c->s.cl_z; a.it0 = t0; a.it1 = t1; a.weight = weight;
   a.d = (int32_t)c->d; a.W = (int32_t)c->W; a.N = c->cfg.N; a.nvec = c->cfg.N + (rs.alpc ? 1 : 0);
-  a.G = s.G; a.per_die = s.per_die; a.B = c->cfg.B; a.m = c->cfg.m;
+  a.G = s.G; a.per_die = s.per_die; a.B = c->cfg.B;
   a.rpw = (c->cfg.B + kColRowWaves - 1) / kColRowWaves; a.S = (64 * s.k + 255) / 256;
   a.bits = c->quant ? c->cfg.bits : 0; a.scheme = c->quant ? c->cfg.scheme : -1; a.loss = c->prob.loss;
   a.tag0 = rs.tag0; a.spin_limit = c->spin_limit;
@@ -618,7 +615,7 @@ hipError_t launch_columns_epoch(const lpc_ctx *c, const ResidentStep &rs, float 
   a.step_y = rs.step_y; consts(rs.step_y, &a.thr_y, &a.shrink_y);
   a.alpha = rs.alpha; consts(rs.alpha, &a.thr_z, &a.shrink_z);
   a.t1 = rs.tau1; a.t2 = rs.tau2; a.t3 = (float)(1.0 - (double)rs.tau1 - (double)rs.tau2); a.theta = (double)rs.theta;
-  a.scale = (float)(1.0 / (double)c->cfg.B); a.snap_scale = (float)snap_scale;
+  a.scale = (float)(1.0 / (double)c->cfg.B);
   const void *fn = nullptr;
   const int q = !c->quant ? kPlain : (c->cfg.scheme == LPC_SCHEME_A ? kOwnScale : kSharedScale);
 #define LPC_COLUMNS_Q(K_, Q_)                                                                    \

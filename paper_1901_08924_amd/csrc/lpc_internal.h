@@ -145,6 +145,7 @@ struct Scratch {
   unsigned long long *res_trace;  // [m][16] time stamps of the resident loop's phases (lpc_resident_trace)
   unsigned long long *cl_msg, *cl_vec, *cl_scale;  // lpc_cluster.hip: tagged words (cluster_scratch() says how many)
   uint32_t *cl_ctl;     // [16]
+  float *cl_y, *cl_z;   // [d] each: Alg. 2's y and z between the launches of such a loop, or until it is through
   unsigned long long *iter_slots;  // two sets of [tiles][N][4] statistics exchanged between the workgroups of the
                                    // two-launch inner iteration (all ones = empty)
   uint32_t *touched;    // [N][bitmap_words] sparse inner iteration: one bit per 32-coordinate segment of u^i
@@ -197,6 +198,7 @@ struct lpc_ctx {
   bool cols_capable = false;   // ... what form 2 needs
   bool cluster_capable = false;  // the inner loop fits lpc_cluster.hip
   bool columns_capable = false;  // ... or lpc_columns.hip
+  bool loop_waits = false;       // ... and its workgroups wait for each other there
   bool res_capable = false;    // ... what form 3 (the resident inner loop) needs
   bool res_trace_on = false;   // the next resident launches leave their phase time stamps
   uint32_t res_tag = 0;        // tags handed to resident launches so far (each launch takes m + 1)
@@ -267,11 +269,16 @@ size_t resident_ctl_words();
 hipError_t launch_resident_epoch(const lpc_ctx *c, const ResidentStep &rs, hipStream_t st);
 
 // The inner loop of narrow problems in one launch (lpc_cluster.hip); rs.w, rs.ysum are not used.  snap_scale: 1 / the sum
-// of the weights of Alg. 2 step 15.  w_snap: the snapshot, in and out.
+// of the weights of Alg. 2 step 15.  w_snap: the snapshot, in, and out where the launch's workgroups do not wait for each
+// other; where they do (cluster_waits, and lpc_columns.hip), launch_commit_epoch writes it after the last launch, unless
+// one of them gave up, and rs.y, rs.z likewise.
 struct ClusterScratch {
   size_t msg, vec, scale;  // 64-bit words
 };
 bool cluster_supported(const lpc_ctx *c);
+bool cluster_waits(const lpc_ctx *c);
+hipError_t launch_commit_epoch(const lpc_ctx *c, const ResidentStep &rs, double snap_scale, float *w_snap,
+                               hipStream_t st);
 ClusterScratch cluster_scratch(const lpc_ctx *c);
 // Iterations t0 .. t1 - 1 of the m; `weight` is that of iteration t0 (Alg. 2 step 15), what lies between two launches
 // of one loop is left in s.w and s.ysum.  n_clipped (or null) is added to.
@@ -285,8 +292,8 @@ struct ColumnScratch {
 };
 bool columns_supported(const lpc_ctx *c);
 ColumnScratch columns_scratch(const lpc_ctx *c);
-hipError_t launch_columns_epoch(const lpc_ctx *c, const ResidentStep &rs, float *w_snap, double snap_scale, int32_t t0,
-                                int32_t t1, double weight, bool traced, uint32_t *n_clipped, hipStream_t st);
+hipError_t launch_columns_epoch(const lpc_ctx *c, const ResidentStep &rs, int32_t t0, int32_t t1, double weight,
+                                bool traced, uint32_t *n_clipped, hipStream_t st);
 
 // CSR GLM passes (lpc_csr.hip)
 int csr_head_columns(int64_t d);

@@ -1897,10 +1897,11 @@ __global__ __launch_bounds__(1024) void objective_reg_kernel(const float *__rest
 }
 
 // out[0] = scale * sum of the n_loss loss partials (or *base where there are none) + sum of the n <= 256 partials: a
-// call's one number, handed to the waiting host (hand_over).  One workgroup; fixed order.
+// call's one number, handed to the waiting host (hand_over) with the context's flags: out[1].  One workgroup; fixed order.
 __global__ __launch_bounds__(kThreads) void fold_result_kernel(const double *__restrict__ partial, int32_t n,
                                                                const double *__restrict__ loss, int32_t n_loss,
                                                                double scale, const double *__restrict__ base,
+                                                               const uint32_t *__restrict__ flags,
                                                                double *__restrict__ out) {
   __shared__ double red[4];
   const int tid = threadIdx.x;
@@ -1917,6 +1918,7 @@ __global__ __launch_bounds__(kThreads) void fold_result_kernel(const double *__r
   __syncthreads();
   if (tid == 0) {
     *out = (n_loss > 0 ? (((red[0] + red[1]) + red[2]) + red[3]) * scale : base ? *base : 0.0) + t;
+    reinterpret_cast<unsigned long long *>(out)[1] = flags[0];
     hand_over(out);
   }
 }
@@ -2459,7 +2461,7 @@ int32_t result_groups(const lpc_ctx *c) {
 hipError_t launch_fold_result(const lpc_ctx *c, int32_t groups, const double *loss, int32_t n_loss, double scale,
                               const double *base, double *out, hipStream_t st) {
   hipLaunchKernelGGL(fold_result_kernel, dim3(1), dim3(kThreads), 0, st, (const double *)c->s.stat_part, groups, loss,
-                     n_loss, scale, base, out);
+                     n_loss, scale, base, (const uint32_t *)c->s.flags, out);
   return hipGetLastError();
 }
 

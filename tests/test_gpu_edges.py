@@ -170,6 +170,52 @@ def test_epoch_in_one_launch_that_gives_up_waiting_says_so(d):
     ctx.close()
 
 
+# one workgroup per worker and column blocks; two iterations, so that the last one's waits are among those that run out
+@pytest.mark.parametrize("d,N,over", [(90, 8, {}), (200, 5, dict(algo=lpco.ALGO_ALPC_GC)), (4096, 8, {}), (4096, 8, dict(bits=32)),
+                                      (2049, 3, dict(algo=lpco.ALGO_ALPC_GC, scheme=lpco.SCHEME_B))])
+def test_epoch_that_gives_up_does_not_take_place(d, N, over):
+    """However many polls the waits are given: either w, y and z are the epoch's, or they are what they were and every call
+    that answers to the host says so until the flags are taken."""
+    from paper_1901_08924_amd import lpc
+    sp = lpc_synth.make("c2", n=2048, d=d, N=N, B=16, seed=d)
+    ctx = gpu_context(sp, **dict(dict(m=2, L=2.0, tau2=0.5, eta=0.1), **over))
+    start = [(0.1 * np.random.default_rng(k).standard_normal(d)).astype(np.float32) for k in range(3)]
+
+    def epoch(spin, call):
+        ctx.tune(lpc.TUNE_SPIN_LIMIT, spin)
+        w, y, z = map(to_dev, start)
+        call(w, 3, y, z)
+        return [t.cpu().numpy() for t in (w, y, z)], w
+
+    want, w = epoch(1 << 15, ctx.epoch)
+    P = ctx.objective(w)
+    assert ctx.take_device_flags() == 0 and not np.array_equal(want[0], start[0])
+    for call in (ctx.epoch, ctx.epoch_traced):
+        for spin in (0, 1, 1, 2, 4, 8):
+            got, w = epoch(spin, call)
+            gave_up = not np.array_equal(got[0], want[0])
+            assert gave_up or spin > 0
+            for g, v in zip(got, start if gave_up else want):
+                assert np.array_equal(g, v)
+            if gave_up:
+                for answer in (lambda: ctx.objective(w), lambda: ctx.gradient_mapping(w, 0.1)):
+                    with pytest.raises(lpc.LpcError) as e:
+                        answer()
+                    assert e.value.code == lpc.EDEVICE
+                assert ctx.take_device_flags() == lpc.EDEVICE
+            assert ctx.take_device_flags() == 0
+            assert (ctx.objective(w) == P) == (not gave_up)
+    ctx.tune(lpc.TUNE_SPIN_LIMIT, 0)
+    if over.get("bits", 4) < 32:
+        with pytest.raises(lpc.LpcError):
+            ctx.clip_sweep(to_dev(start[0]), [0.5], 1)
+        with pytest.raises(lpc.LpcError):
+            ctx.epoch_traced(to_dev(start[0]), 3, to_dev(start[1]), to_dev(start[2]), coded=True)
+    with pytest.raises(lpc.LpcError):
+        ctx.epoch_report(to_dev(start[0]), 3, to_dev(start[1]), to_dev(start[2]))
+    ctx.close()
+
+
 @pytest.mark.parametrize("bits", [2, 3, 5, 7, 8, 9, 10, 13, 16])
 @pytest.mark.parametrize("d,N", [(1, 2), (31, 3), (66, 5), (1025, 1), (20003, 9)])
 def test_shared_scale_receiver_at_every_width(bits, d, N):
