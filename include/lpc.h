@@ -370,6 +370,9 @@ lpc_status lpc_debug_gemm(const float *A, const float *B, float *C, int32_t M, i
  *     their u^i differ in the last bits.  Every form gives the same bits from run to run.
  *   LPC_TUNE_ITER_TILE: form 1: coordinates per workgroup of the second launch, 64 or 128;
  *   LPC_TUNE_ITER_THREADS: form 1: its threads per workgroup, 256 or 512;
+ *   LPC_TUNE_COMPUTE_UNITS: the compute units that the default form's workgroups, which wait for each other, may count on
+ *     (not set: the device's).  Where other work holds part of the GPU; an epoch whose launch needs more, or is refused
+ *     by the runtime, takes form 0.
  *   LPC_TUNE_SPIN_LIMIT: form 1 (for the others see there): polls before a workgroup gives up waiting (it then finishes
  *     normally with what it has and lpc_take_device_flags reports LPC_EDEVICE); 0 makes every wait give up at once (tests of that path).
  * LPC_EINVAL for an unknown key or value, LPC_EUNSUPPORTED where the context cannot run the form. */
@@ -377,7 +380,8 @@ typedef enum {
   LPC_TUNE_ITER_FORM = 0,
   LPC_TUNE_ITER_TILE = 1,
   LPC_TUNE_ITER_THREADS = 2,
-  LPC_TUNE_SPIN_LIMIT = 3
+  LPC_TUNE_SPIN_LIMIT = 3,
+  LPC_TUNE_COMPUTE_UNITS = 4
 } lpc_tune_key;
 lpc_status lpc_tune(lpc_ctx *ctx, int32_t key, int64_t value);
 

@@ -226,6 +226,12 @@ lpc_status fill_ctx(lpc_ctx *c, const lpc_problem *p, const lpc_config *cfg) {
   // calls answer LPC_EUNSUPPORTED.
   c->grad_ok = p->loss != LPC_LOSS_MLP_SOFTMAX && !is_csr(*p) && dense_supported(p->d, p->ldx, p->X);
   c->cus = 256;  // MI355X
+  // a partition of one has fewer: what its launches may wait for (the sizes of the others, which fix orders of sums, stay)
+  int device = 0, units = 0;
+  if (hipGetDevice(&device) == hipSuccess &&
+      hipDeviceGetAttribute(&units, hipDeviceAttributeMultiprocessorCount, device) == hipSuccess && units > 0)
+    c->device_cus = units;
+  c->usable_cus = c->device_cus;
   c->csr = is_csr(*p);
   c->mlp = p->loss == LPC_LOSS_MLP_SOFTMAX;
   if (c->mlp) {
@@ -549,6 +555,10 @@ lpc_status lpc_tune(lpc_ctx *ctx, int32_t key, int64_t value) {
       if (value != 256 && value != 512) return LPC_EINVAL;
       ctx->iter_threads = (int32_t)value;
       return LPC_OK;
+    case LPC_TUNE_COMPUTE_UNITS:
+      if (value < 1 || value > ctx->device_cus) return LPC_EINVAL;
+      ctx->usable_cus = (int32_t)value;
+      return LPC_OK;
     case LPC_TUNE_SPIN_LIMIT:
       if (value < 0 || value > (int64_t)(1 << 24)) return LPC_EINVAL;
       ctx->spin_limit = (uint32_t)value;
@@ -804,19 +814,22 @@ lpc_status lpc_epoch(lpc_ctx *ctx, float *w_snap, float *y, float *z, uint32_t e
     };
     // what the loop leaves becomes the caller's, unless a workgroup gave up waiting for the others
     const bool commits = c->loop_waits;
+    bool refused = false;  // the runtime does not take the first launch: nothing has happened, the separate ones follow
     if (!tracing) {
       ProfScope ps(c, LPC_PROF_RESIDENT, st);
-      LPC_TRY_HIP(launch(0, g.m, 1.0, nullptr));
-      return commits ? dev(launch_commit_epoch(c, rs, 1.0 / wsum, w_snap, st)) : LPC_OK;
+      refused = launch(0, g.m, 1.0, nullptr) != hipSuccess;
+    } else {
+      double weight = 1.0;
+      for (int32_t t = 0; t < g.m && !refused; ++t) {
+        if (c->quant) LPC_TRY_HIP(launch_fill_u32(s.n_clipped, 0u, g.N, st));
+        refused = launch(t, t + 1, weight, c->quant ? s.n_clipped : nullptr) != hipSuccess;
+        if (refused && t > 0) return LPC_EDEVICE;
+        if (!refused) LPC_TRY(record_iteration(c, t, st));
+        weight *= (double)rs.theta;
+      }
     }
-    double weight = 1.0;
-    for (int32_t t = 0; t < g.m; ++t) {
-      if (c->quant) LPC_TRY_HIP(launch_fill_u32(s.n_clipped, 0u, g.N, st));
-      LPC_TRY_HIP(launch(t, t + 1, weight, c->quant ? s.n_clipped : nullptr));
-      LPC_TRY(record_iteration(c, t, st));
-      weight *= (double)rs.theta;
-    }
-    return commits ? dev(launch_commit_epoch(c, rs, 1.0 / wsum, w_snap, st)) : LPC_OK;
+    if (!refused) return commits ? dev(launch_commit_epoch(c, rs, 1.0 / wsum, w_snap, st)) : LPC_OK;
+    (void)hipGetLastError();  // the launches below ask for theirs
   }
   if (g.algo == LPC_ALGO_LPC) {
     LPC_TRY_HIP(launch_copy(s.w, w_snap, c->d, st));  // x_0 = x~

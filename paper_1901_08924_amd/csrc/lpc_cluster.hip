@@ -608,6 +608,7 @@ hipError_t launch_commit_epoch(const lpc_ctx *c, const ResidentStep &rs, double 
 hipError_t launch_cluster_epoch(const lpc_ctx *c, const ResidentStep &rs, float *w_snap, double snap_scale, int32_t t0,
                                 int32_t t1, double weight, uint32_t *n_clipped, hipStream_t st) {
   const Shape s = shape_of(c);
+  if (s.G > c->usable_cus) return hipErrorCooperativeLaunchTooLarge;
   ClusterArgs a{};
   a.X = c->prob.X; a.ldx = c->prob.ldx; a.n = c->n; a.y = c->prob.y; a.z_snap = rs.z_snap; a.mu = rs.mu;
   // one workgroup in a launch: nobody can give up, the caller's vectors are written in place
@@ -670,7 +671,7 @@ hipError_t launch_cluster_epoch(const lpc_ctx *c, const ResidentStep &rs, float 
   }
   // workgroup k of a launch runs on die k mod 8: every eighth one works, the others leave at once, so that the words
   // cross inside one die's L2 (only the speed depends on it)
-  a.spread = s.G <= 32 ? 8 : 1;
+  a.spread = 8 * s.G <= c->usable_cus ? 8 : 1;
   return hipLaunchCooperativeKernel(fn, dim3((unsigned)(s.G * a.spread)), dim3(kClThreads), args, (unsigned)s.lds, st);
 }
 

@@ -564,7 +564,7 @@ Shape shape_of(const lpc_ctx *c) {
     const bool extra = alpc && N % kDies == 0;  // the shared batch's group spread over what the workers leave
     const int per_die = (N + (extra ? 0 : alpc) + kDies - 1) / kDies;
     const int slots = per_die * G + (extra ? (G + kDies - 1) / kDies : 0);
-    if (k < 12 ? G > 16 || slots > 24 : G > 32 || slots * kDies > c->cus) continue;
+    if (slots * kDies > c->device_cus || (k < 12 ? G > 16 || slots > 24 : G > 32)) continue;
     s.k = k; s.G = G; s.per_die = per_die; s.slots = slots;
     return s;
   }
@@ -590,6 +590,7 @@ ColumnScratch columns_scratch(const lpc_ctx *c) {
 hipError_t launch_columns_epoch(const lpc_ctx *c, const ResidentStep &rs, int32_t t0, int32_t t1, double weight,
                                 bool traced, uint32_t *n_clipped, hipStream_t st) {
   const Shape s = shape_of(c);
+  if (s.slots * kDies > c->usable_cus) return hipErrorCooperativeLaunchTooLarge;
   ColumnArgs a{};
   a.X = c->prob.X; a.ldx = c->prob.ldx; a.n = c->n; a.y = c->prob.y; a.z_snap = rs.z_snap; a.mu = rs.mu;
   a.w_snap = rs.w_snap; a.yv = t0 > 0 ? c->s.cl_y : rs.y; a.zv = t0 > 0 ? c->s.cl_z : rs.z; a.flags = c->s.flags;

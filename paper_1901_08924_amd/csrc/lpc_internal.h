@@ -185,7 +185,8 @@ struct lpc_ctx {
   int32_t full_grad_wgs;  // workgroups of the snapshot pass (= partial rows it writes)
   int32_t vr_parts;       // partial rows per worker written by the worker pass
   int32_t stat_slots;     // statistic partials per vector
-  int32_t cus;            // compute units of the device (256 on MI355X)
+  int32_t cus;            // compute units that launches are sized for (256: an MI355X)
+  int32_t device_cus = 256, usable_cus = 256;  // the device's; those that workgroups waiting for each other may count on
   int32_t fold_slices;    // slices of the two-level fold of the snapshot pass's partial rows
   // form of the small-d dense inner iteration (lpc_tune): -1 = not chosen (form 0, or lpc_cluster.hip,
   // lpc_columns.hip); 0 = rows, fold, exchange (three launches); 1 = rows,

@@ -216,6 +216,33 @@ def test_epoch_that_gives_up_does_not_take_place(d, N, over):
     ctx.close()
 
 
+@pytest.mark.parametrize("d,N,over", [(90, 16, {}), (512, 4, {}), (4096, 8, {}), (4096, 8, dict(algo=lpco.ALGO_ALPC_GC))])
+def test_epoch_whose_launch_is_refused_takes_the_separate_launches(d, N, over):
+    from paper_1901_08924_amd import lpc
+    sp = lpc_synth.make("c2", n=2048, d=d, N=N, B=16, seed=d)
+    ctx, form0 = (gpu_context(sp, **dict(dict(m=4, L=2.0, tau2=0.5), **over)) for _ in range(2))
+    form0.tune(lpc.TUNE_ITER_FORM, 0)
+
+    def epoch(c, traced):
+        w, y, z = to_dev(sp.w0), to_dev(sp.w0), to_dev(sp.w0)
+        (c.epoch_traced if traced else c.epoch)(w, 1, y, z)
+        assert c.take_device_flags() == 0
+        return np.stack([t.cpu().numpy() for t in (w, y, z)])
+
+    for traced in (False, True):
+        whole, separate = epoch(ctx, traced), epoch(form0, traced)
+        ctx.tune(lpc.TUNE_COMPUTE_UNITS, 3)
+        assert np.array_equal(epoch(ctx, traced), separate)
+        ctx.tune(lpc.TUNE_COMPUTE_UNITS, 256)
+        assert np.array_equal(epoch(ctx, traced), whole)
+        assert not np.array_equal(whole, separate)      # another order of sums shows which route it was
+    for value in (0, 257, -1):
+        with pytest.raises(lpc.LpcError):
+            ctx.tune(lpc.TUNE_COMPUTE_UNITS, value)
+    ctx.close()
+    form0.close()
+
+
 @pytest.mark.parametrize("bits", [2, 3, 5, 7, 8, 9, 10, 13, 16])
 @pytest.mark.parametrize("d,N", [(1, 2), (31, 3), (66, 5), (1025, 1), (20003, 9)])
 def test_shared_scale_receiver_at_every_width(bits, d, N):
