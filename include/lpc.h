@@ -343,7 +343,7 @@ lpc_status lpc_debug_gemm(const float *A, const float *B, float *C, int32_t M, i
 /* ---- tuning and test aid (no passage of the paper) -----------------------------------------
  * Form and launch shape of the inner iteration on small dense problems (d_pad <= 16384, N <= 64).
  *   LPC_TUNE_ITER_FORM:
- *     not set: form 0; on narrow problems (d <= 256, or d <= 1024 and b > 8, and a batch that fits the registers of one workgroup, every scheme,
+ *     -1, or not set: form 0; on narrow problems (d <= 256, or d <= 1024 and b > 8, and a batch that fits the registers of one workgroup, every scheme,
  *       with or without quantization; not while the stream is being captured) all m inner iterations in one cooperative
  *       launch with a workgroup per worker, whose waits LPC_TUNE_SPIN_LIMIT bounds as it does form 3's; on wide problems
  *       (d <= 24576, B <= 64, b <= 8 or quantization off, as far as the workers' column blocks fit the compute units)

@@ -542,7 +542,7 @@ lpc_status lpc_tune(lpc_ctx *ctx, int32_t key, int64_t value) {
   if (!ctx) return LPC_ENULL;
   switch (key) {
     case LPC_TUNE_ITER_FORM:
-      if (value < 0 || value > 3) return LPC_EINVAL;
+      if (value < -1 || value > 3) return LPC_EINVAL;
       if ((value == 1 && !ctx->iter2_capable) || (value == 2 && !ctx->cols_capable) || (value == 3 && !ctx->res_capable))
         return LPC_EUNSUPPORTED;
       ctx->iter_form = (int32_t)value;

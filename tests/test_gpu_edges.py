@@ -243,6 +243,27 @@ def test_epoch_whose_launch_is_refused_takes_the_separate_launches(d, N, over):
     form0.close()
 
 
+def test_default_form_can_be_chosen_again():
+    from paper_1901_08924_amd import lpc
+    sp = lpc_synth.make("c2", n=2048, d=4096, N=4, B=16)
+    ctx = gpu_context(sp, m=4)
+
+    def epoch():
+        w = to_dev(sp.w0)
+        ctx.epoch(w, 1)
+        return w.cpu().numpy()
+
+    default = epoch()
+    ctx.tune(lpc.TUNE_ITER_FORM, 0)
+    assert not np.array_equal(epoch(), default)
+    ctx.tune(lpc.TUNE_ITER_FORM, -1)
+    assert np.array_equal(epoch(), default)
+    for form in (-2, 4):
+        with pytest.raises(lpc.LpcError):
+            ctx.tune(lpc.TUNE_ITER_FORM, form)
+    ctx.close()
+
+
 @pytest.mark.parametrize("bits", [2, 3, 5, 7, 8, 9, 10, 13, 16])
 @pytest.mark.parametrize("d,N", [(1, 2), (31, 3), (66, 5), (1025, 1), (20003, 9)])
 def test_shared_scale_receiver_at_every_width(bits, d, N):
