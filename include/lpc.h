@@ -132,7 +132,7 @@ lpc_status lpc_full_grad(lpc_ctx *ctx, const float *w, float *mu, float *z, doub
  * stats[i] = { |u^i|_inf, sum_j u_j, sum_j u_j^2, number of non-finite u_j }
  * (4 doubles per worker, may be NULL).  kind = LPC_BATCH_SHARED draws the one
  * batch J that ALPC-SVRG's double sampling shares between all workers and
- * writes row worker_begin only.  z_snap (n floats: X w_snap, as produced by
+ * writes row worker_begin only.  A worker's row is the same bits whichever range it is computed in.  z_snap (n floats: X w_snap, as produced by
  * lpc_full_grad) lets each sampled row be read once; NULL recomputes it. */
 lpc_status lpc_worker_vr_grad(lpc_ctx *ctx, const float *w, const float *w_snap, const float *z_snap,
                               uint32_t epoch, uint32_t iter, int32_t kind, int32_t worker_begin, int32_t worker_end,

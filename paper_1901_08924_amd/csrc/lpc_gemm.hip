@@ -313,6 +313,8 @@ struct TileWalker {
 // The order in which a workgroup walks K: tiles further down start four slabs further on.  Rows are often a multiple of
 // 4 KB apart, so that all rows of a slab, and the slabs that the workgroups of a die walk in step, lie in one or two
 // channels of the L2; the rotation spreads them (4096 x 1024 x 3072: 161 -> 146 us).
+// Not where the rows are the samples of several workers (GemmArgs::rows_alike): a sum's order must not depend on its row.
+// (There it gives nothing either: an epoch of the 3072-1024-1024-10 net 18.52 ms with it, 18.37 without.)
 __device__ __forceinline__ int rotated(int slab, int nslab, uint32_t tile) {
   const int at = slab + (int)((4u * tile) % (uint32_t)nslab);
   return at >= nslab ? at - nslab : at;
@@ -345,6 +347,7 @@ __global__ __launch_bounds__(256, 2) void gemm_tile_kernel(GemmArgs g) {
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
 
   const int nslab = (g.K + BK - 1) / BK, total = nslab * g.nseg;
+  const uint32_t turn = g.rows_alike ? 0u : blockIdx.y;
   float ra[2][8], rb[NJ][8];
   TileWalker<TA> wa;
   TileWalker<!TB> wb;
@@ -357,7 +360,7 @@ __global__ __launch_bounds__(256, 2) void gemm_tile_kernel(GemmArgs g) {
   }
   auto fetch = [&](int at) {
     const int s = at < nslab ? 0 : 1;
-    const int slab = rotated(s ? at - nslab : at, nslab, blockIdx.y);
+    const int slab = rotated(s ? at - nslab : at, nslab, turn);
     if constexpr (FULL) {
 #pragma unroll
       for (int h = 0; h < 2; ++h) wa.fetch(s, slab, h, ra[h]);
@@ -454,6 +457,7 @@ __global__ __launch_bounds__(512, 1) void gemm_pair_kernel(GemmArgs g) {
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
 
   const int nslab = (g.K + BK - 1) / BK, total = nslab * g.nseg;
+  const uint32_t turn = g.rows_alike ? 0u : blockIdx.y;
   float ra0[8], rb0[8], ra1[8], rb1[8];
   TileWalker<TA> wa;
   TileWalker<!TB> wb;
@@ -467,7 +471,7 @@ __global__ __launch_bounds__(512, 1) void gemm_pair_kernel(GemmArgs g) {
   auto fetch = [&](int at, float (&ra)[8], float (&rb)[8]) {
     at = at < total ? at : total - 1;  // past the end: a repeated load that nobody uses
     const int s = at < nslab ? 0 : 1;
-    const int slab = rotated(s ? at - nslab : at, nslab, blockIdx.y);
+    const int slab = rotated(s ? at - nslab : at, nslab, turn);
     if constexpr (FULL) {
       wa.fetch(s, slab, 0, ra);
       wb.fetch(s, slab, 0, rb);
@@ -659,7 +663,10 @@ __global__ __launch_bounds__(64 * NW) void gemm_small_kernel(GemmArgs g) {
     tile_statistics<NW>(g, red, tid, bz, (int64_t)blockIdx.y * gridDim.x + blockIdx.x, fmx, ssum, ssq, sbad);
 }
 
-// Which kernel and tile a product takes, from its sizes alone (the number of statistic partials follows from it).
+// Which kernel and tile a product takes, from its sizes alone (the number of statistic partials follows from it).  A worker
+// pass takes the sizes of all workers' rows, also where a call computes one of them (each kernel adds in an order of its own):
+// one worker of 16 of the 3072-1024-1024-10 net, B = 128, takes 265 us so, 137 us with kernels chosen for it alone; all 16
+// 472 us.
 // Single products on one MI355X, us (128 x 128 tile / 128 x 64 / 128 x 128 by eight wavefronts / 32 x 32 by four / 64 x
 // 64 by eight; tiles of 128 x 128 in brackets), which the lines below are drawn from:
 //   4096 x 4096 x 4096 [1024]     691 / 787 / 702 / 2540 / -       many tiles per CU: they cover each other
@@ -677,8 +684,9 @@ struct Plan {
   bool far = false;  // rows too far apart for 31-bit offsets within a tile
 };
 Plan plan_of(const GemmArgs &g) {
+  const int64_t rows = g.plan_rows > 0 ? g.plan_rows : g.M, batch = g.plan_batch > 0 ? g.plan_batch : g.batch;
   const auto tiles = [&](int tm, int tn) {
-    return (int64_t)((g.M + tm - 1) / tm) * ((g.N + tn - 1) / tn) * g.batch;
+    return (int64_t)((rows + tm - 1) / tm) * ((g.N + tn - 1) / tn) * batch;
   };
   for (int s = 0; s < g.nseg; ++s)
     if (g.lda[s] >= (1 << 22) || g.ldb[s] >= (1 << 22)) return {32, 32, 4, true};
@@ -840,7 +848,10 @@ __global__ __launch_bounds__(256) void gemm_skinny_tn_kernel(GemmArgs g, int kc)
 
 }  // namespace
 
-bool gemm_takes_matrix_cores(const GemmArgs &g) { return !(g.N <= kSkinnyN && !g.transB && g.M >= 64); }
+// (a transposed A's M is a layer's width, the other's the samples of a call, which must not decide)
+bool gemm_takes_matrix_cores(const GemmArgs &g) {
+  return !(g.N <= kSkinnyN && !g.transB && (g.M >= 64 || !g.transA));
+}
 
 int gemm_tiles(const GemmArgs &g) {
   const Plan p = plan_of(g);

@@ -49,6 +49,10 @@ struct GemmArgs {
   const float *relu_mask;  // same layout as C
   int accumulate;
   int nseg, batch;
+  // The kernel, and with it the order of every sum, is chosen for this many rows and batch items, whatever the launch's own
+  // (0: its own): a worker's vector is the same whichever others a call computes with it.
+  int plan_rows, plan_batch;
+  int rows_alike;  // rows are samples: every tile of them walks K in the same order, for the same reason
   // optional: every tile also leaves the statistics (|max|, sum, sum of squares, non-finite count) of the values
   // it stored as partial number stat_slot0 + tile index of its batch item (matrix-core path only)
   double *stat_part;

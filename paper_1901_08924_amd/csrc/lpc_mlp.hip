@@ -409,8 +409,10 @@ LastIn last_layer_input(const Net &nn, const float *in0, int64_t ld0) {
   return li;
 }
 
+// plan_rows (here and below): the rows that the products' kernels are chosen for, where those of a call may be fewer
+// (a worker pass: all workers' rows, also for a call that computes some workers); 0: `rows`.
 hipError_t forward(const Net &nn, const float *W, int64_t wstride, int nsets, const float *in0, int64_t ld0, int rows,
-                   hipStream_t st) {
+                   int plan_rows, hipStream_t st) {
   const bool skip_last = last_layer_input(nn, in0, ld0).fused;
   for (int l = 0; l < nn.L; ++l) {
     if (l == nn.L - 1 && skip_last) break;  // logits are formed inside the fused last-layer launch
@@ -426,7 +428,7 @@ hipError_t forward(const Net &nn, const float *W, int64_t wstride, int nsets, co
     g.strideC = nn.rows_cap * nn.dims[l + 1];
     g.M = rows; g.N = nn.dims[l + 1]; g.K = nn.dims[l];
     g.alpha = 1.0f; g.bias = W + nn.c->mlp_boff[l]; g.strideBias = wstride; g.relu = (l + 1 < nn.L) ? 1 : 0;
-    g.nseg = 1; g.batch = nsets;
+    g.nseg = 1; g.batch = nsets; g.plan_rows = plan_rows; g.rows_alike = plan_rows > 0 ? 1 : 0;
     hipError_t e = launch_gemm(g, st);
     if (e != hipSuccess) return e;
   }
@@ -436,7 +438,7 @@ hipError_t forward(const Net &nn, const float *W, int64_t wstride, int nsets, co
 // Deltas of every layer from the logits down for sets 0..nsets-1; set 1 (the snapshot parameters) gets
 // negated deltas, so that the weight gradients of the two sets add up to the variance-reduced difference.
 hipError_t backward_data(const Net &nn, const float *W, int64_t wstride, int nsets, const float *in0, int64_t ld0,
-                         const float *labels, int rows, double *row_loss, hipStream_t st) {
+                         const float *labels, int rows, int plan_rows, double *row_loss, hipStream_t st) {
   const int classes = nn.dims[nn.L];
   const LastIn li = last_layer_input(nn, in0, ld0);
   int first = nn.L - 1;  // highest layer whose input delta is still to be formed by a product
@@ -468,7 +470,7 @@ hipError_t backward_data(const Net &nn, const float *W, int64_t wstride, int nse
     g.C = nn.del(l, 0); g.ldc = nn.dims[l]; g.strideC = nn.rows_cap * nn.dims[l];
     g.M = rows; g.N = nn.dims[l]; g.K = nn.dims[l + 1];
     g.alpha = 1.0f; g.relu_mask = nn.act(l, 0);
-    g.nseg = 1; g.batch = nsets;
+    g.nseg = 1; g.batch = nsets; g.plan_rows = plan_rows; g.rows_alike = plan_rows > 0 ? 1 : 0;
     hipError_t e = launch_gemm(g, st);
     if (e != hipSuccess) return e;
   }
@@ -511,7 +513,7 @@ void mlp_plan(lpc_ctx *c) {
   int64_t widest = 0, skinny = 0;
   for (int l = 0; l < L; ++l) {
     GemmArgs g{};
-    g.M = dims[l]; g.N = dims[l + 1];
+    g.M = dims[l]; g.N = dims[l + 1]; g.transA = 1;
     if (dims[l + 1] > widest) widest = dims[l + 1];
     if (!gemm_takes_matrix_cores(g) && (int64_t)dims[l] * dims[l + 1] > skinny) skinny = (int64_t)dims[l] * dims[l + 1];
   }
@@ -528,9 +530,9 @@ hipError_t launch_mlp_full_grad(const lpc_ctx *c, const float *w, float *mu, dou
     const int rows = (int)((n_rows - r0 < chunk) ? n_rows - r0 : chunk);
     const float *in0 = c->prob.X + r0 * c->prob.ldx;
     const float *labels = c->prob.y + r0;
-    hipError_t e = forward(nn, w, 0, 1, in0, c->prob.ldx, rows, st);
+    hipError_t e = forward(nn, w, 0, 1, in0, c->prob.ldx, rows, 0, st);
     if (e != hipSuccess) return e;
-    e = backward_data(nn, w, 0, 1, in0, c->prob.ldx, labels, rows, f_out ? c->s.mlp_loss : nullptr, st);
+    e = backward_data(nn, w, 0, 1, in0, c->prob.ldx, labels, rows, 0, f_out ? c->s.mlp_loss : nullptr, st);
     if (e != hipSuccess) return e;
     if (f_out)
       hipLaunchKernelGGL(sum_rows_loss_kernel, dim3(1), dim3(256), 0, st, (const double *)c->s.mlp_loss, rows,
@@ -611,6 +613,7 @@ hipError_t launch_mlp_vr_grad(const lpc_ctx *c, const float *w, const float *w_s
                               int32_t *stat_slots_used, hipStream_t st) {
   Net nn{c->prob.mlp_nlayers, c->mlp_dims.data(), c, c->mlp_cap};
   const int nw = worker_end - worker_begin, B = c->cfg.B, rows = nw * B;
+  const int plan_rows = c->cfg.N * B;  // u^i must not depend on which workers this call computes
   const int in0 = nn.dims[0];
   hipLaunchKernelGGL(gather_rows_kernel, dim3((unsigned)rows), dim3(256), 0, st, c->prob.X, c->prob.ldx, c->prob.y,
                      c->n, in0, key, tag, worker_begin, B, c->s.mlp_xb, c->s.mlp_yb);
@@ -620,9 +623,9 @@ hipError_t launch_mlp_vr_grad(const lpc_ctx *c, const float *w, const float *w_s
   const intptr_t wbytes = (intptr_t)w_snap - (intptr_t)w;
   if (wbytes % 16 != 0) return hipErrorInvalidValue;
   const int64_t wstride = (int64_t)(wbytes / (intptr_t)sizeof(float));
-  hipError_t e = forward(nn, w, wstride, 2, c->s.mlp_xb, in0, rows, st);
+  hipError_t e = forward(nn, w, wstride, 2, c->s.mlp_xb, in0, rows, plan_rows, st);
   if (e != hipSuccess) return e;
-  e = backward_data(nn, w, wstride, 2, c->s.mlp_xb, in0, c->s.mlp_yb, rows, nullptr, st);
+  e = backward_data(nn, w, wstride, 2, c->s.mlp_xb, in0, c->s.mlp_yb, rows, plan_rows, nullptr, st);
   if (e != hipSuccess) return e;
   const float alpha = (float)(1.0 / (double)B);
   // Statistics of u^i (Sec. 3.2 needs |u|_inf before anything can be quantized): the kernels that write u^i leave
@@ -664,7 +667,7 @@ hipError_t launch_mlp_vr_grad(const lpc_ctx *c, const float *w, const float *w_s
     GemmArgs g{};
     g.transA = 1;
     g.C = U + c->mlp_woff[l]; g.ldc = out; g.strideC = c->d_pad;
-    g.M = in; g.N = out; g.K = B; g.alpha = alpha; g.batch = nw;
+    g.M = in; g.N = out; g.K = B; g.alpha = alpha; g.batch = nw; g.plan_batch = c->cfg.N;
     if (l == 0) {
       // same input rows for both sets: the deltas were added by the bias pass above, contract once
       g.nseg = 1;

@@ -39,6 +39,27 @@ def to_dev(a):
     return torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0")
 
 
+def assert_vectors_do_not_depend_on_the_range(ctx, sp):
+    """u^i and its statistics, bit for bit, whether a call computes all workers, some of them or one."""
+    import torch
+    rng = np.random.default_rng(5)
+    ws = to_dev((sp.w0 + 0.05 * rng.standard_normal(sp.d)).astype(np.float32))
+    w = to_dev((sp.w0 + 0.07 * rng.standard_normal(sp.d)).astype(np.float32))
+    zs, N = None, ctx.N
+    if sp.mlp_dims is None:
+        zs = torch.empty(sp.n, device="cuda")
+        ctx.full_grad(ws, torch.empty(sp.d, device="cuda"), zs)
+    half, outs = N // 2, []
+    for ranges in ([(0, N)], [(i, i + 1) for i in range(N)], [(half, N)] + ([(0, half)] if half else [])):
+        U = torch.full((N, ctx.d_pad), 9.0, device="cuda")
+        stats = torch.zeros(N, 4, dtype=torch.float64, device="cuda")
+        for begin, end in ranges:
+            ctx.worker_vr_grad(w, ws, zs, 1, 2, U, stats, worker_begin=begin, worker_end=end)
+        outs.append((U.cpu().numpy(), stats.cpu().numpy()))
+    for U, stats in outs[1:]:
+        assert np.array_equal(U, outs[0][0]) and np.array_equal(stats, outs[0][1])
+
+
 def batch_grad_inf(sp, w, epoch, iter_, tag, worker):
     """|grad f_B(w)|_inf for the batch B that `worker` draws at (epoch, iter): the oracle's full gradient over a
     problem made of exactly the sampled rows (duplicates kept).  The scale a variance-reduced difference of

@@ -6,7 +6,7 @@ import pytest
 
 import lpc_synth
 from oracle import lpco
-from _common import gpu_context, oracle_config, oracle_problem, to_dev
+from _common import assert_vectors_do_not_depend_on_the_range, gpu_context, oracle_config, oracle_problem, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -120,6 +120,18 @@ def test_mlp_worker_vr_gradient(dims, n, N, B):
             assert np.abs(got[i] - U_o[i]).max() <= 2e-5 * ref_scale
             assert not got[i, sp.d:].any()
         assert np.array_equal(stats.cpu().numpy()[:rows, 0], np.abs(got[:, :sp.d]).max(axis=1).astype(np.float64))
+    ctx.close()
+
+
+# products of a worker and of all of them on either side of the lines between the kernels; batches that are no multiple of
+# a tile; a last layer with few classes whose product takes the vector units
+@pytest.mark.parametrize("dims,N,B", [((64, 96, 33), 4, 16), ((300, 129, 70, 10), 4, 32), ((777, 391, 129, 33), 6, 50),
+                                      ((33, 18, 10), 4, 20), ((512, 640, 10), 16, 64), ((1024, 640, 256, 40), 9, 128),
+                                      ((40,) + (24,) * 9 + (5,), 3, 8)])
+def test_mlp_worker_vectors_do_not_depend_on_the_range(dims, N, B):
+    sp = lpc_synth.make("c5", n=1200, dims=dims, N=N, B=B, n_full=1200)
+    ctx = gpu_context(sp, clip_mode=lpco.CLIP_CSIGMA, clip=1.0)
+    assert_vectors_do_not_depend_on_the_range(ctx, sp)
     ctx.close()
 
 
