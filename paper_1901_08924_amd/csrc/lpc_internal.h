@@ -361,7 +361,7 @@ hipError_t launch_reduce_parts(const lpc_ctx *c, const float *part, int32_t part
 constexpr int kStatsNone = 0, kStatsFinal = 1, kStatsPartial = 2;
 bool fused_exchange_supported(const lpc_ctx *c);
 bool own_statistics(const lpc_ctx *c);  // launch_fused_exchange without statistic partials (nslots = 0)
-int reduce_parts_waves(const lpc_ctx *c, int32_t parts, int32_t nvec);
+int reduce_parts_waves(const lpc_ctx *c, int32_t parts);
 struct AlpcStep;
 hipError_t launch_cols_exchange(const lpc_ctx *c, const float *U, StreamKey key, uint32_t *packed, float *delta_out,
                                 const float *mu, float step, const float *w_in, float *w_out, const AlpcStep *al,

@@ -1948,13 +1948,14 @@ inline dim3 grid1d(int64_t n, int threads) { return dim3((unsigned)((n + threads
 
 }  // namespace
 
-// Wavefronts per workgroup of the fold of `parts` partial rows into nvec vectors (they take interleaved rows, which
+// Wavefronts per workgroup of the fold of `parts` partial rows into a vector (they take interleaved rows, which
 // fixes the order of the sum).  A wavefront takes eight partial rows per step: two wavefronts for up to 16 rows
 // when the launch has workgroups to spare, four otherwise (measured back to back on one machine: 16 rows and 2176
 // workgroups, two against four wavefronts +0.9 % inner iterations/s, eight -3.9 %; 16 rows and 4 workgroups,
-// two -2 %; 32 rows, two -2.3 %, eight +0.2 %)
-int reduce_parts_waves(const lpc_ctx *c, int32_t parts, int32_t nvec) {
-  const int64_t wgs = ((c->d_pad + 63) / 64) * (int64_t)nvec;
+// two -2 %; 32 rows, two -2.3 %, eight +0.2 %).  The vectors of an iteration count, not the call's: a vector is the same
+// whichever others a call computes with it.
+int reduce_parts_waves(const lpc_ctx *c, int32_t parts) {
+  const int64_t wgs = ((c->d_pad + 63) / 64) * (int64_t)(c->cfg.N + (c->cfg.algo != LPC_ALGO_LPC ? 1 : 0));
   return (parts <= 16 && wgs >= 2 * c->cus) ? 2 : 4;
 }
 
@@ -1964,7 +1965,7 @@ hipError_t launch_reduce_parts(const lpc_ctx *c, const float *part, int32_t part
   // `out` and `stats_out` point at the row of the first vector of this launch; vec_begin only selects
   // the scratch slots (statistics, quantizer parameters).
   const dim3 grid((unsigned)((c->d_pad + 63) / 64), (unsigned)nvec);
-  if (reduce_parts_waves(c, parts, nvec) == 2)
+  if (reduce_parts_waves(c, parts) == 2)
     LPC_LAUNCH_TIMED(reduce_parts_kernel<2>, grid, dim3(128), st, part, parts, c->d, c->d_pad, scale, out, ld_out,
                      vec_begin, (int32_t)stats_mode, sinks_of(c, stats_out));
   else
@@ -2313,7 +2314,7 @@ hipError_t launch_fused_iter(const lpc_ctx *c, StreamKey key, uint32_t *packed, 
     extra = warm_setup(c, key, false, &a);
   }
   ia.part = c->s.part; ia.parts = c->vr_parts; ia.nvec = c->cfg.N + (al ? 1 : 0);
-  ia.nwf = reduce_parts_waves(c, c->vr_parts, ia.nvec);
+  ia.nwf = reduce_parts_waves(c, c->vr_parts);
   ia.vec4 = (c->d % 4 == 0) ? 1 : 0;
   ia.scale = (float)(1.0 / (double)c->cfg.B);
   const int64_t set_words = fused_iter_slot_words(c) / 2;

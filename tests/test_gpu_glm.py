@@ -4,7 +4,7 @@ import pytest
 
 import lpc_synth
 from oracle import lpco
-from _common import batch_grad_inf, gpu_context, oracle_config, oracle_problem, to_dev
+from _common import assert_vectors_do_not_depend_on_the_range, batch_grad_inf, gpu_context, oracle_config, oracle_problem, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -102,6 +102,15 @@ def test_worker_vr_gradient(name, n, d, N, B, cached):
         U = torch.full((N, dp), 9.0, device="cuda")
         ctx.worker_vr_grad(dws, dws, None, 0, 0, U, None)
         assert not U.any().item()
+    ctx.close()
+
+
+@pytest.mark.parametrize("name,d,N,B", [("c1", 90, 8, 64), ("c2", 2048, 16, 16), ("c2", 4096, 8, 64), ("c4", 8192, 16, 8),
+                                         ("c2", 20000, 8, 4), ("c3", 50_000, 8, 64)])
+def test_worker_vectors_do_not_depend_on_the_range(name, d, N, B):
+    sp = lpc_synth.make(name, n=2048, d=d, N=N, B=B, seed=d)
+    ctx = gpu_context(sp, clip_mode=lpco.CLIP_CSIGMA, clip=1.0)
+    assert_vectors_do_not_depend_on_the_range(ctx, sp)
     ctx.close()
 
 
