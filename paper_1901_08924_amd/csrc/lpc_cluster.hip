@@ -66,7 +66,7 @@ struct ClusterArgs {
 enum : int { kPlain = 0, kOwnScale = 1, kSharedScale = 2 };
 
 // K: 64-column chunks of a row (d <= 64 K); RW: rows a wavefront holds; Q: the messages; ALPC: Alg. 2 and 3.
-template <int K, int RW, int Q, bool ALPC>
+template <int K, int RW, int Q, bool ALPC>  // Q == kPlain: K <= 4 only
 __global__ __launch_bounds__(kClThreads) void cluster_epoch_kernel(ClusterArgs a) {
   if (blockIdx.x % a.spread != 0) return;  // whole workgroups: see launch_cluster_epoch
   touch_kernel_arguments<(int)(sizeof(ClusterArgs))>();
@@ -539,6 +539,7 @@ Shape shape_of(const lpc_ctx *c) {
   const int32_t nvec = c->cfg.N + (c->cfg.algo != LPC_ALGO_LPC ? 1 : 0), B = c->cfg.B;
   if (c->csr || c->mlp || !c->grad_ok || c->n_full != c->n || c->n >= ((int64_t)1 << 31)) return s;
   if (c->d > 1024 || nvec > 64 || c->cfg.m < 1) return s;
+  if (c->d > 256 && !c->quant) return s;  // vectors in full precision cross in column blocks (lpc_columns.hip)
   if ((int64_t)c->cfg.N * (c->quant ? c->W + 1 : 1) > 8192) return s;
   const int chunks = (int)((c->d + 63) / 64);
   s.k = chunks <= 1 ? 1 : (chunks <= 2 ? 2 : (chunks <= 4 ? 4 : (chunks <= 8 ? 8 : 16)));
@@ -644,13 +645,15 @@ hipError_t launch_cluster_epoch(const lpc_ctx *c, const ResidentStep &rs, float 
   if (q == Q_)                                                                                                   \
     fn = rs.alpc ? reinterpret_cast<const void *>(&cluster_epoch_kernel<K_, RW_, Q_, true>)                      \
                  : reinterpret_cast<const void *>(&cluster_epoch_kernel<K_, RW_, Q_, false>);
+#define LPC_CLUSTER_MESSAGES(K_, RW_)                                                                            \
+  if (s.k == K_ && s.rw == RW_) { LPC_CLUSTER_Q(K_, RW_, kOwnScale) LPC_CLUSTER_Q(K_, RW_, kSharedScale) }
 #define LPC_CLUSTER(K_, RW_)                                                                                     \
-  if (s.k == K_ && s.rw == RW_) {                                                                                \
-    LPC_CLUSTER_Q(K_, RW_, kPlain) LPC_CLUSTER_Q(K_, RW_, kOwnScale) LPC_CLUSTER_Q(K_, RW_, kSharedScale)        \
-  }
+  LPC_CLUSTER_MESSAGES(K_, RW_)                                                                                  \
+  if (s.k == K_ && s.rw == RW_) { LPC_CLUSTER_Q(K_, RW_, kPlain) }
   LPC_CLUSTER(1, 4) LPC_CLUSTER(1, 16) LPC_CLUSTER(2, 4) LPC_CLUSTER(2, 16) LPC_CLUSTER(4, 4) LPC_CLUSTER(4, 8)
-  LPC_CLUSTER(8, 4) LPC_CLUSTER(16, 2)
+  LPC_CLUSTER_MESSAGES(8, 4) LPC_CLUSTER_MESSAGES(16, 2)
 #undef LPC_CLUSTER
+#undef LPC_CLUSTER_MESSAGES
 #undef LPC_CLUSTER_Q
   if (!fn) return hipErrorInvalidValue;
   if (s.lds > 60000) {  // wide rows only: once per thread and instantiation, for the most that any launch takes

@@ -137,6 +137,27 @@ def test_narrow_epochs_in_one_launch(d, N, B, over):
     _epochs_as_the_oracle(d, N, B, over)
 
 
+# rows of 257 to 1024 columns with messages of more than eight bits: a thread per coordinate of u^i; the largest batches
+# that fit the registers (64 rows up to d = 512, 32 beyond) and the most workers whose messages do
+@pytest.mark.parametrize("d,N,B,over", [
+    (257, 5, 64, dict(bits=9)), (300, 3, 7, dict(bits=16, scheme=lpco.SCHEME_C)), (320, 16, 33, dict(bits=12, scheme=lpco.SCHEME_B)),
+    (500, 2, 1, dict(bits=10, clip_mode=1, clip=2.0)), (512, 8, 64, dict(bits=9, algo=lpco.ALGO_ALPC_GC)),
+    (513, 4, 32, dict(bits=11)), (777, 9, 17, dict(bits=13, scheme=lpco.SCHEME_B, algo=lpco.ALGO_ALPC_GC)),
+    (1000, 2, 2, dict(bits=16, clip_mode=1, clip=1.0, algo=lpco.ALGO_ALPC_SC)), (1024, 15, 32, dict(bits=16)),
+    (1024, 3, 31, dict(bits=9, scheme=lpco.SCHEME_C, algo=lpco.ALGO_ALPC_GC))])
+def test_narrow_epochs_with_long_messages_in_one_launch(d, N, B, over):
+    from paper_1901_08924_amd import lpc
+    over = dict(over, L=2.0 if d % 2 else d + 8.0 * d ** 0.5)
+    _epochs_as_the_oracle(d, N, B, over)
+    sp = lpc_synth.make("c4", n=2048, d=d, N=N, B=B, seed=d)
+    ctx = gpu_context(sp, **dict(dict(m=2, tau2=0.5, sigma=1e-2), **over))
+    ctx.tune(lpc.TUNE_SPIN_LIMIT, 0)       # a loop of workgroups that wait for each other, or nothing would run out
+    w, y, z = to_dev(sp.w0), to_dev(sp.w0), to_dev(sp.w0)
+    ctx.epoch(w, 0, y, z)
+    assert ctx.take_device_flags() == lpc.EDEVICE
+    ctx.close()
+
+
 # column blocks of 128 to 768 columns, groups of 2 to 32 workgroups, the shared batch's group on a die of its own or spread
 # over what the workers leave; batches of 64 rows are the largest, the last three take the separate launches
 @pytest.mark.parametrize("d,N,B,over", [
