@@ -656,16 +656,9 @@ hipError_t launch_cluster_epoch(const lpc_ctx *c, const ResidentStep &rs, float 
 #undef LPC_CLUSTER_MESSAGES
 #undef LPC_CLUSTER_Q
   if (!fn) return hipErrorInvalidValue;
-  if (s.lds > 60000) {  // wide rows only: once per thread and instantiation, for the most that any launch takes
-    static thread_local const void *prepared[48] = {};
-    bool known = false;
-    for (const void *p : prepared) known = known || p == fn;
-    if (!known) {
-      const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kClLds);
-      if (e != hipSuccess) return e;
-      for (const void *&p : prepared)
-        if (!p) { p = fn; break; }
-    }
+  if (s.lds > 60000) {  // wide rows only; asked for at every launch, because it holds for the current device alone
+    const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kClLds);
+    if (e != hipSuccess) return e;
   }
   void *args[] = {&a};
   if (s.G == 1) {
