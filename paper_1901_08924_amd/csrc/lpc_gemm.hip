@@ -663,6 +663,47 @@ __global__ __launch_bounds__(64 * NW) void gemm_small_kernel(GemmArgs g) {
     tile_statistics<NW>(g, red, tid, bz, (int64_t)blockIdx.y * gridDim.x + blockIdx.x, fmx, ssum, ssq, sbad);
 }
 
+// One element of C in fp32 multiply-adds, k after k.
+template <bool TA, bool TB>
+__device__ __forceinline__ float plain_sum(const GemmArgs &g, int64_t bz, int row, int col) {
+  float t = 0.0f;
+  for (int s = 0; s < g.nseg; ++s) {
+    const float *A = (s ? g.A[1] : g.A[0]) + bz * (s ? g.strideA[1] : g.strideA[0]);
+    const float *B = (s ? g.B[1] : g.B[0]) + bz * (s ? g.strideB[1] : g.strideB[0]);
+    const int64_t lda = s ? g.lda[1] : g.lda[0], ldb = s ? g.ldb[1] : g.ldb[0];
+    for (int k = 0; k < g.K; ++k)
+      t = fmaf(TA ? A[k * lda + row] : A[row * lda + k], TB ? B[col * ldb + k] : B[k * ldb + col], t);
+  }
+  return t;
+}
+
+// Sums of at most kFewProducts products (two classes; a batch of one row): there the five small parts and what is left
+// out weigh more than the fp32 roundings they replace (error as above, K = 1: 2.5e-8 fp32, 3.4e-8 in parts; 2: 3.1e-8,
+// 3.4e-8; 3: 3.5e-8, 3.3e-8; 10: 5.9e-8, 3.4e-8; 64: 1.4e-7, 5.5e-8).  A 32 x 32 tile by four wavefronts.
+constexpr int kFewProducts = 2;
+template <bool TA, bool TB>
+__global__ __launch_bounds__(256) void gemm_few_kernel(GemmArgs g) {
+  __shared__ double red[16];
+  const int tid = threadIdx.x, col = blockIdx.x * 32 + (tid & 31);
+  const int64_t bz = blockIdx.z;
+  float fmx = 0.0f;
+  double ssum = 0.0, ssq = 0.0, sbad = 0.0;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int row = blockIdx.y * 32 + (tid >> 5) + 8 * r;
+    if (row < g.M && col < g.N) {
+      const float val = skinny_store(g, g.C + bz * g.strideC, bz, row, col, plain_sum<TA, TB>(g, bz, row, col));
+      if (isfinite(val)) {
+        fmx = fmaxf(fmx, fabsf(val)); ssum += (double)val; ssq += (double)val * (double)val;
+      } else {
+        sbad += 1.0;
+      }
+    }
+  }
+  if (g.stat_part)  // uniform
+    tile_statistics(g, red, tid, bz, (int64_t)blockIdx.y * gridDim.x + blockIdx.x, fmx, ssum, ssq, sbad);
+}
+
 // Which kernel and tile a product takes, from its sizes alone (the number of statistic partials follows from it).  A worker
 // pass takes the sizes of all workers' rows, also where a call computes one of them (each kernel adds in an order of its own):
 // one worker of 16 of the 3072-1024-1024-10 net, B = 128, takes 265 us so, 137 us with kernels chosen for it alone; all 16
@@ -680,7 +721,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_small_kernel(GemmArgs g) {
 //   1000 x  896 x  896 B' [56]     55 /  40 /  39 /   61 / 35       loads touch a line per lane)
 struct Plan {
   int tile_m, tile_n;
-  int waves;  // 0: the tile kernel, 1: its eight-wavefront form, else the small kernel with that many
+  int waves;  // 0: the tile kernel, 1: its eight-wavefront form, 2: few products, else the small kernel with that many
   bool far = false;  // rows too far apart for 31-bit offsets within a tile
 };
 Plan plan_of(const GemmArgs &g) {
@@ -688,6 +729,7 @@ Plan plan_of(const GemmArgs &g) {
   const auto tiles = [&](int tm, int tn) {
     return (int64_t)((rows + tm - 1) / tm) * ((g.N + tn - 1) / tn) * batch;
   };
+  if ((int64_t)g.K * g.nseg <= kFewProducts) return {32, 32, 2};
   for (int s = 0; s < g.nseg; ++s)
     if (g.lda[s] >= (1 << 22) || g.ldb[s] >= (1 << 22)) return {32, 32, 4, true};
   const int64_t k = (int64_t)g.K * g.nseg, t128 = tiles(128, 128), t64 = tiles(64, 64);
@@ -986,6 +1028,7 @@ hipError_t launch_gemm(const GemmArgs &g, hipStream_t st) {
 #define LPC_GEMM_LAUNCH(TA_, TB_)                                                                             \
   do {                                                                                                        \
     if (p.far) hipLaunchKernelGGL((gemm_small_kernel<TA_, TB_, 32, 4, true>), grid, dim3(256), 0, st, g);     \
+    else if (p.waves == 2) hipLaunchKernelGGL((gemm_few_kernel<TA_, TB_>), grid, dim3(256), 0, st, g);        \
     else if (p.waves == 0 && p.tile_n == 128) LPC_GEMM_TILE(gemm_tile_kernel, 256, TA_, TB_, 128);                 \
     else if (p.waves == 0) LPC_GEMM_TILE(gemm_tile_kernel, 256, TA_, TB_, 64);                                \
     else if (p.waves == 1) LPC_GEMM_TILE(gemm_pair_kernel, 512, TA_, TB_);                                    \

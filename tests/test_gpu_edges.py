@@ -41,6 +41,24 @@ def test_products_hold_fp32_precision_at_every_tile_edge(M, N, K, tA, tB):
     assert (np.abs(got - ref) / bound).max() < 1e-6 and np.isfinite(got).all()
 
 
+@pytest.mark.parametrize("tA,tB", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("K", [1, 2, 3, 4, 7, 8, 10, 15, 16, 17, 32, 33, 50, 100, 333])
+@pytest.mark.parametrize("M,N", [(300, 129), (1050, 650)])
+def test_products_are_no_less_exact_than_fp32_multiply_adds(M, N, K, tA, tB):
+    """2-norm of the error against 64 bits: at most that of a chain of fp32 multiply-adds; as long as that chain is what a
+    short product takes, its bits."""
+    rng = np.random.default_rng(K)
+    A, B = rng.standard_normal((M, K), dtype=np.float32), rng.standard_normal((K, N), dtype=np.float32)
+    got = _gemm(to_dev(A.T.copy() if tA else A), to_dev(B.T.copy() if tB else B), tA, tB)
+    A, B = A.astype(np.float64), B.astype(np.float64)
+    chain = np.zeros((M, N), np.float32)
+    for k in range(K):          # (the product of two fp32 numbers is exact in 64 bits)
+        chain = (chain.astype(np.float64) + np.outer(A[:, k], B[k])).astype(np.float32)
+    if K <= 2:
+        assert np.array_equal(got, chain)
+    assert np.linalg.norm(got - A @ B) <= np.linalg.norm(chain - A @ B)
+
+
 @pytest.mark.parametrize("M,N,K", [(40, 33, 70), (700, 700, 200), (2048, 1280, 256), (8192, 640, 64)])
 def test_products_use_all_24_bits_of_their_operands(M, N, K):
     """Integers of up to 24 bits times +-1 with few terms per sum: every result is exact or a part was dropped."""
