@@ -5,20 +5,26 @@
 // The only dense contractions of the hot path are the MLP's layer products, so this is where MFMA is used.  Inputs,
 // accumulation and results are fp32, and so is the precision, but the products are taken on the bf16 matrix
 // instructions: the fp32 ones (v_mfma_f32_32x32x2_f32) run at 157 TFLOP/s, the bf16 ones at sixteen times that.  Every
-// operand is cut, while it is staged, into three bf16 numbers that add up to it exactly,
+// operand is cut, while it is staged, into three bf16 numbers that add up to it exactly (the split of Henry, Tang and
+// Heinecke, "Leveraging the bfloat16 Artificial Intelligence Datatype For Higher-Precision Computations", ARITH 2019),
 //
 //   x = h + m + l,   h = bf16(x), m = bf16(x - h), l = x - h - m      (8 + 8 + 8 bits, each rounded to nearest),
 //
-// and x*y is taken as hh' + hm' + mh' + mm' + hl' + lh': six products, each exact in fp32, added up in fp32.  What is
-// left out, ml' + lm' + ll', is below 2^-24 |xy| (|m| <= 2^-8 |x|, |l| <= 2^-16 |x|, rounded to nearest, so of either
-// sign): less than the rounding of one fp32 addition of the sum.  Measured against fp64 (2-norm of the error over that of
-// the result, operands N(0,1)): K = 1024 / 2048 / 3072: 4.9e-7 / 7.0e-7 / 8.6e-7, where the
-// fp32 matrix instructions gave 5.7e-7 / 8.1e-7 / 9.9e-7; all operands positive: 3.4e-7 / 4.5e-7 / 4.7e-7 against
-// 4.9e-7 / 7.0e-7 / 7.4e-7 (a bf16 instruction adds sixteen products before it rounds, an fp32 one two).  (An infinite operand gives NaN where fp32 gives an infinity or NaN.)
+// and x*y is taken as hh' + hm' + mh' + mm' + hl' + lh': six products, each exact in fp32, added up in fp32, the small
+// ones first.  What is left out, ml' + lm' + ll', is at most 2^-24 |xy| (|m| <= 2^-8 |x|, |l| <= 2^-17 |x|): as much as
+// the rounding of one fp32 addition.  Measured against fp64 (2-norm of the error over that of the result, operands N(0,1),
+// fp32 matrix instructions -> this): K = 3: 3.5e-8 -> 3.3e-8, 10: 5.9e-8 -> 3.4e-8, 64: 1.4e-7 -> 5.5e-8 (small kernel),
+// 1.1e-7 (tile kernel), 128: 2.0e-7 -> 8.1e-8, 1.6e-7; 1024: 5.7e-7 -> 1.7e-7 to 2.4e-7 where wavefronts split K, 4.9e-7
+// in the tile kernel, 3072: 9.9e-7 -> 3.0e-7 to 4.3e-7, 8.6e-7; less again where all operands are positive (a bf16
+// instruction adds sixteen products before it rounds, an fp32 one two).  Sums of one or two products are less exact so
+// (gemm_few_kernel).  What bf16 has no room for: infinities and numbers that round to one (store_tile puts them right), and
+// the third part of an operand below 2^-110, which is then off by up to 2^-134.
 //
-// Two kernels share the epilogue's options:
+// Four kernels share the epilogue's options:
 //   gemm_tile_kernel: 128 x TN tiles of C through LDS, for products with enough tiles to occupy the chip;
-//   gemm_small_kernel: 32 x 32 tiles whose wavefronts split K between them, for the others.
+//   gemm_pair_kernel: the 128 x 128 tile by eight wavefronts, where there is about one tile per compute unit;
+//   gemm_small_kernel: 32 x 32 or 64 x 64 tiles whose wavefronts split K between them, for the others;
+//   gemm_few_kernel: sums of one or two products.
 // Operands may be given transposed (weight gradients A'D and data gradients D W' need it) and the K range may consist
 // of two segments with their own base pointers (the difference of two weight gradients is one contraction over stacked
 // rows).
@@ -141,6 +147,40 @@ __device__ __forceinline__ void fetch8(const float *__restrict__ p, int64_t ld, 
   }
 }
 
+// one element of C through all options of the launch
+__device__ __forceinline__ float skinny_store(const GemmArgs &g, float *C, int64_t bz, int row, int col, float acc) {
+  const int64_t off = (int64_t)row * g.ldc + col;
+  float val = g.alpha * acc + (g.bias ? g.bias[bz * g.strideBias + col] : 0.0f);
+  if (g.relu) val = relu(val);
+  if (g.relu_mask) val = g.relu_mask[off + (C - g.C)] > 0.0f ? val : 0.0f;
+  if (g.accumulate) val += C[off];
+  C[off] = val;
+  return val;
+}
+
+// One element of C in fp32 multiply-adds, k after k, four loads of either operand at a time; once a NaN, it stays one.
+template <bool TA, bool TB>
+__device__ __forceinline__ float plain_sum(const GemmArgs &g, int64_t bz, int row, int col) {
+  float t = 0.0f;
+  for (int s = 0; s < g.nseg; ++s) {
+    const float *A = (s ? g.A[1] : g.A[0]) + bz * (s ? g.strideA[1] : g.strideA[0]);
+    const float *B = (s ? g.B[1] : g.B[0]) + bz * (s ? g.strideB[1] : g.strideB[0]);
+    const int64_t lda = s ? g.lda[1] : g.lda[0], ldb = s ? g.ldb[1] : g.ldb[0];
+    for (int k0 = 0; k0 < g.K && t == t; k0 += 4) {
+      float a[4], b[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int k = k0 + i < g.K ? k0 + i : g.K - 1;
+        a[i] = TA ? A[k * lda + row] : A[row * lda + k];
+        b[i] = TB ? B[col * ldb + k] : B[k * ldb + col];
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) t = k0 + i < g.K ? fmaf(a[i], b[i], t) : t;
+    }
+  }
+  return t;
+}
+
 // Epilogue of one output tile: C (+)= alpha*acc (+ bias, ReLU, ReLU mask), and the statistics of the stored
 // values (per thread in fp32 -- at most 64 terms --, in fp64 across threads).
 // Accumulator layout of the 32x32 MFMA: lane l holds column (l % 32); register v holds row
@@ -186,56 +226,67 @@ __device__ __forceinline__ void store_tile_as(const GemmArgs &g, const floatx16 
   }
 }
 
-// Picks the instantiation for the (uniform) options of this launch: the MLP's products use four combinations;
-// anything else takes the general one.
-template <int TN, bool FULL>
+// Picks the instantiation for the (uniform) options of this launch: the MLP's products use five combinations;
+// anything else takes the general one, and so does a wavefront whose tile holds a NaN.  The bf16 parts cannot give an
+// infinity back (the second part of one is inf - inf), and round a finite number above the largest bf16, 3.39e38, to one:
+// what comes out as NaN is formed again in fp32 multiply-adds, where it may be an infinity or a number.
+template <bool TA, bool TB, int TN, bool FULL>
 __device__ __forceinline__ void store_tile(const GemmArgs &g, const floatx16 (&acc)[2][TN / 64], int m0, int n0,
                                            int64_t bz, int lane, int wm, int wn, float &fmx, float &ssum, float &ssq,
                                            float &sbad) {
   const bool bias = g.bias != nullptr, relu_on = g.relu != 0, mask = g.relu_mask != nullptr, accu = g.accumulate != 0,
              stat = g.stat_part != nullptr;
-  if (bias && relu_on && !mask && !accu && !stat)          // forward layer
-    store_tile_as<TN, FULL, true, true, false, false, false>(g, acc, m0, n0, bz, lane, wm, wn, fmx, ssum, ssq, sbad);
-  else if (!bias && !relu_on && mask && !accu && !stat)    // data gradient
-    store_tile_as<TN, FULL, false, false, true, false, false>(g, acc, m0, n0, bz, lane, wm, wn, fmx, ssum, ssq, sbad);
-  else if (!bias && !relu_on && !mask && !accu && stat)    // a worker's weight gradient, with its statistics
-    store_tile_as<TN, FULL, false, false, false, false, true>(g, acc, m0, n0, bz, lane, wm, wn, fmx, ssum, ssq, sbad);
-  else if (!bias && !relu_on && !mask && !stat && accu)    // snapshot weight gradient, accumulating
-    store_tile_as<TN, FULL, false, false, false, true, false>(g, acc, m0, n0, bz, lane, wm, wn, fmx, ssum, ssq, sbad);
-  else if (!bias && !relu_on && !mask && !stat)            // snapshot weight gradient, first chunk or block
-    store_tile_as<TN, FULL, false, false, false, false, false>(g, acc, m0, n0, bz, lane, wm, wn, fmx, ssum, ssq, sbad);
-  else {
-    // general: every option decided per element
-    constexpr int NJ = TN / 64;
-    float *C = g.C + bz * g.strideC;
-    const float *mk = mask ? g.relu_mask + bz * g.strideC : nullptr;
+  float odd = 0.0f;
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
+  for (int i = 0; i < 2; ++i)
 #pragma unroll
-      for (int j = 0; j < NJ; ++j) {
-        const int col = n0 + wn + 32 * j + (lane & 31);
-        if (col >= g.N) continue;
-        const float bv = bias ? g.bias[bz * g.strideBias + col] : 0.0f;
+    for (int j = 0; j < TN / 64; ++j)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int row = m0 + wm + 32 * i + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-          if (row >= g.M) continue;
-          const int64_t off = (int64_t)row * g.ldc + col;
-          float val = g.alpha * acc[i][j][v] + bv;
-          if (relu_on) val = relu(val);
-          if (mk) val = mk[off] > 0.0f ? val : 0.0f;
-          if (accu) val += C[off];
-          C[off] = val;
-          if (stat) {
-            if (isfinite(val)) {
-              fmx = fmaxf(fmx, fabsf(val)); ssum += val; ssq = fmaf(val, val, ssq);
-            } else {
-              sbad += 1.0f;
-            }
-          }
-        }
+      for (int v = 0; v < 16; ++v) odd = fmaf(acc[i][j][v], 0.0f, odd);  // NaN where one is, or an infinity
+  if (__ballot(odd != odd) == 0ull) {
+    if (bias && relu_on && !mask && !accu && !stat)          // forward layer
+      return store_tile_as<TN, FULL, true, true, false, false, false>(g, acc, m0, n0, bz, lane, wm, wn, fmx, ssum, ssq, sbad);
+    if (!bias && !relu_on && mask && !accu && !stat)    // data gradient
+      return store_tile_as<TN, FULL, false, false, true, false, false>(g, acc, m0, n0, bz, lane, wm, wn, fmx, ssum, ssq, sbad);
+    if (!bias && !relu_on && !mask && !accu && stat)    // a worker's weight gradient, with its statistics
+      return store_tile_as<TN, FULL, false, false, false, false, true>(g, acc, m0, n0, bz, lane, wm, wn, fmx, ssum, ssq, sbad);
+    if (!bias && !relu_on && !mask && !stat && accu)    // snapshot weight gradient, accumulating
+      return store_tile_as<TN, FULL, false, false, false, true, false>(g, acc, m0, n0, bz, lane, wm, wn, fmx, ssum, ssq, sbad);
+    if (!bias && !relu_on && !mask && !stat)            // snapshot weight gradient, first chunk or block
+      return store_tile_as<TN, FULL, false, false, false, false, false>(g, acc, m0, n0, bz, lane, wm, wn, fmx, ssum, ssq, sbad);
+  }
+  // general: every option decided per element
+  constexpr int NJ = TN / 64;
+  float *C = g.C + bz * g.strideC;
+  auto store = [&](int row, int col, float sum) {
+    const float val = skinny_store(g, C, bz, row, col, sum);
+    if (stat) {
+      if (isfinite(val)) {
+        fmx = fmaxf(fmx, fabsf(val)); ssum += val; ssq = fmaf(val, val, ssq);
+      } else {
+        sbad += 1.0f;
       }
     }
+  };
+  const int row0 = m0 + wm + 4 * (lane >> 5), col0 = n0 + wn + (lane & 31);
+  unsigned long long again = 0ull;  // element 16 (i NJ + j) + v
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int row = row0 + 32 * i + 8 * (v >> 2) + (v & 3), col = col0 + 32 * j;
+        if (row >= g.M || col >= g.N) continue;
+        if (acc[i][j][v] == acc[i][j][v]) store(row, col, acc[i][j][v]);
+        else again |= 1ull << (16 * (i * NJ + j) + v);
+      }
+    }
+  }
+  for (; again; again &= again - 1ull) {
+    const int e = __builtin_ctzll(again), v = e & 15, ij = e >> 4;
+    const int row = row0 + 32 * (ij / NJ) + 8 * (v >> 2) + (v & 3), col = col0 + 32 * (ij % NJ);
+    store(row, col, plain_sum<TA, TB>(g, bz, row, col));
   }
 }
 
@@ -254,17 +305,6 @@ __device__ __forceinline__ void tile_statistics(const GemmArgs &g, double *red, 
     double *p = g.stat_part + bz * g.stat_batch_stride + ((int64_t)g.stat_slot0 + tile) * 4;
     p[0] = a_t; p[1] = s_t; p[2] = q_t; p[3] = b_t;
   }
-}
-
-// one element of C through all options of the launch
-__device__ __forceinline__ float skinny_store(const GemmArgs &g, float *C, int64_t bz, int row, int col, float acc) {
-  const int64_t off = (int64_t)row * g.ldc + col;
-  float val = g.alpha * acc + (g.bias ? g.bias[bz * g.strideBias + col] : 0.0f);
-  if (g.relu) val = relu(val);
-  if (g.relu_mask) val = g.relu_mask[off + (C - g.C)] > 0.0f ? val : 0.0f;
-  if (g.accumulate) val += C[off];
-  C[off] = val;
-  return val;
 }
 
 // The same eight values for whole tiles, slab after slab (BK = 32 k each), with next to no address arithmetic: buffer
@@ -419,7 +459,7 @@ __global__ __launch_bounds__(256, 2) void gemm_tile_kernel(GemmArgs g) {
   }
 
   float fmx = 0.0f, ssum = 0.0f, ssq = 0.0f, sbad = 0.0f;
-  store_tile<TN, FULL>(g, acc, m0, n0, bz, lane, wm, wn, fmx, ssum, ssq, sbad);
+  store_tile<TA, TB, TN, FULL>(g, acc, m0, n0, bz, lane, wm, wn, fmx, ssum, ssq, sbad);
   if (g.stat_part) {
     __syncthreads();  // LDS has been read; the statistics may have it
     tile_statistics(g, reinterpret_cast<double *>(&As[0][0]), tid, bz, (int64_t)blockIdx.y * gridDim.x + blockIdx.x,
@@ -558,7 +598,7 @@ __global__ __launch_bounds__(512, 1) void gemm_pair_kernel(GemmArgs g) {
       for (int j = 0; j < 2; ++j)
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[i][j][v] += hand[((i * 2 + j) * 16 + v) * 64 + lane];
-    store_tile<128, FULL>(g, acc, m0, n0, bz, lane, wm, wn, fmx, ssum, ssq, sbad);
+    store_tile<TA, TB, 128, FULL>(g, acc, m0, n0, bz, lane, wm, wn, fmx, ssum, ssq, sbad);
   }
   if (g.stat_part) {
     __syncthreads();
@@ -634,6 +674,16 @@ __global__ __launch_bounds__(64 * NW) void gemm_small_kernel(GemmArgs g) {
   }
   float fmx = 0.0f;
   double ssum = 0.0, ssq = 0.0, sbad = 0.0;
+  auto store = [&](int row, int col, float sum) {
+    const float val = skinny_store(g, g.C + bz * g.strideC, bz, row, col, sum);
+    if (isfinite(val)) {
+      fmx = fmaxf(fmx, fabsf(val)); ssum += (double)val; ssq += (double)val * (double)val;
+    } else {
+      sbad += 1.0;
+    }
+  };
+  constexpr int kEach = 1024 / (64 * NW);  // elements of a 32 x 32 part per thread
+  uint32_t again = 0u;                     // those that came out as NaN
 #pragma unroll
   for (int i = 0; i < I; ++i) {
 #pragma unroll
@@ -643,38 +693,25 @@ __global__ __launch_bounds__(64 * NW) void gemm_small_kernel(GemmArgs g) {
       for (int v = 0; v < 16; ++v) part[wave][8 * (v >> 2) + 4 * (lane >> 5) + (v & 3)][lane & 31] = acc[i][j][v];
       __syncthreads();
 #pragma unroll
-      for (int c = 0; c < 1024 / (64 * NW); ++c) {  // element e: row e / 32, column e % 32
+      for (int c = 0; c < kEach; ++c) {  // element e: row e / 32, column e % 32
         const int e = c * 64 * NW + tid, row = m0 + 32 * i + (e >> 5), col = n0 + 32 * j + (e & 31);
         float t = part[0][e >> 5][e & 31];
 #pragma unroll
         for (int w = 1; w < NW; ++w) t += part[w][e >> 5][e & 31];
         if (row < g.M && col < g.N) {
-          const float val = skinny_store(g, g.C + bz * g.strideC, bz, row, col, t);
-          if (isfinite(val)) {
-            fmx = fmaxf(fmx, fabsf(val)); ssum += (double)val; ssq += (double)val * (double)val;
-          } else {
-            sbad += 1.0;
-          }
+          if (t == t) store(row, col, t);
+          else again |= 1u << ((i * I + j) * kEach + c);
         }
       }
     }
   }
+  for (; again; again &= again - 1u) {  // see store_tile
+    const int b = __builtin_ctz(again), ij = b / kEach, e = (b % kEach) * 64 * NW + tid;
+    const int row = m0 + 32 * (ij / I) + (e >> 5), col = n0 + 32 * (ij % I) + (e & 31);
+    store(row, col, plain_sum<TA, TB>(g, bz, row, col));
+  }
   if (g.stat_part)  // uniform
     tile_statistics<NW>(g, red, tid, bz, (int64_t)blockIdx.y * gridDim.x + blockIdx.x, fmx, ssum, ssq, sbad);
-}
-
-// One element of C in fp32 multiply-adds, k after k.
-template <bool TA, bool TB>
-__device__ __forceinline__ float plain_sum(const GemmArgs &g, int64_t bz, int row, int col) {
-  float t = 0.0f;
-  for (int s = 0; s < g.nseg; ++s) {
-    const float *A = (s ? g.A[1] : g.A[0]) + bz * (s ? g.strideA[1] : g.strideA[0]);
-    const float *B = (s ? g.B[1] : g.B[0]) + bz * (s ? g.strideB[1] : g.strideB[0]);
-    const int64_t lda = s ? g.lda[1] : g.lda[0], ldb = s ? g.ldb[1] : g.ldb[0];
-    for (int k = 0; k < g.K; ++k)
-      t = fmaf(TA ? A[k * lda + row] : A[row * lda + k], TB ? B[col * ldb + k] : B[k * ldb + col], t);
-  }
-  return t;
 }
 
 // Sums of at most kFewProducts products (two classes; a batch of one row): there the five small parts and what is left
