@@ -783,8 +783,8 @@ lpc_status lpc_epoch(lpc_ctx *ctx, float *w_snap, float *y, float *z, uint32_t e
   Scratch &s = c->s;
   hipStream_t st = as_stream(stream);
   const lpc_config &g = c->cfg;
-  // evaluation runs take the unfused launches, whose quantizer reports the clip counts, or a launch per iteration of the
-  // narrow problems' loop
+  // evaluation runs take the unfused launches, whose quantizer reports the clip counts, or, where the inner loop would be
+  // one launch, a launch of it per iteration
   const bool tracing = c->trace_delta || c->trace_nclip || c->count_clipped || c->trace_coded_host;
   // communication step 1
   LPC_TRY(full_grad_impl(c, w_snap, s.mu, s.z_snap, nullptr, c->n_full, st));
@@ -1181,7 +1181,7 @@ lpc_status lpc_clip_sweep(lpc_ctx *ctx, const float *w0, int32_t n_clip, const f
       if (clipped_out_host)
         LPC_TRY_HIP(hipMemcpyAsync(&clipped_out_host[k], c->s.clip_total, sizeof(uint64_t), hipMemcpyDeviceToHost, st));
       c->count_clipped = false;
-      return lpc_objective(c, w_work, &P_out_host[k], stream);  // synchronises the stream
+      return lpc_objective(c, w_work, &P_out_host[k], stream);  // returns once the stream has got there
     }();
   }
   c->count_clipped = false;

@@ -1,6 +1,6 @@
 // The inner loop of an epoch (Alg. 1 steps 5-11; Alg. 2 steps 5-15) in one launch for narrow dense problems (d <= 256, or
-// d <= 1024 with more than 8 bits; a worker's batch small enough for the registers of one workgroup): a workgroup per worker, as in the paper, or one
-// workgroup for all of them where even that is more than the work needs.
+// d <= 1024 with more than 8 bits; a worker's batch small enough for the registers of one workgroup): a workgroup per
+// worker, as in the paper, or one workgroup for all of them where even that is more than the work needs.
 //
 // Such an iteration moves tens or hundreds of KB and takes a few thousand instructions; as three launches (rows, fold,
 // exchange; five or six for the schemes (b) and (c)) it is 11 to 33 us of launch gaps and first trips to memory.  Here a
@@ -21,11 +21,11 @@
 // (launch_commit_epoch), and the calls that answer to the host report LPC_EDEVICE.  One workgroup waits for nobody and
 // writes the caller's vectors itself.
 // What bounds an iteration is the chain of dependent steps: rows 1.1 us, statistics 0.5 us, codes 0.5 us, messages there
-// and back 0.9 us, receiver and update 0.9 us (d = 90, N = 8, B = 64: 3.9 us; the words stay inside one die's L2).
-// Measured on MI355X, whole epochs, three launches per iteration -> this kernel, us per inner iteration:
-//   d = 64, N = 4, B = 16: 9.8 -> 2.9        d = 90, N = 8, B = 64: 11.4 -> 3.9     d = 256, N = 16, B = 32: 12.5 -> 5.0
-//   d = 512, N = 8, B = 64: 12.6 -> 6.0      d = 1000, N = 16, B = 32: 13.5 -> 9.7
-//   scheme (b), d = 256, N = 4, B = 16: 21.9 -> 4.9;  quantization off, d = 64, N = 4, B = 16: 14.9 -> 2.1
+// and back 0.9 us, receiver and update 0.9 us (d = 90, N = 8, B = 64; the words stay inside one die's L2).
+// Measured on MI355X, snapshot pass (n = 16384) and 128 iterations, separate launches -> this kernel, us per iteration:
+//   d = 64, N = 4, B = 16: 10.4 -> 3.0       d = 90, N = 8, B = 64: 11.6 -> 4.3     d = 256, N = 16, B = 32: 11.7 -> 5.2
+//   d = 512, N = 8, B = 64, b = 9: 11.6 -> 6.7     d = 1000, N = 14, B = 32, b = 9: 12.9 -> 10.2
+//   scheme (b), d = 256, N = 4, B = 16: 21.8 -> 4.8;  quantization off, d = 64, N = 4, B = 16: 15.6 -> 2.1
 // Steps that paid: the kernel made for its messages and algorithm (23 %: one branch less in every phase), no division
 // inside the loop and messages assembled by LDS atomics instead of a loop over a word's codes (25 %), labels and snapshot
 // slopes fetched with the rows (8 %).
@@ -611,34 +611,17 @@ hipError_t launch_cluster_epoch(const lpc_ctx *c, const ResidentStep &rs, float 
   const Shape s = shape_of(c);
   if (s.G > c->usable_cus) return hipErrorCooperativeLaunchTooLarge;
   ClusterArgs a{};
-  a.X = c->prob.X; a.ldx = c->prob.ldx; a.n = c->n; a.y = c->prob.y; a.z_snap = rs.z_snap; a.mu = rs.mu;
+  fill_loop_args(a, c, rs, t0, t1, weight, n_clipped);
   // one workgroup in a launch: nobody can give up, the caller's vectors are written in place
   const bool alone = s.G == 1, last = alone && t1 == c->cfg.m;
-  a.w_snap = w_snap; a.yv = !alone && t0 > 0 ? c->s.cl_y : rs.y; a.zv = !alone && t0 > 0 ? c->s.cl_z : rs.z;
+  if (!alone && t0 > 0) { a.yv = c->s.cl_y; a.zv = c->s.cl_z; }
   float *kept = rs.alpc ? c->s.ysum : c->s.w;
   a.in = kept; a.out = last ? w_snap : kept; a.out_scale = last ? (float)snap_scale : 1.0f;
   a.y_out = alone ? rs.y : c->s.cl_y; a.z_out = alone ? rs.z : c->s.cl_z;
-  a.packed = c->s.packed; a.delta_out = c->s.delta; a.flags = c->s.flags;
-  a.ctl = c->s.cl_ctl; a.msg = c->s.cl_msg; a.vec = c->s.cl_vec; a.scale_ex = c->s.cl_scale;
-  a.it0 = t0; a.it1 = t1; a.weight = weight; a.n_clipped = n_clipped;
-  a.d = (int32_t)c->d; a.dp = (int32_t)c->d_pad; a.W = (int32_t)c->W; a.N = c->cfg.N;
-  a.nvec = c->cfg.N + (rs.alpc ? 1 : 0); a.nv = s.nv; a.G = s.G; a.wpv = s.wpv; a.rpw = s.rpw;
-  a.B = c->cfg.B; a.bits = c->quant ? c->cfg.bits : 0; a.scheme = c->quant ? c->cfg.scheme : -1;
-  a.loss = c->prob.loss;
-  a.tag0 = rs.tag0; a.spin_limit = c->spin_limit;
+  a.packed = c->s.packed; a.delta_out = c->s.delta;
+  a.msg = c->s.cl_msg; a.vec = c->s.cl_vec; a.scale_ex = c->s.cl_scale;
+  a.dp = (int32_t)c->d_pad; a.nv = s.nv; a.G = s.G; a.wpv = s.wpv; a.rpw = s.rpw;
   a.inv_w1 = (uint32_t)((0x100000000ull + (uint64_t)a.W) / ((uint64_t)a.W + 1));
-  a.qs.bits = c->cfg.bits; a.qs.clip_mode = c->cfg.clip_mode; a.qs.clip = c->cfg.clip; a.qs.enabled = 1;
-  a.key = rs.key;
-  const double l1 = (double)c->prob.lambda1, l2 = (double)c->prob.lambda2;
-  auto consts = [&](float step, float *thr, float *shrink) {
-    *thr = (float)((double)step * l1);
-    *shrink = (float)(1.0 / (1.0 + (double)step * l2));
-  };
-  a.step = rs.step; consts(rs.step, &a.thr, &a.shrink);
-  a.step_y = rs.step_y; consts(rs.step_y, &a.thr_y, &a.shrink_y);
-  a.alpha = rs.alpha; consts(rs.alpha, &a.thr_z, &a.shrink_z);
-  a.t1 = rs.tau1; a.t2 = rs.tau2; a.t3 = (float)(1.0 - (double)rs.tau1 - (double)rs.tau2); a.theta = (double)rs.theta;
-  a.scale = (float)(1.0 / (double)c->cfg.B);
   const void *fn = nullptr;
   const int q = !c->quant ? kPlain : (c->cfg.scheme == LPC_SCHEME_A ? kOwnScale : kSharedScale);
 #define LPC_CLUSTER_Q(K_, RW_, Q_)                                                                               \

@@ -24,9 +24,9 @@
 // words, gradient 0.4, statistics 0.7 + 1.0, codes 0.5, their words across the dies 1.5, update 0.4); at d = 20000 the rows
 // (41 MB in 10 us, paced) and that memory rests while margins are formed.
 // Measured on MI355X, snapshot pass (n = 16384) and 128 iterations, separate launches -> this kernel, us per iteration:
-//   d = 1500, N = 2, B = 16: 13.6 -> 4.6    d = 1500, N = 16, B = 64: 16.0 -> 7.2    d = 4096, N = 8, B = 64: 16.2 -> 7.3
-//   d = 12000, N = 16, B = 40: 30.3 -> 14.0    d = 20000, N = 8, B = 64: 29.0 -> 15.5    d = 20000, N = 2, B = 8: 19.1 -> 9.2
-//   d = 8192, N = 16, B = 64: Alg. 3 21.3 -> 12.8, scheme (b) 34.7 -> 13.7
+//   d = 300, N = 8, B = 64: 11.8 -> 5.6    d = 1500, N = 2, B = 16: 11.1 -> 4.7    d = 1500, N = 16, B = 64: 15.3 -> 7.3
+//   d = 4096, N = 8, B = 64: 14.9 -> 7.5    d = 12000, N = 16, B = 40: 31.1 -> 15.1    d = 20000, N = 8, B = 64: 29.1 -> 15.8
+//   d = 20000, N = 2, B = 8: 17.9 -> 9.1    d = 8192, N = 16, B = 64: Alg. 3 22.0 -> 12.7, scheme (b) 29.9 -> 13.7
 // Steps that paid: all words of a wait requested together (waiting for them one after another: field words 3.4 us instead
 // of 1.5), rows requested after the barrier and paced (21 % at d = 12000), blocks of 256 instead of 128 columns at d = 4096
 // (25 %), the random words drawn while the rows' wavefronts work.  Steps that did not: rows
@@ -549,7 +549,10 @@ struct Shape {
 };
 
 // The launch for a context, or k = 0 where the kernel does not apply: the batch must fit the registers of the row
-// wavefronts (64 rows), four codes a word (b <= 8), and the groups the dies.
+// wavefronts, four codes a word (b <= 8), and the groups the dies.  Eight rows per wavefront, 64 in all, are what its
+// registers hold of the widest block.  Narrower blocks leave room for more, but there is no instantiation with more: one
+// row past the line takes the separate launches (d = 4096, N = 8: B = 64 7.5 us per iteration here, 14.9 there; B = 65 15.4,
+// B = 128 16.8 there).
 // Few workgroups wait for fewer words, many have fewer rows to fetch.  Up to 16 workgroups per group and 24 per die the
 // narrowest block is the fastest (us per iteration by K = 4, 6, 8, 10, 12: d = 4096, N = 8, B = 64: 7.6, 8.3, 8.3, -, -;
 // d = 5000, N = 16, B = 30: -, 8.4, 7.9, 8.1, 8.2), beyond that the widest is (d = 8192, N = 8: 11.8, 10.5, 9.8, 9.8, 9.9; Alg. 3,
@@ -592,31 +595,14 @@ hipError_t launch_columns_epoch(const lpc_ctx *c, const ResidentStep &rs, int32_
   const Shape s = shape_of(c);
   if (s.slots * kDies > c->usable_cus) return hipErrorCooperativeLaunchTooLarge;
   ColumnArgs a{};
-  a.X = c->prob.X; a.ldx = c->prob.ldx; a.n = c->n; a.y = c->prob.y; a.z_snap = rs.z_snap; a.mu = rs.mu;
-  a.w_snap = rs.w_snap; a.yv = t0 > 0 ? c->s.cl_y : rs.y; a.zv = t0 > 0 ? c->s.cl_z : rs.z; a.flags = c->s.flags;
-  a.packed = traced ? c->s.packed : nullptr; a.delta_out = c->s.delta; a.n_clipped = n_clipped;
-  a.ctl = c->s.cl_ctl;
+  fill_loop_args(a, c, rs, t0, t1, weight, n_clipped);
+  if (t0 > 0) { a.yv = c->s.cl_y; a.zv = c->s.cl_z; }
+  a.x_mid = c->s.w; a.ysum_mid = c->s.ysum; a.y_mid = c->s.cl_y; a.z_mid = c->s.cl_z;
+  a.packed = traced ? c->s.packed : nullptr; a.delta_out = c->s.delta;
   const ColumnScratch w = columns_scratch(c);
   a.marg = c->s.cl_msg; a.stats = a.marg + w.marg; a.scale_ex = a.stats + w.stats; a.msg = a.scale_ex + w.scale;
   a.vec = a.msg + w.msg;
-  a.x_mid = c->s.w; a.ysum_mid = c->s.ysum; a.y_mid = c->s.cl_y; a.z_mid = c->s.cl_z; a.it0 = t0; a.it1 = t1; a.weight = weight;
-  a.d = (int32_t)c->d; a.W = (int32_t)c->W; a.N = c->cfg.N; a.nvec = c->cfg.N + (rs.alpc ? 1 : 0);
-  a.G = s.G; a.per_die = s.per_die; a.B = c->cfg.B;
-  a.rpw = (c->cfg.B + kColRowWaves - 1) / kColRowWaves; a.S = (64 * s.k + 255) / 256;
-  a.bits = c->quant ? c->cfg.bits : 0; a.scheme = c->quant ? c->cfg.scheme : -1; a.loss = c->prob.loss;
-  a.tag0 = rs.tag0; a.spin_limit = c->spin_limit;
-  a.qs.bits = c->cfg.bits; a.qs.clip_mode = c->cfg.clip_mode; a.qs.clip = c->cfg.clip; a.qs.enabled = 1;
-  a.key = rs.key;
-  const double l1 = (double)c->prob.lambda1, l2 = (double)c->prob.lambda2;
-  auto consts = [&](float step, float *thr, float *shrink) {
-    *thr = (float)((double)step * l1);
-    *shrink = (float)(1.0 / (1.0 + (double)step * l2));
-  };
-  a.step = rs.step; consts(rs.step, &a.thr, &a.shrink);
-  a.step_y = rs.step_y; consts(rs.step_y, &a.thr_y, &a.shrink_y);
-  a.alpha = rs.alpha; consts(rs.alpha, &a.thr_z, &a.shrink_z);
-  a.t1 = rs.tau1; a.t2 = rs.tau2; a.t3 = (float)(1.0 - (double)rs.tau1 - (double)rs.tau2); a.theta = (double)rs.theta;
-  a.scale = (float)(1.0 / (double)c->cfg.B);
+  a.G = s.G; a.per_die = s.per_die; a.rpw = (c->cfg.B + kColRowWaves - 1) / kColRowWaves; a.S = (64 * s.k + 255) / 256;
   const void *fn = nullptr;
   const int q = !c->quant ? kPlain : (c->cfg.scheme == LPC_SCHEME_A ? kOwnScale : kSharedScale);
 #define LPC_COLUMNS_Q(K_, Q_)                                                                    \

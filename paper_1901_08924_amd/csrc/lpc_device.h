@@ -286,6 +286,30 @@ __device__ __forceinline__ void st_word(u64 *p, uint32_t v, uint32_t tag) {
   __hip_atomic_store(p, (u64)v | ((u64)tag << 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// What the launches of both have in common (host).
+template <class Args>
+void fill_loop_args(Args &a, const lpc_ctx *c, const ResidentStep &rs, int32_t t0, int32_t t1, double weight,
+                    uint32_t *n_clipped) {
+  a.X = c->prob.X; a.ldx = c->prob.ldx; a.n = c->n; a.y = c->prob.y; a.z_snap = rs.z_snap; a.mu = rs.mu;
+  a.w_snap = rs.w_snap; a.yv = rs.y; a.zv = rs.z;
+  a.n_clipped = n_clipped; a.flags = c->s.flags; a.ctl = c->s.cl_ctl;
+  a.d = (int32_t)c->d; a.W = (int32_t)c->W; a.N = c->cfg.N; a.nvec = c->cfg.N + (rs.alpc ? 1 : 0); a.B = c->cfg.B;
+  a.it0 = t0; a.it1 = t1; a.bits = c->quant ? c->cfg.bits : 0; a.scheme = c->quant ? c->cfg.scheme : -1;
+  a.loss = c->prob.loss; a.tag0 = rs.tag0; a.spin_limit = c->spin_limit;
+  a.qs.bits = c->cfg.bits; a.qs.clip_mode = c->cfg.clip_mode; a.qs.clip = c->cfg.clip; a.qs.enabled = 1;
+  a.key = rs.key;
+  const double l1 = (double)c->prob.lambda1, l2 = (double)c->prob.lambda2;
+  auto consts = [&](float step, float *thr, float *shrink) {
+    *thr = (float)((double)step * l1);
+    *shrink = (float)(1.0 / (1.0 + (double)step * l2));
+  };
+  a.step = rs.step; consts(rs.step, &a.thr, &a.shrink);
+  a.step_y = rs.step_y; consts(rs.step_y, &a.thr_y, &a.shrink_y);
+  a.alpha = rs.alpha; consts(rs.alpha, &a.thr_z, &a.shrink_z);
+  a.t1 = rs.tau1; a.t2 = rs.tau2; a.t3 = (float)(1.0 - (double)rs.tau1 - (double)rs.tau2);
+  a.scale = (float)(1.0 / (double)c->cfg.B); a.theta = (double)rs.theta; a.weight = weight;
+}
+
 // The value of a tagged word, once it is there.  Gives up (ok = false) after `limit` polls or when another workgroup has.
 __device__ __forceinline__ uint32_t wait_word(const u64 *p, uint32_t tag, uint32_t limit, const uint32_t *gave_up,
                                               uint32_t launch_tag, bool &ok) {

@@ -3,8 +3,8 @@
 // prefix-code size it implies (entropy coding of the messages, Sec. 6.1), and
 // the left-hand side of Theorem 2's step-size conditions (eq. (6), (7)), and the emission of the entropy-coded
 // bit stream (canonical prefix code, codewords most significant bit first).
-// None of these runs inside an epoch; they are written for clarity, with fp64
-// accumulation in a fixed order.
+// None of these runs inside an epoch.  Sums are fp64, in a fixed order; the launches are wide and leave what the host asks
+// for in a slot that it polls, because a monitored run calls them after every epoch.
 #include <hip/hip_runtime.h>
 
 #include <functional>

@@ -710,7 +710,7 @@ hipError_t launch_mlp_vr_grad(const lpc_ctx *c, const float *w, const float *w_s
     e = launch_range_stats(c, U, c->d_pad, vec0, nw, ranges, slot, st);
     if (e != hipSuccess) return e;
     slot += ranges.n;
-    if (slot > c->stat_slots) return hipErrorInvalidValue;  // cannot happen: a tile covers at least 64 coordinates
+    if (slot > c->stat_slots) return hipErrorInvalidValue;  // cannot happen: fill_ctx counts 32 x 32 tiles, and 64-column blocks
     if (stats_mode == kStatsFinal) {
       e = launch_finalize_stats(c, vec0, nw, slot, stats_out, st);
       if (e != hipSuccess) return e;
