@@ -756,6 +756,11 @@ __global__ __launch_bounds__(256) void gemm_few_kernel(GemmArgs g) {
 //    600 x  391 x  777 [20]        52 /  37 /  36 /   13 / 16
 //   2048 x  512 x  512 B' [64]     29 /  20 /  20 /   49 / 29      (both operands k-contiguous: the small kernel's
 //   1000 x  896 x  896 B' [56]     55 /  40 /  39 /   61 / 35       loads touch a line per lane)
+// Between these points the lines are coarse: over 1050 single products (64 to 10240 rows, K from 10 to 3072) the choice takes
+// 1.14 times the best kernel's time on average, and up to six times where K is at most 160, A not transposed and fewer than
+// 100 tiles of 128 x 128 (1024 x 768 x 64 B' [48]: 6.5 / 5.2 / 6.8 / 32 / 21), or 1.4 times from 257 to 639 tiles (5120 x 1024 x
+// 200 [320]: 26 / 23 / 32).  Lines drawn from all of those made epochs of 24 nets 0.88 to 1.07 times as long, 0.99 on average
+// (operands that the launch before wrote are not where a repeated product finds its own): the coarse ones stayed.
 struct Plan {
   int tile_m, tile_n;
   int waves;  // 0: the tile kernel, 1: its eight-wavefront form, 2: few products, else the small kernel with that many

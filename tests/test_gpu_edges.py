@@ -21,11 +21,11 @@ def _gemm(A, B, tA, tB):
     return C.cpu().numpy()
 
 
-# one product of each kernel (32 x 32, 64 x 64, 128 x 64, 128 x 128 by four and by eight wavefronts), with and without
+# products of each kernel (32 x 32, 64 x 64, 128 x 64, 128 x 128 by four and by eight wavefronts), with and without
 # remainders in every direction
 GEMMS = [(1, 17, 1), (33, 31, 15), (32, 32, 16), (31, 65, 33), (70, 700, 17), (640, 660, 161), (641, 1000, 479),
          (1025, 1601, 7), (2048, 1920, 33), (1920, 1281, 161), (1921, 1280, 193), (2048, 1280, 256), (4096, 2560, 32),
-         (3201, 3330, 35)]
+         (3201, 3330, 35), (640, 704, 512), (2048, 1920, 320), (1921, 1300, 353), (3584, 2048, 192)]
 
 
 @pytest.mark.parametrize("M,N,K", GEMMS)
