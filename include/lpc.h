@@ -229,9 +229,10 @@ lpc_status lpc_gradient_mapping(lpc_ctx *ctx, const float *w, float eta, double 
  * entropy coding (Sec. 6.1: the optimal prefix code of that message's own histogram; 32*d with
  * quantization off; add 32 bits for delta and Table 1's fan-out for a total as in Sec. 6.1's table of
  * communication costs); asking for it synchronises the stream once per message.  Each of the three may be
- * NULL; all NULL is lpc_epoch.  The traced epoch takes the unfused launches
- * (statistics, quantizer, receiver, prox as separate kernels) for every data kind; for Alg. 1 in
- * LPC_CLIP_LAMBDA mode on dense data its iterates equal lpc_epoch's bit for bit, elsewhere to rounding.
+ * NULL; all NULL is lpc_epoch.  Where lpc_epoch takes one launch for the inner loop (dense data, see
+ * LPC_TUNE_ITER_FORM), the traced epoch takes one per iteration and its iterates are the same bits.  Elsewhere it takes
+ * the unfused launches (statistics, quantizer, receiver, prox as separate kernels): for Alg. 1 in LPC_CLIP_LAMBDA mode on
+ * dense data its iterates equal lpc_epoch's bit for bit, else to rounding.
  * Asynchronous unless coded_bits_host is given. */
 lpc_status lpc_epoch_traced(lpc_ctx *ctx, float *w_snap, float *y, float *z, uint32_t epoch, float *delta_trace,
                             uint32_t *nclip_trace, uint64_t *coded_bits_host, void *stream);
@@ -246,7 +247,7 @@ lpc_status lpc_bits_per_iteration(int64_t d, int32_t bits, int32_t N, int32_t sc
  * Table 1 figure of the context's scheme; messages = m*N; clipped = the coordinates outside dom(delta, b) summed
  * over all messages (Sec. 3.2's d_lambda, the quantity Lemma 2 bounds the error with); max_delta = the largest
  * scale factor any message was quantized with (eq. (3)); nonfinite = 1 if a vector handed to the quantizer held a
- * NaN or Inf (the context's flag is cleared).  The epoch takes the unfused launches, as lpc_epoch_traced does. */
+ * NaN or Inf (the context's flag is cleared).  The epoch takes the launches that lpc_epoch_traced takes. */
 typedef struct {
   uint64_t bits_sent, messages, clipped;
   float max_delta;
@@ -343,11 +344,12 @@ lpc_status lpc_debug_gemm(const float *A, const float *B, float *C, int32_t M, i
 /* ---- tuning and test aid (no passage of the paper) -----------------------------------------
  * Form and launch shape of the inner iteration on small dense problems (d_pad <= 16384, N <= 64).
  *   LPC_TUNE_ITER_FORM:
- *     -1, or not set: form 0; on narrow problems (d <= 256, or d <= 1024 and b > 8, and a batch that fits the registers of one workgroup, every scheme,
- *       with or without quantization; not while the stream is being captured) all m inner iterations in one cooperative
- *       launch with a workgroup per worker, whose waits LPC_TUNE_SPIN_LIMIT bounds as it does form 3's; on wide problems
- *       (d <= 24576, B <= 64, b <= 8 or quantization off, as far as the workers' column blocks fit the compute units)
- *       likewise with a group of workgroups per worker.
+ *     -1, or not set: form 0; on narrow problems (d <= 256, or d <= 1024 and b > 8, and a batch that fits the registers of
+ *       one workgroup; every scheme, with or without quantization; not while the stream is being captured) all m inner
+ *       iterations in one launch, cooperative with a workgroup per worker whose waits LPC_TUNE_SPIN_LIMIT bounds, or of one
+ *       workgroup for all; on wide problems (d <= 24576, B <= 64, b <= 8 or quantization off, as far as the workers' column
+ *       blocks fit the compute units) likewise with a group of workgroups per worker.  Such an epoch takes place as a whole
+ *       or not at all (lpc_epoch).
  *     0: three launches: the workers' rows (whole rows per workgroup, partial gradient rows out), their fold, the
  *       exchange.
  *     1: two launches: the workers' rows, then fold + exchange in one launch whose workgroups wait, for a bounded

@@ -1703,8 +1703,8 @@ __global__ void share_delta_kernel(QParams *qp, int32_t nvec, QuantSpec qs, floa
 }
 
 // A thread takes four coordinates (one block of random words, a 16-byte store): neighbouring threads share words, but
-// d = 150,001 makes 586 workgroups of 64 where a 32-coordinate segment per thread made 19 of 256.  Two workers are
-// requested together.  us a launch, segment per thread -> this: d = 150,001, N = 8, b = 4: 6.2 -> see the end of the line
+// d = 150,001 makes 586 workgroups of 64 where a 32-coordinate segment per thread made 19 of 256.  Four workers are
+// requested together.  us a launch, segment per thread -> this: d = 150,001, N = 8, b = 4: 6.2 -> 3.4
 template <int B, bool REQUANT>
 __global__ __launch_bounds__(kSharedThreads) void dequantize_shared_kernel(const uint32_t *__restrict__ packed,
                                                                            int64_t W, const float *__restrict__ delta,

@@ -192,8 +192,9 @@ def _epochs_as_the_oracle(d, N, B, over):
     (1000, 7, 32, dict(bits=7)), (1024, 4, 17, dict(algo=lpco.ALGO_ALPC_GC)), (1024, 63, 2, dict(bits=32)),
     (1024, 2, 33, {}), (1025, 2, 4, {})])
 def test_narrow_epochs_in_one_launch(d, N, B, over):
-    """Alg. 1-3 on narrow dense data, both sides of every line of the one-launch form: coordinates of w, y and z as the
-    oracle's (up to a few flipped rounding decisions), the same bits from run to run."""
+    """Alg. 1-3 on narrow dense data (one workgroup, a workgroup per worker and, past d = 256, column blocks; batches too large
+    for any of them take the separate launches): coordinates of w, y and z as the oracle's (up to a few flipped rounding
+    decisions), the same bits from run to run."""
     _epochs_as_the_oracle(d, N, B, over)
 
 
@@ -218,7 +219,7 @@ def test_narrow_epochs_with_long_messages_in_one_launch(d, N, B, over):
     ctx.close()
 
 
-# column blocks of 128 to 768 columns, groups of 2 to 32 workgroups, the shared batch's group on a die of its own or spread
+# column blocks of 256 to 768 columns, groups of 5 to 32 workgroups, the shared batch's group on a die of its own or spread
 # over what the workers leave; batches of 64 rows are the largest, the last three take the separate launches
 @pytest.mark.parametrize("d,N,B,over", [
     (1025, 2, 1, {}), (1100, 8, 64, dict(clip_mode=1, clip=2.0)), (1281, 16, 33, dict(algo=lpco.ALGO_ALPC_GC)),
@@ -230,7 +231,7 @@ def test_narrow_epochs_with_long_messages_in_one_launch(d, N, B, over):
     (16388, 8, 10, dict(clip_mode=1, clip=1.0, scheme=lpco.SCHEME_B)), (20000, 8, 64, dict(bits=6)), (24576, 1, 2, {}),
     (24580, 2, 4, {}), (1100, 2, 65, {}), (1100, 3, 4, dict(bits=9))])
 def test_wide_epochs_in_one_launch(d, N, B, over):
-    """The same by blocks of columns (d > 1024).  L, as the method asks, bounds the squared norms of the rows (1 for the odd
+    """The same by blocks of columns, past the widths of the test above.  L, as the method asks, bounds the squared norms of the rows (1 for the odd
     widths' rows, about d +- 6 sqrt(d) for the others'): steps of 1/L do not grow a difference in the last bit."""
     _epochs_as_the_oracle(d, N, B, dict(over, L=2.0 if d % 2 else d + 8.0 * d ** 0.5))
 
