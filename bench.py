@@ -60,12 +60,14 @@ def algorithmic_work(sp, dp, nnz):
         entries = float(N) * B * nnz / n
         sparse = (bits < 32 and sp.algo == 0 and getattr(sp, "scheme", 0) == 0 and d >= 4 * 8192
                   and 8.0 * B * nnz / n <= d)
+        # one launch of the whole inner loop (bits <= 16, N <= 16): the pairs of the sampled rows in, the iterate stays on the chip
+        whole = {"resident": (sp.m * 8.0 * (N + (1 if sp.algo != 0 else 0)) * B * nnz / n, "bytes")}
         if sparse:
             # u^i stays sparse: the pairs of the sampled rows in, one contribution per entry out; the exchange
             # must still read every worker's packed message and update all d coordinates (w, mu in; w out)
-            return {"full_rows": full, "vr_rows": (12.0 * entries, "bytes"),
+            return {**whole, "full_rows": full, "vr_rows": (12.0 * entries, "bytes"),
                     "exchange": (N * bits * dp / 8.0 + 16.0 * d, "bytes")}
-        return {"full_rows": full,
+        return {**whole, "full_rows": full,
                 "vr_rows": (8.0 * entries + 8.0 * N * dp, "bytes"),     # rows + zero and write U
                 "exchange": (msg, "bytes")}
     nvec = N + (1 if sp.algo != 0 else 0)   # Alg. 2, 3 also draw the shared batch J

@@ -27,6 +27,7 @@ SOURCES = [
     ("lpc_resident.hip", ["-ffp-contract=off"]),   # holds the quantizer's arithmetic too
     ("lpc_cluster.hip", ["-ffp-contract=off"]),    # likewise
     ("lpc_columns.hip", ["-ffp-contract=off"]),    # likewise
+    ("lpc_lists.hip", ["-ffp-contract=off"]),      # likewise
     ("lpc_host.cpp", []),      # host-only logic: no device code (also built with sanitizers by the tests)
 ]
 HEADERS = ["lpc_internal.h", "lpc_device.h"]

@@ -157,7 +157,7 @@ size_t layout(lpc_ctx *c, char *base) {
   s.csc_rows = (int32_t *)take((c->csr ? (size_t)c->prob.nnz : 4) * sizeof(int32_t));
   s.csc_vals = (float *)take((c->csr ? (size_t)c->prob.nnz : 4) * sizeof(float));
   s.csc_coef = (float *)take((c->csr ? (size_t)c->n : 4) * sizeof(float));
-  s.csr_plan = (RowPlan *)take((c->csr_sparse ? (size_t)c->cfg.m * N1 * c->cfg.B : 1) * sizeof(RowPlan));
+  s.csr_plan = (RowPlan *)take((c->csr_sparse || c->lists_capable ? (size_t)c->cfg.m * N1 * c->cfg.B : 1) * sizeof(RowPlan));
   s.warm_sink = (float *)take(sizeof(float));
   s.touched = (uint32_t *)take((c->csr_sparse ? (size_t)N1 * c->bitmap_words : 4) * sizeof(uint32_t));
   {
@@ -184,6 +184,10 @@ size_t layout(lpc_ctx *c, char *base) {
       const ColumnScratch w = columns_scratch(c);
       cs.msg = w.marg + w.stats + w.scale + w.msg + w.vec;
     }
+    if (c->lists_capable) {
+      const ListScratch li = lists_scratch(c);
+      cs.msg = li.xw + li.slope + li.stat;
+    }
     s.cl_msg = (unsigned long long *)take(cs.msg * sizeof(unsigned long long));
     s.cl_vec = (unsigned long long *)take(cs.vec * sizeof(unsigned long long));
     s.cl_scale = (unsigned long long *)take(cs.scale * sizeof(unsigned long long));
@@ -193,6 +197,13 @@ size_t layout(lpc_ctx *c, char *base) {
     s.cl_z = (float *)take(held * sizeof(float));
   }
   s.iter_slots = (unsigned long long *)take((c->iter2_capable ? (size_t)fused_iter_slot_words(c) : 1) * sizeof(unsigned long long));
+  if (c->lists_capable) {
+    const ListScratch li = lists_scratch(c);
+    s.li_off = (uint32_t *)take(li.off * sizeof(uint32_t));
+    s.li_ent = (unsigned long long *)take(li.entries * sizeof(unsigned long long));
+    s.li_cols = (uint32_t *)take(li.entries * sizeof(uint32_t));
+    s.li_state = (float *)take(li.state * sizeof(float));
+  }
   if (c->mlp) {
     s.mlp_xb = (float *)take((size_t)c->mlp_rows * c->mlp_dims[0] * sizeof(float));
     s.mlp_yb = (float *)take((size_t)c->mlp_rows * sizeof(float));
@@ -289,6 +300,7 @@ lpc_status fill_ctx(lpc_ctx *c, const lpc_problem *p, const lpc_config *cfg) {
   // a column block would hold all columns
   c->columns_capable = (c->d > 256 || !c->cluster_capable) && columns_supported(c);
   if (c->columns_capable) c->cluster_capable = false;
+  c->lists_capable = lists_supported(c);
   c->loop_waits = c->columns_capable || (c->cluster_capable && cluster_waits(c));
   // measured on MI355X (inner iterations/s, forms 0 / 1 / 2): d = 4096, N = 8, B = 64: 59.9 k / 50.6 k / 47.6 k;
   // d = 8192, N = 16 (+ shared batch), B = 64: 32.3 k / - / 20.2 k.  Form 1 pays about 3 us per trip of the statistics
@@ -506,7 +518,7 @@ lpc_status lpc_create(lpc_ctx **ctx_out, const lpc_problem *problem, const lpc_c
     delete c;
     return LPC_EDEVICE;
   }
-  if (c->cluster_capable || c->columns_capable) {  // the same for the loops in one launch
+  if (c->cluster_capable || c->columns_capable || c->lists_capable) {  // the same for the loops in one launch
     const size_t words = ((char *)(c->s.cl_ctl + 16) - (char *)c->s.cl_msg) / sizeof(uint32_t);
     if (launch_fill_u32(reinterpret_cast<uint32_t *>(c->s.cl_msg), 0u, (int64_t)words, nullptr) != hipSuccess ||
         hipStreamSynchronize(nullptr) != hipSuccess) {
@@ -523,7 +535,8 @@ lpc_status lpc_create(lpc_ctx **ctx_out, const lpc_problem *problem, const lpc_c
       return LPC_EDEVICE;
     }
   }
-  if (c->csr && build_csc_tail(c, nullptr) != hipSuccess) {
+  if ((c->lists_capable && finish_lists(c, nullptr) != hipSuccess) ||
+      (c->csr && build_csc_tail(c, nullptr) != hipSuccess)) {
     delete c;
     return LPC_EDEVICE;
   }
@@ -789,9 +802,10 @@ lpc_status lpc_epoch(lpc_ctx *ctx, float *w_snap, float *y, float *z, uint32_t e
   // communication step 1
   LPC_TRY(full_grad_impl(c, w_snap, s.mu, s.z_snap, nullptr, c->n_full, st));
   const float *zs = (c->n_full == c->n) ? s.z_snap : nullptr;  // margins cached only when every row was visited
-  if ((c->cluster_capable || c->columns_capable) && c->iter_form < 0 && !capturing(st)) {
-    // all m inner iterations in one launch, which starts from the snapshot and leaves the next one.
-    // (Not where the stream is being captured: a replay would repeat the launch's tags.)
+  const bool lists = c->lists_capable && !tracing;
+  if ((c->cluster_capable || c->columns_capable || lists) && c->iter_form < 0 && !capturing(st)) {
+    // all m inner iterations in one launch (CSR data: a launch per list_iters), which starts from the snapshot and leaves the
+    // next one.  (Not where the stream is being captured: a replay would repeat the launch's tags.)
     ResidentStep rs{};
     rs.z_snap = zs; rs.mu = s.mu; rs.w_snap = w_snap; rs.key = key_of(c, epoch, 0); rs.theta = 1.0f; rs.step = g.eta;
     double wsum = 1.0;
@@ -814,8 +828,25 @@ lpc_status lpc_epoch(lpc_ctx *ctx, float *w_snap, float *y, float *z, uint32_t e
     };
     // what the loop leaves becomes the caller's, unless a workgroup gave up waiting for the others
     const bool commits = c->loop_waits;
-    bool refused = false;  // the runtime does not take the first launch: nothing has happened, the separate ones follow
-    if (!tracing) {
+    if (lists) {
+      bool runs = true;
+      {
+        ProfScope ps(c, LPC_PROF_RESIDENT, st);
+        double weight = 1.0;
+        runs = launch_lists_begin(c, rs, st) == hipSuccess;
+        for (int32_t t = 0; t < g.m && runs; t += c->list_iters) {
+          const int32_t t1 = t + c->list_iters < g.m ? t + c->list_iters : g.m;
+          runs = launch_lists_epoch(c, rs, t, t1, weight, st) == hipSuccess;
+          if (!runs && t > 0) return LPC_EDEVICE;
+          for (int32_t k = t; k < t1; ++k) weight *= (double)rs.theta;
+        }
+      }
+      if (runs) return dev(launch_lists_commit(c, rs, 1.0 / wsum, w_snap, st));
+    }
+    bool refused = lists;  // the runtime does not take the first launch: nothing has happened, the separate ones follow
+    if (lists) {
+      // nothing has happened that the launches below would see
+    } else if (!tracing) {
       ProfScope ps(c, LPC_PROF_RESIDENT, st);
       refused = launch(0, g.m, 1.0, nullptr) != hipSuccess;
     } else {

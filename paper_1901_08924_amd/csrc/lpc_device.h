@@ -276,7 +276,8 @@ __device__ __forceinline__ void tile_dots_finish(const DotsArgs &a, const float 
   }
 }
 
-// ---- tagged words: (value, tag) pairs that cross between workgroups of one launch (lpc_cluster.hip, lpc_columns.hip)
+// ---- tagged words: (value, tag) pairs that cross between workgroups of one launch (lpc_cluster.hip, lpc_columns.hip,
+// lpc_lists.hip)
 typedef unsigned long long u64;
 
 __device__ __forceinline__ u64 ld_word(const u64 *p) {
@@ -286,14 +287,11 @@ __device__ __forceinline__ void st_word(u64 *p, uint32_t v, uint32_t tag) {
   __hip_atomic_store(p, (u64)v | ((u64)tag << 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// What the launches of both have in common (host).
+// What the launches of all such loops have in common (host): the method's numbers ...
 template <class Args>
-void fill_loop_args(Args &a, const lpc_ctx *c, const ResidentStep &rs, int32_t t0, int32_t t1, double weight,
-                    uint32_t *n_clipped) {
-  a.X = c->prob.X; a.ldx = c->prob.ldx; a.n = c->n; a.y = c->prob.y; a.z_snap = rs.z_snap; a.mu = rs.mu;
-  a.w_snap = rs.w_snap; a.yv = rs.y; a.zv = rs.z;
-  a.n_clipped = n_clipped; a.flags = c->s.flags; a.ctl = c->s.cl_ctl;
-  a.d = (int32_t)c->d; a.W = (int32_t)c->W; a.N = c->cfg.N; a.nvec = c->cfg.N + (rs.alpc ? 1 : 0); a.B = c->cfg.B;
+void fill_method_args(Args &a, const lpc_ctx *c, const ResidentStep &rs, int32_t t0, int32_t t1, double weight) {
+  a.flags = c->s.flags; a.ctl = c->s.cl_ctl;
+  a.d = (int32_t)c->d; a.N = c->cfg.N; a.nvec = c->cfg.N + (rs.alpc ? 1 : 0); a.B = c->cfg.B;
   a.it0 = t0; a.it1 = t1; a.bits = c->quant ? c->cfg.bits : 0; a.scheme = c->quant ? c->cfg.scheme : -1;
   a.loss = c->prob.loss; a.tag0 = rs.tag0; a.spin_limit = c->spin_limit;
   a.qs.bits = c->cfg.bits; a.qs.clip_mode = c->cfg.clip_mode; a.qs.clip = c->cfg.clip; a.qs.enabled = 1;
@@ -308,6 +306,16 @@ void fill_loop_args(Args &a, const lpc_ctx *c, const ResidentStep &rs, int32_t t
   a.alpha = rs.alpha; consts(rs.alpha, &a.thr_z, &a.shrink_z);
   a.t1 = rs.tau1; a.t2 = rs.tau2; a.t3 = (float)(1.0 - (double)rs.tau1 - (double)rs.tau2);
   a.scale = (float)(1.0 / (double)c->cfg.B); a.theta = (double)rs.theta; a.weight = weight;
+}
+
+// ... and dense data
+template <class Args>
+void fill_loop_args(Args &a, const lpc_ctx *c, const ResidentStep &rs, int32_t t0, int32_t t1, double weight,
+                    uint32_t *n_clipped) {
+  a.X = c->prob.X; a.ldx = c->prob.ldx; a.n = c->n; a.y = c->prob.y; a.z_snap = rs.z_snap; a.mu = rs.mu;
+  a.w_snap = rs.w_snap; a.yv = rs.y; a.zv = rs.z;
+  a.n_clipped = n_clipped; a.W = (int32_t)c->W;
+  fill_method_args(a, c, rs, t0, t1, weight);
 }
 
 // The value of a tagged word, once it is there.  Gives up (ok = false) after `limit` polls or when another workgroup has.

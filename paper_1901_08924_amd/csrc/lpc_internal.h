@@ -149,6 +149,11 @@ struct Scratch {
   unsigned long long *res_trace;  // [m][16] time stamps of the resident loop's phases (lpc_resident_trace)
   unsigned long long *cl_msg, *cl_vec, *cl_scale;  // lpc_cluster.hip: tagged words (cluster_scratch() says how many)
   uint32_t *cl_ctl;     // [16]
+  // lpc_lists.hip (its words lie from cl_msg on)
+  uint32_t *li_off;           // lists of a launch's iterations: bounds, entries (pairs of words)
+  unsigned long long *li_ent;
+  uint32_t *li_cols;          // ... columns
+  float *li_state;            // ... and the problem's vectors in the owners' order
   float *cl_y, *cl_z;   // [d] each: Alg. 2's y and z between the launches of such a loop, or until it is through
   unsigned long long *iter_slots;  // two sets of [tiles][N][4] statistics exchanged between the workgroups of the
                                    // two-launch inner iteration (all ones = empty)
@@ -203,6 +208,9 @@ struct lpc_ctx {
   bool cols_capable = false;   // ... what form 2 needs
   bool cluster_capable = false;  // the inner loop fits lpc_cluster.hip
   bool columns_capable = false;  // ... or lpc_columns.hip
+  bool lists_capable = false;    // ... or, CSR data, lpc_lists.hip: a launch takes list_iters iterations
+  int32_t list_iters = 0, list_pos_bits = 0, list_k_bits = 0;
+  int64_t list_cap = 0;          // entries of a list at most
   bool loop_waits = false;       // ... and its workgroups wait for each other there
   bool res_capable = false;    // ... what form 3 (the resident inner loop) needs
   bool res_trace_on = false;   // the next resident launches leave their phase time stamps
@@ -299,6 +307,20 @@ bool columns_supported(const lpc_ctx *c);
 ColumnScratch columns_scratch(const lpc_ctx *c);
 hipError_t launch_columns_epoch(const lpc_ctx *c, const ResidentStep &rs, int32_t t0, int32_t t1, double weight,
                                 bool traced, uint32_t *n_clipped, hipStream_t st);
+
+// The same of CSR problems, workgroups by columns (lpc_lists.hip).  lists_begin once per epoch, lists_epoch for every
+// list_iters iterations, lists_commit after the last.
+struct ListScratch {
+  size_t xw, slope, stat;  // 64-bit words, from s.cl_msg
+  size_t entries;          // 64-bit words
+  size_t state, off;       // 32-bit words
+};
+bool lists_supported(const lpc_ctx *c);
+ListScratch lists_scratch(const lpc_ctx *c);
+hipError_t finish_lists(lpc_ctx *c, hipStream_t st);
+hipError_t launch_lists_begin(const lpc_ctx *c, const ResidentStep &rs, hipStream_t st);
+hipError_t launch_lists_epoch(const lpc_ctx *c, const ResidentStep &rs, int32_t t0, int32_t t1, double weight, hipStream_t st);
+hipError_t launch_lists_commit(const lpc_ctx *c, const ResidentStep &rs, double snap_scale, float *w_snap, hipStream_t st);
 
 // CSR GLM passes (lpc_csr.hip)
 int csr_head_columns(int64_t d);

@@ -1,0 +1,1134 @@
+// The inner loop of an epoch (Alg. 1 steps 5-11; Alg. 2 steps 5-15) on CSR data in one launch (one per 128 iterations):
+// P = 256 workgroups, each the owner of the columns c = p mod P for all vectors, with its slice of the iterate in LDS.
+//
+// As separate launches an iteration of n = d = 2^20, N = 16, B = 256, 40 entries a row is 36 us of kernels (worker pass 11.2,
+// statistics 10.6, quantizer 7.3, receiver and update of all d coordinates 6.3), although it samples 1.3 MB.  Here the update
+// of the coordinates that no row touches never leaves a workgroup, u^i is formed where its column lives, and what crosses
+// between workgroups, as tagged words, is
+//   1. the iterate at the columns that the next iteration's rows hold, from their owners to the rows' wavefronts,
+//   2. a row's slope difference, from its wavefront to the owners of its columns,
+//   3. the statistics of u^i, from every owner to all of them, by way of a wavefront per vector and die; each derives the scale
+//      factors.
+// The draws do not depend on the iterates, so what an owner has to add up is known ahead: list_build_kernel leaves, for every
+// iteration, vector and owner, the sampled entries with their columns together and in batch-position order.  Wavefront i
+// of an owner takes vector i's list: slope times value, a segmented sum (one fixed order, so epochs repeat bit for bit),
+// eq. (3), rules (1) and (2); the codes meet in LDS, a field per vector and column, and a lane per touched column takes
+// eq. (4) and the update.
+// Neighbouring columns belong to different owners because text-like data has its frequent columns side by side.
+// Reuse of words: a column's x word is kept once, written again when its owner has the slopes of every row that holds the
+// column, hence after those rows' wavefronts read it.  Slopes and statistics have two sets: set t is written again at t + 2 by
+// somebody who has seen words of t + 1 from every owner (by way of the iterate of t + 2, in a slope's case), and an owner
+// writes those after it has done with the slopes and statistics of t.
+// The launch is cooperative; waits are bounded as in lpc_columns.hip, and a launch that gave up leaves the caller's vectors alone.
+//
+// Bound by the four trips of words (store to load about 1.2 us each) and by the owner of the most frequent column, whose lists
+// are six times as long as the others'.  Measured on MI355X, separate launches -> these kernels, us per iteration, the lists
+// (2.6 there) included: n = d = 2^20, N = 16, B = 256, b = 2: 35.5 -> 12.3; d = 150001, N = 8 + J, B = 100, b = 4: 30.6 -> 11.0.
+// Steps that paid, us per iteration of the first: registers loaded ahead without a join that waits for them and waits for
+// them before the next store, not behind it, together with priority for rows and sums over what only fills the waits, 1.0;
+// columns found by the builder instead of here and words stored as soon as they are known, 1.9; half of the trips' time went
+// where words of several dies shared a line: a line belongs to one workgroup, or to one die.  Steps that did not: copies of the
+// frequent columns' words per die (+ 1.1), the lists requested while the statistics travel (+ 1.2), pauses between polls (0),
+// P = 128 (+ 1.8).
+#include <hip/hip_runtime.h>
+
+#include "lpc_device.h"
+#include "lpc_internal.h"
+
+namespace lpc {
+
+namespace {
+
+constexpr int kLiThreads = 1024, kLiWaves = kLiThreads / 64;
+constexpr int kLiRows = 2;      // sampled rows of a wavefront
+constexpr int kLiChunks = 5;    // 64-entry chunks of a vector's list that a wavefront holds in registers
+constexpr int kLiPairs = 2;     // ... and 64-column chunks of its columns
+constexpr int kLiLds = 156 * 1024;
+constexpr int kOwnBins = 4;     // bins per owner of the list's partition: the first ones hold one column each,
+constexpr int kSubBins = 8;     // ... the others a quarter of the rest
+constexpr int kMaxBatch = 512;
+constexpr int kKeyCap = 6400;   // keys of shared bins that a workgroup of the builder sorts at once
+constexpr int kHeld = 16;       // rows whose columns a wavefront of the builder holds
+constexpr int kDies = 8;
+constexpr int kLine = 16;       // words of a 128-byte line
+constexpr uint32_t kNoEntry = 0xffffffffu, kLast = 0x80000000u;
+
+// ---------------------------------------------------------------------------------------------------------------------
+// The lists.  A workgroup takes one vector's batch of one iteration; entry (column c, batch position pos, k-th of its row)
+// has the key lc << (pos_bits + k_bits) | pos << k_bits | k, lc = c / P, unique in an owner's list.
+struct ListBuildArgs {
+  const int32_t *col_idx;
+  const float *vals;
+  RowPlan *plan;        // of the first iteration of the launch; its margins become slopes
+  uint32_t *off;        // [iterations][nvec][P + 1]
+  uint2 *ent;           // [iterations][nvec][cap]: batch position (kLast: its column's last entry), value
+  uint32_t *cols;       // [iterations][nvec][cap]: a list's columns lc + 1, from its first entry's place on
+  uint32_t *n_cols;     // [iterations][nvec][P]
+  int64_t cap;
+  int32_t B, pshift, pos_bits, k_bits, map_words, loss;
+};
+
+__device__ __forceinline__ uint32_t list_bin(uint32_t c, int pshift) {
+  const uint32_t p = c & ((1u << pshift) - 1u), lc = c >> pshift;
+  return p * kSubBins + (lc < (uint32_t)kOwnBins ? lc : kOwnBins + (lc & (uint32_t)(kSubBins - kOwnBins - 1)));
+}
+
+// An entry's place is its bin's first place plus its rank there.  In the bins of one column (the 4 P first ones: text-like
+// data has half of its entries there, hundreds in a bin) the rank is a count of bits in a map of the batch positions; in the
+// others an entry counts the smaller keys, five of them on average.  No sum or place depends on timing.
+// Bound by the instructions of the last walk (about 130 per row and wavefront).
+__global__ __launch_bounds__(kLiThreads, 8) void list_build_kernel(ListBuildArgs a) {
+  extern __shared__ uint32_t build_lds[];  // kKeyCap keys, then the maps: [4 P][map_words]
+  __shared__ uint32_t start[2048 + 1], ends[2048];
+  __shared__ int32_t lo_sh[kMaxBatch], len_sh[kMaxBatch];
+  __shared__ uint32_t total_a[kLiWaves], total_b[kLiWaves], twice;
+  uint32_t *keys = build_lds, *maps = build_lds + kKeyCap;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int bins = kSubBins << a.pshift;  // at most 2048
+  RowPlan *rows = a.plan + (int64_t)blockIdx.x * a.B;
+  uint2 *out = a.ent + (int64_t)blockIdx.x * a.cap;
+  for (int r = tid; r < a.B; r += kLiThreads) {
+    const RowPlan row = rows[r];
+    lo_sh[r] = row.lo;
+    len_sh[r] = row.hi - row.lo;
+    rows[r].z = loss_slope(a.loss, row.z, row.y);
+  }
+  if (tid == 0) twice = 0u;
+  const int held = kHeld * kLiWaves, groups = (a.B + held - 1) / held;
+  int32_t c[kHeld];
+  auto load = [&](int g) {  // row g * held + q * kLiWaves + wave
+#pragma unroll
+    for (int q = 0; q < kHeld; ++q) {
+      const int r = g * held + q * kLiWaves + wave;
+      c[q] = -1;
+      if (r < a.B && lane < len_sh[r]) c[q] = a.col_idx[lo_sh[r] + lane];
+    }
+  };
+  // f(column, row, index in the row) for every entry of group g, the first 64 of a row from registers
+  auto walk = [&](int g, auto f) {
+#pragma unroll
+    for (int q = 0; q < kHeld; ++q) {
+      const int r = g * held + q * kLiWaves + wave;
+      if (r >= a.B) break;  // uniform
+      if (c[q] >= 0) f((uint32_t)c[q], r, (uint32_t)lane, q);
+      const int32_t len = len_sh[r];
+      for (int32_t k = 64 + lane; k < len; k += 64) f((uint32_t)a.col_idx[lo_sh[r] + k], r, (uint32_t)k, -1);
+    }
+  };
+  auto single = [&](uint32_t bin) { return (bin & (kSubBins - 1)) < (uint32_t)kOwnBins; };
+  auto map_of = [&](uint32_t bin) { return maps + ((bin / kSubBins) * kOwnBins + (bin & (kSubBins - 1))) * a.map_words; };
+  bool mapped = true;  // false: a row holds a column twice, all bins are counted
+  for (;;) {
+    for (int b = tid; b < 2048; b += kLiThreads) start[b] = 0u;
+    for (int w = tid; w < (kOwnBins << a.pshift) * a.map_words; w += kLiThreads) maps[w] = 0u;
+    __syncthreads();
+    for (int g = 0; g < groups; ++g) {
+      load(g);
+      walk(g, [&](uint32_t col, int r, uint32_t, int) {
+        const uint32_t bin = list_bin(col, a.pshift);
+        if (mapped && single(bin)) {
+          const uint32_t bit = 1u << (r & 31);
+          if (atomicOr(&map_of(bin)[r >> 5], bit) & bit) twice = 1u;
+        } else {
+          atomicAdd(&start[bin], 1u);
+        }
+      });
+    }
+    __syncthreads();
+    if (!mapped || twice == 0u) break;  // uniform: nobody writes it behind the barrier
+    mapped = false;
+  }
+  // ---- the bins' first places, and the shared bins' first keys: two exclusive scans, two bins per thread
+  {
+    uint32_t n[2], m[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const uint32_t bin = 2 * tid + i;
+      const bool by_map = mapped && single(bin) && (int)bin < bins;
+      m[i] = by_map ? 0u : start[bin];
+      n[i] = m[i];
+      if (by_map)
+        for (int w = 0; w < a.map_words; ++w) n[i] += __popc(map_of(bin)[w]);
+    }
+    uint32_t sa = n[0] + n[1], sb = m[0] + m[1];
+    for (int o = 1; o < 64; o <<= 1) {
+      const uint32_t ua = __shfl_up(sa, o, 64), ub = __shfl_up(sb, o, 64);
+      if (lane >= o) { sa += ua; sb += ub; }
+    }
+    if (lane == 63) { total_a[wave] = sa; total_b[wave] = sb; }
+    __syncthreads();
+    for (int w = 0; w < wave; ++w) { sa += total_a[w]; sb += total_b[w]; }
+    start[2 * tid] = sa - n[0] - n[1];
+    start[2 * tid + 1] = sa - n[1];
+    ends[2 * tid] = sb - m[0] - m[1];  // the cursors of the next walk, which leaves them at the bins' ends
+    ends[2 * tid + 1] = sb - m[1];
+    if (tid == kLiThreads - 1) start[2048] = sa;
+  }
+  __syncthreads();
+  for (int p = tid; p <= 1 << a.pshift; p += kLiThreads)
+    a.off[(int64_t)blockIdx.x * ((1 << a.pshift) + 1) + p] = start[p * kSubBins];
+  uint32_t all_keys = 0;
+  for (int w = 0; w < kLiWaves; ++w) all_keys += total_b[w];
+  // ---- as many bins at a time as the keys have room for (all of them unless rows are long)
+  for (int b0 = 0; b0 < bins;) {
+    const uint32_t base = ends[b0];  // still the first key
+    auto first_key = [&](int b) { return b < bins ? ends[b] : all_keys; };
+    int b1 = bins;
+    if (all_keys - base > (uint32_t)kKeyCap) {
+      int lo = b0 + 1, hi = bins;
+      while (lo < hi) {
+        const int mid = (lo + hi + 1) / 2;
+        if (first_key(mid) - base <= (uint32_t)kKeyCap) lo = mid; else hi = mid - 1;
+      }
+      b1 = lo;
+    }
+    const bool too_many = first_key(b1) - base > (uint32_t)kKeyCap;  // one bin is more than that
+    __syncthreads();
+    if (!too_many) {
+      for (int g = 0; g < groups; ++g) {
+        if (groups > 1) load(g);
+        walk(g, [&](uint32_t col, int r, uint32_t k, int) {
+          const uint32_t bin = list_bin(col, a.pshift);
+          if ((int)bin < b0 || (int)bin >= b1 || (mapped && single(bin))) return;
+          keys[atomicAdd(&ends[bin], 1u) - base] = ((col >> a.pshift) << a.pos_bits | (uint32_t)r) << a.k_bits | k;
+        });
+      }
+      __syncthreads();
+    }
+    for (int g = 0; g < groups; ++g) {
+      if (groups > 1) load(g);
+      float v[kHeld];
+#pragma unroll
+      for (int q = 0; q < kHeld; ++q) {
+        const int r = g * held + q * kLiWaves + wave;
+        v[q] = c[q] >= 0 ? a.vals[lo_sh[r < a.B ? r : 0] + lane] : 0.0f;
+      }
+      walk(g, [&](uint32_t col, int r, uint32_t k, int q) {
+        const uint32_t bin = list_bin(col, a.pshift);
+        if ((int)bin < b0 || (int)bin >= b1) return;
+        const uint32_t pair = (col >> a.pshift) << a.pos_bits | (uint32_t)r, key = pair << a.k_bits | k;
+        uint32_t at = start[bin];
+        if (mapped && single(bin)) {
+          const uint32_t *map = map_of(bin);
+          for (int w = 0; w < r >> 5; ++w) at += __popc(map[w]);
+          at += __popc(map[r >> 5] & ((1u << (r & 31)) - 1u));
+        } else if (!too_many) {
+          const uint32_t hi = ends[bin] - base;
+          for (uint32_t i = (int)bin > b0 ? ends[bin - 1] - base : 0u; i < hi; ++i) at += keys[i] < key ? 1u : 0u;
+        } else {
+          // No data meant for these kernels come here (6400 entries of a batch in one of 2048 bins), but they are not refused:
+          // an entry counts the smaller keys of the whole batch, from memory.
+          for (int r2 = 0; r2 < a.B; ++r2) {
+            for (int32_t k2 = 0; k2 < len_sh[r2]; ++k2) {
+              const uint32_t c2 = (uint32_t)a.col_idx[lo_sh[r2] + k2];
+              if (list_bin(c2, a.pshift) != bin) continue;
+              at += (((c2 >> a.pshift) << a.pos_bits | (uint32_t)r2) << a.k_bits | (uint32_t)k2) < key ? 1u : 0u;
+            }
+          }
+        }
+        float val = 0.0f;
+        if (q >= 0) {
+#pragma unroll
+          for (int i = 0; i < kHeld; ++i) val = i == q ? v[i] : val;
+        } else {
+          val = a.vals[lo_sh[r] + (int32_t)k];
+        }
+        out[at] = make_uint2(pair, __builtin_bit_cast(uint32_t, val));
+      });
+    }
+    __syncthreads();
+    b0 = b1;
+  }
+  // ---- the lists' columns, a wavefront a list at a time
+  const int P = 1 << a.pshift;
+  uint32_t *cols = a.cols + (int64_t)blockIdx.x * a.cap;
+  for (int p0 = wave; p0 < P; p0 += 2 * kLiWaves) {
+    uint32_t first[2], end[2];
+    uint2 e[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int p = p0 + q * kLiWaves;
+      first[q] = p < P ? start[p * kSubBins] : 0u;
+      end[q] = p < P ? start[(p + 1) * kSubBins] : 0u;
+      e[q] = make_uint2(kNoEntry, 0u);
+      if (first[q] + lane < end[q]) e[q] = out[first[q] + lane];
+    }
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      uint32_t n = 0, before = kNoEntry;
+      for (uint32_t i = first[q]; i < end[q]; i += 64) {
+        if (i != first[q]) {
+          e[q].x = kNoEntry;
+          if (i + lane < end[q]) e[q] = out[i + lane];
+        }
+        const bool in = i + lane < end[q];
+        const uint32_t lc = in ? e[q].x >> a.pos_bits : kNoEntry - 1u;
+        const uint32_t prev = (uint32_t)__builtin_amdgcn_update_dpp((int)before, (int)lc, 0x138, 0xF, 0xF, false);  // wave_shr:1
+        const uint64_t heads = __ballot(lc != prev && in);
+        // behind the chunk: another column, or the list's end
+        const uint32_t next = i + 64 < end[q] ? (uint32_t)__builtin_amdgcn_readfirstlane((int)(out[i + 64].x >> a.pos_bits)) : kNoEntry;
+        const uint32_t after = (uint32_t)__builtin_amdgcn_update_dpp((int)next, (int)lc, 0x130, 0xF, 0xF, false);   // wave_shl:1
+        before = read_lane(lc, 63);
+        if (in) {
+          out[i + lane].x = (e[q].x & ((1u << a.pos_bits) - 1u)) | (lc != after ? kLast : 0u);
+          if ((heads >> lane) & 1ull) cols[first[q] + n + __popcll(heads & ((1ull << lane) - 1ull))] = lc + 1u;
+        }
+        n += (uint32_t)__popcll(heads);
+      }
+      const int p = p0 + q * kLiWaves;
+      if (p < P && lane == 0) a.n_cols[(int64_t)blockIdx.x * P + p] = n;
+    }
+  }
+}
+
+// Snapshot margins of the planned rows where the snapshot pass did not visit every row: a wavefront per row.
+__global__ __launch_bounds__(256) void plan_margins_kernel(const int32_t *__restrict__ col_idx, const float *__restrict__ vals,
+                                                           const float *__restrict__ w_snap, int64_t rows,
+                                                           RowPlan *__restrict__ plan) {
+  const int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  if (r >= rows) return;
+  const RowPlan p = plan[r];
+  float s = 0.0f;
+  for (int32_t e = p.lo + lane; e < p.hi; e += 64) s = __builtin_fmaf(vals[e], w_snap[col_idx[e]], s);
+  s = wave_sum(s);
+  if (lane == 0) plan[r].z = s;
+}
+
+__global__ __launch_bounds__(256) void longest_row_kernel(const int32_t *__restrict__ row_ptr, int64_t n,
+                                                          int32_t *__restrict__ out) {
+  int32_t most = 0;
+  for (int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x; r < n; r += (int64_t)gridDim.x * 256) {
+    const int32_t len = row_ptr[r + 1] - row_ptr[r];
+    most = len > most ? len : most;
+  }
+  atomicMax(out, most);
+}
+
+// ---------------------------------------------------------------------------------------------------------------------
+// A vector between the caller's order and the owners' (element lc of owner p = coordinate lc P + p), a tile of 32 lc by 64 p.
+struct DealArgs {
+  const float *from[4];
+  float *to[4];
+  float scale[4];
+  const uint32_t *ctl;  // dealt back: not where a launch with this tag gave up
+  uint32_t launch_tag;
+  int32_t d, S, pshift, back;
+};
+
+__global__ __launch_bounds__(256) void deal_kernel(DealArgs a) {
+  if (a.back && a.ctl[0] == a.launch_tag) return;
+  __shared__ float tile[32][65];
+  const float *from = a.from[blockIdx.z];
+  float *to = a.to[blockIdx.z];
+  const int l0 = blockIdx.x * 32, p0 = blockIdx.y * 64, P = 1 << a.pshift;
+  if (!a.back) {
+    for (int e = threadIdx.x; e < 32 * 64; e += 256) {
+      const int l = e >> 6, p = e & 63;
+      const int64_t c = (int64_t)(l0 + l) * P + p0 + p;
+      tile[l][p] = c < a.d ? from[c] : 0.0f;
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < 32 * 64; e += 256) {
+      const int p = e >> 5, l = e & 31;
+      if (l0 + l < a.S) to[(int64_t)(p0 + p) * a.S + l0 + l] = tile[l][p];
+    }
+  } else {
+    const float scale = a.scale[blockIdx.z];
+    for (int e = threadIdx.x; e < 32 * 64; e += 256) {
+      const int p = e >> 5, l = e & 31;
+      tile[l][p] = l0 + l < a.S ? from[(int64_t)(p0 + p) * a.S + l0 + l] : 0.0f;
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < 32 * 64; e += 256) {
+      const int l = e >> 6, p = e & 63;
+      const int64_t c = (int64_t)(l0 + l) * P + p0 + p;
+      if (c < a.d) to[c] = tile[l][p] * scale;
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------------------------------------------------
+struct ListArgs {
+  const int32_t *col_idx;
+  const float *vals;
+  const RowPlan *plan;     // [iterations][nvec * B] of this launch
+  const uint32_t *off;     // of this launch
+  uint2 *ent;
+  const uint32_t *cols, *n_cols;
+  int64_t cap;
+  const float *mu, *ws;    // the owners' order, here and below
+  float *x, *y, *z, *ysum;
+  // [P][S]; [2][nvec * B]; [2][N][5][P]; [2][N][dies][kLine]
+  u64 *xw, *slope, *stat, *stat2;
+  uint32_t *flags, *ctl;
+  int32_t d, S, pshift, N, nvec, B, it0, it1, bits, fields, words, scheme, loss;
+  uint32_t tag0, spin_limit;
+  QuantSpec qs;
+  StreamKey key;
+  float scale, step, thr, shrink;
+  float step_y, thr_y, shrink_y, alpha, thr_z, shrink_z, t1, t2, t3;
+  double theta, weight;
+};
+
+// Inclusive sums over the runs of lanes that `heads` begins, one fixed order; the first run goes on from `carry`.
+__device__ __forceinline__ float run_sums(float v, uint64_t heads, float carry, int lane) {
+  if (lane == 0) v += carry;
+  const uint64_t upto = (heads | 1ull) & (~0ull >> (63 - lane));
+  const int dist = lane - (63 - __builtin_clzll(upto));  // lanes of the run below this one
+  float t;
+  t = dpp_move<0x111>(v); v += dist >= 1 ? t : 0.0f;  // row_shr:1, 2, 4, 8
+  t = dpp_move<0x112>(v); v += dist >= 2 ? t : 0.0f;
+  t = dpp_move<0x114>(v); v += dist >= 4 ? t : 0.0f;
+  t = dpp_move<0x118>(v); v += dist >= 8 ? t : 0.0f;
+  // a row of 16 lanes takes what the row below ended with, then the upper half what the lower ended with
+  const float r0 = read_lane(v, 15), r2 = read_lane(v, 47);
+  const int row = lane >> 4;
+  v += ((row & 1) && dist > (lane & 15)) ? (row == 1 ? r0 : r2) : 0.0f;
+  const float half = read_lane(v, 31);
+  v += (lane >= 32 && dist > (lane & 31)) ? half : 0.0f;
+  return v;
+}
+
+// PLAIN: lambda clipping and scale factors of the workers' own (scheme (a)), the paper's way in all its experiments.
+// Everything that is requested ahead goes through buffers, whose lanes past the end read 0: a load under a condition is joined
+// with the other case's value, and the join waits for it.
+template <bool ALPC, bool PLAIN>
+__global__ __launch_bounds__(kLiThreads) void list_epoch_kernel(ListArgs a) {
+  touch_kernel_arguments<(int)(sizeof(ListArgs))>();
+  extern __shared__ __attribute__((aligned(16))) float lds[];
+  __shared__ float delta_sh[kLiWaves];
+  __shared__ uint32_t fail_sh[2], count[3], over_sh;
+  __shared__ uint32_t stage[kLiWaves][64 * kLiPairs];  // a wavefront's own: sums on their way to their columns' lanes
+  const int S = a.S;
+  float *xs = lds, *mus = xs + S;
+  float *zs = mus + S, *ysums = zs + (ALPC ? S : 0), *wss = ysums + (ALPC ? S : 0), *uhs = wss + (ALPC ? S : 0);
+  uint32_t *codes = reinterpret_cast<uint32_t *>(uhs + (ALPC ? S : 0));  // [words][S]
+  uint32_t *marks = codes + a.words * S;                                   // [3][(S + 31) / 32]: set t % 3 the columns of t
+  const int mark_words = (S + 31) / 32;
+  uint16_t *touched = reinterpret_cast<uint16_t *>(marks + 3 * mark_words);  // [2][S]
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int p = blockIdx.x, P = 1 << a.pshift, die = p & (kDies - 1), per_die = P / kDies;
+
+  // an earlier launch of this epoch gave up
+  if (tid == 0) over_sh = __hip_atomic_load(a.ctl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == a.tag0 + 1u ? 1u : 0u;
+  if (tid < 3) count[tid] = 0u;
+  if (tid < 2) fail_sh[tid] = 0u;
+  if (tid < kLiWaves) delta_sh[tid] = 0.0f;
+  for (int l = tid; l < S; l += kLiThreads) {
+    const int64_t at = (int64_t)p * S + l;
+    mus[l] = a.mu[at];
+    if (ALPC) {
+      const float z = a.z[at], w = a.ws[at], y = a.y[at];
+      zs[l] = z;
+      wss[l] = w;
+      uhs[l] = 0.0f;
+      ysums[l] = a.it0 > 0 ? a.ysum[at] : 0.0f;
+      xs[l] = (a.t1 * z + a.t2 * w) + a.t3 * y;
+    } else {
+      xs[l] = a.it0 > 0 ? a.x[at] : a.ws[at];
+    }
+  }
+  for (int e = tid; e < a.words * S; e += kLiThreads) codes[e] = 0u;
+  for (int e = tid; e < 3 * mark_words; e += kLiThreads) marks[e] = 0u;
+  __syncthreads();
+  if (over_sh) return;  // uniform
+
+  // `loads` requests the words that a lane still lacks and says whether all are there; the wavefront waits as one.  (Words that
+  // are there are not asked for again: what polls is in the way of what they wait for.)
+  auto poll = [&](uint32_t limit, bool &ok, auto loads) {
+    if (!ok) return;
+    for (uint32_t k = 0; k < limit; ++k) {
+      if (__ballot(!loads()) == 0ull) return;
+      if ((k & 63u) == 63u &&
+          __builtin_amdgcn_readfirstlane((int)__hip_atomic_load(a.ctl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) ==
+              (int)(a.tag0 + 1u))
+        break;
+    }
+    ok = false;
+  };
+  // ---- rows of this wavefront: batch positions of all vectors, consecutive ones in a workgroup (their slopes share a line)
+  const int total_rows = a.nvec * a.B;
+  int slot[kLiRows];
+  bool has_row[kLiRows];
+#pragma unroll
+  for (int q = 0; q < kLiRows; ++q) {
+    slot[q] = (q * P + p) * kLiWaves + wave;
+    has_row[q] = slot[q] < total_rows;
+  }
+  auto buffer = [](const void *from, uint32_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(from), 0, (int)bytes, 0x00027000);
+  };
+  typedef uint32_t words4 __attribute__((ext_vector_type(4)));
+  typedef uint32_t words2 __attribute__((ext_vector_type(2)));
+  words4 row[kLiRows];   // a RowPlan: first entry, end, label, snapshot slope
+  int32_t len[kLiRows];
+  uint32_t rx[kLiRows];  // of lane l: the column of the row's entry l, then where its x word lies, in bytes; kNoEntry: none
+  uint32_t rv[kLiRows];  // ... and the entry's value
+  auto x_at = [&](uint32_t c) { return 8u * ((c & (uint32_t)(P - 1)) * (uint32_t)S + (c >> a.pshift)); };
+  auto x_word = [&](uint32_t at) { return ld_word(reinterpret_cast<const u64 *>(reinterpret_cast<const char *>(a.xw) + at)); };
+  auto fetch_rows = [&](int t) {
+#pragma unroll
+    for (int q = 0; q < kLiRows; ++q)
+      row[q] = __builtin_amdgcn_raw_buffer_load_b128(buffer(a.plan + (int64_t)(t - a.it0) * total_rows + slot[q], has_row[q] ? 16u : 0u), 0, 0, 0);
+  };
+  auto fetch_pairs = [&]() {
+#pragma unroll
+    for (int q = 0; q < kLiRows; ++q) {
+      const int32_t lo = __builtin_amdgcn_readfirstlane((int)row[q].x);
+      len[q] = __builtin_amdgcn_readfirstlane((int)row[q].y) - lo;
+      rx[q] = __builtin_amdgcn_raw_buffer_load_b32(buffer(a.col_idx + lo, 4u * (uint32_t)len[q]), 4 * lane, 0, 0);
+      rv[q] = __builtin_amdgcn_raw_buffer_load_b32(buffer(a.vals + lo, 4u * (uint32_t)len[q]), 4 * lane, 0, 0);
+    }
+  };
+  // ---- this wavefront's list: vector `wave`'s entries in this workgroup's columns
+  const bool quantizes = wave < a.N, listed = wave < a.nvec;
+  // the shared batch's vector where the workers have all wavefronts
+  const bool adds_shared = ALPC && a.N == kLiWaves && wave == 0;
+  struct List {
+    int64_t at;    // its first entry
+    int32_t n;     // entries
+    int32_t cols;  // columns
+  };
+  // lane l: the list's first entry, its end, its number of columns (l = 0, 1, 2)
+  auto bounds_of = [&](int t, int v) {
+    const int64_t k = (int64_t)(t - a.it0) * a.nvec + v;
+    const uint32_t *from = lane == 2 ? a.n_cols + k * P + p : a.off + k * (P + 1) + p + (lane & 1);
+    return *from;
+  };
+  auto list_of = [&](int t, int v, uint32_t b) {
+    const uint32_t first = read_lane(b, 0);
+    return List{((int64_t)(t - a.it0) * a.nvec + v) * a.cap + first, (int32_t)(read_lane(b, 1) - first), (int32_t)read_lane(b, 2)};
+  };
+  auto is_long = [&](const List &l) { return l.n > 64 * kLiChunks || l.cols > 64 * kLiPairs; };
+  words2 ent[kLiChunks], ent_n[kLiChunks];
+  uint32_t col[kLiPairs], col_n[kLiPairs];  // lc + 1; a lane without a column: 0
+  List list{0, 0, 0}, list_n{0, 0, 0};
+  uint32_t bounds = 0;
+  auto fetch_list = [&](const List &l, words2 (&e)[kLiChunks], uint32_t (&c)[kLiPairs]) {
+#pragma unroll
+    for (int r = 0; r < kLiChunks; ++r) {
+      e[r] = words2{0u, 0u};
+      if (r * 64 < l.n)  // uniform
+        e[r] = __builtin_amdgcn_raw_buffer_load_b64(buffer(a.ent + l.at, 8u * (uint32_t)l.n), 8 * lane + 512 * r, 0, 0);
+    }
+#pragma unroll
+    for (int k = 0; k < kLiPairs; ++k) {
+      c[k] = 0u;
+      if (k * 64 < l.cols) c[k] = __builtin_amdgcn_raw_buffer_load_b32(buffer(a.cols + l.at, 4u * (uint32_t)l.cols), 4 * lane + 256 * k, 0, 0);
+    }
+  };
+  // the coming iteration's touched columns, each once
+  auto mark = [&](int t, uint32_t lc1) {
+    bool first = false;
+    const uint32_t lc = lc1 - 1u;
+    if (lc1 != 0u) {
+      const uint32_t bit = 1u << (lc & 31u);
+      first = !(atomicOr(&marks[(t % 3) * mark_words + (lc >> 5)], bit) & bit);
+    }
+    const uint64_t m = __ballot(first);
+    if (m == 0ull) return;
+    uint32_t at = 0;
+    if (lane == 0) at = atomicAdd(&count[t % 3], (uint32_t)__popcll(m));
+    at = __builtin_amdgcn_readfirstlane((int)at);
+    if (first) touched[(t & 1) * S + at + __popcll(m & ((1ull << lane) - 1ull))] = (uint16_t)lc;
+  };
+  auto mark_from = [&](int t, const List &l, int i) {  // columns i .. from memory
+    for (; i < l.cols; i += 64) mark(t, i + lane < l.cols ? a.cols[l.at + i + lane] : 0u);
+  };
+  auto mark_list = [&](int t, const List &l, const uint32_t (&c)[kLiPairs]) {
+#pragma unroll
+    for (int k = 0; k < kLiPairs; ++k)
+      if (k * 64 < l.cols) mark(t, c[k]);
+    mark_from(t, l, 64 * kLiPairs);
+  };
+  auto put_x = [&](int t, uint32_t lc, float x) {  // the iterate where iteration t's rows look
+    st_word(a.xw + (uint32_t)(p * S) + lc, __builtin_bit_cast(uint32_t, x), a.tag0 + (uint32_t)t + 1u);
+  };
+  // The wait for all that has been requested ahead, before the next words are stored: a wait for a load behind a store is one
+  // for the store to arrive as well.
+  auto settle = [&] {
+#pragma unroll
+    for (int q = 0; q < kLiRows; ++q) {
+      rx[q] = lane < len[q] ? x_at(rx[q]) : kNoEntry;
+      asm volatile("" : "+v"(rx[q]), "+v"(rv[q]), "+v"(row[q]));
+    }
+#pragma unroll
+    for (int r = 0; r < kLiChunks; ++r) asm volatile("" : "+v"(ent_n[r]));
+#pragma unroll
+    for (int k = 0; k < kLiPairs; ++k) asm volatile("" : "+v"(col_n[k]));
+    asm volatile("" : "+v"(bounds));
+  };
+  if (listed) {
+    list_n = list_of(a.it0, wave, bounds_of(a.it0, wave));
+    bounds = bounds_of(a.it0 + 1 < a.it1 ? a.it0 + 1 : a.it0, wave);
+  }
+  fetch_list(list_n, ent_n, col_n);
+  if (listed) mark_list(a.it0, list_n, col_n);
+  if (adds_shared) mark_from(a.it0, list_of(a.it0, a.N, bounds_of(a.it0, a.N)), 0);
+  fetch_rows(a.it0);
+  fetch_pairs();
+  settle();
+  __syncthreads();
+  for (uint32_t i = tid; i < count[a.it0 % 3]; i += kLiThreads) {
+    const uint32_t lc = touched[(a.it0 & 1) * S + i];
+    put_x(a.it0, lc, xs[lc]);
+  }
+
+  const bool csigma = !PLAIN && a.qs.clip_mode != LPC_CLIP_LAMBDA;
+  const float inv_n = 1.0f / (float)a.N;
+  const float hi_q = (float)((1 << a.bits) / 2 - 1), lo_q = -(float)((1 << a.bits) / 2);
+  const uint32_t mask = (1u << a.bits) - 1u;
+  const int my_word = wave / a.fields, my_shift = (wave - my_word * a.fields) * a.bits;
+  double weight = a.weight;
+  bool gave_up = false;
+  for (int t = a.it0; t < a.it1; ++t) {
+    const int par = t & 1;
+    const uint32_t tag = a.tag0 + (uint32_t)t + 1u;
+    const uint32_t limit = t == a.it0 ? (a.spin_limit > 0xffffffu ? ~0u : a.spin_limit * 256u) : a.spin_limit;
+    const bool more = t + 1 < a.it1;
+    bool ok = true;
+    auto there = [&](u64 w) { return (uint32_t)(w >> 32) == tag; };
+    list = list_n;
+#pragma unroll
+    for (int r = 0; r < kLiChunks; ++r) ent[r] = ent_n[r];
+#pragma unroll
+    for (int k = 0; k < kLiPairs; ++k) col[k] = col_n[k];
+    // ---- 1. the rows' margins and slope differences
+    __builtin_amdgcn_s_setprio(3);
+    {
+      u64 xw[kLiRows];
+#pragma unroll
+      for (int q = 0; q < kLiRows; ++q) xw[q] = rx[q] != kNoEntry ? 0ull : (u64)tag << 32;
+      poll(limit, ok, [&] {
+        bool all = true;
+#pragma unroll
+        for (int q = 0; q < kLiRows; ++q)
+          if (!there(xw[q])) xw[q] = x_word(rx[q]);
+#pragma unroll
+        for (int q = 0; q < kLiRows; ++q) all = all && there(xw[q]);
+        return all;
+      });
+#pragma unroll
+      for (int q = 0; q < kLiRows; ++q) {
+        if (!has_row[q]) continue;  // uniform
+        float s = __builtin_bit_cast(float, rv[q]) * __builtin_bit_cast(float, (uint32_t)xw[q]);  // lanes without an entry: 0 * 0
+        for (int32_t k = 64; k < len[q]; k += 64) {  // rows longer than 64 entries
+          const int64_t e = (int32_t)row[q].x + (k + lane < len[q] ? k + lane : len[q] - 1);
+          const uint32_t at = x_at((uint32_t)a.col_idx[e]);
+          const float v = a.vals[e];
+          u64 far = 0;
+          poll(limit, ok, [&] { if (!there(far)) far = x_word(at); return there(far); });
+          s = k + lane < len[q] ? __builtin_fmaf(v, __builtin_bit_cast(float, (uint32_t)far), s) : s;
+        }
+        const float z = wave_sum(s);
+        // (x_0 of Alg. 1 is the snapshot: its differences are exactly zero; the builder left the snapshot's slope in row.z)
+        const uint32_t label = row[q].z, snap = row[q].w;
+        const float diff = loss_slope(a.loss, z, __builtin_bit_cast(float, label)) - __builtin_bit_cast(float, snap);
+        const float coef = ALPC || t > 0 ? diff * a.scale : 0.0f;
+        if (lane == 0) st_word(a.slope + par * total_rows + slot[q], __builtin_bit_cast(uint32_t, coef), tag);
+      }
+    }
+    __builtin_amdgcn_s_setprio(0);
+    // ---- while the slopes travel: the coming iteration's rows and entries requested, this one's random words
+    {
+      const int t1 = more ? t + 1 : t;  // (the last one's own again, to no purpose)
+      fetch_rows(t1);
+      list_n = list_of(t1, wave, bounds);
+      if (!listed) list_n.n = list_n.cols = 0;
+      fetch_list(list_n, ent_n, col_n);
+      bounds = bounds_of(t + 2 < a.it1 ? t + 2 : t1, listed ? wave : 0);
+    }
+    auto random_word = [&](uint32_t lc) {
+      StreamKey k = a.key;
+      k.iter = (uint32_t)t;
+      const Philox4 b = stream_block(k, kTagQuant, (uint32_t)wave, (lc << (a.pshift - 2)) | ((uint32_t)p >> 2));
+      return (p & 2) ? ((p & 1) ? b.w : b.z) : ((p & 1) ? b.y : b.x);
+    };
+    uint32_t rnd[kLiPairs];
+    float u[kLiPairs];
+#pragma unroll
+    for (int k = 0; k < kLiPairs; ++k) {
+      rnd[k] = 0u;
+      u[k] = 0.0f;
+      if (quantizes && k * 64 < list.cols) rnd[k] = random_word(col[k] - 1u);
+    }
+    // ---- 2. u^i at this workgroup's columns
+    // A list in memory: the k-th column's sum replaces the value of the list's k-th entry (which has been taken by then).
+    auto form_long = [&](const List &l, int v) {
+      const u64 *sl = a.slope + par * total_rows + v * a.B;
+      float open = 0.0f;
+      bool closed = true;
+      int n = 0;
+      for (int i = 0; i < l.n; i += 64) {
+        const uint2 e = i + lane < l.n ? a.ent[l.at + i + lane] : make_uint2(kLast, 0u);
+        u64 f = 0;
+        poll(limit, ok, [&] { if (!there(f)) f = ld_word(sl + (e.x & ~kLast)); return there(f); });
+        const uint64_t ends = __ballot((e.x & kLast) != 0u);
+        const uint64_t heads = (ends << 1) | (closed ? 1ull : 0ull);
+        const float s = run_sums(__builtin_bit_cast(float, (uint32_t)f) * __builtin_bit_cast(float, e.y), heads, closed ? 0.0f : open, lane);
+        open = read_lane(s, 63);
+        closed = (ends >> 63) & 1ull;
+        if (((ends >> lane) & 1ull) && i + lane < l.n)
+          a.ent[l.at + n + __popcll(ends & ((1ull << lane) - 1ull))].y = __builtin_bit_cast(uint32_t, s);
+        n += __popcll(ends);
+      }
+      __threadfence_block();  // other lanes read the sums
+    };
+    auto sum_at = [&](const List &l, int k) { return __builtin_bit_cast(float, a.ent[l.at + k].y); };
+    float mx = 0.0f;
+    double sum = 0.0, sumsq = 0.0;
+    bool bad = false;
+    auto take = [&](float v) {
+      const bool fin = isfinite(v);
+      const float f = fin ? v : 0.0f;
+      bad |= !fin;
+      mx = fmaxf(mx, fabsf(f));
+      if (csigma) { sum += (double)f; sumsq += (double)f * (double)f; }
+    };
+    const bool long_list = is_long(list);
+    if (listed) {
+      if (!long_list) {
+        const u64 *sl = a.slope + par * total_rows + wave * a.B;
+        u64 w[kLiChunks];
+#pragma unroll
+        for (int r = 0; r < kLiChunks; ++r) w[r] = r * 64 + lane < list.n ? 0ull : (u64)tag << 32;
+        poll(limit, ok, [&] {
+          bool all = true;
+#pragma unroll
+          for (int r = 0; r < kLiChunks; ++r)
+            if (r * 64 < list.n && !there(w[r])) w[r] = ld_word(sl + (ent[r].x & ~kLast));
+#pragma unroll
+          for (int r = 0; r < kLiChunks; ++r) all = all && there(w[r]);
+          return all;
+        });
+        __builtin_amdgcn_s_setprio(3);
+        // A column's sum, at its last entry, goes to the column's lane.  `open`: what the lanes hold of a column that goes on
+        // behind the chunk; chunks of one column only, as in the most frequent columns' lists, add lane by lane.
+        float open = 0.0f;
+        uint32_t closed = 1u;
+        int n = 0;
+#pragma unroll
+        for (int r = 0; r < kLiChunks; ++r) {
+          if (r * 64 < list.n) {
+            const uint64_t ends = __ballot((ent[r].x & kLast) != 0u);
+            const uint32_t value = ent[r].y;
+            float s = __builtin_bit_cast(float, (uint32_t)w[r]) * __builtin_bit_cast(float, value);
+            if ((ends << 1) == 0ull) {  // the chunk is one column's
+              open = closed ? s : open + s;
+              if (ends != 0ull) s = wave_sum(open);
+            } else {
+              const uint64_t heads = (ends << 1) | closed;
+              if (heads != ~0ull) s = run_sums(s, heads, closed ? 0.0f : wave_sum(open), lane);
+              open = lane == 63 ? s : 0.0f;
+            }
+            closed = (uint32_t)(ends >> 63);
+            if ((ends >> lane) & 1ull) stage[wave][n + __popcll(ends & ((1ull << lane) - 1ull))] = __builtin_bit_cast(uint32_t, s);
+            n += __popcll(ends);
+          }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int k = 0; k < kLiPairs; ++k) {
+          if (k * 64 < list.cols) {
+            if (col[k] != 0u) u[k] = __builtin_bit_cast(float, stage[wave][k * 64 + lane]);
+            take(u[k]);
+            if (ALPC && !quantizes && col[k] != 0u) uhs[col[k] - 1u] = u[k];
+          }
+        }
+      } else {
+        form_long(list, wave);
+        for (int k = lane; k < list.cols; k += 64) {
+          take(sum_at(list, k));
+          if (ALPC && !quantizes) uhs[a.cols[list.at + k] - 1u] = sum_at(list, k);
+        }
+      }
+    }
+    if (quantizes) {
+      mx = wave_max(mx);
+      if (csigma) { sum = wave_sum(sum); sumsq = wave_sum(sumsq); }
+      if (__ballot(bad) != 0ull && lane == 0) atomicOr(&a.flags[0], 1u);
+      u64 *st = a.stat + ((int64_t)par * a.N + wave) * 5 * P + die * per_die + p / kDies;
+      uint32_t mine = __builtin_bit_cast(uint32_t, mx);
+      if (csigma) {
+        const u64 s = __builtin_bit_cast(u64, sum), s2 = __builtin_bit_cast(u64, sumsq);
+        if (lane > 0) mine = (uint32_t)((lane < 3 ? s : s2) >> (lane & 1 ? 0 : 32));
+      }
+      if (lane < (csigma ? 5 : 1)) st_word(st + (int64_t)lane * P, mine, tag);
+    }
+    // One wavefront per vector and die takes the statistics of its die's owners together, every wavefront those of the dies:
+    // all owners' words read by all of them are 8 MB for 16 vectors.
+    float am = 0.0f;
+    auto gather = [&](const u64 *from, int64_t stride, int words) {  // words <= 64, of lanes 0 .. words - 1
+      u64 h[5] = {};
+      poll(limit, ok, [&] {
+        bool all = true;
+#pragma unroll
+        for (int i = 0; i < (PLAIN ? 1 : 5); ++i)
+          if ((i == 0 || csigma) && !there(h[i])) h[i] = ld_word(from + i * stride);
+#pragma unroll
+        for (int i = 0; i < (PLAIN ? 1 : 5); ++i) all = all && (there(h[i]) || (i > 0 && !csigma));
+        return all;
+      });
+      am = wave_max(__builtin_bit_cast(float, (uint32_t)h[0]));
+      if (csigma) {
+        const double d1 = __builtin_bit_cast(double, (h[1] & 0xffffffffull) | (h[2] << 32));
+        const double d2 = __builtin_bit_cast(double, (h[3] & 0xffffffffull) | (h[4] << 32));
+        sum = wave_sum(lane < words ? d1 : 0.0);
+        sumsq = wave_sum(lane < words ? d2 : 0.0);
+      }
+    };
+    if (quantizes && p / kDies == wave * per_die / kLiWaves) {
+      gather(a.stat + ((int64_t)par * a.N + wave) * 5 * P + die * per_die + (lane < per_die ? lane : per_die - 1), P, per_die);
+      uint32_t mine = __builtin_bit_cast(uint32_t, am);
+      if (csigma) {
+        const u64 s = __builtin_bit_cast(u64, sum), s2 = __builtin_bit_cast(u64, sumsq);
+        if (lane > 0) mine = (uint32_t)((lane < 3 ? s : s2) >> (lane & 1 ? 0 : 32));
+      }
+      if (lane < (csigma ? 5 : 1)) st_word(a.stat2 + (((int64_t)par * a.N + wave) * kDies + die) * kLine + lane, mine, tag);
+    }
+    __builtin_amdgcn_s_setprio(0);
+    // ---- while the statistics travel: the coming rows' pairs and columns, and the coordinates that no row of this iteration
+    // touches
+    fetch_pairs();
+    for (int l = 4 * tid; l < S; l += 4 * kLiThreads) {  // S is a multiple of four
+      const uint32_t taken = marks[(t % 3) * mark_words + (l >> 5)] >> (l & 31);
+      const float4 m4 = *reinterpret_cast<const float4 *>(mus + l);
+      float4 x4 = *reinterpret_cast<const float4 *>(xs + l);
+      float *x = &x4.x;
+      const float *m = &m4.x;
+      if (ALPC) {
+        float4 z4 = *reinterpret_cast<const float4 *>(zs + l), sum4 = *reinterpret_cast<const float4 *>(ysums + l);
+        const float4 w4 = *reinterpret_cast<const float4 *>(wss + l);
+        float *z = &z4.x, *acc = &sum4.x;
+        const float *w = &w4.x;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          const float yn = prox_scalar(x[c], 0.0f + m[c], a.step_y, a.thr_y, a.shrink_y);
+          const float zn = prox_scalar(z[c], 0.0f + m[c], a.alpha, a.thr_z, a.shrink_z);
+          const bool stays = (taken >> c) & 1u;
+          z[c] = stays ? z[c] : zn;
+          acc[c] = stays ? acc[c] : (t == 0 ? (float)weight * yn : acc[c] + (float)weight * yn);
+          x[c] = stays ? x[c] : (a.t1 * zn + a.t2 * w[c]) + a.t3 * yn;
+          if (!more && !stays) a.y[(int64_t)p * S + l + c] = yn;
+        }
+        *reinterpret_cast<float4 *>(zs + l) = z4;
+        *reinterpret_cast<float4 *>(ysums + l) = sum4;
+      } else {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          const float xn = prox_scalar(x[c], 0.0f + m[c], a.step, a.thr, a.shrink);
+          x[c] = (taken >> c) & 1u ? x[c] : xn;
+        }
+      }
+      *reinterpret_cast<float4 *>(xs + l) = x4;
+    }
+    if (adds_shared) {  // the shared batch's difference, in full precision
+      const List l = list_of(t, a.N, bounds_of(t, a.N));
+      form_long(l, a.N);
+      for (int k = lane; k < l.cols; k += 64) uhs[a.cols[l.at + k] - 1u] = sum_at(l, k);
+      if (more) mark_from(t + 1, list_of(t + 1, a.N, bounds_of(t + 1, a.N)), 0);
+    }
+    if (more && listed) mark_list(t + 1, list_n, col_n);
+    // ---- 3. the scale factors (Sec. 3.2, eq. (3)), as in lpc_columns.hip
+    QParams q{0.0f, 0.0f, 0.0f, 0.0f};
+    if (quantizes) {
+      gather(a.stat2 + (((int64_t)par * a.N + wave) * kDies + (lane & (kDies - 1))) * kLine, 1, kDies);
+      if (csigma) {
+        q = make_qparams(a.qs, (double)am, sum, sumsq, a.d);
+      } else {
+        const float delta = a.qs.clip * am / hi_q, rd = 1.0f / delta;
+        const bool live = delta > 0.0f && isfinite(rd);
+        q.delta = live ? delta : 0.0f;
+        q.rdelta = live ? rd : 0.0f;
+      }
+      if (lane == 0) delta_sh[wave] = q.delta;
+    }
+    if (!PLAIN && a.scheme != LPC_SCHEME_A) {  // the largest of the N scale factors
+      __syncthreads();
+      const float dmax = wave_max(lane < a.N ? delta_sh[lane] : 0.0f);
+      const float rd = 1.0f / dmax;
+      const bool live = dmax > 0.0f && isfinite(rd);
+      q.delta = live ? dmax : 0.0f;
+      q.rdelta = live ? rd : 0.0f;
+    }
+    __builtin_amdgcn_s_setprio(3);
+    // ---- codes (Sec. 3.2 rules (1), (2)) into their columns' fields
+    if (quantizes) {
+      auto code_of = [&](float v, uint32_t word, uint32_t lc) {
+        const float s = fminf(fmaxf(v * q.rdelta, lo_q), hi_q);
+        const float base = floorf(s), frac = s - base;
+        const float unif = (float)(word >> 8) * 0x1.0p-24f;
+        const int32_t code = q.delta > 0.0f ? (int32_t)base + ((unif < frac) ? 1 : 0) : 0;
+        if (code != 0) atomicOr(&codes[my_word * S + lc], ((uint32_t)code & mask) << my_shift);
+      };
+      if (!long_list) {
+#pragma unroll
+        for (int k = 0; k < kLiPairs; ++k)
+          if (k * 64 < list.cols && col[k] != 0u) code_of(u[k], rnd[k], col[k] - 1u);
+      } else {
+        for (int k = lane; k < list.cols; k += 64) {
+          const uint32_t lc = a.cols[list.at + k] - 1u;
+          code_of(sum_at(list, k), random_word(lc), lc);
+        }
+      }
+    }
+    if (!ok) fail_sh[par] = 1u;
+    settle();
+    __syncthreads();
+    // ---- the receiver (eq. (4), or the integer sums of schemes (b), (c)) and the update of the touched columns; those that
+    // the next iteration's rows hold are published at once, and so are the others that they hold
+    {
+      const uint32_t *next = marks + ((t + 1) % 3) * mark_words, *now = marks + (t % 3) * mark_words;
+      auto marked = [&](const uint32_t *m, uint32_t lc) { return (m[lc >> 5] >> (lc & 31u)) & 1u; };
+      const uint32_t n = count[t % 3];
+      const float dl = lane < kLiWaves ? delta_sh[lane] : 0.0f;
+      for (uint32_t i0 = wave * 64; i0 < n; i0 += kLiThreads) {  // whole wavefronts
+        const bool in = i0 + lane < n;
+        const uint32_t lc = in ? touched[par * S + i0 + lane] : 0u;
+        const float m = mus[lc], x0 = xs[lc];
+        const bool goes = in && more && marked(next, lc) != 0u;
+        float avg = 0.0f;
+        int32_t isum = 0;
+        int v = 0;
+        for (int wd = 0; wd < a.words; ++wd) {
+          uint32_t f = in ? codes[wd * S + lc] : 0u;
+          if (in) codes[wd * S + lc] = 0u;
+          const int last = v + a.fields < a.N ? v + a.fields : a.N;
+          if (__ballot(f != 0u) == 0ull) {
+            v = last;
+            continue;
+          }
+          for (int shift = 0; v < last; v += 4) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              if (v + i < last) {
+                const int32_t code = __builtin_amdgcn_sbfe((int)f, (uint32_t)shift, (uint32_t)a.bits);
+                if (PLAIN || a.scheme == LPC_SCHEME_A) avg = __builtin_fmaf(read_lane(dl, v + i), (float)code, avg);
+                else isum += code;
+              }
+              shift += a.bits;
+            }
+          }
+          v = last;
+        }
+        if (PLAIN || a.scheme == LPC_SCHEME_A) {
+          avg *= inv_n;
+        } else {
+          const float mean_code = (float)isum * inv_n;
+          if (a.scheme == LPC_SCHEME_B) {
+            avg = q.delta * mean_code;
+          } else {  // eq. (5): the average rounded once more
+            const float s = fminf(fmaxf(mean_code, lo_q), hi_q);
+            const float base = floorf(s), frac = s - base;
+            StreamKey k = a.key;
+            k.iter = (uint32_t)t;
+            const float unif = (float)(stream_word(k, kTagRequant, 0u, (lc << a.pshift) | (uint32_t)p) >> 8) * 0x1.0p-24f;
+            avg = q.delta * (float)((int32_t)base + ((unif < frac) ? 1 : 0));
+          }
+        }
+        if (in) {
+          float x1;
+          if (ALPC) {
+            const float yn = prox_scalar(x0, avg + m, a.step_y, a.thr_y, a.shrink_y);
+            const float zn = prox_scalar(zs[lc], uhs[lc] + m, a.alpha, a.thr_z, a.shrink_z);
+            uhs[lc] = 0.0f;
+            zs[lc] = zn;
+            ysums[lc] = t == 0 ? (float)weight * yn : ysums[lc] + (float)weight * yn;
+            x1 = (a.t1 * zn + a.t2 * wss[lc]) + a.t3 * yn;
+            if (!more) a.y[(int64_t)p * S + lc] = yn;
+          } else {
+            x1 = prox_scalar(x0, avg + m, a.step, a.thr, a.shrink);
+          }
+          if (goes) put_x(t + 1, lc, x1);
+          xs[lc] = x1;
+        }
+      }
+      if (more) {
+        const uint32_t n1 = count[(t + 1) % 3];
+        for (uint32_t i = (kLiWaves - 1 - wave) * 64 + lane; i < n1; i += kLiThreads) {  // the other wavefronts first
+          const uint32_t lc = touched[(1 - par) * S + i];
+          if (!marked(now, lc)) put_x(t + 1, lc, xs[lc]);
+        }
+      }
+      // of t - 1: nobody reads it any more, the first to write it is behind the barrier
+      if (tid < mark_words) marks[((t + 2) % 3) * mark_words + tid] = 0u;
+      for (int e = tid + kLiThreads; e < mark_words; e += kLiThreads) marks[((t + 2) % 3) * mark_words + e] = 0u;
+      if (tid == 0) count[(t + 2) % 3] = 0u;
+    }
+    if (ALPC) weight *= a.theta;
+    __syncthreads();
+    if (fail_sh[par] != 0u) { gave_up = true; break; }  // uniform: written before the first barrier, next at t + 2
+  }
+  if (gave_up) {  // the others find the word at their next wait
+    if (tid == 0) {
+      __hip_atomic_store(a.ctl, a.tag0 + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      atomicOr(&a.flags[0], 2u);
+    }
+    return;
+  }
+  for (int l = tid; l < S; l += kLiThreads) {
+    const int64_t at = (int64_t)p * S + l;
+    if (ALPC) {
+      a.z[at] = zs[l];
+      a.ysum[at] = ysums[l];
+    } else {
+      a.x[at] = xs[l];
+    }
+  }
+}
+
+// Iterations of a launch.  n = d = 2^20, N = 16, B = 256: an epoch of 256 takes 3.80, 3.60 and 3.49 ms with 32, 64 and 128
+constexpr int kListIters = 128;
+
+struct Shape {
+  int pshift, S, fields, words;
+  size_t lds;
+};
+
+int bits_for(int64_t values) {  // of a number in [0, values)
+  int b = 0;
+  while (((int64_t)1 << b) < values) ++b;
+  return b;
+}
+
+// What does not depend on the rows' lengths; S = 0 where the kernel does not apply: a wavefront per vector, two rows per
+// wavefront at most, and the slices must fit LDS.
+Shape shape_of(const lpc_ctx *c) {
+  Shape s{};
+  if (!c->csr || !c->quant || c->cfg.bits > 16 || c->cfg.N > kLiWaves || c->cfg.m < 1 || c->prob.nnz <= 0) return s;
+  s.pshift = 8;
+  const int P = 1 << s.pshift;
+  const bool alpc = c->cfg.algo != LPC_ALGO_LPC;
+  const int64_t rows = (int64_t)(c->cfg.N + (alpc ? 1 : 0)) * c->cfg.B, S = (c->d + 4 * P - 1) / (4 * P) * 4;
+  if (c->cfg.B > kMaxBatch || rows > (int64_t)kLiRows * kLiWaves * P || S > 65535 || P > c->device_cus) return s;
+  s.fields = 32 / c->cfg.bits;
+  s.words = (c->cfg.N + s.fields - 1) / s.fields;
+  s.lds = 4 * (size_t)S * ((alpc ? 6 : 2) + s.words + 1) + 12 * (size_t)((S + 31) / 32);
+  if (s.lds > (size_t)kLiLds - 18 * 1024) return s;
+  s.S = (int)S;
+  return s;
+}
+
+int64_t list_rows(const lpc_ctx *c) { return (int64_t)(c->cfg.N + (c->cfg.algo != LPC_ALGO_LPC ? 1 : 0)) * c->cfg.B; }
+int64_t list_iters(const lpc_ctx *c) { return c->cfg.m < kListIters ? c->cfg.m : kListIters; }
+
+}  // namespace
+
+bool lists_supported(const lpc_ctx *c) { return shape_of(c).S > 0; }
+
+// Room for the lists of kListIters iterations of rows three times as long as the mean; where the longest row is longer,
+// a launch takes fewer iterations (finish_lists).
+ListScratch lists_scratch(const lpc_ctx *c) {
+  const Shape s = shape_of(c);
+  const size_t P = (size_t)1 << s.pshift, N = (size_t)c->cfg.N, rows = (size_t)list_rows(c);
+  ListScratch w;
+  w.xw = P * s.S;
+  w.slope = 2 * rows;
+  w.stat = 2 * N * (5 * P + kDies * kLine);
+  w.state = 6 * P * s.S;
+  w.off = (size_t)list_iters(c) * (rows / c->cfg.B) * (2 * P + 1);  // the lists' bounds, then their numbers of columns
+  const int64_t mean = (c->prob.nnz + c->n - 1) / c->n;
+  w.entries = (size_t)list_iters(c) * rows * (size_t)(3 * mean + 16);
+  return w;
+}
+
+// Once per context, when the rows' lengths are known: how many iterations a launch takes, or that the kernels do not apply.
+// Waits for `st`.
+hipError_t finish_lists(lpc_ctx *c, hipStream_t st) {
+  const Shape s = shape_of(c);
+  int32_t longest = 0, *dev = reinterpret_cast<int32_t *>(c->s.li_state);
+  hipError_t e = launch_fill_u32(reinterpret_cast<uint32_t *>(dev), 0u, 1, st);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(longest_row_kernel, dim3((unsigned)(c->n < 256 * 1024 ? (c->n + 255) / 256 : 1024)), dim3(256), 0, st,
+                     c->prob.row_ptr, c->n, dev);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  e = hipMemcpyAsync(&longest, dev, sizeof(longest), hipMemcpyDeviceToHost, st);
+  if (e == hipSuccess) e = hipStreamSynchronize(st);
+  if (e != hipSuccess) return e;
+  if (longest < 1) longest = 1;
+  const int lc_bits = bits_for(s.S), pos_bits = c->cfg.B > 1 ? bits_for(c->cfg.B) : 1, k_bits = bits_for(longest);
+  c->list_pos_bits = pos_bits;
+  c->list_k_bits = k_bits;
+  c->list_cap = (int64_t)c->cfg.B * longest;
+  const int64_t lists = list_rows(c) / c->cfg.B;
+  const int64_t fit = (int64_t)lists_scratch(c).entries / (lists * c->list_cap);
+  c->list_iters = (int32_t)(fit < list_iters(c) ? fit : list_iters(c));
+  // four iterations per launch: with fewer the launches around them cost what the loop saves
+  c->lists_capable = lc_bits + pos_bits + k_bits <= 32 && lc_bits + pos_bits <= 30 &&
+                     c->list_iters >= (c->cfg.m < 4 ? c->cfg.m : 4);
+  return hipSuccess;
+}
+
+hipError_t launch_lists_begin(const lpc_ctx *c, const ResidentStep &rs, hipStream_t st) {
+  const Shape s = shape_of(c);
+  if ((1 << s.pshift) > c->usable_cus) return hipErrorCooperativeLaunchTooLarge;
+  hipError_t e = launch_csr_plan(c, rs.z_snap, rs.key, rs.alpc, st);
+  if (e != hipSuccess) return e;
+  if (!rs.z_snap) {
+    const int64_t rows = (int64_t)c->cfg.m * list_rows(c);
+    hipLaunchKernelGGL(plan_margins_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, st, c->prob.col_idx, c->prob.vals,
+                       rs.w_snap, rows, c->s.csr_plan);
+  }
+  const size_t slice = (size_t)s.S << s.pshift;
+  DealArgs a{};
+  a.d = (int32_t)c->d; a.S = s.S; a.pshift = s.pshift;
+  a.from[0] = rs.mu; a.from[1] = rs.w_snap; a.from[2] = rs.y; a.from[3] = rs.z;
+  for (int i = 0; i < 4; ++i) a.to[i] = c->s.li_state + i * slice;
+  hipLaunchKernelGGL(deal_kernel, dim3((unsigned)((s.S + 31) / 32), (1u << s.pshift) / 64, rs.alpc ? 4 : 2), dim3(256), 0, st, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_lists_epoch(const lpc_ctx *c, const ResidentStep &rs, int32_t t0, int32_t t1, double weight, hipStream_t st) {
+  const Shape s = shape_of(c);
+  const int P = 1 << s.pshift, nvec = c->cfg.N + (rs.alpc ? 1 : 0);
+  ListBuildArgs b{};
+  b.col_idx = c->prob.col_idx; b.vals = c->prob.vals; b.plan = c->s.csr_plan + (int64_t)t0 * nvec * c->cfg.B;
+  b.off = c->s.li_off; b.ent = reinterpret_cast<uint2 *>(c->s.li_ent); b.cols = c->s.li_cols;
+  b.n_cols = b.off + (size_t)list_iters(c) * nvec * (P + 1); b.cap = c->list_cap;
+  b.B = c->cfg.B; b.pshift = s.pshift; b.pos_bits = c->list_pos_bits; b.k_bits = c->list_k_bits;
+  b.map_words = (b.B + 31) / 32; b.loss = c->prob.loss;
+  const void *build = reinterpret_cast<const void *>(&list_build_kernel);
+  const int build_lds = 4 * (kKeyCap + kOwnBins * P * b.map_words);
+  hipError_t e = hipFuncSetAttribute(build, hipFuncAttributeMaxDynamicSharedMemorySize, build_lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(list_build_kernel, dim3((unsigned)((t1 - t0) * nvec)), dim3(kLiThreads), build_lds, st, b);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  ListArgs a{};
+  fill_method_args(a, c, rs, t0, t1, weight);
+  a.col_idx = b.col_idx; a.vals = b.vals; a.plan = b.plan; a.off = b.off; a.ent = b.ent; a.cols = b.cols; a.n_cols = b.n_cols; a.cap = b.cap;
+  const size_t slice = (size_t)s.S * P;
+  float *state = c->s.li_state;
+  a.mu = state; a.ws = state + slice; a.y = state + 2 * slice; a.z = state + 3 * slice; a.x = state + 4 * slice;
+  a.ysum = state + 5 * slice;
+  const ListScratch w = lists_scratch(c);
+  a.xw = c->s.cl_msg; a.slope = a.xw + w.xw; a.stat = a.slope + w.slope;
+  a.stat2 = a.stat + 2 * (size_t)c->cfg.N * 5 * P;
+  a.S = s.S; a.pshift = s.pshift; a.fields = s.fields; a.words = s.words;
+  const bool plain = c->cfg.clip_mode == LPC_CLIP_LAMBDA && c->cfg.scheme == LPC_SCHEME_A;
+  const void *fn = rs.alpc ? (plain ? reinterpret_cast<const void *>(&list_epoch_kernel<true, true>)
+                                    : reinterpret_cast<const void *>(&list_epoch_kernel<true, false>))
+                           : (plain ? reinterpret_cast<const void *>(&list_epoch_kernel<false, true>)
+                                    : reinterpret_cast<const void *>(&list_epoch_kernel<false, false>));
+  e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)s.lds);
+  if (e != hipSuccess) return e;
+  void *args[] = {&a};
+  return hipLaunchCooperativeKernel(fn, dim3((unsigned)P), dim3(kLiThreads), args, (unsigned)s.lds, st);
+}
+
+// The next snapshot and Alg. 2's vectors, unless a launch of the epoch gave up
+hipError_t launch_lists_commit(const lpc_ctx *c, const ResidentStep &rs, double snap_scale, float *w_snap, hipStream_t st) {
+  const Shape s = shape_of(c);
+  const size_t slice = (size_t)s.S << s.pshift;
+  float *state = c->s.li_state;
+  DealArgs a{};
+  a.d = (int32_t)c->d; a.S = s.S; a.pshift = s.pshift; a.back = 1; a.ctl = c->s.cl_ctl; a.launch_tag = rs.tag0 + 1u;
+  a.from[0] = state + (rs.alpc ? 5 : 4) * slice; a.to[0] = w_snap; a.scale[0] = rs.alpc ? (float)snap_scale : 1.0f;
+  a.from[1] = state + 2 * slice; a.to[1] = rs.y; a.scale[1] = 1.0f;
+  a.from[2] = state + 3 * slice; a.to[2] = rs.z; a.scale[2] = 1.0f;
+  hipLaunchKernelGGL(deal_kernel, dim3((unsigned)((s.S + 31) / 32), (1u << s.pshift) / 64, rs.alpc ? 3 : 1), dim3(256), 0, st, a);
+  return hipGetLastError();
+}
+
+}  // namespace lpc

@@ -232,3 +232,101 @@ def test_sparse_inner_iteration_of_alpc_svrg(algo, scheme, bits, clip_mode, clip
         assert diff.max() <= 0.05 * scale
     for a, b in zip(runs[0][:3], runs[1][:3]):
         assert np.array_equal(a, b)
+
+
+def _csr_problem(d, N, B, rows, seed=3):
+    """Logistic regression on 2000 unit rows; rows(rng, r) gives row r's columns."""
+    sp = lpc_synth.make("c3", n=2000, d=d, nnz_mean=4, N=N, B=B)
+    rng = np.random.default_rng(seed)
+    cols = [np.sort(np.asarray(rows(rng, r), dtype=np.int32)) for r in range(sp.n)]
+    rp = np.zeros(sp.n + 1, dtype=np.int32)
+    np.cumsum([c.size for c in cols], out=rp[1:])
+    vals = [rng.standard_normal(c.size) / max(1.0, np.sqrt(c.size)) for c in cols]
+    sp.csr = (rp, np.concatenate(cols).astype(np.int32), np.concatenate(vals).astype(np.float32))
+    sp.w0 = (0.1 * rng.standard_normal(d)).astype(np.float32)
+    return sp
+
+
+def _zipf(d, mean):
+    return lambda rng, r: np.unique(np.minimum(d - 1, (rng.pareto(0.7, 1 + r % (2 * mean)) * 2).astype(np.int64)))
+
+
+def _one_bin(rng, r):  # columns of one owner, a quarter of its own
+    return 5 + 256 * (4 + 4 * rng.choice(200, 16, replace=False))
+
+
+@pytest.mark.parametrize("d,N,B,rows,over", [
+    (1, 2, 3, lambda rng, r: [0], {}),                                             # one column, 255 owners without any
+    (200, 1, 1, _zipf(200, 4), dict(bits=5)),
+    (257, 16, 33, _zipf(257, 10), dict(bits=16, scheme=lpco.SCHEME_C)),
+    (1000, 16, 40, _zipf(1000, 8), dict(algo=lpco.ALGO_ALPC_GC, bits=3)),          # seventeen lists, sixteen wavefronts
+    (4096, 5, 20, _zipf(4096, 300), {}),                                           # rows past 64 entries
+    (5000, 4, 50, lambda rng, r: [] if r % 3 else _zipf(5000, 9)(rng, r), dict(bits=4, clip_mode=1, clip=2.0)),  # empty rows
+    (5001, 3, 512, lambda rng, r: list(range(10)) + [10 + r], dict(bits=4)),       # lists past five chunks
+    (5003, 3, 200, lambda rng, r: rng.integers(0, 40, 30), dict(bits=6)),          # a row holds a column several times
+    (60000, 2, 512, lambda rng, r: rng.choice(60000, 60, replace=False), {}),      # more keys than the builder holds at once
+    (262144, 2, 512, _one_bin, dict(m=2)),                                         # ... in one bin; lists past 128 columns
+    (3000, 2, 4, _zipf(3000, 20), dict(m=131, n_full=700)),                        # a second launch; margins taken by the plan
+    (3000, 15, 64, _zipf(3000, 20), dict(algo=lpco.ALGO_ALPC_SC, scheme=lpco.SCHEME_B, bits=4)),
+    (2999, 7, 9, _zipf(2999, 6), dict(algo=lpco.ALGO_ALPC_GC, scheme=lpco.SCHEME_C, bits=7, n_full=900, clip_mode=1, clip=1.0))])
+def test_csr_epochs_in_one_launch(d, N, B, rows, over):
+    """Workgroups by columns, lists of the sampled entries: agreement with the oracle's dense arithmetic up to a few flipped
+    rounding decisions (a flip moves a coordinate by eta*delta/N), and the same bits run to run."""
+    sp = _csr_problem(d, N, B, rows)
+    over = dict(dict(m=6, L=0.5, eta=0.4, bits=2, sigma=1e-3, tau2=0.5), **over)
+    runs = []
+    for _ in range(2):
+        ctx = gpu_context(sp, **over)
+        vec = [to_dev(sp.w0) for _ in range(3)]
+        for s in range(2):
+            ctx.epoch(vec[0], s, vec[1], vec[2])
+        assert ctx.take_device_flags() == 0
+        runs.append([v.cpu().numpy() for v in vec])
+        ctx.close()
+    p, _k = oracle_problem(sp)
+    cfg = oracle_config(sp, **over)
+    want = [sp.w0.copy() for _ in range(3)]
+    for s in range(2):
+        lpco.epoch(p, cfg, want[0], s, want[1], want[2])
+    P = lpco.objective(p, want[0])
+    assert abs(lpco.objective(p, runs[0][0]) - P) <= 1e-4 * abs(P)
+    for got, again, w in zip(*runs, want):
+        assert np.array_equal(got, again)
+        diff, scale = np.abs(got - w), np.abs(w).max()
+        assert (diff > 1e-5 * scale).mean() <= max(2e-3, 2.0 / d) and diff.max() <= 0.05 * scale
+
+
+@pytest.mark.parametrize("over", [{}, dict(algo=lpco.ALGO_ALPC_GC, scheme=lpco.SCHEME_B)])
+def test_csr_epoch_that_gives_up_or_is_refused(over):
+    """The caller's vectors are the epoch's or what they were, whatever the waits are given; a launch that does not fit
+    takes the separate ones."""
+    from paper_1901_08924_amd import lpc
+    sp = _csr_problem(3000, 5, 64, _zipf(3000, 20))
+    ctx, form0 = (gpu_context(sp, **dict(dict(m=6, bits=4, L=0.5, eta=0.4, tau2=0.5), **over)) for _ in range(2))
+    form0.tune(lpc.TUNE_ITER_FORM, 0)
+
+    def epoch(c, spin=1 << 15):
+        c.tune(lpc.TUNE_SPIN_LIMIT, spin)
+        vec = [to_dev(sp.w0) for _ in range(3)]
+        c.profile_enable(True)
+        c.epoch(vec[0], 1, vec[1], vec[2])
+        c.profile_enable(False)
+        one_launch = c.profile_read()["vr_rows"][1] == 0
+        return np.stack([v.cpu().numpy() for v in vec]), c.take_device_flags(), one_launch
+
+    want, flags, one_launch = epoch(ctx)
+    separate, flags_s, one_launch_s = epoch(form0)
+    assert flags == flags_s == 0 and one_launch and not one_launch_s
+    assert np.abs(want - separate).max() <= 1e-3
+    for spin in (0, 1, 2, 4):
+        got, flags, _ = epoch(ctx, spin)
+        assert np.array_equal(got, want if flags == 0 else np.stack([sp.w0] * 3))
+        assert flags == lpc.EDEVICE or (flags == 0 and spin > 0)
+    ctx.tune(lpc.TUNE_COMPUTE_UNITS, 255)
+    got, flags, one_launch = epoch(ctx)
+    assert flags == 0 and not one_launch and np.array_equal(got, separate)
+    ctx.tune(lpc.TUNE_COMPUTE_UNITS, 256)
+    got, flags, one_launch = epoch(ctx)
+    assert flags == 0 and one_launch and np.array_equal(got, want)
+    ctx.close()
+    form0.close()
