@@ -23,7 +23,7 @@
 // Four kernels share the epilogue's options:
 //   gemm_tile_kernel: 128 x TN tiles of C through LDS, for products with enough tiles to occupy the chip;
 //   gemm_pair_kernel: the 128 x 128 tile by eight wavefronts, where there is about one tile per compute unit;
-//   gemm_small_kernel: 32 x 32 or 64 x 64 tiles whose wavefronts split K between them, for the others;
+//   gemm_small_kernel: 32 x 32 or 64 x 64 tiles whose sixteen or eight wavefronts split K between them, for the others;
 //   gemm_few_kernel: sums of one or two products.
 // Operands may be given transposed (weight gradients A'D and data gradients D W' need it) and the K range may consist
 // of two segments with their own base pointers (the difference of two weight gradients is one contraction over stacked
@@ -610,13 +610,17 @@ __global__ __launch_bounds__(512, 1) void gemm_pair_kernel(GemmArgs g) {
 // The small kernel.  A workgroup owns a T x T tile of C (T = 32 or 64) and its NW wavefronts take the 16-deep steps of
 // K (of both segments) in turn, each straight from memory into the operand layout of the matrix instruction (lane l: row
 // or column l % 32, k 8*(l / 32) .. +7), DEPTH steps ahead; the NW partial tiles are added in wavefront order through LDS.
-// For products with too few tiles to occupy the chip, whose K loop would be a chain of trips to memory: 300 x 391 x
-// 777 12 us (64 us in 128 x 64 tiles on the fp32 instructions), 777 x 391 x 5003 transposed 59 us (588 us).
+// For products with too few tiles to occupy the chip, whose K loop would be a chain of trips to memory.  A 32 x 32 tile has
+// sixteen wavefronts, a workgroup per CU or two: with four of them a SIMD had one, which waited for its loads by itself, and a
+// wavefront whose steps ran out asked for its last one again, a line per lane.  What the stores need besides the sum (bias, mask,
+// the old C) is requested before the first step.  Epochs, us, four wavefronts -> eight -> sixteen: 777-391-129-33 (N = 6, B =
+// 50) 3241 -> 2959 -> 2730; 944-76-94-10 (N = 3, B = 80) 2314 -> - -> 1874; 256-64-576-2 (N = 6, B = 48) 1084 -> - -> 845; 2 to 26 %
+// less on 22 drawn nets.  (Eight or four wavefronts where K has no more steps gave nothing.)
 // FAR: operands whose rows are too far apart for fetch8.
 template <bool TA, bool TB, int T, int NW, bool FAR = false>
 __global__ __launch_bounds__(64 * NW) void gemm_small_kernel(GemmArgs g) {
   touch_kernel_arguments<(int)(sizeof(GemmArgs))>();
-  constexpr int I = T / 32, DEPTH = T == 32 ? 4 : 2;
+  constexpr int I = T / 32, DEPTH = T == 32 && NW < 16 ? 4 : 2;
   __shared__ float part[NW][32][32];  // one 32 x 32 part of the tile at a time
   __shared__ double red[4 * NW];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -633,7 +637,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_small_kernel(GemmArgs g) {
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
   float ra[DEPTH][I][8], rb[DEPTH][I][8];
   auto fetch = [&](int at, float (&a)[I][8], float (&b)[I][8]) {
-    at = at < total ? at : total - 1;  // past the end: a repeated load that nobody uses
+    if (at >= total) return;           // uniform
     const bool first = at < steps;     // no indexing of the argument arrays by a run-time value
     const int k0 = (first ? at : at - steps) * 16;
     const float *A = (first ? g.A[0] : g.A[1]) + bz * (first ? g.strideA[0] : g.strideA[1]);
@@ -650,6 +654,27 @@ __global__ __launch_bounds__(64 * NW) void gemm_small_kernel(GemmArgs g) {
       }
     }
   };
+  // what the stores will need, requested first: element c of part (i, j) of the tile is row 32 i + e / 32, column 32 j + e % 32,
+  // e = 64 NW c + tid
+  constexpr int kEach = 1024 / (64 * NW);
+  float bias[I * I * kEach], mask[I * I * kEach], old[I * I * kEach];
+  if constexpr (!FAR) {
+    const int rows = g.M - m0 < T ? g.M - m0 : T;
+    const uint32_t ldc4 = (uint32_t)g.ldc * 4u, bytes = (uint32_t)(rows - 1) * ldc4 + (uint32_t)(g.N - n0) * 4u;
+    const int64_t at = bz * g.strideC + (int64_t)m0 * g.ldc + n0;
+    auto request = [&](const float *p, uint32_t size, bool wide, float (&r)[I * I * kEach]) {
+      const __amdgpu_buffer_rsrc_t rs = buffer_of(p, size);
+#pragma unroll
+      for (int k = 0; k < I * I * kEach; ++k) {
+        const int e = (k % kEach) * 64 * NW + tid, row = 32 * (k / kEach / I) + (e >> 5), col = 32 * (k / kEach % I) + (e & 31);
+        const uint32_t off = (wide ? (uint32_t)row * ldc4 : 0u) + (uint32_t)col * 4u;
+        r[k] = buffer_float(rs, m0 + row < g.M && n0 + col < g.N ? off : kOutside);
+      }
+    };
+    if (g.bias) request(g.bias + bz * g.strideBias + n0, (uint32_t)(g.N - n0) * 4u, false, bias);
+    if (g.relu_mask) request(g.relu_mask + at, bytes, true, mask);
+    if (g.accumulate) request(g.C + at, bytes, true, old);
+  }
 #pragma unroll
   for (int d = 0; d < DEPTH; ++d) fetch(wave + d * NW, ra[d], rb[d]);
   for (int at = wave; at < total; at += DEPTH * NW) {
@@ -674,15 +699,13 @@ __global__ __launch_bounds__(64 * NW) void gemm_small_kernel(GemmArgs g) {
   }
   float fmx = 0.0f;
   double ssum = 0.0, ssq = 0.0, sbad = 0.0;
-  auto store = [&](int row, int col, float sum) {
-    const float val = skinny_store(g, g.C + bz * g.strideC, bz, row, col, sum);
+  auto count = [&](float val) {
     if (isfinite(val)) {
       fmx = fmaxf(fmx, fabsf(val)); ssum += (double)val; ssq += (double)val * (double)val;
     } else {
       sbad += 1.0;
     }
   };
-  constexpr int kEach = 1024 / (64 * NW);  // elements of a 32 x 32 part per thread
   uint32_t again = 0u;                     // those that came out as NaN
 #pragma unroll
   for (int i = 0; i < I; ++i) {
@@ -699,8 +722,20 @@ __global__ __launch_bounds__(64 * NW) void gemm_small_kernel(GemmArgs g) {
 #pragma unroll
         for (int w = 1; w < NW; ++w) t += part[w][e >> 5][e & 31];
         if (row < g.M && col < g.N) {
-          if (t == t) store(row, col, t);
-          else again |= 1u << ((i * I + j) * kEach + c);
+          if (t == t) {
+            float val;
+            if constexpr (FAR) {
+              val = skinny_store(g, g.C + bz * g.strideC, bz, row, col, t);
+            } else {
+              const int k = (i * I + j) * kEach + c;
+              val = g.alpha * t + (g.bias ? bias[k] : 0.0f);
+              if (g.relu) val = relu(val);
+              if (g.relu_mask) val = mask[k] > 0.0f ? val : 0.0f;
+              if (g.accumulate) val += old[k];
+              g.C[bz * g.strideC + (int64_t)row * g.ldc + col] = val;
+            }
+            count(val);
+          } else again |= 1u << ((i * I + j) * kEach + c);
         }
       }
     }
@@ -708,7 +743,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_small_kernel(GemmArgs g) {
   for (; again; again &= again - 1u) {  // see store_tile
     const int b = __builtin_ctz(again), ij = b / kEach, e = (b % kEach) * 64 * NW + tid;
     const int row = m0 + 32 * (ij / I) + (e >> 5), col = n0 + 32 * (ij % I) + (e & 31);
-    store(row, col, plain_sum<TA, TB>(g, bz, row, col));
+    count(skinny_store(g, g.C + bz * g.strideC, bz, row, col, plain_sum<TA, TB>(g, bz, row, col)));
   }
   if (g.stat_part)  // uniform
     tile_statistics<NW>(g, red, tid, bz, (int64_t)blockIdx.y * gridDim.x + blockIdx.x, fmx, ssum, ssq, sbad);
@@ -745,8 +780,8 @@ __global__ __launch_bounds__(256) void gemm_few_kernel(GemmArgs g) {
 // pass takes the sizes of all workers' rows, also where a call computes one of them (each kernel adds in an order of its own):
 // one worker of 16 of the 3072-1024-1024-10 net, B = 128, takes 265 us so, 137 us with kernels chosen for it alone; all 16
 // 472 us.
-// Single products on one MI355X, us (128 x 128 tile / 128 x 64 / 128 x 128 by eight wavefronts / 32 x 32 by four / 64 x
-// 64 by eight; tiles of 128 x 128 in brackets), which the lines below are drawn from:
+// Single products on one MI355X, us (128 x 128 tile / 128 x 64 / 128 x 128 by eight wavefronts / 32 x 32 by four, as it was / 64
+// x 64 by eight; tiles of 128 x 128 in brackets), which the lines below are drawn from:
 //   4096 x 4096 x 4096 [1024]     691 / 787 / 702 / 2540 / -       many tiles per CU: they cover each other
 //   4096 x 1024 x 1024 [256]       69 /  60 /  51 /  149 / 97      about one tile per CU: eight wavefronts on it
 //   8192 x  640 x   64 [320]     10.5 / 9.8 /  16 /   24 / 25      a short K: what surrounds the loop counts
@@ -760,7 +795,9 @@ __global__ __launch_bounds__(256) void gemm_few_kernel(GemmArgs g) {
 // 1.14 times the best kernel's time on average, and up to six times where K is at most 160, A not transposed and fewer than
 // 100 tiles of 128 x 128 (1024 x 768 x 64 B' [48]: 6.5 / 5.2 / 6.8 / 32 / 21), or 1.4 times from 257 to 639 tiles (5120 x 1024 x
 // 200 [320]: 26 / 23 / 32).  Lines drawn from all of those made epochs of 24 nets 0.88 to 1.07 times as long, 0.99 on average
-// (operands that the launch before wrote are not where a repeated product finds its own): the coarse ones stayed.
+// (operands that the launch before wrote are not where a repeated product finds its own): the coarse ones stayed.  With sixteen
+// wavefronts on a 32 x 32 tile: 64 x 64 tiles from 200 or 400 on instead of 100 made epochs of 16 nets 0.2 and 2.8 % longer, the
+// tile kernel from 100 tiles of 128 x 64 on (K up to 256) 2.8 % shorter, but its sums are less exact: not taken.
 struct Plan {
   int tile_m, tile_n;
   int waves;  // 0: the tile kernel, 1: its eight-wavefront form, 2: few products, else the small kernel with that many
@@ -772,6 +809,7 @@ Plan plan_of(const GemmArgs &g) {
     return (int64_t)((rows + tm - 1) / tm) * ((g.N + tn - 1) / tn) * batch;
   };
   if ((int64_t)g.K * g.nseg <= kFewProducts) return {32, 32, 2};
+  if (g.ldc >= (1 << 22)) return {32, 32, 4, true};
   for (int s = 0; s < g.nseg; ++s)
     if (g.lda[s] >= (1 << 22) || g.ldb[s] >= (1 << 22)) return {32, 32, 4, true};
   const int64_t k = (int64_t)g.K * g.nseg, t128 = tiles(128, 128), t64 = tiles(64, 64);
@@ -779,7 +817,7 @@ Plan plan_of(const GemmArgs &g) {
   if (k <= 160 && tiles(128, 64) >= 200) return {128, 64, 0};
   if (t128 >= 150 || (t128 >= 60 && k <= 640 && !g.transA && g.transB)) return {128, 128, 1};
   if (k > 160 && t64 >= 100) return {64, 64, 8};
-  return {32, 32, 4};
+  return {32, 32, 16};
 }
 
 // ---- outputs with at most 16 columns (the last layer of the MLP) -------------------------------------
@@ -1075,7 +1113,7 @@ hipError_t launch_gemm(const GemmArgs &g, hipStream_t st) {
     else if (p.waves == 0) LPC_GEMM_TILE(gemm_tile_kernel, 256, TA_, TB_, 64);                                \
     else if (p.waves == 1) LPC_GEMM_TILE(gemm_pair_kernel, 512, TA_, TB_);                                    \
     else if (p.tile_m == 64) LPC_GEMM_SMALL(TA_, TB_, 64, 8);                                                 \
-    else LPC_GEMM_SMALL(TA_, TB_, 32, 4);                                                                     \
+    else LPC_GEMM_SMALL(TA_, TB_, 32, 16);                                                                    \
   } while (0)
   if (!g.transA && !g.transB) LPC_GEMM_LAUNCH(false, false);
   else if (!g.transA && g.transB) LPC_GEMM_LAUNCH(false, true);

@@ -63,6 +63,32 @@ def test_products_are_no_less_exact_than_fp32_multiply_adds(M, N, K, tA, tB):
     assert np.linalg.norm(got - A @ B) <= np.linalg.norm(chain - A @ B)
 
 
+# 32 x 32 tiles by sixteen wavefronts with fewer, as many and more steps of K; 64 x 64 by eight; rows of C too far apart for
+# offsets within a tile
+@pytest.mark.parametrize("M,N,K,ldc", [(1, 3, 4, 3), (33, 31, 16, 40), (32, 33, 257, 33), (65, 64, 1030, 70), (640, 660, 161, 663),
+                                       (5, 7, 40, 1 << 22), (34, 2, 90, (1 << 22) - 1)])
+@pytest.mark.parametrize("relu,accumulate", [(0, 0), (1, 0), (0, 1), (1, 1)])
+def test_small_products_through_the_options_of_a_store(M, N, K, ldc, relu, accumulate):
+    import torch
+    from paper_1901_08924_amd import lpc
+    rng = np.random.default_rng(M + K)
+    A, B = rng.standard_normal((M, K), dtype=np.float32), rng.standard_normal((K, N), dtype=np.float32)
+    bias, C0 = rng.standard_normal(N, dtype=np.float32), rng.standard_normal((M, N), dtype=np.float32)
+    C = torch.full((M, ldc), 7.0, device="cuda")
+    C[:, :N] = to_dev(C0)
+    dA, dB, db = to_dev(A), to_dev(B), to_dev(bias)
+    rc = lpc.lib.lpc_debug_gemm(dA.data_ptr(), dB.data_ptr(), C.data_ptr(), M, N, K, K, N, ldc, 0, 0, 0.5, db.data_ptr(), relu,
+                                accumulate, torch.cuda.current_stream().cuda_stream)
+    assert rc == 0
+    want = 0.5 * (A.astype(np.float64) @ B.astype(np.float64)) + bias
+    want = (np.maximum(want, 0.0) if relu else want) + (C0 if accumulate else 0.0)
+    bound = 0.5 * np.abs(A).astype(np.float64) @ np.abs(B) + np.abs(bias) + np.abs(C0)
+    # the product as in the first test here, three more roundings
+    most = min((1.5 + 6 * ((K + 15) // 16 - 1)) * 2.0 ** -23, 1e-6) + 3 * 2.0 ** -24
+    assert (np.abs(C[:, :N].cpu().numpy() - want) / bound).max() <= most
+    assert bool((C[:, N:] == 7.0).all())
+
+
 @pytest.mark.parametrize("M,N,K", GEMMS[1:])
 @pytest.mark.parametrize("tA,tB", [(0, 0), (0, 1), (1, 0), (1, 1)])
 def test_products_of_infinite_and_of_the_largest_numbers(M, N, K, tA, tB):
