@@ -201,7 +201,7 @@ size_t layout(lpc_ctx *c, char *base) {
     const ListScratch li = lists_scratch(c);
     s.li_off = (uint32_t *)take(li.off * sizeof(uint32_t));
     s.li_ent = (unsigned long long *)take(li.entries * sizeof(unsigned long long));
-    s.li_cols = (uint32_t *)take(li.entries * sizeof(uint32_t));
+    s.li_cols = (uint32_t *)take(2 * li.entries * sizeof(uint32_t));
     s.li_state = (float *)take(li.state * sizeof(float));
   }
   if (c->mlp) {

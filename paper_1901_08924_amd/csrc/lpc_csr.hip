@@ -857,6 +857,7 @@ hipError_t launch_csr_vr_grad(const lpc_ctx *c, const float *w, const float *w_s
 // workgroups per worker of the sparse worker pass: one round of rows each
 // (measured on n = d = 2^20, N = 16, B = 256: two rounds per workgroup, hence three planes per worker instead of
 // five, make this pass 7 us slower and the statistics pass 3.4 us faster)
+int csr_sparse_block() { return kRowGroups; }
 int csr_sparse_parts(int32_t B) { return (B + kRowGroups - 1) / kRowGroups; }
 
 // Leading columns the sparse inner iteration treats densely.  Twice the snapshot pass's head when d is large: the

@@ -152,7 +152,7 @@ struct Scratch {
   // lpc_lists.hip (its words lie from cl_msg on)
   uint32_t *li_off;           // lists of a launch's iterations: bounds, entries (pairs of words)
   unsigned long long *li_ent;
-  uint32_t *li_cols;          // ... columns
+  uint32_t *li_cols;          // ... columns, pieces
   float *li_state;            // ... and the problem's vectors in the owners' order
   float *cl_y, *cl_z;   // [d] each: Alg. 2's y and z between the launches of such a loop, or until it is through
   unsigned long long *iter_slots;  // two sets of [tiles][N][4] statistics exchanged between the workgroups of the
@@ -330,6 +330,7 @@ hipError_t build_csc_tail(lpc_ctx *c, hipStream_t st);
 hipError_t launch_csr_full_grad(const lpc_ctx *c, const float *w, float *mu, float *z, bool want_loss, int64_t n_rows,
                                 hipStream_t st);
 int csr_sparse_parts(int32_t B);
+int csr_sparse_block();  // batch positions of a part
 int csr_sparse_head_columns(int64_t d);
 // plus_shared: every iteration's plan holds one more vector, the shared batch J of Alg. 2 (N+1 vectors of B rows)
 hipError_t launch_csr_plan(const lpc_ctx *c, const float *z_snap, StreamKey key0, bool plus_shared, hipStream_t st);

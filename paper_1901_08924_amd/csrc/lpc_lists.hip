@@ -11,9 +11,11 @@
 //      factors.
 // The draws do not depend on the iterates, so what an owner has to add up is known ahead: list_build_kernel leaves, for every
 // iteration, vector and owner, the sampled entries with their columns together and in batch-position order.  Wavefront i
-// of an owner takes vector i's list: slope times value, a segmented sum (one fixed order, so epochs repeat bit for bit),
-// eq. (3), rules (1) and (2); the codes meet in LDS, a field per vector and column, and a lane per touched column takes
-// eq. (4) and the update.
+// of an owner takes vector i's list: slope times value, sums, eq. (3), rules (1) and (2); the codes meet in LDS, a field per
+// vector and column, and a lane per touched column takes eq. (4) and the update.
+// Margins and sums are added up in the order of the separate launches (a column's entries in blocks of batch positions, the
+// blocks in order: a list is cut in pieces of one column and block), so an epoch's bits do not depend on the route.  A
+// segmented scan over the lanes would be 0.9 us per iteration less (16 vectors), and another rounding now and then.
 // Neighbouring columns belong to different owners because text-like data has its frequent columns side by side.
 // Reuse of words: a column's x word is kept once, written again when its owner has the slopes of every row that holds the
 // column, hence after those rows' wavefronts read it.  Slopes and statistics have two sets: set t is written again at t + 2 by
@@ -23,7 +25,7 @@
 //
 // Bound by the four trips of words (store to load about 1.2 us each) and by the owner of the most frequent column, whose lists
 // are six times as long as the others'.  Measured on MI355X, separate launches -> these kernels, us per iteration, the lists
-// (2.6 there) included: n = d = 2^20, N = 16, B = 256, b = 2: 35.5 -> 12.3; d = 150001, N = 8 + J, B = 100, b = 4: 30.6 -> 11.0.
+// (3.0 there) included: n = d = 2^20, N = 16, B = 256, b = 2: 35.5 -> 13.4; d = 150001, N = 8 + J, B = 100, b = 4: 30.6 -> 11.8.
 // Steps that paid, us per iteration of the first: registers loaded ahead without a join that waits for them and waits for
 // them before the next store, not behind it, together with priority for rows and sums over what only fills the waits, 1.0;
 // columns found by the builder instead of here and words stored as soon as they are known, 1.9; half of the trips' time went
@@ -61,11 +63,12 @@ struct ListBuildArgs {
   const float *vals;
   RowPlan *plan;        // of the first iteration of the launch; its margins become slopes
   uint32_t *off;        // [iterations][nvec][P + 1]
-  uint2 *ent;           // [iterations][nvec][cap]: batch position (kLast: its column's last entry), value
+  uint2 *ent;           // [iterations][nvec][cap]: batch position, value
   uint32_t *cols;       // [iterations][nvec][cap]: a list's columns lc + 1, from its first entry's place on
-  uint32_t *n_cols;     // [iterations][nvec][P]
+  uint32_t *pieces;     // [iterations][nvec][cap]: likewise the first entries of its pieces (kLast: its column's last one)
+  uint32_t *n_cols;     // [iterations][nvec][P][2]: how many of both
   int64_t cap;
-  int32_t B, pshift, pos_bits, k_bits, map_words, loss;
+  int32_t B, pshift, pos_bits, k_bits, map_words, loss, block;
 };
 
 __device__ __forceinline__ uint32_t list_bin(uint32_t c, int pshift) {
@@ -239,9 +242,10 @@ __global__ __launch_bounds__(kLiThreads, 8) void list_build_kernel(ListBuildArgs
     __syncthreads();
     b0 = b1;
   }
-  // ---- the lists' columns, a wavefront a list at a time
+  // ---- the lists' columns and pieces, a wavefront a list at a time
   const int P = 1 << a.pshift;
-  uint32_t *cols = a.cols + (int64_t)blockIdx.x * a.cap;
+  uint32_t *cols = a.cols + (int64_t)blockIdx.x * a.cap, *pieces = a.pieces + (int64_t)blockIdx.x * a.cap;
+  const uint32_t per_block = a.block < a.B ? 65536u / (uint32_t)a.block + 1u : 0u;  // pos / block = pos * this >> 16, pos < 512
   for (int p0 = wave; p0 < P; p0 += 2 * kLiWaves) {
     uint32_t first[2], end[2];
     uint2 e[2];
@@ -255,44 +259,58 @@ __global__ __launch_bounds__(kLiThreads, 8) void list_build_kernel(ListBuildArgs
     }
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
-      uint32_t n = 0, before = kNoEntry;
+      // of an entry: column and block of batch positions
+      auto place_of = [&](uint32_t x) {
+        return (x >> a.pos_bits) << 4 | ((x & ((1u << a.pos_bits) - 1u)) * per_block) >> 16;
+      };
+      uint32_t n = 0, m = 0, before = kNoEntry, open = 0;  // open: where the last piece so far begins
       for (uint32_t i = first[q]; i < end[q]; i += 64) {
         if (i != first[q]) {
           e[q].x = kNoEntry;
           if (i + lane < end[q]) e[q] = out[i + lane];
         }
         const bool in = i + lane < end[q];
-        const uint32_t lc = in ? e[q].x >> a.pos_bits : kNoEntry - 1u;
-        const uint32_t prev = (uint32_t)__builtin_amdgcn_update_dpp((int)before, (int)lc, 0x138, 0xF, 0xF, false);  // wave_shr:1
-        const uint64_t heads = __ballot(lc != prev && in);
-        // behind the chunk: another column, or the list's end
-        const uint32_t next = i + 64 < end[q] ? (uint32_t)__builtin_amdgcn_readfirstlane((int)(out[i + 64].x >> a.pos_bits)) : kNoEntry;
-        const uint32_t after = (uint32_t)__builtin_amdgcn_update_dpp((int)next, (int)lc, 0x130, 0xF, 0xF, false);   // wave_shl:1
-        before = read_lane(lc, 63);
+        const uint32_t at = in ? place_of(e[q].x) : kNoEntry - 16u;
+        const uint32_t prev = (uint32_t)__builtin_amdgcn_update_dpp((int)before, (int)at, 0x138, 0xF, 0xF, false);  // wave_shr:1
+        before = read_lane(at, 63);
+        const uint64_t columns = __ballot(at >> 4 != prev >> 4 && in), heads = __ballot(at != prev && in);
+        const uint64_t below = (1ull << lane) - 1ull;
         if (in) {
-          out[i + lane].x = (e[q].x & ((1u << a.pos_bits) - 1u)) | (lc != after ? kLast : 0u);
-          if ((heads >> lane) & 1ull) cols[first[q] + n + __popcll(heads & ((1ull << lane) - 1ull))] = lc + 1u;
+          out[i + lane].x = e[q].x & ((1u << a.pos_bits) - 1u);
+          if ((columns >> lane) & 1ull) cols[first[q] + n + __popcll(columns & below)] = (at >> 4) + 1u;
+          if ((heads >> lane) & 1ull) {
+            // the column's last piece: the next piece begins a column, or there is none (this chunk's last one: see below)
+            const uint64_t above = heads & ~below & ~(1ull << lane);
+            const bool last = above != 0ull && ((columns >> __builtin_ctzll(above)) & 1ull);
+            pieces[first[q] + m + __popcll(heads & below)] = i - first[q] + lane | (last ? kLast : 0u);
+          }
         }
-        n += (uint32_t)__popcll(heads);
+        if (heads != 0ull) {
+          if (m != 0u && lane == 0 && ((columns >> __builtin_ctzll(heads)) & 1ull)) pieces[first[q] + m - 1u] = open | kLast;
+          open = i - first[q] + 63u - (uint32_t)__builtin_clzll(heads);
+        }
+        n += (uint32_t)__popcll(columns);
+        m += (uint32_t)__popcll(heads);
       }
+      if (m != 0u && lane == 0) pieces[first[q] + m - 1u] = open | kLast;
       const int p = p0 + q * kLiWaves;
-      if (p < P && lane == 0) a.n_cols[(int64_t)blockIdx.x * P + p] = n;
+      if (p < P && lane < 2) a.n_cols[((int64_t)blockIdx.x * P + p) * 2 + lane] = lane == 0 ? n : m;
     }
   }
 }
 
-// Snapshot margins of the planned rows where the snapshot pass did not visit every row: a wavefront per row.
+// Snapshot margins of the planned rows where the snapshot pass did not visit every row: sixteen lanes per row, in the order
+// of the worker pass (lpc_csr.hip).
 __global__ __launch_bounds__(256) void plan_margins_kernel(const int32_t *__restrict__ col_idx, const float *__restrict__ vals,
                                                            const float *__restrict__ w_snap, int64_t rows,
                                                            RowPlan *__restrict__ plan) {
-  const int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  if (r >= rows) return;
+  const int64_t r = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4);
+  if (r >= rows) return;  // whole rows of sixteen lanes
   const RowPlan p = plan[r];
   float s = 0.0f;
-  for (int32_t e = p.lo + lane; e < p.hi; e += 64) s = __builtin_fmaf(vals[e], w_snap[col_idx[e]], s);
-  s = wave_sum(s);
-  if (lane == 0) plan[r].z = s;
+  for (int32_t e = p.lo + (int32_t)(threadIdx.x & 15); e < p.hi; e += 16) s = __builtin_fmaf(vals[e], w_snap[col_idx[e]], s);
+  s = row16_sum(s);
+  if ((threadIdx.x & 15) == 0) plan[r].z = s;
 }
 
 __global__ __launch_bounds__(256) void longest_row_kernel(const int32_t *__restrict__ row_ptr, int64_t n,
@@ -356,13 +374,14 @@ struct ListArgs {
   const uint32_t *off;     // of this launch
   uint2 *ent;
   const uint32_t *cols, *n_cols;
+  uint32_t *pieces;
   int64_t cap;
   const float *mu, *ws;    // the owners' order, here and below
   float *x, *y, *z, *ysum;
   // [P][S]; [2][nvec * B]; [2][N][5][P]; [2][N][dies][kLine]
   u64 *xw, *slope, *stat, *stat2;
   uint32_t *flags, *ctl;
-  int32_t d, S, pshift, N, nvec, B, it0, it1, bits, fields, words, scheme, loss;
+  int32_t d, S, pshift, block, N, nvec, B, it0, it1, bits, fields, words, scheme, loss;
   uint32_t tag0, spin_limit;
   QuantSpec qs;
   StreamKey key;
@@ -370,25 +389,6 @@ struct ListArgs {
   float step_y, thr_y, shrink_y, alpha, thr_z, shrink_z, t1, t2, t3;
   double theta, weight;
 };
-
-// Inclusive sums over the runs of lanes that `heads` begins, one fixed order; the first run goes on from `carry`.
-__device__ __forceinline__ float run_sums(float v, uint64_t heads, float carry, int lane) {
-  if (lane == 0) v += carry;
-  const uint64_t upto = (heads | 1ull) & (~0ull >> (63 - lane));
-  const int dist = lane - (63 - __builtin_clzll(upto));  // lanes of the run below this one
-  float t;
-  t = dpp_move<0x111>(v); v += dist >= 1 ? t : 0.0f;  // row_shr:1, 2, 4, 8
-  t = dpp_move<0x112>(v); v += dist >= 2 ? t : 0.0f;
-  t = dpp_move<0x114>(v); v += dist >= 4 ? t : 0.0f;
-  t = dpp_move<0x118>(v); v += dist >= 8 ? t : 0.0f;
-  // a row of 16 lanes takes what the row below ended with, then the upper half what the lower ended with
-  const float r0 = read_lane(v, 15), r2 = read_lane(v, 47);
-  const int row = lane >> 4;
-  v += ((row & 1) && dist > (lane & 15)) ? (row == 1 ? r0 : r2) : 0.0f;
-  const float half = read_lane(v, 31);
-  v += (lane >= 32 && dist > (lane & 31)) ? half : 0.0f;
-  return v;
-}
 
 // PLAIN: lambda clipping and scale factors of the workers' own (scheme (a)), the paper's way in all its experiments.
 // Everything that is requested ahead goes through buffers, whose lanes past the end read 0: a load under a condition is joined
@@ -399,7 +399,8 @@ __global__ __launch_bounds__(kLiThreads) void list_epoch_kernel(ListArgs a) {
   extern __shared__ __attribute__((aligned(16))) float lds[];
   __shared__ float delta_sh[kLiWaves];
   __shared__ uint32_t fail_sh[2], count[3], over_sh;
-  __shared__ uint32_t stage[kLiWaves][64 * kLiPairs];  // a wavefront's own: sums on their way to their columns' lanes
+  // a wavefront's own: products on their way to their pieces' lanes, then the pieces' sums to their columns'
+  __shared__ float stage[kLiWaves][64 * kLiChunks + 8];
   const int S = a.S;
   float *xs = lds, *mus = xs + S;
   float *zs = mus + S, *ysums = zs + (ALPC ? S : 0), *wss = ysums + (ALPC ? S : 0), *uhs = wss + (ALPC ? S : 0);
@@ -486,26 +487,30 @@ __global__ __launch_bounds__(kLiThreads) void list_epoch_kernel(ListArgs a) {
   // the shared batch's vector where the workers have all wavefronts
   const bool adds_shared = ALPC && a.N == kLiWaves && wave == 0;
   struct List {
-    int64_t at;    // its first entry
-    int32_t n;     // entries
-    int32_t cols;  // columns
+    int64_t at;      // its first entry
+    int32_t n;       // entries
+    int32_t cols;    // columns
+    int32_t pieces;  // runs of one column and one block of batch positions
   };
-  // lane l: the list's first entry, its end, its number of columns (l = 0, 1, 2)
+  // lane l: the list's first entry, its end, its number of columns, of pieces (l = 0 .. 3)
   auto bounds_of = [&](int t, int v) {
     const int64_t k = (int64_t)(t - a.it0) * a.nvec + v;
-    const uint32_t *from = lane == 2 ? a.n_cols + k * P + p : a.off + k * (P + 1) + p + (lane & 1);
-    return *from;
+    const uint32_t *from = lane & 2 ? a.n_cols + (k * P + p) * 2 : a.off + k * (P + 1) + p;
+    return from[lane & 1];
   };
   auto list_of = [&](int t, int v, uint32_t b) {
     const uint32_t first = read_lane(b, 0);
-    return List{((int64_t)(t - a.it0) * a.nvec + v) * a.cap + first, (int32_t)(read_lane(b, 1) - first), (int32_t)read_lane(b, 2)};
+    return List{((int64_t)(t - a.it0) * a.nvec + v) * a.cap + first, (int32_t)(read_lane(b, 1) - first), (int32_t)read_lane(b, 2),
+                (int32_t)read_lane(b, 3)};
   };
-  auto is_long = [&](const List &l) { return l.n > 64 * kLiChunks || l.cols > 64 * kLiPairs; };
+  auto is_long = [&](const List &l) { return l.n > 64 * kLiChunks || l.pieces > 64 * kLiPairs; };
   words2 ent[kLiChunks], ent_n[kLiChunks];
   uint32_t col[kLiPairs], col_n[kLiPairs];  // lc + 1; a lane without a column: 0
-  List list{0, 0, 0}, list_n{0, 0, 0};
+  // first entry and kLast, then (sized) the length from bit 12 on as well; a lane without a piece: 0
+  uint32_t piece[kLiPairs], piece_n[kLiPairs];
+  List list{0, 0, 0, 0}, list_n{0, 0, 0, 0};
   uint32_t bounds = 0;
-  auto fetch_list = [&](const List &l, words2 (&e)[kLiChunks], uint32_t (&c)[kLiPairs]) {
+  auto fetch_list = [&](const List &l, words2 (&e)[kLiChunks], uint32_t (&c)[kLiPairs], uint32_t (&f)[kLiPairs]) {
 #pragma unroll
     for (int r = 0; r < kLiChunks; ++r) {
       e[r] = words2{0u, 0u};
@@ -516,8 +521,29 @@ __global__ __launch_bounds__(kLiThreads) void list_epoch_kernel(ListArgs a) {
     for (int k = 0; k < kLiPairs; ++k) {
       c[k] = 0u;
       if (k * 64 < l.cols) c[k] = __builtin_amdgcn_raw_buffer_load_b32(buffer(a.cols + l.at, 4u * (uint32_t)l.cols), 4 * lane + 256 * k, 0, 0);
+      f[k] = 0u;
+      if (k * 64 < l.pieces)
+        f[k] = __builtin_amdgcn_raw_buffer_load_b32(buffer(a.pieces + l.at, 4u * (uint32_t)l.pieces), 4 * lane + 256 * k, 0, 0);
     }
   };
+  // the pieces' lengths, and the longest one (of a list that is not long: entries and lengths are below 2^12)
+  auto size_pieces = [&](const List &l, uint32_t (&f)[kLiPairs]) {
+    uint32_t longest = 0;
+#pragma unroll
+    for (int k = 0; k < kLiPairs; ++k) {
+      if (k * 64 < l.pieces) {
+        uint32_t next = (uint32_t)l.n;
+        if ((k + 1) * 64 < l.pieces) next = read_lane(f[k + 1 < kLiPairs ? k + 1 : k], 0) & ~kLast;
+        uint32_t after = (uint32_t)__builtin_amdgcn_update_dpp((int)next, (int)f[k], 0x130, 0xF, 0xF, false) & ~kLast;  // wave_shl:1
+        if (k * 64 + lane + 1 >= l.pieces) after = (uint32_t)l.n;
+        const uint32_t size = k * 64 + lane < l.pieces ? after - (f[k] & ~kLast) : 0u;
+        f[k] |= size << 12;
+        longest = size > longest ? size : longest;
+      }
+    }
+    return (int)wave_max((float)longest);
+  };
+  int longest = 0, longest_n = 0;
   // the coming iteration's touched columns, each once
   auto mark = [&](int t, uint32_t lc1) {
     bool first = false;
@@ -545,6 +571,10 @@ __global__ __launch_bounds__(kLiThreads) void list_epoch_kernel(ListArgs a) {
   auto put_x = [&](int t, uint32_t lc, float x) {  // the iterate where iteration t's rows look
     st_word(a.xw + (uint32_t)(p * S) + lc, __builtin_bit_cast(uint32_t, x), a.tag0 + (uint32_t)t + 1u);
   };
+  auto staged = [] {  // what the wavefront wrote to its stage is there, what it read has been read
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  };
   // The wait for all that has been requested ahead, before the next words are stored: a wait for a load behind a store is one
   // for the store to arrive as well.
   auto settle = [&] {
@@ -556,15 +586,16 @@ __global__ __launch_bounds__(kLiThreads) void list_epoch_kernel(ListArgs a) {
 #pragma unroll
     for (int r = 0; r < kLiChunks; ++r) asm volatile("" : "+v"(ent_n[r]));
 #pragma unroll
-    for (int k = 0; k < kLiPairs; ++k) asm volatile("" : "+v"(col_n[k]));
+    for (int k = 0; k < kLiPairs; ++k) asm volatile("" : "+v"(col_n[k]), "+v"(piece_n[k]));
     asm volatile("" : "+v"(bounds));
   };
   if (listed) {
     list_n = list_of(a.it0, wave, bounds_of(a.it0, wave));
     bounds = bounds_of(a.it0 + 1 < a.it1 ? a.it0 + 1 : a.it0, wave);
   }
-  fetch_list(list_n, ent_n, col_n);
+  fetch_list(list_n, ent_n, col_n, piece_n);
   if (listed) mark_list(a.it0, list_n, col_n);
+  if (!is_long(list_n)) longest_n = size_pieces(list_n, piece_n);
   if (adds_shared) mark_from(a.it0, list_of(a.it0, a.N, bounds_of(a.it0, a.N)), 0);
   fetch_rows(a.it0);
   fetch_pairs();
@@ -593,7 +624,8 @@ __global__ __launch_bounds__(kLiThreads) void list_epoch_kernel(ListArgs a) {
 #pragma unroll
     for (int r = 0; r < kLiChunks; ++r) ent[r] = ent_n[r];
 #pragma unroll
-    for (int k = 0; k < kLiPairs; ++k) col[k] = col_n[k];
+    for (int k = 0; k < kLiPairs; ++k) { col[k] = col_n[k]; piece[k] = piece_n[k]; }
+    longest = longest_n;
     // ---- 1. the rows' margins and slope differences
     __builtin_amdgcn_s_setprio(3);
     {
@@ -612,16 +644,33 @@ __global__ __launch_bounds__(kLiThreads) void list_epoch_kernel(ListArgs a) {
 #pragma unroll
       for (int q = 0; q < kLiRows; ++q) {
         if (!has_row[q]) continue;  // uniform
-        float s = __builtin_bit_cast(float, rv[q]) * __builtin_bit_cast(float, (uint32_t)xw[q]);  // lanes without an entry: 0 * 0
+        // Lane l < 16 adds the entries l, l + 16, ..., then the sixteen lanes, as the worker pass of lpc_csr.hip does: the margin of
+        // x~ is then the snapshot pass's, and an epoch's numbers are those of the separate launches.  (Lanes past the row's
+        // end: 0 * 0.)
+        float s = 0.0f;
+        auto add_rows = [&](uint32_t v, uint32_t x) {  // four entries per lane, of the four rows of sixteen lanes
+          const auto v1 = __builtin_amdgcn_permlane16_swap(v, v, false, false), x1 = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+          const auto v2 = __builtin_amdgcn_permlane32_swap(v, v, false, false), x2 = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+          const uint32_t va = v1[1], xa = x1[1];
+          const auto v3 = __builtin_amdgcn_permlane32_swap(va, va, false, false), x3 = __builtin_amdgcn_permlane32_swap(xa, xa, false, false);
+          const uint32_t vb = v2[1], xb = x2[1], vc = v3[1], xc = x3[1];
+          s = __builtin_fmaf(__builtin_bit_cast(float, v), __builtin_bit_cast(float, x), s);
+          s = __builtin_fmaf(__builtin_bit_cast(float, va), __builtin_bit_cast(float, xa), s);
+          s = __builtin_fmaf(__builtin_bit_cast(float, vb), __builtin_bit_cast(float, xb), s);
+          s = __builtin_fmaf(__builtin_bit_cast(float, vc), __builtin_bit_cast(float, xc), s);
+        };
+        add_rows(rv[q], (uint32_t)xw[q]);
         for (int32_t k = 64; k < len[q]; k += 64) {  // rows longer than 64 entries
           const int64_t e = (int32_t)row[q].x + (k + lane < len[q] ? k + lane : len[q] - 1);
           const uint32_t at = x_at((uint32_t)a.col_idx[e]);
           const float v = a.vals[e];
           u64 far = 0;
           poll(limit, ok, [&] { if (!there(far)) far = x_word(at); return there(far); });
-          s = k + lane < len[q] ? __builtin_fmaf(v, __builtin_bit_cast(float, (uint32_t)far), s) : s;
+          const bool in = k + lane < len[q];
+          add_rows(in ? __builtin_bit_cast(uint32_t, v) : 0u, in ? (uint32_t)far : 0u);
         }
-        const float z = wave_sum(s);
+        s = row16_sum(s);
+        const float z = read_lane(s, 0);
         // (x_0 of Alg. 1 is the snapshot: its differences are exactly zero; the builder left the snapshot's slope in row.z)
         const uint32_t label = row[q].z, snap = row[q].w;
         const float diff = loss_slope(a.loss, z, __builtin_bit_cast(float, label)) - __builtin_bit_cast(float, snap);
@@ -635,8 +684,8 @@ __global__ __launch_bounds__(kLiThreads) void list_epoch_kernel(ListArgs a) {
       const int t1 = more ? t + 1 : t;  // (the last one's own again, to no purpose)
       fetch_rows(t1);
       list_n = list_of(t1, wave, bounds);
-      if (!listed) list_n.n = list_n.cols = 0;
-      fetch_list(list_n, ent_n, col_n);
+      if (!listed) list_n.n = list_n.cols = list_n.pieces = 0;
+      fetch_list(list_n, ent_n, col_n, piece_n);
       bounds = bounds_of(t + 2 < a.it1 ? t + 2 : t1, listed ? wave : 0);
     }
     auto random_word = [&](uint32_t lc) {
@@ -654,28 +703,52 @@ __global__ __launch_bounds__(kLiThreads) void list_epoch_kernel(ListArgs a) {
       if (quantizes && k * 64 < list.cols) rnd[k] = random_word(col[k] - 1u);
     }
     // ---- 2. u^i at this workgroup's columns
-    // A list in memory: the k-th column's sum replaces the value of the list's k-th entry (which has been taken by then).
+    // Sums over the pieces of a column, piece after piece, at its last one (chunk of 64 pieces; `open`: the sum of the pieces of
+    // its first column in the chunk before, if it goes on).  After j turns a lane has its column's sum if it is the piece j.
+    const int blocks = (a.B + a.block - 1) / a.block;
+    auto sum_pieces = [&](float part, uint64_t ends, float &open, bool &closed) {
+      const uint64_t heads = (ends << 1) | (closed ? 1ull : 0ull);
+      const bool head = (heads >> lane) & 1ull;
+      float s = part;
+      for (int j = 1; j < blocks; ++j) {
+        const float below = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, open), __builtin_bit_cast(int, s),
+                                                                                  0x138, 0xF, 0xF, false));  // wave_shr:1
+        s = head ? part : below + part;
+      }
+      open = read_lane(s, 63);
+      closed = (ends >> 63) & 1ull;
+      return s;
+    };
+    // A list in memory: products in the entries' place, then the k-th column's sum in that of the k-th piece (which has been
+    // read by then).
     auto form_long = [&](const List &l, int v) {
       const u64 *sl = a.slope + par * total_rows + v * a.B;
+      for (int i = 0; i < l.n; i += 64) {
+        const uint2 e = a.ent[l.at + (i + lane < l.n ? i + lane : l.n - 1)];
+        u64 f = 0;
+        poll(limit, ok, [&] { if (!there(f)) f = ld_word(sl + e.x); return there(f); });
+        if (i + lane < l.n)
+          a.ent[l.at + i + lane].y = __float_as_uint(__uint_as_float((uint32_t)f) * __uint_as_float(e.y));
+      }
+      __threadfence_block();  // other lanes read the products
       float open = 0.0f;
       bool closed = true;
       int n = 0;
-      for (int i = 0; i < l.n; i += 64) {
-        const uint2 e = i + lane < l.n ? a.ent[l.at + i + lane] : make_uint2(kLast, 0u);
-        u64 f = 0;
-        poll(limit, ok, [&] { if (!there(f)) f = ld_word(sl + (e.x & ~kLast)); return there(f); });
-        const uint64_t ends = __ballot((e.x & kLast) != 0u);
-        const uint64_t heads = (ends << 1) | (closed ? 1ull : 0ull);
-        const float s = run_sums(__builtin_bit_cast(float, (uint32_t)f) * __builtin_bit_cast(float, e.y), heads, closed ? 0.0f : open, lane);
-        open = read_lane(s, 63);
-        closed = (ends >> 63) & 1ull;
-        if (((ends >> lane) & 1ull) && i + lane < l.n)
-          a.ent[l.at + n + __popcll(ends & ((1ull << lane) - 1ull))].y = __builtin_bit_cast(uint32_t, s);
+      for (int i = 0; i < l.pieces; i += 64) {
+        const bool in = i + lane < l.pieces;
+        const uint32_t f = in ? a.pieces[l.at + i + lane] : 0u;
+        const int32_t end = i + lane + 1 < l.pieces ? (int32_t)(a.pieces[l.at + i + lane + 1] & ~kLast) : l.n;
+        float part = 0.0f;
+        if (in)
+          for (int32_t k = (int32_t)(f & ~kLast); k < end; ++k) part += __uint_as_float(a.ent[l.at + k].y);
+        const uint64_t ends = __ballot((f & kLast) != 0u);
+        const float s = sum_pieces(part, ends, open, closed);
+        if ((ends >> lane) & 1ull) a.pieces[l.at + n + __popcll(ends & ((1ull << lane) - 1ull))] = __builtin_bit_cast(uint32_t, s);
         n += __popcll(ends);
       }
       __threadfence_block();  // other lanes read the sums
     };
-    auto sum_at = [&](const List &l, int k) { return __builtin_bit_cast(float, a.ent[l.at + k].y); };
+    auto sum_at = [&](const List &l, int k) { return __builtin_bit_cast(float, a.pieces[l.at + k]); };
     float mx = 0.0f;
     double sum = 0.0, sumsq = 0.0;
     bool bad = false;
@@ -697,42 +770,78 @@ __global__ __launch_bounds__(kLiThreads) void list_epoch_kernel(ListArgs a) {
           bool all = true;
 #pragma unroll
           for (int r = 0; r < kLiChunks; ++r)
-            if (r * 64 < list.n && !there(w[r])) w[r] = ld_word(sl + (ent[r].x & ~kLast));
+            if (r * 64 < list.n && !there(w[r])) w[r] = ld_word(sl + ent[r].x);
 #pragma unroll
           for (int r = 0; r < kLiChunks; ++r) all = all && there(w[r]);
           return all;
         });
         __builtin_amdgcn_s_setprio(3);
-        // A column's sum, at its last entry, goes to the column's lane.  `open`: what the lanes hold of a column that goes on
-        // behind the chunk; chunks of one column only, as in the most frequent columns' lists, add lane by lane.
-        float open = 0.0f;
-        uint32_t closed = 1u;
-        int n = 0;
+        // Products to their pieces' lanes, each of which adds its own one after the other; the order is that of the worker pass
+        // (rows of a block in batch order, then the blocks).
+        float *mine = stage[wave];
 #pragma unroll
         for (int r = 0; r < kLiChunks; ++r) {
-          if (r * 64 < list.n) {
-            const uint64_t ends = __ballot((ent[r].x & kLast) != 0u);
-            const uint32_t value = ent[r].y;
-            float s = __builtin_bit_cast(float, (uint32_t)w[r]) * __builtin_bit_cast(float, value);
-            if ((ends << 1) == 0ull) {  // the chunk is one column's
-              open = closed ? s : open + s;
-              if (ends != 0ull) s = wave_sum(open);
-            } else {
-              const uint64_t heads = (ends << 1) | closed;
-              if (heads != ~0ull) s = run_sums(s, heads, closed ? 0.0f : wave_sum(open), lane);
-              open = lane == 63 ? s : 0.0f;
+          const uint32_t value = ent[r].y;
+          if (r * 64 < list.n) mine[r * 64 + lane] = __builtin_bit_cast(float, (uint32_t)w[r]) * __builtin_bit_cast(float, value);
+        }
+        staged();
+#pragma unroll
+        for (int k = 0; k < kLiPairs; ++k) {
+          if (k * 64 < list.pieces) {
+            const int first = (int)(piece[k] & 0xfffu), size = (int)((piece[k] >> 12) & 0xfffu);
+            float s = mine[first];
+            if (longest > 1) {  // uniform
+              auto from = [&](int i) { return mine + (first + i < 64 * kLiChunks ? first + i : 64 * kLiChunks); };
+              // eight at a time, requested ahead, as long as a lane has them; then each lane's last ones (-0: nothing added)
+              const int rest = size > 0 ? 1 + ((size - 1) & ~7) : 1;
+              float last[7];
+#pragma unroll
+              for (int i = 0; i < 7; ++i) last[i] = from(rest)[i];
+              if (longest > 8) {
+                float now[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) now[i] = from(1)[i];
+                for (int done = 1; done + 8 <= longest; done += 8) {
+                  float next[8];
+#pragma unroll
+                  for (int i = 0; i < 8; ++i) next[i] = from(done + 8)[i];
+                  float eight = s;
+#pragma unroll
+                  for (int i = 0; i < 8; ++i) eight += now[i];
+                  s = done + 8 <= size ? eight : s;
+#pragma unroll
+                  for (int i = 0; i < 8; ++i) now[i] = next[i];
+                }
+              }
+#pragma unroll
+              for (int i = 0; i < 7; ++i) s += rest + i < size ? last[i] : -0.0f;
             }
-            closed = (uint32_t)(ends >> 63);
-            if ((ends >> lane) & 1ull) stage[wave][n + __popcll(ends & ((1ull << lane) - 1ull))] = __builtin_bit_cast(uint32_t, s);
-            n += __popcll(ends);
+            u[k] = s;
           }
         }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
+        if (list.pieces != list.cols) {  // uniform
+          float open = 0.0f;
+          bool closed = true;
+          int n = 0;
+          staged();
+#pragma unroll
+          for (int k = 0; k < kLiPairs; ++k) {
+            if (k * 64 < list.pieces) {
+              const uint64_t ends = __ballot((piece[k] & kLast) != 0u);
+              const float s = sum_pieces(u[k], ends, open, closed);
+              if ((ends >> lane) & 1ull) mine[n + __popcll(ends & ((1ull << lane) - 1ull))] = s;
+              n += __popcll(ends);
+            }
+          }
+          staged();
+#pragma unroll
+          for (int k = 0; k < kLiPairs; ++k)
+            if (k * 64 < list.cols) u[k] = mine[k * 64 + lane];
+        }
 #pragma unroll
         for (int k = 0; k < kLiPairs; ++k) {
           if (k * 64 < list.cols) {
-            if (col[k] != 0u) u[k] = __builtin_bit_cast(float, stage[wave][k * 64 + lane]);
+            if (col[k] == 0u) u[k] = 0.0f;
             take(u[k]);
             if (ALPC && !quantizes && col[k] != 0u) uhs[col[k] - 1u] = u[k];
           }
@@ -831,6 +940,7 @@ __global__ __launch_bounds__(kLiThreads) void list_epoch_kernel(ListArgs a) {
       if (more) mark_from(t + 1, list_of(t + 1, a.N, bounds_of(t + 1, a.N)), 0);
     }
     if (more && listed) mark_list(t + 1, list_n, col_n);
+    if (!is_long(list_n)) longest_n = size_pieces(list_n, piece_n);
     // ---- 3. the scale factors (Sec. 3.2, eq. (3)), as in lpc_columns.hip
     QParams q{0.0f, 0.0f, 0.0f, 0.0f};
     if (quantizes) {
@@ -1006,12 +1116,14 @@ Shape shape_of(const lpc_ctx *c) {
   s.fields = 32 / c->cfg.bits;
   s.words = (c->cfg.N + s.fields - 1) / s.fields;
   s.lds = 4 * (size_t)S * ((alpc ? 6 : 2) + s.words + 1) + 12 * (size_t)((S + 31) / 32);
-  if (s.lds > (size_t)kLiLds - 18 * 1024) return s;
+  if (s.lds > (size_t)kLiLds - 24 * 1024) return s;
   s.S = (int)S;
   return s;
 }
 
 int64_t list_rows(const lpc_ctx *c) { return (int64_t)(c->cfg.N + (c->cfg.algo != LPC_ALGO_LPC ? 1 : 0)) * c->cfg.B; }
+// Batch positions that are added up by themselves, as the separate launches do
+int32_t list_block(const lpc_ctx *c) { return c->csr_sparse ? csr_sparse_block() : kMaxBatch; }
 int64_t list_iters(const lpc_ctx *c) { return c->cfg.m < kListIters ? c->cfg.m : kListIters; }
 
 }  // namespace
@@ -1028,7 +1140,7 @@ ListScratch lists_scratch(const lpc_ctx *c) {
   w.slope = 2 * rows;
   w.stat = 2 * N * (5 * P + kDies * kLine);
   w.state = 6 * P * s.S;
-  w.off = (size_t)list_iters(c) * (rows / c->cfg.B) * (2 * P + 1);  // the lists' bounds, then their numbers of columns
+  w.off = (size_t)list_iters(c) * (rows / c->cfg.B) * (3 * P + 1);  // the lists' bounds, then their numbers of columns and pieces
   const int64_t mean = (c->prob.nnz + c->n - 1) / c->n;
   w.entries = (size_t)list_iters(c) * rows * (size_t)(3 * mean + 16);
   return w;
@@ -1068,7 +1180,7 @@ hipError_t launch_lists_begin(const lpc_ctx *c, const ResidentStep &rs, hipStrea
   if (e != hipSuccess) return e;
   if (!rs.z_snap) {
     const int64_t rows = (int64_t)c->cfg.m * list_rows(c);
-    hipLaunchKernelGGL(plan_margins_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, st, c->prob.col_idx, c->prob.vals,
+    hipLaunchKernelGGL(plan_margins_kernel, dim3((unsigned)((rows + 15) / 16)), dim3(256), 0, st, c->prob.col_idx, c->prob.vals,
                        rs.w_snap, rows, c->s.csr_plan);
   }
   const size_t slice = (size_t)s.S << s.pshift;
@@ -1086,6 +1198,7 @@ hipError_t launch_lists_epoch(const lpc_ctx *c, const ResidentStep &rs, int32_t 
   ListBuildArgs b{};
   b.col_idx = c->prob.col_idx; b.vals = c->prob.vals; b.plan = c->s.csr_plan + (int64_t)t0 * nvec * c->cfg.B;
   b.off = c->s.li_off; b.ent = reinterpret_cast<uint2 *>(c->s.li_ent); b.cols = c->s.li_cols;
+  b.pieces = c->s.li_cols + lists_scratch(c).entries; b.block = list_block(c);
   b.n_cols = b.off + (size_t)list_iters(c) * nvec * (P + 1); b.cap = c->list_cap;
   b.B = c->cfg.B; b.pshift = s.pshift; b.pos_bits = c->list_pos_bits; b.k_bits = c->list_k_bits;
   b.map_words = (b.B + 31) / 32; b.loss = c->prob.loss;
@@ -1097,7 +1210,8 @@ hipError_t launch_lists_epoch(const lpc_ctx *c, const ResidentStep &rs, int32_t 
   if ((e = hipGetLastError()) != hipSuccess) return e;
   ListArgs a{};
   fill_method_args(a, c, rs, t0, t1, weight);
-  a.col_idx = b.col_idx; a.vals = b.vals; a.plan = b.plan; a.off = b.off; a.ent = b.ent; a.cols = b.cols; a.n_cols = b.n_cols; a.cap = b.cap;
+  a.col_idx = b.col_idx; a.vals = b.vals; a.plan = b.plan; a.off = b.off; a.ent = b.ent; a.cols = b.cols; a.n_cols = b.n_cols;
+  a.pieces = b.pieces; a.block = b.block; a.cap = b.cap;
   const size_t slice = (size_t)s.S * P;
   float *state = c->s.li_state;
   a.mu = state; a.ws = state + slice; a.y = state + 2 * slice; a.z = state + 3 * slice; a.x = state + 4 * slice;
