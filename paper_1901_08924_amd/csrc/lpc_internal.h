@@ -150,7 +150,7 @@ struct Scratch {
   unsigned long long *cl_msg, *cl_vec, *cl_scale;  // lpc_cluster.hip: tagged words (cluster_scratch() says how many)
   uint32_t *cl_ctl;     // [16]
   // lpc_lists.hip (its words lie from cl_msg on)
-  uint32_t *li_off;           // lists of a launch's iterations: bounds, entries (pairs of words)
+  uint32_t *li_off;           // lists of a launch's iterations: records, entries (pairs of words)
   unsigned long long *li_ent;
   uint32_t *li_cols;          // ... columns, pieces
   float *li_state;            // ... and the problem's vectors in the owners' order

@@ -25,7 +25,7 @@
 //
 // Bound by the four trips of words (store to load about 1.2 us each) and by the owner of the most frequent column, whose lists
 // are six times as long as the others'.  Measured on MI355X, separate launches -> these kernels, us per iteration, the lists
-// (3.0 there) included: n = d = 2^20, N = 16, B = 256, b = 2: 35.5 -> 13.4; d = 150001, N = 8 + J, B = 100, b = 4: 30.6 -> 11.8.
+// (1.7 there) included: n = d = 2^20, N = 16, B = 256, b = 2: 35.5 -> 11.9; d = 150001, N = 8 + J, B = 100, b = 4: 30.6 -> 11.1.
 // Steps that paid, us per iteration of the first: registers loaded ahead without a join that waits for them and waits for
 // them before the next store, not behind it, together with priority for rows and sums over what only fills the waits, 1.0;
 // columns found by the builder instead of here and words stored as soon as they are known, 1.9; half of the trips' time went
@@ -46,10 +46,13 @@ constexpr int kLiRows = 2;      // sampled rows of a wavefront
 constexpr int kLiChunks = 5;    // 64-entry chunks of a vector's list that a wavefront holds in registers
 constexpr int kLiPairs = 2;     // ... and 64-column chunks of its columns
 constexpr int kLiLds = 156 * 1024;
-constexpr int kOwnBins = 4;     // bins per owner of the list's partition: the first ones hold one column each,
-constexpr int kSubBins = 8;     // ... the others a quarter of the rest
+constexpr int kOwnerBits = 8, kOwners = 1 << kOwnerBits;
+constexpr int kOwnBins = 4;     // an owner's first columns, with a map of batch positions each; the others: bins of a quarter
 constexpr int kMaxBatch = 512;
-constexpr int kKeyCap = 6400;   // keys of shared bins that a workgroup of the builder sorts at once
+constexpr int kKeyChunks = 100; // 64-entry chunks of the others' keys that a workgroup of the builder sorts at once
+constexpr int kKeyCap = 64 * kKeyChunks;
+constexpr int kRecord = 5;      // words of a list's record: first entry, entries, columns, pieces, longest piece
+constexpr int kSortChunks = (kKeyChunks + kLiWaves - 1) / kLiWaves;
 constexpr int kHeld = 16;       // rows whose columns a wavefront of the builder holds
 constexpr int kDies = 8;
 constexpr int kLine = 16;       // words of a 128-byte line
@@ -62,34 +65,60 @@ struct ListBuildArgs {
   const int32_t *col_idx;
   const float *vals;
   RowPlan *plan;        // of the first iteration of the launch; its margins become slopes
-  uint32_t *off;        // [iterations][nvec][P + 1]
+  uint32_t *rec;        // [iterations][nvec][P][kRecord]
   uint2 *ent;           // [iterations][nvec][cap]: batch position, value
   uint32_t *cols;       // [iterations][nvec][cap]: a list's columns lc + 1, from its first entry's place on
-  uint32_t *pieces;     // [iterations][nvec][cap]: likewise the first entries of its pieces (kLast: its column's last one)
-  uint32_t *n_cols;     // [iterations][nvec][P][2]: how many of both
+  uint32_t *pieces;     // [iterations][nvec][cap]: likewise its pieces' first entries (kLast: its column's last one); with the
+                        // piece's length from bit 12 on if the list has no more entries than a wavefront takes in registers
   int64_t cap;
-  int32_t B, pshift, pos_bits, k_bits, map_words, loss, block;
+  int32_t B, pos_bits, k_bits, map_words, map_space, key_space, loss, block;
 };
 
-__device__ __forceinline__ uint32_t list_bin(uint32_t c, int pshift) {
-  const uint32_t p = c & ((1u << pshift) - 1u), lc = c >> pshift;
-  return p * kSubBins + (lc < (uint32_t)kOwnBins ? lc : kOwnBins + (lc & (uint32_t)(kSubBins - kOwnBins - 1)));
+// A buffer of its own for a row or list: loads past its end are 0, without a branch.
+__device__ __forceinline__ auto buffer(const void *from, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(from), 0, (int)bytes, 0x00027000);
 }
 
-// An entry's place is its bin's first place plus its rank there.  In the bins of one column (the 4 P first ones: text-like
-// data has half of its entries there, hundreds in a bin) the rank is a count of bits in a map of the batch positions; in the
-// others an entry counts the smaller keys, five of them on average.  No sum or place depends on timing.
-// Bound by the instructions of the last walk (about 130 per row and wavefront).
+// An owner's first four columns (text-like data has more than half of its entries there, hundreds in a column) have a map of
+// the batch positions each: an entry's rank is a count of bits, the pieces are counts of bits of a block.  The other entries'
+// keys are put in the owner's four bins in any order, counted against the five or so others of their bin, written back in order,
+// and walked in that order: heads of columns and pieces are votes of 64 neighbours, and counts of votes place them.  No sum or
+// place depends on timing.
+// Entries go to memory by way of LDS: stored from where they are read, one line each, the address units were busy throughout
+// and lines left the L2 half full (0.77 GB written for 0.24).  Registers must not spill: 30 of them are as many bytes as the lists.
+// Bound by instructions (2370 of the vector units per wavefront and batch) and LDS.  Two workgroups to a CU: 80 KB for B = 256.
+// Measured on MI355X, lists of 128 iterations of n = d = 2^20, 16 vectors, B = 256, 40 entries a row: 214 us; 64 iterations of
+// d = 150001, 9 vectors, B = 100, 24 entries: 40 (each entry placed by itself, a wavefront per list to find heads: 362, 63).
 __global__ __launch_bounds__(kLiThreads, 8) void list_build_kernel(ListBuildArgs a) {
-  extern __shared__ uint32_t build_lds[];  // kKeyCap keys, then the maps: [4 P][map_words]
-  __shared__ uint32_t start[2048 + 1], ends[2048];
-  __shared__ int32_t lo_sh[kMaxBatch], len_sh[kMaxBatch];
+  extern __shared__ uint32_t build_lds[];
+  __shared__ uint32_t cursor[kOwnBins * kOwners];     // key slots of a bin: the next one
+  __shared__ uint32_t single_at[kOwnBins * kOwners];  // a mapped column's first entry, of the mapped ones
+  __shared__ uint32_t first[kOwners + 1], slot0[kOwners + 1];  // an owner's first entry, first key slot
+  __shared__ uint32_t singles[kOwners], longest[kOwners];      // pieces << 16 | columns of the mapped ones; longest piece
+  __shared__ uint64_t votes_mem[2 * (kKeyChunks + 1)];
+  __shared__ uint32_t before[kKeyChunks + 1];  // pieces << 16 | columns of the chunks before
   __shared__ uint32_t total_a[kLiWaves], total_b[kLiWaves], twice;
-  uint32_t *keys = build_lds, *maps = build_lds + kKeyCap;
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int bins = kSubBins << a.pshift;  // at most 2048
+  int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // Between the phases: what is derived from these is not to be kept in registers, let alone in memory, from one to the next.
+  auto part = [&] {
+    asm volatile("" : "+v"(tid));
+    lane = tid & 63;
+    wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  };
+  constexpr int P = kOwners, kBins = kOwnBins * P;  // bin: column mod kBins
+  // first maps [map_words][4 P], for every other of their words the bits before it, and staged entries; then keys with owners and values
+  uint32_t *maps = build_lds, *key_values = build_lds, *keys = build_lds + a.map_space;
+  uint8_t *owner = reinterpret_cast<uint8_t *>(keys + kKeyCap);
+  uint16_t *ranks = reinterpret_cast<uint16_t *>(keys);
+  const int n_ranks = kBins * ((a.map_words + 1) / 2), n_stage = (a.key_space - n_ranks / 2) * 4 / 6;
+  uint32_t *stage_value = keys + n_ranks / 2;
+  uint16_t *stage_pos = reinterpret_cast<uint16_t *>(stage_value + n_stage);
+  uint64_t *col_heads = votes_mem, *heads = votes_mem + kKeyChunks + 1;
+  uint32_t *one0 = reinterpret_cast<uint32_t *>(votes_mem);  // before there are heads: an owner's first entry of the mapped ones
+  int32_t *lo_sh = reinterpret_cast<int32_t *>(keys + a.key_space), *len_sh = lo_sh + a.B;
   RowPlan *rows = a.plan + (int64_t)blockIdx.x * a.B;
   uint2 *out = a.ent + (int64_t)blockIdx.x * a.cap;
+  uint32_t *cols = a.cols + (int64_t)blockIdx.x * a.cap, *pieces = a.pieces + (int64_t)blockIdx.x * a.cap;
   for (int r = tid; r < a.B; r += kLiThreads) {
     const RowPlan row = rows[r];
     lo_sh[r] = row.lo;
@@ -99,203 +128,413 @@ __global__ __launch_bounds__(kLiThreads, 8) void list_build_kernel(ListBuildArgs
   if (tid == 0) twice = 0u;
   const int held = kHeld * kLiWaves, groups = (a.B + held - 1) / held;
   int32_t c[kHeld];
-  auto load = [&](int g) {  // row g * held + q * kLiWaves + wave
+  bool far = false;  // a row of the wavefront's has more than 64 entries
+  uint32_t row_lo, row_len;  // lane q's: row g * held + q * kLiWaves + wave
+  auto take_rows = [&](int g) {
+    const int r = g * held + lane * kLiWaves + wave;
+    const bool has = lane < kHeld && r < a.B;
+    row_lo = has ? (uint32_t)lo_sh[r] : 0u;
+    row_len = has ? (uint32_t)len_sh[r] : 0u;
+    far = __ballot(row_len > 64u) != 0ull;
+  };
+  // lane l's of a row's first 64 words (0 past its end)
+  auto row_words = [&](const void *from, int q) {
+    return __builtin_amdgcn_raw_buffer_load_b32(
+        buffer(static_cast<const uint32_t *>(from) + read_lane(row_lo, q), 4u * read_lane(row_len, q)), 4 * lane, 0, 0);
+  };
+  auto load = [&](int g) {
+    take_rows(g);
 #pragma unroll
     for (int q = 0; q < kHeld; ++q) {
-      const int r = g * held + q * kLiWaves + wave;
-      c[q] = -1;
-      if (r < a.B && lane < len_sh[r]) c[q] = a.col_idx[lo_sh[r] + lane];
+      const uint32_t col = row_words(a.col_idx, q);
+      c[q] = (uint32_t)lane < read_lane(row_len, q) ? (int32_t)col : -1;
     }
   };
-  // f(column, row, index in the row) for every entry of group g, the first 64 of a row from registers
-  auto walk = [&](int g, auto f) {
-#pragma unroll
-    for (int q = 0; q < kHeld; ++q) {
-      const int r = g * held + q * kLiWaves + wave;
-      if (r >= a.B) break;  // uniform
-      if (c[q] >= 0) f((uint32_t)c[q], r, (uint32_t)lane, q);
-      const int32_t len = len_sh[r];
-      for (int32_t k = 64 + lane; k < len; k += 64) f((uint32_t)a.col_idx[lo_sh[r] + k], r, (uint32_t)k, -1);
+  // f(column, row, index in the row, value) for the entries past a row's first 64
+  auto walk_far = [&](int g, auto f) {
+    if (!far) return;
+    for (int r = g * held + wave; r < a.B && r < (g + 1) * held; r += kLiWaves) {
+      const int32_t lo = __builtin_amdgcn_readfirstlane(lo_sh[r]), len = __builtin_amdgcn_readfirstlane(len_sh[r]);
+      for (int32_t k = 64 + lane; k < len; k += 64) f((uint32_t)a.col_idx[lo + k], r, (uint32_t)k, lo + k);
     }
   };
-  auto single = [&](uint32_t bin) { return (bin & (kSubBins - 1)) < (uint32_t)kOwnBins; };
-  auto map_of = [&](uint32_t bin) { return maps + ((bin / kSubBins) * kOwnBins + (bin & (kSubBins - 1))) * a.map_words; };
-  bool mapped = true;  // false: a row holds a column twice, all bins are counted
+  auto map_word = [&](uint32_t bin, int w) -> uint32_t & { return maps[w * kBins + (int)bin]; };
+  auto rank_of = [&](uint32_t bin, int r) -> uint32_t {  // bits of a map before position r
+    uint32_t n = ranks[(r >> 6) * kBins + (int)bin] + __popc(map_word(bin, r >> 5) & ((1u << (r & 31)) - 1u));
+    if (r & 32) n += __popc(map_word(bin, (r >> 5) - 1));  // uniform
+    return n;
+  };
+  bool mapped = true;  // false: a row holds a column twice, all entries have keys
   for (;;) {
-    for (int b = tid; b < 2048; b += kLiThreads) start[b] = 0u;
-    for (int w = tid; w < (kOwnBins << a.pshift) * a.map_words; w += kLiThreads) maps[w] = 0u;
+    cursor[tid] = 0u;
+    for (int w = tid; w < kBins * a.map_words; w += kLiThreads) maps[w] = 0u;
     __syncthreads();
+    uint32_t again = 0u;
+    // One atomic per entry, without a branch: a bit of a map, set by adding it (a sum that carries is not used), or a count.
+    auto enter = [&](uint32_t col, int r, bool in) {
+      const uint32_t bin = col & (uint32_t)(kBins - 1);
+      const bool one = mapped && col < (uint32_t)kBins;
+      const uint32_t bit = 1u << (r & 31);
+      const uint32_t old = atomicAdd(one ? &map_word(bin, r >> 5) : &cursor[in ? bin : tid], one ? bit : in ? 1u : 0u);
+      return one ? old & bit : 0u;
+    };
     for (int g = 0; g < groups; ++g) {
       load(g);
-      walk(g, [&](uint32_t col, int r, uint32_t, int) {
-        const uint32_t bin = list_bin(col, a.pshift);
-        if (mapped && single(bin)) {
-          const uint32_t bit = 1u << (r & 31);
-          if (atomicOr(&map_of(bin)[r >> 5], bit) & bit) twice = 1u;
-        } else {
-          atomicAdd(&start[bin], 1u);
-        }
-      });
+#pragma unroll
+      for (int q = 0; q < kHeld; ++q) again |= enter((uint32_t)c[q], g * held + q * kLiWaves + wave, c[q] >= 0);
+      walk_far(g, [&](uint32_t col, int r, uint32_t, int32_t) { again |= enter(col, r, true); });
     }
+    if (again != 0u) twice = 1u;
     __syncthreads();
     if (!mapped || twice == 0u) break;  // uniform: nobody writes it behind the barrier
     mapped = false;
   }
-  // ---- the bins' first places, and the shared bins' first keys: two exclusive scans, two bins per thread
+  part();
+  // ---- first places and key slots: exclusive scans over the bins, one per thread (owner tid / 4); the mapped columns' pieces
+  uint32_t all_keys = 0;
   {
-    uint32_t n[2], m[2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const uint32_t bin = 2 * tid + i;
-      const bool by_map = mapped && single(bin) && (int)bin < bins;
-      m[i] = by_map ? 0u : start[bin];
-      n[i] = m[i];
-      if (by_map)
-        for (int w = 0; w < a.map_words; ++w) n[i] += __popc(map_of(bin)[w]);
-    }
-    uint32_t sa = n[0] + n[1], sb = m[0] + m[1];
+    const int p = tid / kOwnBins, b = tid & (kOwnBins - 1), bin = b * P + p;
+    const uint32_t n_key = cursor[bin];
+    uint32_t n_one = 0, n_pieces = 0, most = n_key != 0u ? 1u : 0u;
+    if (mapped)
+      for (int w = 0; w < a.map_words; ++w) {
+        if ((w & 1) == 0) ranks[w / 2 * kBins + bin] = (uint16_t)n_one;
+        n_one += __popc(map_word(bin, w));
+      }
+    // A map's blocks: their numbers of bits.
+    auto blocks = [&](auto f) {
+      uint32_t prior = 0;
+      for (int x = a.block; x < a.B; x += a.block) {  // uniform
+        const uint32_t upto = rank_of(bin, x);
+        f(upto - prior);
+        prior = upto;
+      }
+      f(n_one - prior);
+    };
+    if (mapped)
+      blocks([&](uint32_t n) {
+        n_pieces += n != 0u ? 1u : 0u;
+        most = max(most, n);
+      });
+    uint32_t sa = n_one + n_key, sb = n_key;
     for (int o = 1; o < 64; o <<= 1) {
       const uint32_t ua = __shfl_up(sa, o, 64), ub = __shfl_up(sb, o, 64);
       if (lane >= o) { sa += ua; sb += ub; }
     }
     if (lane == 63) { total_a[wave] = sa; total_b[wave] = sb; }
     __syncthreads();
-    for (int w = 0; w < wave; ++w) { sa += total_a[w]; sb += total_b[w]; }
-    start[2 * tid] = sa - n[0] - n[1];
-    start[2 * tid + 1] = sa - n[1];
-    ends[2 * tid] = sb - m[0] - m[1];  // the cursors of the next walk, which leaves them at the bins' ends
-    ends[2 * tid + 1] = sb - m[1];
-    if (tid == kLiThreads - 1) start[2048] = sa;
-  }
-  __syncthreads();
-  for (int p = tid; p <= 1 << a.pshift; p += kLiThreads)
-    a.off[(int64_t)blockIdx.x * ((1 << a.pshift) + 1) + p] = start[p * kSubBins];
-  uint32_t all_keys = 0;
-  for (int w = 0; w < kLiWaves; ++w) all_keys += total_b[w];
-  // ---- as many bins at a time as the keys have room for (all of them unless rows are long)
-  for (int b0 = 0; b0 < bins;) {
-    const uint32_t base = ends[b0];  // still the first key
-    auto first_key = [&](int b) { return b < bins ? ends[b] : all_keys; };
-    int b1 = bins;
-    if (all_keys - base > (uint32_t)kKeyCap) {
-      int lo = b0 + 1, hi = bins;
-      while (lo < hi) {
-        const int mid = (lo + hi + 1) / 2;
-        if (first_key(mid) - base <= (uint32_t)kKeyCap) lo = mid; else hi = mid - 1;
-      }
-      b1 = lo;
+    uint32_t all = 0;
+#pragma unroll 4
+    for (int w = 0; w < kLiWaves; ++w) {
+      if (w < wave) { sa += total_a[w]; sb += total_b[w]; }
+      all += total_a[w];
+      all_keys += total_b[w];
     }
-    const bool too_many = first_key(b1) - base > (uint32_t)kKeyCap;  // one bin is more than that
-    __syncthreads();
-    if (!too_many) {
-      for (int g = 0; g < groups; ++g) {
-        if (groups > 1) load(g);
-        walk(g, [&](uint32_t col, int r, uint32_t k, int) {
-          const uint32_t bin = list_bin(col, a.pshift);
-          if ((int)bin < b0 || (int)bin >= b1 || (mapped && single(bin))) return;
-          keys[atomicAdd(&ends[bin], 1u) - base] = ((col >> a.pshift) << a.pos_bits | (uint32_t)r) << a.k_bits | k;
-        });
-      }
-      __syncthreads();
+    sa -= n_one + n_key;
+    sb -= n_key;
+    auto quad_sum = [&](uint32_t x) {  // of an owner's bins up to this one
+      const uint32_t x1 = __shfl_up(x, 1, kOwnBins);
+      x += b >= 1 ? x1 : 0u;
+      const uint32_t x2 = __shfl_up(x, 2, kOwnBins);
+      return x + (b >= 2 ? x2 : 0u);
+    };
+    const uint32_t list = __shfl(sa, 0, kOwnBins), one_at = quad_sum(n_one) - n_one;
+    const uint32_t n_list = __shfl(sa + n_one + n_key, kOwnBins - 1, kOwnBins) - list;
+    const uint32_t mine = n_pieces << 16 | (n_one != 0u ? 1u : 0u), upto = quad_sum(mine);
+    most = max(most, __shfl_xor(most, 1, kOwnBins));
+    most = max(most, __shfl_xor(most, 2, kOwnBins));
+    cursor[bin] = sb;
+    single_at[bin] = sa - sb;
+    if (b == 0) {
+      first[p] = list;
+      slot0[p] = sb;
+      one0[p] = sa - sb;
+      longest[p] = most;
     }
-    for (int g = 0; g < groups; ++g) {
-      if (groups > 1) load(g);
-      float v[kHeld];
-#pragma unroll
-      for (int q = 0; q < kHeld; ++q) {
-        const int r = g * held + q * kLiWaves + wave;
-        v[q] = c[q] >= 0 ? a.vals[lo_sh[r < a.B ? r : 0] + lane] : 0.0f;
-      }
-      walk(g, [&](uint32_t col, int r, uint32_t k, int q) {
-        const uint32_t bin = list_bin(col, a.pshift);
-        if ((int)bin < b0 || (int)bin >= b1) return;
-        const uint32_t pair = (col >> a.pshift) << a.pos_bits | (uint32_t)r, key = pair << a.k_bits | k;
-        uint32_t at = start[bin];
-        if (mapped && single(bin)) {
-          const uint32_t *map = map_of(bin);
-          for (int w = 0; w < r >> 5; ++w) at += __popc(map[w]);
-          at += __popc(map[r >> 5] & ((1u << (r & 31)) - 1u));
-        } else if (!too_many) {
-          const uint32_t hi = ends[bin] - base;
-          for (uint32_t i = (int)bin > b0 ? ends[bin - 1] - base : 0u; i < hi; ++i) at += keys[i] < key ? 1u : 0u;
-        } else {
-          // No data meant for these kernels come here (6400 entries of a batch in one of 2048 bins), but they are not refused:
-          // an entry counts the smaller keys of the whole batch, from memory.
-          for (int r2 = 0; r2 < a.B; ++r2) {
-            for (int32_t k2 = 0; k2 < len_sh[r2]; ++k2) {
-              const uint32_t c2 = (uint32_t)a.col_idx[lo_sh[r2] + k2];
-              if (list_bin(c2, a.pshift) != bin) continue;
-              at += (((c2 >> a.pshift) << a.pos_bits | (uint32_t)r2) << a.k_bits | (uint32_t)k2) < key ? 1u : 0u;
-            }
-          }
-        }
-        float val = 0.0f;
-        if (q >= 0) {
-#pragma unroll
-          for (int i = 0; i < kHeld; ++i) val = i == q ? v[i] : val;
-        } else {
-          val = a.vals[lo_sh[r] + (int32_t)k];
-        }
-        out[at] = make_uint2(pair, __builtin_bit_cast(uint32_t, val));
+    if (b == kOwnBins - 1) singles[p] = upto;
+    if (n_one != 0u) {
+      const uint32_t at = upto - mine;
+      cols[list + (at & 0xffffu)] = (uint32_t)b + 1u;
+      uint32_t k = list + (at >> 16), from = one_at;
+      blocks([&](uint32_t n) {
+        if (n == 0u) return;
+        const uint32_t size = n_list <= 64u * kLiChunks ? n << 12 : 0u;
+        pieces[k++] = from | size | (from + n == one_at + n_one ? kLast : 0u);
+        from += n;
       });
     }
-    __syncthreads();
-    b0 = b1;
+    if (tid == 0) { first[P] = all; slot0[P] = all_keys; one0[P] = all - all_keys; }
   }
-  // ---- the lists' columns and pieces, a wavefront a list at a time
-  const int P = 1 << a.pshift;
-  uint32_t *cols = a.cols + (int64_t)blockIdx.x * a.cap, *pieces = a.pieces + (int64_t)blockIdx.x * a.cap;
-  const uint32_t per_block = a.block < a.B ? 65536u / (uint32_t)a.block + 1u : 0u;  // pos / block = pos * this >> 16, pos < 512
-  for (int p0 = wave; p0 < P; p0 += 2 * kLiWaves) {
-    uint32_t first[2], end[2];
-    uint2 e[2];
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      const int p = p0 + q * kLiWaves;
-      first[q] = p < P ? start[p * kSubBins] : 0u;
-      end[q] = p < P ? start[(p + 1) * kSubBins] : 0u;
-      e[q] = make_uint2(kNoEntry, 0u);
-      if (first[q] + lane < end[q]) e[q] = out[first[q] + lane];
+  __syncthreads();
+  auto bin_of = [&](uint32_t col) { return col & (uint32_t)(kBins - 1); };
+  part();
+  // ---- the mapped columns' entries, as many owners' at a time as there is room for (one's always: 4 B of them at most)
+  for (int p0 = 0; mapped && p0 < P;) {
+    const uint32_t base = one0[p0];
+    int p1 = P;
+    if (one0[P] - base > (uint32_t)n_stage) {
+      int lo = p0 + 1, hi = P;
+      while (lo < hi) {
+        const int mid = (lo + hi + 1) / 2;
+        if (one0[mid] - base <= (uint32_t)n_stage) lo = mid; else hi = mid - 1;
+      }
+      p1 = lo;
     }
+    part();
+    const uint32_t room = one0[p1] - base;
+    auto put = [&](uint32_t col, int r, uint32_t value) {
+      if (col >= (uint32_t)kBins) return;  // (no entry: column 2^32 - 1)
+      const uint32_t at = single_at[col] + rank_of(col, r) - base;
+      if (at >= room) return;
+      stage_value[at] = value;
+      stage_pos[at] = (uint16_t)r;
+    };
+    for (int g = 0; g < groups; ++g) {
+      if (groups > 1) load(g);
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      // of an entry: column and block of batch positions
-      auto place_of = [&](uint32_t x) {
-        return (x >> a.pos_bits) << 4 | ((x & ((1u << a.pos_bits) - 1u)) * per_block) >> 16;
-      };
-      uint32_t n = 0, m = 0, before = kNoEntry, open = 0;  // open: where the last piece so far begins
-      for (uint32_t i = first[q]; i < end[q]; i += 64) {
-        if (i != first[q]) {
-          e[q].x = kNoEntry;
-          if (i + lane < end[q]) e[q] = out[i + lane];
-        }
-        const bool in = i + lane < end[q];
-        const uint32_t at = in ? place_of(e[q].x) : kNoEntry - 16u;
-        const uint32_t prev = (uint32_t)__builtin_amdgcn_update_dpp((int)before, (int)at, 0x138, 0xF, 0xF, false);  // wave_shr:1
-        before = read_lane(at, 63);
-        const uint64_t columns = __ballot(at >> 4 != prev >> 4 && in), heads = __ballot(at != prev && in);
-        const uint64_t below = (1ull << lane) - 1ull;
-        if (in) {
-          out[i + lane].x = e[q].x & ((1u << a.pos_bits) - 1u);
-          if ((columns >> lane) & 1ull) cols[first[q] + n + __popcll(columns & below)] = (at >> 4) + 1u;
-          if ((heads >> lane) & 1ull) {
-            // the column's last piece: the next piece begins a column, or there is none (this chunk's last one: see below)
-            const uint64_t above = heads & ~below & ~(1ull << lane);
-            const bool last = above != 0ull && ((columns >> __builtin_ctzll(above)) & 1ull);
-            pieces[first[q] + m + __popcll(heads & below)] = i - first[q] + lane | (last ? kLast : 0u);
+      for (int q0 = 0; q0 < kHeld; q0 += 8) {
+        uint32_t v[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = row_words(a.vals, q0 + i);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) put((uint32_t)c[q0 + i], g * held + (q0 + i) * kLiWaves + wave, v[i]);
+      }
+      walk_far(g, [&](uint32_t col, int r, uint32_t, int32_t e) { put(col, r, __float_as_uint(a.vals[e])); });
+    }
+    __syncthreads();
+    part();
+    for (int p = p0 + (tid >> 4); p < p1; p += kLiThreads / 16) {  // sixteen lanes a list
+      const uint32_t from = one0[p] - base, n = one0[p + 1] - base - from;
+      for (uint32_t i = tid & 15; i < n; i += 16) out[first[p] + i] = make_uint2(stage_pos[from + i], stage_value[from + i]);
+    }
+    __syncthreads();
+    p0 = p1;
+  }
+  const uint32_t pos_mask = (1u << a.pos_bits) - 1u;
+  const uint32_t per_block = a.block < a.B ? 65536u / (uint32_t)a.block + 1u : 0u;  // pos / block = pos * this >> 16, pos < 512
+  auto place_of = [&](uint32_t pair) { return (pair >> a.pos_bits) << 4 | ((pair & pos_mask) * per_block) >> 16; };  // column, block
+  // ---- as many owners at a time as the keys have room for (all of them unless rows are long)
+  for (int p0 = 0; p0 < P;) {
+    const uint32_t base = slot0[p0];
+    int p1 = P;
+    if (all_keys - base > (uint32_t)kKeyCap) {
+      int lo = p0 + 1, hi = P;
+      while (lo < hi) {
+        const int mid = (lo + hi + 1) / 2;
+        if (slot0[mid] - base <= (uint32_t)kKeyCap) lo = mid; else hi = mid - 1;
+      }
+      p1 = lo;
+    }
+    const int n_keys = (int)(slot0[p1] - base), chunks = (n_keys + 63) / 64;
+    const bool too_many = n_keys > kKeyCap;  // one owner's are more than that
+    __syncthreads();
+    part();
+    auto put_key = [&](uint32_t col, int r, uint32_t k, uint32_t slot, uint32_t value) {
+      key_values[slot] = value;
+      keys[slot] = ((col >> kOwnerBits) << a.pos_bits | (uint32_t)r) << a.k_bits | k;
+      owner[slot] = (uint8_t)col;
+    };
+    const int32_t keyed = mapped ? kBins : 0;  // columns from there on
+    auto mine = [&](uint32_t col) {  // (no entry: -1)
+      return (int32_t)col >= keyed && (col & (uint32_t)(P - 1)) - (uint32_t)p0 < (uint32_t)(p1 - p0);
+    };
+    for (int g = 0; g < groups; ++g) {
+      if (groups > 1 || p0 > 0) load(g);
+      if (!too_many) {
+#pragma unroll
+        for (int q0 = 0; q0 < kHeld; q0 += 8) {
+          uint32_t slot[8], v[8];
+#pragma unroll
+          for (int i = 0; i < 8; ++i) v[i] = row_words(a.vals, q0 + i);
+#pragma unroll
+          for (int i = 0; i < 8; ++i) {  // (the others add nothing, each to a word of its own)
+            const uint32_t col = (uint32_t)c[q0 + i];
+            const bool has = mine(col);
+            slot[i] = atomicAdd(&cursor[has ? bin_of(col) : (uint32_t)tid], has ? 1u : 0u) - base;
+          }
+#pragma unroll
+          for (int i = 0; i < 8; ++i) {
+            const uint32_t col = (uint32_t)c[q0 + i];
+            if (mine(col)) put_key(col, g * held + (q0 + i) * kLiWaves + wave, (uint32_t)lane, slot[i], v[i]);
           }
         }
-        if (heads != 0ull) {
-          if (m != 0u && lane == 0 && ((columns >> __builtin_ctzll(heads)) & 1ull)) pieces[first[q] + m - 1u] = open | kLast;
-          open = i - first[q] + 63u - (uint32_t)__builtin_clzll(heads);
-        }
-        n += (uint32_t)__popcll(columns);
-        m += (uint32_t)__popcll(heads);
       }
-      if (m != 0u && lane == 0) pieces[first[q] + m - 1u] = open | kLast;
-      const int p = p0 + q * kLiWaves;
-      if (p < P && lane < 2) a.n_cols[((int64_t)blockIdx.x * P + p) * 2 + lane] = lane == 0 ? n : m;
+      walk_far(g, [&](uint32_t col, int r, uint32_t k, int32_t e) {
+        if (!too_many && mine(col)) put_key(col, r, k, atomicAdd(&cursor[bin_of(col)], 1u) - base, __float_as_uint(a.vals[e]));
+      });
     }
+    if (too_many) {
+      // No data meant for these kernels come here (6400 entries of a batch in the columns of one owner), but they are not
+      // refused: an entry counts the smaller keys of its bin, from memory.
+      auto each = [&](int rows_from, int step, int32_t k_from, int32_t k_step, auto f) {
+        for (int r = rows_from; r < a.B; r += step) {
+          const int32_t lo = lo_sh[r], len = len_sh[r];
+          for (int32_t k = k_from; k < len; k += k_step) {
+            const uint32_t col = (uint32_t)a.col_idx[lo + k], lc = col >> kOwnerBits;
+            if ((int)(col & (uint32_t)(P - 1)) != p0 || (int32_t)col < keyed) continue;
+            f(lc << a.pos_bits | (uint32_t)r, (uint32_t)k, lo + k);
+          }
+        }
+      };
+      each(wave, kLiWaves, lane, 64, [&](uint32_t pair, uint32_t k, int32_t e) {
+        const uint32_t b = (pair >> a.pos_bits) & (uint32_t)(kOwnBins - 1);
+        uint32_t at = first[p0 + 1] - (slot0[p0 + 1] - cursor[b * P + (uint32_t)p0]);
+        each(0, 1, 0, 1, [&](uint32_t other, uint32_t k2, int32_t) {
+          if (((other >> a.pos_bits) & (uint32_t)(kOwnBins - 1)) == b && (other < pair || (other == pair && k2 < k))) ++at;
+        });
+        out[at] = make_uint2(pair, __float_as_uint(a.vals[e]));
+      });
+    }
+#pragma unroll
+    for (int q = 0; q < kHeld; ++q) c[q] = -1;  // (not kept for another turn)
+    __syncthreads();
+    if (!too_many) {
+      part();
+      // ---- the keys in order
+      uint32_t key[kSortChunks], val[kSortChunks], to[kSortChunks];
+#pragma unroll
+      for (int i = 0; i < kSortChunks; ++i) {
+        const int slot = 64 * (wave + i * kLiWaves) + lane;
+        key[i] = val[i] = to[i] = 0u;
+        if (slot < n_keys) {
+          key[i] = keys[slot];
+          val[i] = key_values[slot];
+          const uint32_t p = owner[slot], b = (key[i] >> (a.pos_bits + a.k_bits)) & (uint32_t)(kOwnBins - 1);
+          const uint32_t hi = cursor[b * P + p] - base, lo = b != 0u ? cursor[b * P + p - P] - base : slot0[p] - base;
+          uint32_t n = lo;
+          for (uint32_t k = lo; k < hi; k += 4) {  // (what lies behind the keys is LDS of this kernel)
+            const uint32_t k0 = keys[k], k1 = keys[k + 1], k2 = keys[k + 2], k3 = keys[k + 3];
+            n += k0 < key[i] ? 1u : 0u;
+            n += k + 1 < hi && k1 < key[i] ? 1u : 0u;
+            n += k + 2 < hi && k2 < key[i] ? 1u : 0u;
+            n += k + 3 < hi && k3 < key[i] ? 1u : 0u;
+          }
+          to[i] = n;
+        }
+      }
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < kSortChunks; ++i)
+        if (64 * (wave + i * kLiWaves) + lane < n_keys) {
+          keys[to[i]] = key[i];
+          key_values[to[i]] = val[i];
+        }
+      __syncthreads();
+      part();
+      // ---- entries, heads of columns and pieces
+#pragma unroll
+      for (int i = 0; i < kSortChunks; ++i) {
+        const int chunk = wave + i * kLiWaves, slot = 64 * chunk + lane;
+        if (chunk >= chunks) break;  // uniform
+        bool col = false, piece = false;
+        if (slot < n_keys) {
+          key[i] = keys[slot];
+          const uint32_t at = place_of(key[i] >> a.k_bits);
+          const uint32_t prev = slot > 0 ? place_of(keys[slot - 1] >> a.k_bits) : 0u;
+          col = slot == 0 || owner[slot] != owner[slot - 1] || at >> 4 != prev >> 4;
+          piece = col || at != prev;
+        }
+        const uint64_t col_votes = __ballot(col), votes = __ballot(piece);
+        if (lane == 0) { col_heads[chunk] = col_votes; heads[chunk] = votes; }
+      }
+      if (tid == 0) { col_heads[chunks] = 0u; heads[chunks] = 0u; }
+      __syncthreads();
+      if (wave == 0) {
+        uint32_t sum = 0;
+        for (int k = 0; k <= chunks; k += 64) {
+          const uint32_t n = k + lane < chunks ? (uint32_t)__popcll(heads[k + lane]) << 16 | (uint32_t)__popcll(col_heads[k + lane]) : 0u;
+          uint32_t s = n;
+          for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t below = __shfl_up(s, o, 64);
+            if (lane >= o) s += below;
+          }
+          if (k + lane <= chunks) before[k + lane] = sum + s - n;
+          sum += read_lane(s, 63);
+        }
+      }
+      __syncthreads();
+      auto count = [&](int slot) {  // of heads below a slot: pieces << 16 | columns
+        const uint64_t below = (1ull << (slot & 63)) - 1ull;
+        return before[slot >> 6] + ((uint32_t)__popcll(heads[slot >> 6] & below) << 16 | (uint32_t)__popcll(col_heads[slot >> 6] & below));
+      };
+      part();
+      for (int p = p0 + tid; p < p1; p += kLiThreads)  // (of the owner's heads before its first slot)
+        singles[p] -= count((int)(slot0[p] - base));
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < kSortChunks; ++i) {
+        const int slot = 64 * (wave + i * kLiWaves) + lane;
+        if (slot < n_keys) {
+          const uint32_t p = owner[slot], list = first[p], n_list = first[p + 1] - list;
+          const int s1 = (int)(slot0[p + 1] - base);
+          const uint32_t at = n_list - (uint32_t)(s1 - slot);  // in the list
+          out[list + at] = make_uint2((key[i] >> a.k_bits) & pos_mask, key_values[slot]);
+          const uint64_t votes = heads[slot >> 6], bit = 1ull << lane;
+          if (votes & bit) {
+            const uint32_t k = singles[p] + count(slot);
+            if (col_heads[slot >> 6] & bit) cols[list + (k & 0xffffu)] = (key[i] >> (a.pos_bits + a.k_bits)) + 1u;
+            int chunk = slot >> 6;
+            uint64_t next = votes & ~bit & ~(bit - 1ull);
+            while (next == 0ull && chunk + 1 < chunks) next = heads[++chunk];
+            int end = next != 0ull ? 64 * chunk + __builtin_ctzll(next) : n_keys;  // (the next owner's first key is a head)
+            const bool last = end >= s1 || ((col_heads[end >> 6] >> (end & 63)) & 1ull);
+            const uint32_t size = (uint32_t)(end - slot);
+            pieces[list + (k >> 16)] = at | (n_list <= 64u * kLiChunks ? size << 12 : 0u) | (last ? kLast : 0u);
+            if (size > 1u) atomicMax(&longest[p], size);
+          }
+        }
+      }
+      __syncthreads();
+      for (int p = p0 + tid; p < p1; p += kLiThreads) {
+        const uint32_t k = singles[p] + count((int)(slot0[p + 1] - base));
+        uint32_t *rec = a.rec + ((int64_t)blockIdx.x * P + p) * kRecord;
+        rec[0] = first[p];
+        rec[1] = first[p + 1] - first[p];
+        rec[2] = k & 0xffffu;
+        rec[3] = k >> 16;
+        rec[4] = longest[p];
+      }
+    } else if (wave == 0) {  // one owner: the pairs from memory
+      const uint32_t list = first[p0], n_list = first[p0 + 1] - list;
+      uint32_t n = singles[p0] & 0xffffu, m = singles[p0] >> 16, prior = kNoEntry, open = 0;  // open: where the last piece begins
+      bool any = false;
+      for (uint32_t i = n_list - (uint32_t)n_keys; i < n_list; i += 64) {
+        const bool in = i + lane < n_list;
+        const uint32_t pair = in ? out[list + i + lane].x : 0u;
+        const uint32_t at = in ? place_of(pair) : kNoEntry - 16u;
+        const uint32_t prev = (uint32_t)__builtin_amdgcn_update_dpp((int)prior, (int)at, 0x138, 0xF, 0xF, false);  // wave_shr:1
+        prior = read_lane(at, 63);
+        const uint64_t col_votes = __ballot(at >> 4 != prev >> 4 && in), votes = __ballot(at != prev && in);
+        const uint64_t below = (1ull << lane) - 1ull;
+        if (in) {
+          out[list + i + lane].x = pair & pos_mask;
+          if ((col_votes >> lane) & 1ull) cols[list + n + __popcll(col_votes & below)] = (at >> 4) + 1u;
+          if ((votes >> lane) & 1ull) {
+            const uint64_t above = votes & ~below & ~(1ull << lane);
+            const bool last = above != 0ull && ((col_votes >> __builtin_ctzll(above)) & 1ull);
+            pieces[list + m + __popcll(votes & below)] = i + lane | (last ? kLast : 0u);
+          }
+        }
+        if (votes != 0ull) {  // the piece before: this chunk's last one waits for the next
+          if (any && lane == 0 && ((col_votes >> __builtin_ctzll(votes)) & 1ull)) pieces[list + m - 1u] = open | kLast;
+          open = i + 63u - (uint32_t)__builtin_clzll(votes);
+          any = true;
+        }
+        n += (uint32_t)__popcll(col_votes);
+        m += (uint32_t)__popcll(votes);
+      }
+      if (lane == 0) {
+        pieces[list + m - 1u] = open | kLast;
+        uint32_t *rec = a.rec + ((int64_t)blockIdx.x * P + p0) * kRecord;
+        rec[0] = list;
+        rec[1] = n_list;
+        rec[2] = n;
+        rec[3] = m;
+        rec[4] = 0u;  // (of no use in a list as long as that)
+      }
+    }
+    __syncthreads();
+    p0 = p1;
   }
 }
 
@@ -371,9 +610,9 @@ struct ListArgs {
   const int32_t *col_idx;
   const float *vals;
   const RowPlan *plan;     // [iterations][nvec * B] of this launch
-  const uint32_t *off;     // of this launch
+  const uint32_t *rec;     // of this launch
   uint2 *ent;
-  const uint32_t *cols, *n_cols;
+  const uint32_t *cols;
   uint32_t *pieces;
   int64_t cap;
   const float *mu, *ws;    // the owners' order, here and below
@@ -457,9 +696,6 @@ __global__ __launch_bounds__(kLiThreads) void list_epoch_kernel(ListArgs a) {
     slot[q] = (q * P + p) * kLiWaves + wave;
     has_row[q] = slot[q] < total_rows;
   }
-  auto buffer = [](const void *from, uint32_t bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(from), 0, (int)bytes, 0x00027000);
-  };
   typedef uint32_t words4 __attribute__((ext_vector_type(4)));
   typedef uint32_t words2 __attribute__((ext_vector_type(2)));
   words4 row[kLiRows];   // a RowPlan: first entry, end, label, snapshot slope
@@ -491,24 +727,21 @@ __global__ __launch_bounds__(kLiThreads) void list_epoch_kernel(ListArgs a) {
     int32_t n;       // entries
     int32_t cols;    // columns
     int32_t pieces;  // runs of one column and one block of batch positions
+    int32_t longest; // entries of the longest one
   };
-  // lane l: the list's first entry, its end, its number of columns, of pieces (l = 0 .. 3)
+  // lane l: word l of the list's record
   auto bounds_of = [&](int t, int v) {
-    const int64_t k = (int64_t)(t - a.it0) * a.nvec + v;
-    const uint32_t *from = lane & 2 ? a.n_cols + (k * P + p) * 2 : a.off + k * (P + 1) + p;
-    return from[lane & 1];
+    return a.rec[(((int64_t)(t - a.it0) * a.nvec + v) * P + p) * kRecord + (lane < kRecord ? lane : 0)];
   };
   auto list_of = [&](int t, int v, uint32_t b) {
-    const uint32_t first = read_lane(b, 0);
-    return List{((int64_t)(t - a.it0) * a.nvec + v) * a.cap + first, (int32_t)(read_lane(b, 1) - first), (int32_t)read_lane(b, 2),
-                (int32_t)read_lane(b, 3)};
+    return List{((int64_t)(t - a.it0) * a.nvec + v) * a.cap + read_lane(b, 0), (int32_t)read_lane(b, 1), (int32_t)read_lane(b, 2),
+                (int32_t)read_lane(b, 3), (int32_t)read_lane(b, 4)};
   };
   auto is_long = [&](const List &l) { return l.n > 64 * kLiChunks || l.pieces > 64 * kLiPairs; };
   words2 ent[kLiChunks], ent_n[kLiChunks];
   uint32_t col[kLiPairs], col_n[kLiPairs];  // lc + 1; a lane without a column: 0
-  // first entry and kLast, then (sized) the length from bit 12 on as well; a lane without a piece: 0
-  uint32_t piece[kLiPairs], piece_n[kLiPairs];
-  List list{0, 0, 0, 0}, list_n{0, 0, 0, 0};
+  uint32_t piece[kLiPairs], piece_n[kLiPairs];  // a lane without a piece: 0
+  List list{0, 0, 0, 0, 0}, list_n{0, 0, 0, 0, 0};
   uint32_t bounds = 0;
   auto fetch_list = [&](const List &l, words2 (&e)[kLiChunks], uint32_t (&c)[kLiPairs], uint32_t (&f)[kLiPairs]) {
 #pragma unroll
@@ -526,24 +759,6 @@ __global__ __launch_bounds__(kLiThreads) void list_epoch_kernel(ListArgs a) {
         f[k] = __builtin_amdgcn_raw_buffer_load_b32(buffer(a.pieces + l.at, 4u * (uint32_t)l.pieces), 4 * lane + 256 * k, 0, 0);
     }
   };
-  // the pieces' lengths, and the longest one (of a list that is not long: entries and lengths are below 2^12)
-  auto size_pieces = [&](const List &l, uint32_t (&f)[kLiPairs]) {
-    uint32_t longest = 0;
-#pragma unroll
-    for (int k = 0; k < kLiPairs; ++k) {
-      if (k * 64 < l.pieces) {
-        uint32_t next = (uint32_t)l.n;
-        if ((k + 1) * 64 < l.pieces) next = read_lane(f[k + 1 < kLiPairs ? k + 1 : k], 0) & ~kLast;
-        uint32_t after = (uint32_t)__builtin_amdgcn_update_dpp((int)next, (int)f[k], 0x130, 0xF, 0xF, false) & ~kLast;  // wave_shl:1
-        if (k * 64 + lane + 1 >= l.pieces) after = (uint32_t)l.n;
-        const uint32_t size = k * 64 + lane < l.pieces ? after - (f[k] & ~kLast) : 0u;
-        f[k] |= size << 12;
-        longest = size > longest ? size : longest;
-      }
-    }
-    return (int)wave_max((float)longest);
-  };
-  int longest = 0, longest_n = 0;
   // the coming iteration's touched columns, each once
   auto mark = [&](int t, uint32_t lc1) {
     bool first = false;
@@ -595,7 +810,6 @@ __global__ __launch_bounds__(kLiThreads) void list_epoch_kernel(ListArgs a) {
   }
   fetch_list(list_n, ent_n, col_n, piece_n);
   if (listed) mark_list(a.it0, list_n, col_n);
-  if (!is_long(list_n)) longest_n = size_pieces(list_n, piece_n);
   if (adds_shared) mark_from(a.it0, list_of(a.it0, a.N, bounds_of(a.it0, a.N)), 0);
   fetch_rows(a.it0);
   fetch_pairs();
@@ -625,7 +839,6 @@ __global__ __launch_bounds__(kLiThreads) void list_epoch_kernel(ListArgs a) {
     for (int r = 0; r < kLiChunks; ++r) ent[r] = ent_n[r];
 #pragma unroll
     for (int k = 0; k < kLiPairs; ++k) { col[k] = col_n[k]; piece[k] = piece_n[k]; }
-    longest = longest_n;
     // ---- 1. the rows' margins and slope differences
     __builtin_amdgcn_s_setprio(3);
     {
@@ -684,7 +897,7 @@ __global__ __launch_bounds__(kLiThreads) void list_epoch_kernel(ListArgs a) {
       const int t1 = more ? t + 1 : t;  // (the last one's own again, to no purpose)
       fetch_rows(t1);
       list_n = list_of(t1, wave, bounds);
-      if (!listed) list_n.n = list_n.cols = list_n.pieces = 0;
+      if (!listed) list_n.n = list_n.cols = list_n.pieces = list_n.longest = 0;
       fetch_list(list_n, ent_n, col_n, piece_n);
       bounds = bounds_of(t + 2 < a.it1 ? t + 2 : t1, listed ? wave : 0);
     }
@@ -731,16 +944,17 @@ __global__ __launch_bounds__(kLiThreads) void list_epoch_kernel(ListArgs a) {
           a.ent[l.at + i + lane].y = __float_as_uint(__uint_as_float((uint32_t)f) * __uint_as_float(e.y));
       }
       __threadfence_block();  // other lanes read the products
+      auto begin_of = [&](uint32_t f) { return (int32_t)(f & (l.n > 64 * kLiChunks ? ~kLast : 0xfffu)); };
       float open = 0.0f;
       bool closed = true;
       int n = 0;
       for (int i = 0; i < l.pieces; i += 64) {
         const bool in = i + lane < l.pieces;
         const uint32_t f = in ? a.pieces[l.at + i + lane] : 0u;
-        const int32_t end = i + lane + 1 < l.pieces ? (int32_t)(a.pieces[l.at + i + lane + 1] & ~kLast) : l.n;
+        const int32_t end = i + lane + 1 < l.pieces ? begin_of(a.pieces[l.at + i + lane + 1]) : l.n;
         float part = 0.0f;
         if (in)
-          for (int32_t k = (int32_t)(f & ~kLast); k < end; ++k) part += __uint_as_float(a.ent[l.at + k].y);
+          for (int32_t k = begin_of(f); k < end; ++k) part += __uint_as_float(a.ent[l.at + k].y);
         const uint64_t ends = __ballot((f & kLast) != 0u);
         const float s = sum_pieces(part, ends, open, closed);
         if ((ends >> lane) & 1ull) a.pieces[l.at + n + __popcll(ends & ((1ull << lane) - 1ull))] = __builtin_bit_cast(uint32_t, s);
@@ -790,18 +1004,18 @@ __global__ __launch_bounds__(kLiThreads) void list_epoch_kernel(ListArgs a) {
           if (k * 64 < list.pieces) {
             const int first = (int)(piece[k] & 0xfffu), size = (int)((piece[k] >> 12) & 0xfffu);
             float s = mine[first];
-            if (longest > 1) {  // uniform
+            if (list.longest > 1) {  // uniform
               auto from = [&](int i) { return mine + (first + i < 64 * kLiChunks ? first + i : 64 * kLiChunks); };
               // eight at a time, requested ahead, as long as a lane has them; then each lane's last ones (-0: nothing added)
               const int rest = size > 0 ? 1 + ((size - 1) & ~7) : 1;
               float last[7];
 #pragma unroll
               for (int i = 0; i < 7; ++i) last[i] = from(rest)[i];
-              if (longest > 8) {
+              if (list.longest > 8) {
                 float now[8];
 #pragma unroll
                 for (int i = 0; i < 8; ++i) now[i] = from(1)[i];
-                for (int done = 1; done + 8 <= longest; done += 8) {
+                for (int done = 1; done + 8 <= list.longest; done += 8) {
                   float next[8];
 #pragma unroll
                   for (int i = 0; i < 8; ++i) next[i] = from(done + 8)[i];
@@ -940,7 +1154,6 @@ __global__ __launch_bounds__(kLiThreads) void list_epoch_kernel(ListArgs a) {
       if (more) mark_from(t + 1, list_of(t + 1, a.N, bounds_of(t + 1, a.N)), 0);
     }
     if (more && listed) mark_list(t + 1, list_n, col_n);
-    if (!is_long(list_n)) longest_n = size_pieces(list_n, piece_n);
     // ---- 3. the scale factors (Sec. 3.2, eq. (3)), as in lpc_columns.hip
     QParams q{0.0f, 0.0f, 0.0f, 0.0f};
     if (quantizes) {
@@ -1108,7 +1321,7 @@ int bits_for(int64_t values) {  // of a number in [0, values)
 Shape shape_of(const lpc_ctx *c) {
   Shape s{};
   if (!c->csr || !c->quant || c->cfg.bits > 16 || c->cfg.N > kLiWaves || c->cfg.m < 1 || c->prob.nnz <= 0) return s;
-  s.pshift = 8;
+  s.pshift = kOwnerBits;
   const int P = 1 << s.pshift;
   const bool alpc = c->cfg.algo != LPC_ALGO_LPC;
   const int64_t rows = (int64_t)(c->cfg.N + (alpc ? 1 : 0)) * c->cfg.B, S = (c->d + 4 * P - 1) / (4 * P) * 4;
@@ -1140,7 +1353,7 @@ ListScratch lists_scratch(const lpc_ctx *c) {
   w.slope = 2 * rows;
   w.stat = 2 * N * (5 * P + kDies * kLine);
   w.state = 6 * P * s.S;
-  w.off = (size_t)list_iters(c) * (rows / c->cfg.B) * (3 * P + 1);  // the lists' bounds, then their numbers of columns and pieces
+  w.off = (size_t)list_iters(c) * (rows / c->cfg.B) * P * kRecord;
   const int64_t mean = (c->prob.nnz + c->n - 1) / c->n;
   w.entries = (size_t)list_iters(c) * rows * (size_t)(3 * mean + 16);
   return w;
@@ -1197,20 +1410,25 @@ hipError_t launch_lists_epoch(const lpc_ctx *c, const ResidentStep &rs, int32_t 
   const int P = 1 << s.pshift, nvec = c->cfg.N + (rs.alpc ? 1 : 0);
   ListBuildArgs b{};
   b.col_idx = c->prob.col_idx; b.vals = c->prob.vals; b.plan = c->s.csr_plan + (int64_t)t0 * nvec * c->cfg.B;
-  b.off = c->s.li_off; b.ent = reinterpret_cast<uint2 *>(c->s.li_ent); b.cols = c->s.li_cols;
+  b.rec = c->s.li_off; b.ent = reinterpret_cast<uint2 *>(c->s.li_ent); b.cols = c->s.li_cols;
   b.pieces = c->s.li_cols + lists_scratch(c).entries; b.block = list_block(c);
-  b.n_cols = b.off + (size_t)list_iters(c) * nvec * (P + 1); b.cap = c->list_cap;
-  b.B = c->cfg.B; b.pshift = s.pshift; b.pos_bits = c->list_pos_bits; b.k_bits = c->list_k_bits;
+  b.cap = c->list_cap;
+  b.B = c->cfg.B; b.pos_bits = c->list_pos_bits; b.k_bits = c->list_k_bits;
   b.map_words = (b.B + 31) / 32; b.loss = c->prob.loss;
   const void *build = reinterpret_cast<const void *>(&list_build_kernel);
-  const int build_lds = 4 * (kKeyCap + kOwnBins * P * b.map_words);
+  const int n_maps = kOwnBins * P * b.map_words;  // words
+  b.map_space = n_maps > kKeyCap ? n_maps : kKeyCap;
+  b.key_space = kKeyCap + kKeyCap / 4;
+  const int n_ranks = kOwnBins * P / 2 * ((b.map_words + 1) / 2);
+  if (b.key_space < n_ranks + 6 * b.B) b.key_space = n_ranks + 6 * b.B;  // ranks, and one owner's mapped entries (6 bytes)
+  const int build_lds = 4 * (b.map_space + b.key_space + 2 * b.B);
   hipError_t e = hipFuncSetAttribute(build, hipFuncAttributeMaxDynamicSharedMemorySize, build_lds);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(list_build_kernel, dim3((unsigned)((t1 - t0) * nvec)), dim3(kLiThreads), build_lds, st, b);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   ListArgs a{};
   fill_method_args(a, c, rs, t0, t1, weight);
-  a.col_idx = b.col_idx; a.vals = b.vals; a.plan = b.plan; a.off = b.off; a.ent = b.ent; a.cols = b.cols; a.n_cols = b.n_cols;
+  a.col_idx = b.col_idx; a.vals = b.vals; a.plan = b.plan; a.rec = b.rec; a.ent = b.ent; a.cols = b.cols;
   a.pieces = b.pieces; a.block = b.block; a.cap = b.cap;
   const size_t slice = (size_t)s.S * P;
   float *state = c->s.li_state;
