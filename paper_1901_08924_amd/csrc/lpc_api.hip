@@ -679,6 +679,21 @@ lpc_status lpc_dequantize_shared(lpc_ctx *ctx, const uint32_t *packed, const flo
                                       as_stream(stream)));
 }
 
+namespace {
+lpc_status exchange_impl(const lpc_ctx *c, const float *U, StreamKey key, uint32_t *packed, float *delta_out, float *u_avg,
+                         hipStream_t st) {
+  // (an average over parts of U that other workgroups still read: launches of their own)
+  const bool apart = u_avg + c->d <= U || U + (int64_t)c->cfg.N * c->d_pad <= u_avg;
+  if (exchange_at_once(c) && (apart || fused_exchange_supported(c))) {
+    int32_t slots = 0;
+    if (!own_statistics(c)) LPC_TRY_HIP(launch_vector_stats(c, U, c->d_pad, 0, c->cfg.N, nullptr, kStatsPartial, &slots, st));
+    return dev(launch_fused_exchange(c, U, slots, key, packed, delta_out, nullptr, 0.0f, nullptr, u_avg, st));
+  }
+  LPC_TRY_HIP(launch_quantize_vectors(c, U, key, packed, delta_out, st));
+  return dev(launch_dequantize_avg(c, packed, delta_out, u_avg, st));
+}
+}  // namespace
+
 lpc_status lpc_exchange(lpc_ctx *ctx, const float *U, uint32_t epoch, uint32_t iter, uint32_t *packed,
                         float *delta_out, float *u_avg, void *stream) {
   if (!ctx || !U || !packed || !delta_out || !u_avg) return LPC_ENULL;
@@ -686,17 +701,7 @@ lpc_status lpc_exchange(lpc_ctx *ctx, const float *U, uint32_t epoch, uint32_t i
   if (!aligned(U, 16) || !aligned(packed, 16) || !aligned(u_avg, 16)) return LPC_ESHAPE;
   hipStream_t st = as_stream(stream);
   const StreamKey key = key_of(ctx, epoch, iter);
-  if (fused_exchange_supported(ctx)) {
-    int32_t slots = 0;
-    if (!own_statistics(ctx))
-      LPC_TRY_HIP(launch_vector_stats(ctx, U, ctx->d_pad, 0, ctx->cfg.N, nullptr, kStatsPartial, &slots, st));
-    LPC_TRY_HIP(launch_fused_exchange(ctx, U, slots, key, packed, delta_out, nullptr, 0.0f, nullptr, u_avg, st));
-    return LPC_OK;
-  }
-  LPC_TRY_HIP(launch_vector_stats(ctx, U, ctx->d_pad, 0, ctx->cfg.N, nullptr, kStatsFinal, nullptr, st));
-  LPC_TRY_HIP(launch_quantize(ctx, U, key, packed, delta_out, nullptr, st));  // nobody reads the clip counts
-  LPC_TRY_HIP(launch_dequantize_avg(ctx, packed, delta_out, u_avg, st));
-  return LPC_OK;
+  return exchange_impl(ctx, U, key, packed, delta_out, u_avg, st);
 }
 
 // ---- lpc_exchange for callers that cannot allocate ---------------------------------------------------------
@@ -771,16 +776,7 @@ lpc_status lpc_exchange_static(int64_t d, int32_t N, int32_t bits, int32_t clip_
   s.n_clipped = reinterpret_cast<uint32_t *>(base + kStaticStatPart + kStaticStats + kStaticQParams);
   s.flags = flags_out ? flags_out : reinterpret_cast<uint32_t *>(base + kStaticBytes - kStaticFlags);
   const StreamKey key = key_of(&c, epoch, iter);
-  if (fused_exchange_supported(&c)) {
-    int32_t slots = 0;
-    if (!own_statistics(&c)) LPC_TRY_HIP(launch_vector_stats(&c, U, c.d_pad, 0, N, nullptr, kStatsPartial, &slots, st));
-    LPC_TRY_HIP(launch_fused_exchange(&c, U, slots, key, packed, delta_out, nullptr, 0.0f, nullptr, u_avg, st));
-    return LPC_OK;
-  }
-  LPC_TRY_HIP(launch_vector_stats(&c, U, c.d_pad, 0, N, nullptr, kStatsFinal, nullptr, st));
-  LPC_TRY_HIP(launch_quantize(&c, U, key, packed, delta_out, nullptr, st));
-  LPC_TRY_HIP(launch_dequantize_avg(&c, packed, delta_out, u_avg, st));
-  return LPC_OK;
+  return exchange_impl(&c, U, key, packed, delta_out, u_avg, st);
 }
 
 lpc_status lpc_prox_step(lpc_ctx *ctx, float *w, const float *u_avg, const float *mu, float step, void *stream) {

@@ -382,6 +382,7 @@ hipError_t launch_reduce_parts(const lpc_ctx *c, const float *part, int32_t part
                                hipStream_t st);
 // stats_mode values of launch_reduce_parts
 constexpr int kStatsNone = 0, kStatsFinal = 1, kStatsPartial = 2;
+bool exchange_at_once(const lpc_ctx *c);
 bool fused_exchange_supported(const lpc_ctx *c);
 bool own_statistics(const lpc_ctx *c);  // launch_fused_exchange without statistic partials (nslots = 0)
 int reduce_parts_waves(const lpc_ctx *c, int32_t parts);
@@ -422,6 +423,8 @@ hipError_t launch_prepare_qparams(const lpc_ctx *c, const double *stats, const f
                                   hipStream_t st);
 hipError_t launch_quantize(const lpc_ctx *c, const float *U, StreamKey key, uint32_t *packed, float *delta_out,
                            uint32_t *n_clipped, hipStream_t st);
+hipError_t launch_quantize_vectors(const lpc_ctx *c, const float *U, StreamKey key, uint32_t *packed, float *delta_out,
+                                   hipStream_t st);
 hipError_t launch_dequantize_avg(const lpc_ctx *c, const uint32_t *packed, const float *delta, float *u_avg,
                                  hipStream_t st);
 hipError_t launch_plain_avg(const lpc_ctx *c, const float *U, float *u_avg, hipStream_t st);

@@ -358,16 +358,12 @@ __device__ __forceinline__ uint32_t assemble_word(const int32_t *__restrict__ co
 
 // ---------------------------------------------------------------------------
 // Quantize + pack.  grid = (tiles of 8192 coordinates, N workers).
-template <int B, bool COUNT, bool SKIP>
-__global__ __launch_bounds__(kThreads) void quantize_kernel(const float *__restrict__ U, int64_t d, int64_t d_pad,
-                                                            const QParams *__restrict__ qp, StreamKey key,
-                                                            uint32_t *__restrict__ packed, int64_t W,
-                                                            float *__restrict__ delta_out,
-                                                            uint32_t *__restrict__ n_clipped) {
-  __shared__ __attribute__((aligned(16))) float tile[kThreads * kPitch];
+template <int B, bool COUNT, bool SKIP, class Params>
+__device__ __forceinline__ uint32_t quantize_tile(const float *__restrict__ U, int64_t d, int64_t d_pad, uint32_t worker,
+                                                  int64_t block, Params params, const StreamKey &key,
+                                                  uint32_t *__restrict__ packed, int64_t W, float *tile) {
   const int tid = threadIdx.x;
-  const uint32_t worker = blockIdx.y;
-  const int64_t tile_base = (int64_t)blockIdx.x * kTileFloats;
+  const int64_t tile_base = block * kTileFloats;
   const float *u = U + (int64_t)worker * d_pad;
   if (tile_base + kTileFloats <= d) {  // uniform: a tile inside the vector needs no checks
 #pragma unroll
@@ -394,9 +390,8 @@ __global__ __launch_bounds__(kThreads) void quantize_kernel(const float *__restr
       *reinterpret_cast<float4 *>(&tile[(e >> 3) * kPitch + (e & 7) * 4]) = v;
     }
   }
+  const QParams q = params();
   __syncthreads();
-  const QParams q = qp[worker];
-  if (blockIdx.x == 0 && tid == 0) delta_out[worker] = q.delta;
   const int64_t seg = tile_base / kSegFloats + tid;
   const bool active = seg * kSegFloats < d_pad;
   uint32_t clipped = 0;
@@ -405,9 +400,26 @@ __global__ __launch_bounds__(kThreads) void quantize_kernel(const float *__restr
     clipped = quantize_segment<B, COUNT, SKIP>([&](int k) { return *reinterpret_cast<const float4 *>(mine + k * 4); }, q, key,
                                          worker, seg, packed + (int64_t)worker * W + seg * B);
   }
+  return clipped;
+}
+
+template <int B, bool COUNT, bool SKIP>
+__global__ __launch_bounds__(kThreads) void quantize_kernel(const float *__restrict__ U, int64_t d, int64_t d_pad,
+                                                            const QParams *__restrict__ qp, StreamKey key,
+                                                            uint32_t *__restrict__ packed, int64_t W,
+                                                            float *__restrict__ delta_out,
+                                                            uint32_t *__restrict__ n_clipped) {
+  __shared__ __attribute__((aligned(16))) float tile[kThreads * kPitch];
+  const uint32_t worker = blockIdx.y;
+  auto params = [&] {
+    const QParams q = qp[worker];
+    if (blockIdx.x == 0 && threadIdx.x == 0) delta_out[worker] = q.delta;
+    return q;
+  };
+  uint32_t clipped = quantize_tile<B, COUNT, SKIP>(U, d, d_pad, worker, blockIdx.x, params, key, packed, W, tile);
   if (COUNT) {
     clipped = wave_sum(clipped);
-    if ((tid & 63) == 0 && clipped) atomicAdd(&n_clipped[worker], clipped);
+    if ((threadIdx.x & 63) == 0 && clipped) atomicAdd(&n_clipped[worker], clipped);
   }
 }
 
@@ -420,27 +432,21 @@ __global__ __launch_bounds__(kThreads) void quantize_kernel(const float *__restr
 // message with a grid stride and request their next word's coordinates ahead (8 to 10 % slower than a thread per
 // word: fresh workgroups cost less than the loop).  Codes, draws and bit layout are those of quantize_kernel.
 // grid = (words of a message / kThreads, N workers).
-template <int B, bool COUNT, bool SKIP>
-__global__ __launch_bounds__(kThreads) void quantize_word_kernel(const float *__restrict__ U, int64_t d, int64_t d_pad,
-                                                                 const QParams *__restrict__ qp, StreamKey key,
-                                                                 uint32_t *__restrict__ packed, int64_t W,
-                                                                 float *__restrict__ delta_out,
-                                                                 uint32_t *__restrict__ n_clipped) {
-  touch_kernel_arguments<(int)(80)>();
+template <int B, bool COUNT, bool SKIP, class Params>
+__device__ __forceinline__ uint32_t quantize_word(const float *__restrict__ U, int64_t d, int64_t d_pad, uint32_t worker,
+                                                  int64_t t, Params params, const StreamKey &key,
+                                                  uint32_t *__restrict__ packed, int64_t W) {
   static_assert(B == 2 || B == 4 || B == 8, "a word holds whole groups of four codes");
   constexpr int kCoords = 32 / B;  // coordinates per word
   constexpr int kBlocks = kCoords / 4;
   constexpr uint32_t mask = (1u << B) - 1u;
-  const uint32_t worker = blockIdx.y;
-  const QParams q = qp[worker];
-  if (blockIdx.x == 0 && threadIdx.x == 0) delta_out[worker] = q.delta;
-  const int64_t t = (int64_t)blockIdx.x * kThreads + threadIdx.x;  // word of the message
   uint32_t clipped = 0;
-  if (t < W) {  // W * kCoords == d_pad: every load stays inside the vector's d_pad floats
-    const float *u = U + (int64_t)worker * d_pad;
-    float4 v[kBlocks];
+  const float *u = U + (int64_t)worker * d_pad;
+  float4 v[kBlocks];  // W * kCoords == d_pad: every load stays inside the vector's d_pad floats
 #pragma unroll
-    for (int k = 0; k < kBlocks; ++k) v[k] = *reinterpret_cast<const float4 *>(u + t * kCoords + 4 * k);
+  for (int k = 0; k < kBlocks; ++k) v[k] = *reinterpret_cast<const float4 *>(u + (t < W ? t : W - 1) * kCoords + 4 * k);
+  const QParams q = params();
+  if (t < W) {
     const int64_t j0 = t * kCoords;
     if (j0 + kCoords > d) {  // the zero padding of the last segment carries code 0 whatever the buffer holds
 #pragma unroll
@@ -492,10 +498,76 @@ __global__ __launch_bounds__(kThreads) void quantize_word_kernel(const float *__
     }
     packed[(int64_t)worker * W + t] = word;
   }
+  return clipped;
+}
+
+template <int B, bool COUNT, bool SKIP>
+__global__ __launch_bounds__(kThreads) void quantize_word_kernel(const float *__restrict__ U, int64_t d, int64_t d_pad,
+                                                                 const QParams *__restrict__ qp, StreamKey key,
+                                                                 uint32_t *__restrict__ packed, int64_t W,
+                                                                 float *__restrict__ delta_out,
+                                                                 uint32_t *__restrict__ n_clipped) {
+  touch_kernel_arguments<(int)(80)>();
+  const uint32_t worker = blockIdx.y;
+  auto params = [&] {
+    const QParams q = qp[worker];
+    if (blockIdx.x == 0 && threadIdx.x == 0) delta_out[worker] = q.delta;
+    return q;
+  };
+  const int64_t t = (int64_t)blockIdx.x * kThreads + threadIdx.x;  // word of the message
+  uint32_t clipped = quantize_word<B, COUNT, SKIP>(U, d, d_pad, worker, t, params, key, packed, W);
   if (COUNT) {
     clipped = wave_sum(clipped);
     if ((threadIdx.x & 63) == 0 && clipped) atomicAdd(&n_clipped[worker], clipped);
   }
+}
+
+// ---------------------------------------------------------------------------
+// Quantize + pack where a vector has few statistic partials and few workgroups (launch_quantize_vectors): each workgroup folds
+// its vector's partials itself (one wavefront, finalize_stats_kernel's order) while its coordinates travel; the first one of
+// a vector leaves the results as that kernel does.  grid = (as the kernels above, N workers).
+template <int B, bool SUMS>
+__global__ __launch_bounds__(kThreads) void fold_quantize_kernel(const float *__restrict__ U, int64_t d, int64_t d_pad,
+                                                                 StatSinks sk, QuantSpec qs, int32_t nslots, StreamKey key,
+                                                                 uint32_t *__restrict__ packed, int64_t W,
+                                                                 float *__restrict__ delta_out) {
+  touch_kernel_arguments<(int)(sizeof(StatSinks) + sizeof(QuantSpec) + sizeof(StreamKey) + 56)>();
+  constexpr bool kWords = 32 % (4 * B) == 0;
+  __shared__ QParams q_sh;
+  __shared__ __attribute__((aligned(16))) float tile[kWords ? 4 : kThreads * kPitch];
+  const int tid = threadIdx.x;
+  const uint32_t worker = blockIdx.y;
+  auto params = [&] {
+    if (tid < 64) {
+      const double *p = sk.stat_part + (int64_t)worker * sk.stat_slots * 4;
+      double amax = 0.0, sum = 0.0, sumsq = 0.0, bad = 0.0;
+      if (SUMS || blockIdx.x == 0) {
+        fold_stat_slots(p, nslots, tid, amax, sum, sumsq, bad);
+      } else {  // clipping by lambda wants the largest magnitude only
+        float mx = 0.0f;
+        for (int k = tid; k < nslots; k += 64) mx = fmaxf(mx, (float)p[4 * k]);
+        amax = (double)wave_max(mx);
+      }
+      const QParams q = make_qparams(qs, amax, sum, sumsq, d);
+      if (tid == 0) {
+        q_sh = q;
+        if (blockIdx.x == 0) {
+          double *o = sk.stats + (int64_t)worker * 4;
+          o[0] = amax; o[1] = sum; o[2] = sumsq; o[3] = bad;
+          if (bad > 0.0) atomicOr(&sk.flags[0], 1u);
+          sk.qparams[worker] = q;
+          sk.n_clipped[worker] = 0u;
+          delta_out[worker] = q.delta;
+        }
+      }
+    }
+    __syncthreads();
+    return q_sh;
+  };
+  if constexpr (kWords)
+    quantize_word<B, false, false>(U, d, d_pad, worker, (int64_t)blockIdx.x * kThreads + tid, params, key, packed, W);
+  else
+    quantize_tile<B, false, false>(U, d, d_pad, worker, blockIdx.x, params, key, packed, W, tile);
 }
 
 // ---------------------------------------------------------------------------
@@ -1992,8 +2064,9 @@ hipError_t launch_finalize_stats(const lpc_ctx *c, int32_t vec_begin, int32_t nv
   return hipGetLastError();
 }
 
-hipError_t launch_vector_stats(const lpc_ctx *c, const float *U, int64_t ld, int32_t vec_begin, int32_t nvec,
-                               double *stats_out, int stats_mode, int32_t *slots_used, hipStream_t st) {
+namespace {
+// Coordinates per statistic partial, and the number of partials of a vector.
+int64_t stat_chunks(const lpc_ctx *c, int64_t *out) {
   // 1K..32K coordinates per workgroup: short vectors spread wide (latency), long ones keep the number of
   // statistic partials (and of fenced arrivals) small
   int64_t chunk = ((c->d / 64 + 1023) / 1024) * 1024;
@@ -2004,6 +2077,15 @@ hipError_t launch_vector_stats(const lpc_ctx *c, const float *U, int64_t ld, int
     chunk = (((c->d + slots - 1) / slots) + 3) / 4 * 4;
     slots = (c->d + chunk - 1) / chunk;
   }
+  *out = chunk;
+  return slots;
+}
+}  // namespace
+
+hipError_t launch_vector_stats(const lpc_ctx *c, const float *U, int64_t ld, int32_t vec_begin, int32_t nvec,
+                               double *stats_out, int stats_mode, int32_t *slots_used, hipStream_t st) {
+  int64_t chunk;
+  const int64_t slots = stat_chunks(c, &chunk);
   const dim3 grid((unsigned)slots, (unsigned)nvec);
   hipLaunchKernelGGL(vector_stats_kernel, grid, dim3(kThreads), 0, st, U, ld, c->d, chunk, vec_begin,
                      sinks_of(c, stats_out));
@@ -2071,6 +2153,43 @@ void dequantize_launch(const lpc_ctx *c, const uint32_t *packed, const float *de
 hipError_t launch_quantize(const lpc_ctx *c, const float *U, StreamKey key, uint32_t *packed, float *delta_out,
                            uint32_t *n_clipped, hipStream_t st) {
 #define CALL(BITS) quantize_launch<BITS>(c, U, key, packed, delta_out, n_clipped, st)
+  LPC_DISPATCH_BITS(c->cfg.bits, CALL)
+#undef CALL
+  return hipGetLastError();
+}
+
+namespace {
+template <int B>
+void fold_quantize_launch(const lpc_ctx *c, const float *U, int32_t slots, StreamKey key, uint32_t *packed, float *delta_out,
+                          hipStream_t st) {
+  const int64_t wgs = 32 % (4 * B) == 0 ? (c->W + kThreads - 1) / kThreads : (c->d_pad + kTileFloats - 1) / kTileFloats;
+  const dim3 grid((unsigned)wgs, (unsigned)c->cfg.N);
+  if (c->cfg.clip_mode == LPC_CLIP_LAMBDA)
+    hipLaunchKernelGGL((fold_quantize_kernel<B, false>), grid, dim3(kThreads), 0, st, U, c->d, c->d_pad, sinks_of(c, nullptr),
+                       spec_of(c), slots, key, packed, c->W, delta_out);
+  else
+    hipLaunchKernelGGL((fold_quantize_kernel<B, true>), grid, dim3(kThreads), 0, st, U, c->d, c->d_pad, sinks_of(c, nullptr),
+                       spec_of(c), slots, key, packed, c->W, delta_out);
+}
+}  // namespace
+
+// Statistics of N vectors, quantize + pack (nobody reads clip counts).  Up to kFoldCoords coordinates in all, the quantizer's
+// workgroups derive the scale factors: a launch less.  Whole exchanges back to back, us (launch -> quantizer): d = 60000 13.4
+// -> 12.5 (N = 2 to 16), d = 400000, N = 8 15.8 -> 15.1, d = 10^6, N = 5 19.0 -> 18.3, and 15.3 -> 12.5 below 300000 where a
+// slower host issues the launches; from 8 M on the folds cost what the launch did (N = 8, d = 10^6: 24.3 -> 24.5; N = 16,
+// d = 4.2 M: 114 -> 134).  Two launches that each held the quantizer of some vectors beside
+// the statistics of others were no faster than one after the other.
+constexpr int64_t kFoldCoords = (int64_t)6 << 20;
+hipError_t launch_quantize_vectors(const lpc_ctx *c, const float *U, StreamKey key, uint32_t *packed, float *delta_out,
+                                   hipStream_t st) {
+  if (c->csr || (int64_t)c->cfg.N * c->d_pad > kFoldCoords) {
+    const hipError_t e = launch_vector_stats(c, U, c->d_pad, 0, c->cfg.N, nullptr, kStatsFinal, nullptr, st);
+    return e == hipSuccess ? launch_quantize(c, U, key, packed, delta_out, nullptr, st) : e;
+  }
+  int32_t slots = 0;
+  const hipError_t e = launch_vector_stats(c, U, c->d_pad, 0, c->cfg.N, nullptr, kStatsPartial, &slots, st);
+  if (e != hipSuccess) return e;
+#define CALL(BITS) fold_quantize_launch<BITS>(c, U, slots, key, packed, delta_out, st)
   LPC_DISPATCH_BITS(c->cfg.bits, CALL)
 #undef CALL
   return hipGetLastError();
@@ -2184,6 +2303,11 @@ int warm_setup(const lpc_ctx *c, StreamKey key, bool shared, FusedArgs *a) {
 bool fused_exchange_supported(const lpc_ctx *c) {
   return c->quant && c->cfg.N <= kFusedMaxN && c->stat_slots <= 256 && c->d_pad <= 16384;
 }
+
+// An exchange by itself (its partials: vector_stats_kernel's): as long as the launch has a workgroup per CU at most.  Statistics,
+// scale factors, quantizer and receiver in launches of their own -> two launches, back to back, us: d = 17000 13.0 -> 10.1,
+// d = 32768 12.8 -> 10.2 (N = 2 to 16); two workgroups per CU, d = 40000 to 60000 and N = 16: 12.6 with the scale factors in the quantizer, 14.5 here.
+bool exchange_at_once(const lpc_ctx *c) { return c->quant && c->cfg.N <= kFusedMaxN && c->d_pad <= 256 * kFusedCoords; }
 
 // One launch for eq. (3), quantize, pack, eq. (4) and (optionally) the proximal step; reads the statistic
 // partials left by launch_reduce_parts(..., kStatsPartial, ...) for vectors 0..N-1.

@@ -138,6 +138,41 @@ def test_products_use_all_24_bits_of_their_operands(M, N, K):
     assert np.array_equal(got, A.astype(np.float64) @ B.astype(np.float64))
 
 
+@pytest.mark.parametrize("mode", [lpco.CLIP_LAMBDA, lpco.CLIP_CSIGMA])
+@pytest.mark.parametrize("d,N,bits", [(16385, 64, 2), (32768, 5, 3), (32769, 16, 4), (50_001, 65, 8), (100_003, 3, 7),
+                                      (786_432, 8, 4), (786_433, 8, 6), (300_000, 2, 16), (32_700, 2, 11)])
+def test_exchange_of_longer_vectors_equals_the_separate_calls(d, N, bits, mode):
+    """Around the lines between the launches an exchange takes: messages, scale factors, average and flags bit for bit, with
+    a vector of zeros, one with a NaN, and an average that overwrites a vector."""
+    import torch
+    sp = lpc_synth.make("c1", n=max(64, N), d=d, N=N, B=1, bits=bits, seed=3)
+    ctx = gpu_context(sp, bits=bits, clip_mode=mode, clip=0.9, m=1)
+    outs = []
+    for separate in (False, True):
+        for special in (False, True):
+            U = to_dev(lpc_synth.gaussian_u(N, d, seed=d + N))
+            if special:
+                U[0] = 0.0
+                U[N - 1, d // 2] = float("nan")
+            packed = torch.empty(N, ctx.W, dtype=torch.int32, device="cuda")
+            delta, avg = torch.empty(N, device="cuda"), torch.empty(d, device="cuda")
+            if separate:
+                stats = torch.empty(N, 4, dtype=torch.float64, device="cuda")
+                ctx.vector_stats(U, N, stats)
+                ctx.quantize_clip(U, stats, None, 1, 2, packed, delta)
+                ctx.dequantize_avg(packed, delta, avg)
+            else:
+                if special:  # 16 bytes past a row's start
+                    avg = U.view(-1)[4:4 + d]
+                ctx.exchange(U, 1, 2, packed, delta, avg)
+            outs.append([t.cpu().numpy() for t in (packed, delta, avg)] + [ctx.take_device_flags()])
+    for a, b in zip(outs[:2], outs[2:]):
+        for x, y in zip(a, b):
+            assert np.array_equal(x, y)
+    assert outs[0][3] == 0 and outs[1][3] != 0
+    ctx.close()
+
+
 @pytest.mark.parametrize("d,N", [(1, 8), (1023, 8), (1024, 8), (1025, 4), (1025, 5), (4097, 1), (8192, 1), (8193, 1)])
 def test_exchange_takes_the_same_statistics_itself(d, N):
     """Short vectors' exchange derives its statistics in its own launch: the outputs of the separate calls, bit for bit,
