@@ -468,8 +468,9 @@ lpc_status record_iteration(lpc_ctx *c, int32_t t, hipStream_t st) {
 }
 
 // communication step 2 of one inner iteration followed by the update of Alg. 1
-// (want_clip_counts: an evaluation run records them; the quantizer is quicker without)
-lpc_status exchange_and_prox(lpc_ctx *c, StreamKey key, float *w, bool want_clip_counts, hipStream_t st) {
+// (want_clip_counts: an evaluation run records them; the quantizer is quicker without; partials > 0: the vectors' statistics
+// are that many partials each)
+lpc_status exchange_and_prox(lpc_ctx *c, StreamKey key, float *w, bool want_clip_counts, int32_t partials, hipStream_t st) {
   Scratch &s = c->s;
   ProfScope ps(c, LPC_PROF_EXCHANGE, st);
   if (c->quant && c->cfg.scheme != LPC_SCHEME_A) {
@@ -479,7 +480,8 @@ lpc_status exchange_and_prox(lpc_ctx *c, StreamKey key, float *w, bool want_clip
     LPC_TRY_HIP(launch_dequantize_shared(c, s.packed, s.delta, c->cfg.scheme == LPC_SCHEME_C, key, s.u_avg, st));
     LPC_TRY_HIP(launch_prox(c, w, s.u_avg, s.mu, c->cfg.eta, st));
   } else if (c->quant) {
-    LPC_TRY_HIP(launch_quantize(c, s.U, key, s.packed, s.delta, want_clip_counts ? s.n_clipped : nullptr, st));
+    if (partials > 0) LPC_TRY_HIP(launch_quantize_partials(c, s.U, partials, key, s.packed, s.delta, st));
+    else LPC_TRY_HIP(launch_quantize(c, s.U, key, s.packed, s.delta, want_clip_counts ? s.n_clipped : nullptr, st));
     LPC_TRY_HIP(launch_dequantize_prox(c, s.packed, s.delta, s.mu, c->cfg.eta, w, nullptr, st));
   } else {
     LPC_TRY_HIP(launch_plain_avg(c, s.U, s.u_avg, st));
@@ -953,11 +955,13 @@ lpc_status lpc_epoch(lpc_ctx *ctx, float *w_snap, float *y, float *z, uint32_t e
         LPC_TRY_HIP(launch_fused_exchange(c, s.U, slots, key, s.packed, s.delta, s.mu, g.eta, s.w, nullptr, st));
       } else {
         c->at_snapshot = t == 0;  // x_0 = x~ (only the column-tile worker pass needs telling)
+        const bool fold = c->mlp && c->quant && g.scheme == LPC_SCHEME_A && !tracing;  // (by the quantizer, if that pays)
+        int32_t slots = 0;
         const lpc_status rc = vr_grad_impl(c, s.w, w_snap, zs, key, kTagBatch, 0, g.N, s.U, nullptr,
-                                           c->quant ? kStatsFinal : kStatsNone, st);
+                                           fold ? kStatsPartial : c->quant ? kStatsFinal : kStatsNone, st, &slots);
         c->at_snapshot = false;
         LPC_TRY(rc);
-        LPC_TRY(exchange_and_prox(c, key, s.w, tracing, st));
+        LPC_TRY(exchange_and_prox(c, key, s.w, tracing, fold ? slots : 0, st));
         if (tracing) LPC_TRY(record_iteration(c, t, st));
       }
     }

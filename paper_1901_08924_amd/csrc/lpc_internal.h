@@ -423,6 +423,8 @@ hipError_t launch_prepare_qparams(const lpc_ctx *c, const double *stats, const f
                                   hipStream_t st);
 hipError_t launch_quantize(const lpc_ctx *c, const float *U, StreamKey key, uint32_t *packed, float *delta_out,
                            uint32_t *n_clipped, hipStream_t st);
+hipError_t launch_quantize_partials(const lpc_ctx *c, const float *U, int32_t slots, StreamKey key, uint32_t *packed,
+                                    float *delta_out, hipStream_t st);
 hipError_t launch_quantize_vectors(const lpc_ctx *c, const float *U, StreamKey key, uint32_t *packed, float *delta_out,
                                    hipStream_t st);
 hipError_t launch_dequantize_avg(const lpc_ctx *c, const uint32_t *packed, const float *delta, float *u_avg,

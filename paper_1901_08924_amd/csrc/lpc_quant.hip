@@ -2159,11 +2159,14 @@ hipError_t launch_quantize(const lpc_ctx *c, const float *U, StreamKey key, uint
 }
 
 namespace {
+// workgroups of a vector
+int64_t quantizer_wgs(const lpc_ctx *c) {
+  return 32 % (4 * c->cfg.bits) == 0 ? (c->W + kThreads - 1) / kThreads : (c->d_pad + kTileFloats - 1) / kTileFloats;
+}
 template <int B>
 void fold_quantize_launch(const lpc_ctx *c, const float *U, int32_t slots, StreamKey key, uint32_t *packed, float *delta_out,
                           hipStream_t st) {
-  const int64_t wgs = 32 % (4 * B) == 0 ? (c->W + kThreads - 1) / kThreads : (c->d_pad + kTileFloats - 1) / kTileFloats;
-  const dim3 grid((unsigned)wgs, (unsigned)c->cfg.N);
+  const dim3 grid((unsigned)quantizer_wgs(c), (unsigned)c->cfg.N);
   if (c->cfg.clip_mode == LPC_CLIP_LAMBDA)
     hipLaunchKernelGGL((fold_quantize_kernel<B, false>), grid, dim3(kThreads), 0, st, U, c->d, c->d_pad, sinks_of(c, nullptr),
                        spec_of(c), slots, key, packed, c->W, delta_out);
@@ -2173,26 +2176,37 @@ void fold_quantize_launch(const lpc_ctx *c, const float *U, int32_t slots, Strea
 }
 }  // namespace
 
-// Statistics of N vectors, quantize + pack (nobody reads clip counts).  Up to kFoldCoords coordinates in all, the quantizer's
-// workgroups derive the scale factors: a launch less.  Whole exchanges back to back, us (launch -> quantizer): d = 60000 13.4
-// -> 12.5 (N = 2 to 16), d = 400000, N = 8 15.8 -> 15.1, d = 10^6, N = 5 19.0 -> 18.3, and 15.3 -> 12.5 below 300000 where a
-// slower host issues the launches; from 8 M on the folds cost what the launch did (N = 8, d = 10^6: 24.3 -> 24.5; N = 16,
-// d = 4.2 M: 114 -> 134).  Two launches that each held the quantizer of some vectors beside
-// the statistics of others were no faster than one after the other.
-constexpr int64_t kFoldCoords = (int64_t)6 << 20;
-hipError_t launch_quantize_vectors(const lpc_ctx *c, const float *U, StreamKey key, uint32_t *packed, float *delta_out,
-                                   hipStream_t st) {
-  if (c->csr || (int64_t)c->cfg.N * c->d_pad > kFoldCoords) {
-    const hipError_t e = launch_vector_stats(c, U, c->d_pad, 0, c->cfg.N, nullptr, kStatsFinal, nullptr, st);
+// Whether the quantizer's workgroups derive the scale factors from a vector's partials: a launch less.  Measured back to
+// back, us (launch -> quantizer): exchanges of d = 60000 13.4 -> 12.5 (N = 2 to 16), d = 400000, N = 8 15.8 -> 15.1, d = 10^6, N = 5
+// 19.0 -> 18.3 (15.3 -> 12.5 below 300000 where a slower host issues the launches); the same from 8 M coordinates in all on
+// (N = 8, d = 10^6: 24.3 -> 24.5) and worse where every workgroup reads many partials (N = 16, d = 4.2 M: 114 -> 134).  Epochs of
+// perceptrons, a partial per tile of a product: 384-127-100, N = 15 1674 -> 1641, 418-108-384-448-2, N = 4 2683 -> 2642 (130 k
+// partials read by all workgroups); 777-391-129-33, N = 6 2729 -> 2755 (950 k), hence the second line.
+// Two launches that each held the quantizer of some vectors beside the statistics of others: no faster than one after the other.
+constexpr int64_t kFoldCoords = (int64_t)6 << 20, kFoldReads = (int64_t)1 << 18;
+bool quantizer_folds(const lpc_ctx *c, int32_t slots) {
+  return !c->csr && (int64_t)c->cfg.N * c->d_pad <= kFoldCoords && c->cfg.N * quantizer_wgs(c) * slots <= kFoldReads;
+}
+
+// Quantize + pack N vectors whose statistics are `slots` partials each (nobody reads clip counts).
+hipError_t launch_quantize_partials(const lpc_ctx *c, const float *U, int32_t slots, StreamKey key, uint32_t *packed,
+                                    float *delta_out, hipStream_t st) {
+  if (!quantizer_folds(c, slots)) {
+    const hipError_t e = launch_finalize_stats(c, 0, c->cfg.N, slots, nullptr, st);
     return e == hipSuccess ? launch_quantize(c, U, key, packed, delta_out, nullptr, st) : e;
   }
-  int32_t slots = 0;
-  const hipError_t e = launch_vector_stats(c, U, c->d_pad, 0, c->cfg.N, nullptr, kStatsPartial, &slots, st);
-  if (e != hipSuccess) return e;
 #define CALL(BITS) fold_quantize_launch<BITS>(c, U, slots, key, packed, delta_out, st)
   LPC_DISPATCH_BITS(c->cfg.bits, CALL)
 #undef CALL
   return hipGetLastError();
+}
+
+// Statistics, quantize + pack of N vectors.
+hipError_t launch_quantize_vectors(const lpc_ctx *c, const float *U, StreamKey key, uint32_t *packed, float *delta_out,
+                                   hipStream_t st) {
+  int32_t slots = 0;
+  const hipError_t e = launch_vector_stats(c, U, c->d_pad, 0, c->cfg.N, nullptr, kStatsPartial, &slots, st);
+  return e == hipSuccess ? launch_quantize_partials(c, U, slots, key, packed, delta_out, st) : e;
 }
 
 hipError_t launch_dequantize_avg(const lpc_ctx *c, const uint32_t *packed, const float *delta, float *u_avg,

@@ -142,3 +142,23 @@ def test_mlp_epochs():
     for P_o, P_g, _ in hist:
         assert abs(P_g - P_o) <= 1e-4 * abs(P_o)
     assert hist[-1][0] < hist[0][0]
+
+
+@pytest.mark.parametrize("dims,N,bits,mode,clip", [((300, 129, 70, 10), 3, 4, lpco.CLIP_LAMBDA, 0.9),
+                                                   ((64, 640, 33), 5, 3, lpco.CLIP_CSIGMA, 2.0),
+                                                   ((200, 90, 9), 2, 8, lpco.CLIP_CSIGMA, 1.0),
+                                                   ((777, 391, 129, 33), 6, 8, lpco.CLIP_LAMBDA, 1.0)])  # too many partials
+def test_mlp_epoch_whose_quantizer_folds_the_statistics(dims, N, bits, mode, clip):
+    """The iterate of an epoch that nobody watches against that of a traced one, whose scale factors have a launch of their
+    own: the same operations in the same order, so the same bits."""
+    sp = lpc_synth.make("c5", n=512, dims=dims, N=N, B=16, n_full=256, m=4)
+    got = []
+    for traced in (False, True):
+        ctx = gpu_context(sp, bits=bits, clip_mode=mode, clip=clip, m=4)
+        w = to_dev(sp.w0)
+        for epoch in range(2):
+            ctx.epoch_traced(w, epoch) if traced else ctx.epoch(w, epoch)
+        assert ctx.take_device_flags() == 0
+        got.append(w.cpu().numpy())
+        ctx.close()
+    assert np.array_equal(*got) and not np.array_equal(got[0], sp.w0)
