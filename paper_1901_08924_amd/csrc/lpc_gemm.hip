@@ -23,7 +23,7 @@
 // Four kernels share the epilogue's options:
 //   gemm_tile_kernel: 128 x TN tiles of C through LDS, for products with enough tiles to occupy the chip;
 //   gemm_pair_kernel: the 128 x 128 tile by eight wavefronts, where there is about one tile per compute unit;
-//   gemm_small_kernel: 32 x 32 or 64 x 64 tiles whose sixteen or eight wavefronts split K between them, for the others;
+//   gemm_small_kernel: 32 x 32 or 64 x 64 tiles whose sixteen, eight or four wavefronts split K between them, for the others;
 //   gemm_few_kernel: sums of one or two products.
 // Operands may be given transposed (weight gradients A'D and data gradients D W' need it) and the K range may consist
 // of two segments with their own base pointers (the difference of two weight gradients is one contraction over stacked
@@ -615,12 +615,16 @@ __global__ __launch_bounds__(512, 1) void gemm_pair_kernel(GemmArgs g) {
 // wavefront whose steps ran out asked for its last one again, a line per lane.  What the stores need besides the sum (bias, mask,
 // the old C) is requested before the first step.  Epochs, us, four wavefronts -> eight -> sixteen: 777-391-129-33 (N = 6, B =
 // 50) 3241 -> 2959 -> 2730; 944-76-94-10 (N = 3, B = 80) 2314 -> - -> 1874; 256-64-576-2 (N = 6, B = 48) 1084 -> - -> 845; 2 to 26 %
-// less on 22 drawn nets.  (Eight or four wavefronts where K has no more steps gave nothing.)
+// less on 22 drawn nets.  (Eight or four wavefronts where K has no more steps gave nothing.)  More tiles than CUs: sixteen
+// wavefronts of 101 registers leave no room for a second workgroup, and the last few tiles ran by themselves; two
+// workgroups of eight, four of four share a CU.  318 x 444 x 592, twice (280 tiles): 12.8 -> 11.3 us; 5821 x 95 x 444 (546): 11.5 -> 7.4;
+// epochs of 777-391-129-33 2727 -> 2606, of 1037-128-472-2, N = 9 878 -> 752, of 48 drawn nets 0.86 to 1.01 times; where K is
+// long each tile is busy by itself (444 x 592 x 5821, 266 tiles: 62 -> 67): sixteen.
 // FAR: operands whose rows are too far apart for fetch8.
 template <bool TA, bool TB, int T, int NW, bool FAR = false>
 __global__ __launch_bounds__(64 * NW) void gemm_small_kernel(GemmArgs g) {
   touch_kernel_arguments<(int)(sizeof(GemmArgs))>();
-  constexpr int I = T / 32, DEPTH = T == 32 && NW < 16 ? 4 : 2;
+  constexpr int I = T / 32, DEPTH = FAR ? 4 : 2;
   __shared__ float part[NW][32][32];  // one 32 x 32 part of the tile at a time
   __shared__ double red[4 * NW];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -817,7 +821,8 @@ Plan plan_of(const GemmArgs &g) {
   if (k <= 160 && tiles(128, 64) >= 200) return {128, 64, 0};
   if (t128 >= 150 || (t128 >= 60 && k <= 640 && !g.transA && g.transB)) return {128, 128, 1};
   if (k > 160 && t64 >= 100) return {64, 64, 8};
-  return {32, 32, 16};
+  const int64_t t32 = tiles(32, 32);
+  return {32, 32, t32 <= 256 || k > 2048 ? 16 : t32 <= 512 ? 8 : 4};
 }
 
 // ---- outputs with at most 16 columns (the last layer of the MLP) -------------------------------------
@@ -1113,6 +1118,8 @@ hipError_t launch_gemm(const GemmArgs &g, hipStream_t st) {
     else if (p.waves == 0) LPC_GEMM_TILE(gemm_tile_kernel, 256, TA_, TB_, 64);                                \
     else if (p.waves == 1) LPC_GEMM_TILE(gemm_pair_kernel, 512, TA_, TB_);                                    \
     else if (p.tile_m == 64) LPC_GEMM_SMALL(TA_, TB_, 64, 8);                                                 \
+    else if (p.waves == 4) LPC_GEMM_SMALL(TA_, TB_, 32, 4);                                                   \
+    else if (p.waves == 8) LPC_GEMM_SMALL(TA_, TB_, 32, 8);                                                   \
     else LPC_GEMM_SMALL(TA_, TB_, 32, 16);                                                                    \
   } while (0)
   if (!g.transA && !g.transB) LPC_GEMM_LAUNCH(false, false);

@@ -64,9 +64,10 @@ def test_products_are_no_less_exact_than_fp32_multiply_adds(M, N, K, tA, tB):
 
 
 # 32 x 32 tiles by sixteen wavefronts with fewer, as many and more steps of K; 64 x 64 by eight; rows of C too far apart for
-# offsets within a tile
+# offsets within a tile; 32 x 32 by eight (272, 288 tiles) and four (528); 270 tiles with a long K
 @pytest.mark.parametrize("M,N,K,ldc", [(1, 3, 4, 3), (33, 31, 16, 40), (32, 33, 257, 33), (65, 64, 1030, 70), (640, 660, 161, 663),
-                                       (5, 7, 40, 1 << 22), (34, 2, 90, (1 << 22) - 1)])
+                                       (5, 7, 40, 1 << 22), (34, 2, 90, (1 << 22) - 1), (500, 513, 33, 513), (511, 545, 130, 547),
+                                       (1030, 500, 37, 500), (300, 900, 2050, 900)])
 @pytest.mark.parametrize("relu,accumulate", [(0, 0), (1, 0), (0, 1), (1, 1)])
 def test_small_products_through_the_options_of_a_store(M, N, K, ldc, relu, accumulate):
     import torch
