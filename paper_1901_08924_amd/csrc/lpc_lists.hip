@@ -1005,20 +1005,24 @@ __global__ __launch_bounds__(kLiThreads) void list_epoch_kernel(ListArgs a) {
             const int first = (int)(piece[k] & 0xfffu), size = (int)((piece[k] >> 12) & 0xfffu);
             float s = mine[first];
             if (list.longest > 1) {  // uniform
-              auto from = [&](int i) { return mine + (first + i < 64 * kLiChunks ? first + i : 64 * kLiChunks); };
-              // eight at a time, requested ahead, as long as a lane has them; then each lane's last ones (-0: nothing added)
-              const int rest = size > 0 ? 1 + ((size - 1) & ~7) : 1;
+              // eight at a time, requested ahead, as long as a lane has them; then each lane's last ones (-0: nothing added).
+              // Lanes that have no more read one address together: 64 addresses at random are five times the LDS's work.
+              const int rest = size > 1 ? 1 + ((size - 1) & ~7) : 1;
+              const float *end = mine + (rest < size ? first + rest : 0);
               float last[7];
 #pragma unroll
-              for (int i = 0; i < 7; ++i) last[i] = from(rest)[i];
+              for (int i = 0; i < 7; ++i) last[i] = end[i];
               if (list.longest > 8) {
+                auto from = [&](int i) { return mine + (i + 8 <= size ? first + i : 0); };
                 float now[8];
+                const float *p = from(1);
 #pragma unroll
-                for (int i = 0; i < 8; ++i) now[i] = from(1)[i];
+                for (int i = 0; i < 8; ++i) now[i] = p[i];
                 for (int done = 1; done + 8 <= list.longest; done += 8) {
                   float next[8];
+                  p = from(done + 8);
 #pragma unroll
-                  for (int i = 0; i < 8; ++i) next[i] = from(done + 8)[i];
+                  for (int i = 0; i < 8; ++i) next[i] = p[i];
                   float eight = s;
 #pragma unroll
                   for (int i = 0; i < 8; ++i) eight += now[i];
