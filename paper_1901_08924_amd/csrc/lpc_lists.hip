@@ -891,7 +891,7 @@ __global__ __launch_bounds__(kLiThreads) void list_epoch_kernel(ListArgs a) {
         if (lane == 0) st_word(a.slope + par * total_rows + slot[q], __builtin_bit_cast(uint32_t, coef), tag);
       }
     }
-    __builtin_amdgcn_s_setprio(0);
+    __builtin_amdgcn_s_setprio(1);
     // ---- while the slopes travel: the coming iteration's rows and entries requested, this one's random words
     {
       const int t1 = more ? t + 1 : t;  // (the last one's own again, to no purpose)
@@ -980,6 +980,7 @@ __global__ __launch_bounds__(kLiThreads) void list_epoch_kernel(ListArgs a) {
         u64 w[kLiChunks];
 #pragma unroll
         for (int r = 0; r < kLiChunks; ++r) w[r] = r * 64 + lane < list.n ? 0ull : (u64)tag << 32;
+        __builtin_amdgcn_s_setprio(0);
         poll(limit, ok, [&] {
           bool all = true;
 #pragma unroll
