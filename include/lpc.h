@@ -342,16 +342,18 @@ lpc_status lpc_debug_gemm(const float *A, const float *B, float *C, int32_t M, i
                           int32_t relu, int32_t accumulate, void *stream);
 
 /* ---- tuning and test aid (no passage of the paper) -----------------------------------------
- * Form and launch shape of the inner iteration on small dense problems (d_pad <= 16384, N <= 64).
+ * Form and launch shape of the inner iteration on small dense problems (d_pad <= 16384, N <= 64), and whether CSR epochs
+ * take the inner loop in one launch.
  *   LPC_TUNE_ITER_FORM:
  *     -1, or not set: form 0; on narrow problems (d <= 256, or d <= 1024 and b > 8, and a batch that fits the registers of
  *       one workgroup; every scheme, with or without quantization; not while the stream is being captured) all m inner
  *       iterations in one launch, cooperative with a workgroup per worker whose waits LPC_TUNE_SPIN_LIMIT bounds, or of one
  *       workgroup for all; on wide problems (d <= 24576, B <= 64, b <= 8 or quantization off, as far as the workers' column
- *       blocks fit the compute units) likewise with a group of workgroups per worker.  Such an epoch takes place as a whole
- *       or not at all (lpc_epoch).
+ *       blocks fit the compute units) likewise with a group of workgroups per worker; on CSR data (b <= 16, N <= 16, B <= 512, at
+ *       most 8192 sampled rows per iteration, 256 compute units) up to 128 inner iterations per launch, the same way, with the
+ *       bits of the separate launches.  Such an epoch takes place as a whole or not at all (lpc_epoch).
  *     0: three launches: the workers' rows (whole rows per workgroup, partial gradient rows out), their fold, the
- *       exchange.
+ *       exchange.  CSR data: the separate launches of its sparse inner iteration.
  *     1: two launches: the workers' rows, then fold + exchange in one launch whose workgroups wait, for a bounded
  *       number of polls, for each other's statistics.
  *     2: two launches with nothing but the launch boundary between them.  The workers' pass runs in 128-column

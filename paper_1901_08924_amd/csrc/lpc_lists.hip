@@ -15,7 +15,7 @@
 // vector and column, and a lane per touched column takes eq. (4) and the update.
 // Margins and sums are added up in the order of the separate launches (a column's entries in blocks of batch positions, the
 // blocks in order: a list is cut in pieces of one column and block), so an epoch's bits do not depend on the route.  A
-// segmented scan over the lanes would be 0.9 us per iteration less (16 vectors), and another rounding now and then.
+// segmented scan over the lanes would be 0.3 us per iteration less (16 vectors), and another rounding now and then.
 // Neighbouring columns belong to different owners because text-like data has its frequent columns side by side.
 // Reuse of words: a column's x word is kept once, written again when its owner has the slopes of every row that holds the
 // column, hence after those rows' wavefronts read it.  Slopes and statistics have two sets: set t is written again at t + 2 by
@@ -25,7 +25,7 @@
 //
 // Bound by the four trips of words (store to load about 1.2 us each) and by the owner of the most frequent column, whose lists
 // are six times as long as the others'.  Measured on MI355X, separate launches -> these kernels, us per iteration, the lists
-// (1.7 there) included: n = d = 2^20, N = 16, B = 256, b = 2: 35.5 -> 11.9; d = 150001, N = 8 + J, B = 100, b = 4: 30.6 -> 11.1.
+// (1.7 there) included: n = d = 2^20, N = 16, B = 256, b = 2: 35.5 -> 11.7; d = 150001, N = 8 + J, B = 100, b = 4: 30.6 -> 11.6.
 // Steps that paid, us per iteration of the first: registers loaded ahead without a join that waits for them and waits for
 // them before the next store, not behind it, together with priority for rows and sums over what only fills the waits, 1.0;
 // columns found by the builder instead of here and words stored as soon as they are known, 1.9; half of the trips' time went
