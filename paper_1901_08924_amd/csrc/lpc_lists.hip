@@ -647,7 +647,7 @@ __global__ __launch_bounds__(kLiThreads) void list_epoch_kernel(ListArgs a) {
   uint32_t *marks = codes + a.words * S;                                   // [3][(S + 31) / 32]: set t % 3 the columns of t
   const int mark_words = (S + 31) / 32;
   uint16_t *touched = reinterpret_cast<uint16_t *>(marks + 3 * mark_words);  // [2][S]
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int p = blockIdx.x, P = 1 << a.pshift, die = p & (kDies - 1), per_die = P / kDies;
 
   // an earlier launch of this epoch gave up
@@ -827,7 +827,14 @@ __global__ __launch_bounds__(kLiThreads) void list_epoch_kernel(ListArgs a) {
   const int my_word = wave / a.fields, my_shift = (wave - my_word * a.fields) * a.bits;
   double weight = a.weight;
   bool gave_up = false;
+  // What derives from these alone is computed again in every iteration: kept, it is 35 registers, which spilled.
+  auto part = [&] {
+    asm volatile("" : "+v"(tid));
+    lane = tid & 63;
+    wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  };
   for (int t = a.it0; t < a.it1; ++t) {
+    if constexpr (ALPC) part();
     const int par = t & 1;
     const uint32_t tag = a.tag0 + (uint32_t)t + 1u;
     const uint32_t limit = t == a.it0 ? (a.spin_limit > 0xffffffu ? ~0u : a.spin_limit * 256u) : a.spin_limit;
