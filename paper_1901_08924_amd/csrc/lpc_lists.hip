@@ -25,7 +25,7 @@
 //
 // Bound by the four trips of words (store to load about 1.2 us each) and by the owner of the most frequent column, whose lists
 // are six times as long as the others'.  Measured on MI355X, separate launches -> these kernels, us per iteration, the lists
-// (1.7 there) included: n = d = 2^20, N = 16, B = 256, b = 2: 35.5 -> 11.7; d = 150001, N = 8 + J, B = 100, b = 4: 30.6 -> 11.6.
+// (1.7 there) included: n = d = 2^20, N = 16, B = 256, b = 2: 35.5 -> 11.7; d = 150001, N = 8 + J, B = 100, b = 4: 30.6 -> 11.0.
 // Steps that paid, us per iteration of the first: registers loaded ahead without a join that waits for them and waits for
 // them before the next store, not behind it, together with priority for rows and sums over what only fills the waits, 1.0;
 // columns found by the builder instead of here and words stored as soon as they are known, 1.9; half of the trips' time went
