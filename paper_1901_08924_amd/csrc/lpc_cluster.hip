@@ -78,7 +78,11 @@ __global__ __launch_bounds__(kClThreads) void cluster_epoch_kernel(ClusterArgs a
   __shared__ uint32_t fail_sh;
   constexpr int D = 64 * K, RG = (RW + 3) / 4;
   constexpr bool kWaveOwns = K <= 4;  // a wavefront holds a whole vector, four coordinates per lane
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // What derives from these alone is else kept in registers for the whole loop, and takes others with it.  Where taking them afresh
+  // in every iteration pays: d = 90, N = 8, B = 64, 905 iterations 3784 -> 3616 us, fifteen drawn problems of these kernels 0.95 to
+  // 1.006 times; the others of Alg. 1 the same, Alg. 2 and 3 up to 1.12 times.
+  constexpr bool kAfresh = !ALPC && Q == kOwnScale && K >= 2 && K <= 4 && RW == 4;
   const int g = blockIdx.x / a.spread, v0 = g * a.nv;
   const int nv = a.nvec - v0 < a.nv ? a.nvec - v0 : a.nv;  // this workgroup's vectors: v0 .. v0 + nv - 1
   const int nB = a.nv * a.B, dp = a.dp, W1 = a.W + 1;
@@ -177,6 +181,11 @@ __global__ __launch_bounds__(kClThreads) void cluster_epoch_kernel(ClusterArgs a
   if (quantizes) random_words(a.it0);
   bool gave_up = false;
   for (int t = a.it0; t < a.it1; ++t) {
+    if constexpr (kAfresh) {
+      asm volatile("" : "+v"(tid));
+      lane = tid & 63;
+      wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    }
     const int par = t & 1;
     const uint32_t tag = a.tag0 + (uint32_t)t + 1u;
     bool ok = true;
