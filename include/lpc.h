@@ -99,7 +99,8 @@ typedef struct {
 
 /* ---- context ------------------------------------------------------------ */
 
-/* Bytes of device scratch the context needs for this problem/config. */
+/* Bytes of device scratch the context needs for this problem/config.  For CSR data that includes the lists of the inner loop in
+ * one launch (LPC_TUNE_ITER_FORM): at most twice the entries' bytes, 128 MB for little and 1 GB for much data. */
 size_t lpc_workspace_bytes(const lpc_problem *problem, const lpc_config *config);
 
 /* Validates problem and config, copies both, and lays the scratch buffers out

@@ -1316,6 +1316,11 @@ __global__ __launch_bounds__(kLiThreads) void list_epoch_kernel(ListArgs a) {
 
 // Iterations of a launch.  n = d = 2^20, N = 16, B = 256: an epoch of 256 takes 3.80, 3.60 and 3.49 ms with 32, 64 and 128
 constexpr int kListIters = 128;
+// A launch and its lists are about 40 us.  Against the separate launches' 44.5, 22, 27, 21 us per iteration (n = 60000, 40 entries
+// drawn per row, N = 16, B = 256; N = 4, B = 32; d = 2^20, N = 16, B = 64; d = 4500, N = 4, B = 64): 128 iterations a launch 14.5, 8.6,
+// 11.1, 8.1, 16: 16.7, 10.8, 13.0, 10.6, 8: 21.1, 13.5, 16.2, 13.3, 5: 26.7, 16.7, 20.0, 16.6, 4: -, 19.4, 22.1, 18.5
+constexpr int kLeastIters = 4;
+constexpr int kEntryBytes = 16;  // of a list's entry in `ent`, `cols` and `pieces`
 
 struct Shape {
   int pshift, S, fields, words;
@@ -1328,16 +1333,33 @@ int bits_for(int64_t values) {  // of a number in [0, values)
   return b;
 }
 
+int64_t list_rows(const lpc_ctx *c) { return (int64_t)(c->cfg.N + (c->cfg.algo != LPC_ALGO_LPC ? 1 : 0)) * c->cfg.B; }
+int64_t list_mean(const lpc_ctx *c) { return (c->prob.nnz + c->n - 1) / c->n; }
+// Batch positions that are added up by themselves, as the separate launches do
+int32_t list_block(const lpc_ctx *c) { return c->csr_sparse ? csr_sparse_block() : kMaxBatch; }
+int64_t list_iters(const lpc_ctx *c) { return c->cfg.m < kListIters ? c->cfg.m : kListIters; }
+
+// What the lists may add to the workspace, bytes: as much again as the entries themselves take (8 bytes each) and the
+// column-major copy of them that the workspace holds anyway, but 128 MB for little data and 1 GB for much; the epoch's draws are
+// a part of it where the separate launches do not keep them too.  A launch takes the iterations whose lists fit.
+int64_t list_budget(const lpc_ctx *c) {
+  const int64_t data = 16 * c->prob.nnz, least = (int64_t)128 << 20, most = (int64_t)1 << 30;
+  const int64_t draws = c->csr_sparse ? 0 : (int64_t)sizeof(RowPlan) * c->cfg.m * (c->cfg.N + 1) * c->cfg.B;
+  return (data < least ? least : data > most ? most : data) - draws;
+}
+
 // What does not depend on the rows' lengths; S = 0 where the kernel does not apply: a wavefront per vector, two rows per
-// wavefront at most, and the slices must fit LDS.
+// wavefront at most, the slices must fit LDS, and the lists of kLeastIters iterations of mean rows what the workspace may grow by.
 Shape shape_of(const lpc_ctx *c) {
   Shape s{};
   if (!c->csr || !c->quant || c->cfg.bits > 16 || c->cfg.N > kLiWaves || c->cfg.m < 1 || c->prob.nnz <= 0) return s;
   s.pshift = kOwnerBits;
   const int P = 1 << s.pshift;
   const bool alpc = c->cfg.algo != LPC_ALGO_LPC;
-  const int64_t rows = (int64_t)(c->cfg.N + (alpc ? 1 : 0)) * c->cfg.B, S = (c->d + 4 * P - 1) / (4 * P) * 4;
+  const int64_t rows = list_rows(c), S = (c->d + 4 * P - 1) / (4 * P) * 4;
   if (c->cfg.B > kMaxBatch || rows > (int64_t)kLiRows * kLiWaves * P || S > 65535 || P > c->device_cus) return s;
+  const int64_t least = c->cfg.m < kLeastIters ? c->cfg.m : kLeastIters;
+  if (kEntryBytes * least * rows * list_mean(c) > list_budget(c)) return s;
   s.fields = 32 / c->cfg.bits;
   s.words = (c->cfg.N + s.fields - 1) / s.fields;
   s.lds = 4 * (size_t)S * ((alpc ? 6 : 2) + s.words + 1) + 12 * (size_t)((S + 31) / 32);
@@ -1346,17 +1368,12 @@ Shape shape_of(const lpc_ctx *c) {
   return s;
 }
 
-int64_t list_rows(const lpc_ctx *c) { return (int64_t)(c->cfg.N + (c->cfg.algo != LPC_ALGO_LPC ? 1 : 0)) * c->cfg.B; }
-// Batch positions that are added up by themselves, as the separate launches do
-int32_t list_block(const lpc_ctx *c) { return c->csr_sparse ? csr_sparse_block() : kMaxBatch; }
-int64_t list_iters(const lpc_ctx *c) { return c->cfg.m < kListIters ? c->cfg.m : kListIters; }
-
 }  // namespace
 
 bool lists_supported(const lpc_ctx *c) { return shape_of(c).S > 0; }
 
-// Room for the lists of kListIters iterations of rows three times as long as the mean; where the longest row is longer,
-// a launch takes fewer iterations (finish_lists).
+// Room for the lists of kListIters iterations of rows three times as long as the mean, as far as the budget goes; how many
+// iterations of the longest row that is, finish_lists says.
 ListScratch lists_scratch(const lpc_ctx *c) {
   const Shape s = shape_of(c);
   const size_t P = (size_t)1 << s.pshift, N = (size_t)c->cfg.N, rows = (size_t)list_rows(c);
@@ -1366,8 +1383,8 @@ ListScratch lists_scratch(const lpc_ctx *c) {
   w.stat = 2 * N * (5 * P + kDies * kLine);
   w.state = 6 * P * s.S;
   w.off = (size_t)list_iters(c) * (rows / c->cfg.B) * P * kRecord;
-  const int64_t mean = (c->prob.nnz + c->n - 1) / c->n;
-  w.entries = (size_t)list_iters(c) * rows * (size_t)(3 * mean + 16);
+  const size_t all = (size_t)list_iters(c) * rows * (size_t)(3 * list_mean(c) + 16), most = (size_t)(list_budget(c) / kEntryBytes);
+  w.entries = all < most ? all : most;
   return w;
 }
 
@@ -1392,9 +1409,8 @@ hipError_t finish_lists(lpc_ctx *c, hipStream_t st) {
   const int64_t lists = list_rows(c) / c->cfg.B;
   const int64_t fit = (int64_t)lists_scratch(c).entries / (lists * c->list_cap);
   c->list_iters = (int32_t)(fit < list_iters(c) ? fit : list_iters(c));
-  // four iterations per launch: with fewer the launches around them cost what the loop saves
   c->lists_capable = lc_bits + pos_bits + k_bits <= 32 && lc_bits + pos_bits <= 30 &&
-                     c->list_iters >= (c->cfg.m < 4 ? c->cfg.m : 4);
+                     c->list_iters >= (c->cfg.m < kLeastIters ? c->cfg.m : kLeastIters);
   return hipSuccess;
 }
 

@@ -66,6 +66,21 @@ def test_workspace_size_grows_with_the_problem(lpc):
     assert big >= 9 * 4096 * 4 + 8 * 512 * 4 + 65536 * 4
 
 
+@pytest.mark.parametrize("n,d,per_row,N,B,m,algo", [
+    (1 << 20, 1 << 20, 40, 16, 256, 256, 0), (20242, 47236, 74, 16, 256, 256, 0), (19996, 1355191, 455, 16, 64, 128, 0),
+    (4000, 5000, 4950, 8, 64, 128, 0), (100000, 20000, 1000, 16, 256, 128, 2), (100000, 2000, 2000, 16, 512, 128, 0),
+    (350000, 10 ** 6, 3728, 16, 512, 128, 0), (200003, 150001, 24, 8, 100, 64, 2), (60000, 4500, 30, 16, 256, 100000, 0)])
+def test_lists_of_csr_epochs_take_a_bounded_share_of_the_workspace(lpc, n, d, per_row, N, B, m, algo):
+    """Past sixteen workers epochs on CSR data take separate launches, which keep no lists: what the lists add is at most twice the
+    data (128 MB for little, 1 GB for much), beside the iterate and state in the owners' order and 16 MB of words and records."""
+    p = lpc.Problem()
+    p.n, p.d, p.loss, p.nnz = n, d, lpc.LOSS_LOGISTIC, n * per_row
+    p.row_ptr = p.col_idx = p.vals = p.y = 0x10000
+    with_lists, without = (lpc.lib.lpc_workspace_bytes(C.byref(p), C.byref(
+        lpc.make_config(algo=algo, N=workers, B=B, m=m, bits=4, L=1.0))) for workers in (N, 17))
+    assert 0 < with_lists <= without + min(max(16 * p.nnz, 128 << 20), 1 << 30) + 32 * d + (16 << 20)
+
+
 @pytest.mark.parametrize("field,value,code", [
     ("bits", 1, -1),      # 2^(b-1)-1 = 0 in eq. (3)
     ("bits", 0, -1), ("bits", 17, -1), ("bits", 31, -1),
