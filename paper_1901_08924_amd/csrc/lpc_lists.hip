@@ -326,7 +326,6 @@ __global__ __launch_bounds__(kLiThreads, 8) void list_build_kernel(ListBuildArgs
       p1 = lo;
     }
     const int n_keys = (int)(slot0[p1] - base), chunks = (n_keys + 63) / 64;
-    const bool too_many = n_keys > kKeyCap;  // one owner's are more than that
     __syncthreads();
     part();
     auto put_key = [&](uint32_t col, int r, uint32_t k, uint32_t slot, uint32_t value) {
@@ -340,198 +339,134 @@ __global__ __launch_bounds__(kLiThreads, 8) void list_build_kernel(ListBuildArgs
     };
     for (int g = 0; g < groups; ++g) {
       if (groups > 1 || p0 > 0) load(g);
-      if (!too_many) {
 #pragma unroll
-        for (int q0 = 0; q0 < kHeld; q0 += 8) {
-          uint32_t slot[8], v[8];
+      for (int q0 = 0; q0 < kHeld; q0 += 8) {
+        uint32_t slot[8], v[8];
 #pragma unroll
-          for (int i = 0; i < 8; ++i) v[i] = row_words(a.vals, q0 + i);
+        for (int i = 0; i < 8; ++i) v[i] = row_words(a.vals, q0 + i);
 #pragma unroll
-          for (int i = 0; i < 8; ++i) {  // (the others add nothing, each to a word of its own)
-            const uint32_t col = (uint32_t)c[q0 + i];
-            const bool has = mine(col);
-            slot[i] = atomicAdd(&cursor[has ? bin_of(col) : (uint32_t)tid], has ? 1u : 0u) - base;
-          }
+        for (int i = 0; i < 8; ++i) {  // (the others add nothing, each to a word of its own)
+          const uint32_t col = (uint32_t)c[q0 + i];
+          const bool has = mine(col);
+          slot[i] = atomicAdd(&cursor[has ? bin_of(col) : (uint32_t)tid], has ? 1u : 0u) - base;
+        }
 #pragma unroll
-          for (int i = 0; i < 8; ++i) {
-            const uint32_t col = (uint32_t)c[q0 + i];
-            if (mine(col)) put_key(col, g * held + (q0 + i) * kLiWaves + wave, (uint32_t)lane, slot[i], v[i]);
-          }
+        for (int i = 0; i < 8; ++i) {
+          const uint32_t col = (uint32_t)c[q0 + i];
+          if (mine(col)) put_key(col, g * held + (q0 + i) * kLiWaves + wave, (uint32_t)lane, slot[i], v[i]);
         }
       }
       walk_far(g, [&](uint32_t col, int r, uint32_t k, int32_t e) {
-        if (!too_many && mine(col)) put_key(col, r, k, atomicAdd(&cursor[bin_of(col)], 1u) - base, __float_as_uint(a.vals[e]));
-      });
-    }
-    if (too_many) {
-      // No data meant for these kernels come here (6400 entries of a batch in the columns of one owner), but they are not
-      // refused: an entry counts the smaller keys of its bin, from memory.
-      auto each = [&](int rows_from, int step, int32_t k_from, int32_t k_step, auto f) {
-        for (int r = rows_from; r < a.B; r += step) {
-          const int32_t lo = lo_sh[r], len = len_sh[r];
-          for (int32_t k = k_from; k < len; k += k_step) {
-            const uint32_t col = (uint32_t)a.col_idx[lo + k], lc = col >> kOwnerBits;
-            if ((int)(col & (uint32_t)(P - 1)) != p0 || (int32_t)col < keyed) continue;
-            f(lc << a.pos_bits | (uint32_t)r, (uint32_t)k, lo + k);
-          }
-        }
-      };
-      each(wave, kLiWaves, lane, 64, [&](uint32_t pair, uint32_t k, int32_t e) {
-        const uint32_t b = (pair >> a.pos_bits) & (uint32_t)(kOwnBins - 1);
-        uint32_t at = first[p0 + 1] - (slot0[p0 + 1] - cursor[b * P + (uint32_t)p0]);
-        each(0, 1, 0, 1, [&](uint32_t other, uint32_t k2, int32_t) {
-          if (((other >> a.pos_bits) & (uint32_t)(kOwnBins - 1)) == b && (other < pair || (other == pair && k2 < k))) ++at;
-        });
-        out[at] = make_uint2(pair, __float_as_uint(a.vals[e]));
+        if (mine(col)) put_key(col, r, k, atomicAdd(&cursor[bin_of(col)], 1u) - base, __float_as_uint(a.vals[e]));
       });
     }
 #pragma unroll
     for (int q = 0; q < kHeld; ++q) c[q] = -1;  // (not kept for another turn)
     __syncthreads();
-    if (!too_many) {
-      part();
-      // ---- the keys in order
-      uint32_t key[kSortChunks], val[kSortChunks], to[kSortChunks];
+    part();
+    // ---- the keys in order
+    uint32_t key[kSortChunks], val[kSortChunks], to[kSortChunks];
 #pragma unroll
-      for (int i = 0; i < kSortChunks; ++i) {
-        const int slot = 64 * (wave + i * kLiWaves) + lane;
-        key[i] = val[i] = to[i] = 0u;
-        if (slot < n_keys) {
-          key[i] = keys[slot];
-          val[i] = key_values[slot];
-          const uint32_t p = owner[slot], b = (key[i] >> (a.pos_bits + a.k_bits)) & (uint32_t)(kOwnBins - 1);
-          const uint32_t hi = cursor[b * P + p] - base, lo = b != 0u ? cursor[b * P + p - P] - base : slot0[p] - base;
-          uint32_t n = lo;
-          for (uint32_t k = lo; k < hi; k += 4) {  // (what lies behind the keys is LDS of this kernel)
-            const uint32_t k0 = keys[k], k1 = keys[k + 1], k2 = keys[k + 2], k3 = keys[k + 3];
-            n += k0 < key[i] ? 1u : 0u;
-            n += k + 1 < hi && k1 < key[i] ? 1u : 0u;
-            n += k + 2 < hi && k2 < key[i] ? 1u : 0u;
-            n += k + 3 < hi && k3 < key[i] ? 1u : 0u;
-          }
-          to[i] = n;
+    for (int i = 0; i < kSortChunks; ++i) {
+      const int slot = 64 * (wave + i * kLiWaves) + lane;
+      key[i] = val[i] = to[i] = 0u;
+      if (slot < n_keys) {
+        key[i] = keys[slot];
+        val[i] = key_values[slot];
+        const uint32_t p = owner[slot], b = (key[i] >> (a.pos_bits + a.k_bits)) & (uint32_t)(kOwnBins - 1);
+        const uint32_t hi = cursor[b * P + p] - base, lo = b != 0u ? cursor[b * P + p - P] - base : slot0[p] - base;
+        uint32_t n = lo;
+        for (uint32_t k = lo; k < hi; k += 4) {  // (what lies behind the keys is LDS of this kernel)
+          const uint32_t k0 = keys[k], k1 = keys[k + 1], k2 = keys[k + 2], k3 = keys[k + 3];
+          n += k0 < key[i] ? 1u : 0u;
+          n += k + 1 < hi && k1 < key[i] ? 1u : 0u;
+          n += k + 2 < hi && k2 < key[i] ? 1u : 0u;
+          n += k + 3 < hi && k3 < key[i] ? 1u : 0u;
         }
+        to[i] = n;
       }
-      __syncthreads();
+    }
+    __syncthreads();
 #pragma unroll
-      for (int i = 0; i < kSortChunks; ++i)
-        if (64 * (wave + i * kLiWaves) + lane < n_keys) {
-          keys[to[i]] = key[i];
-          key_values[to[i]] = val[i];
-        }
-      __syncthreads();
-      part();
-      // ---- entries, heads of columns and pieces
+    for (int i = 0; i < kSortChunks; ++i)
+      if (64 * (wave + i * kLiWaves) + lane < n_keys) {
+        keys[to[i]] = key[i];
+        key_values[to[i]] = val[i];
+      }
+    __syncthreads();
+    part();
+    // ---- entries, heads of columns and pieces
 #pragma unroll
-      for (int i = 0; i < kSortChunks; ++i) {
-        const int chunk = wave + i * kLiWaves, slot = 64 * chunk + lane;
-        if (chunk >= chunks) break;  // uniform
-        bool col = false, piece = false;
-        if (slot < n_keys) {
-          key[i] = keys[slot];
-          const uint32_t at = place_of(key[i] >> a.k_bits);
-          const uint32_t prev = slot > 0 ? place_of(keys[slot - 1] >> a.k_bits) : 0u;
-          col = slot == 0 || owner[slot] != owner[slot - 1] || at >> 4 != prev >> 4;
-          piece = col || at != prev;
-        }
-        const uint64_t col_votes = __ballot(col), votes = __ballot(piece);
-        if (lane == 0) { col_heads[chunk] = col_votes; heads[chunk] = votes; }
+    for (int i = 0; i < kSortChunks; ++i) {
+      const int chunk = wave + i * kLiWaves, slot = 64 * chunk + lane;
+      if (chunk >= chunks) break;  // uniform
+      bool col = false, piece = false;
+      if (slot < n_keys) {
+        key[i] = keys[slot];
+        const uint32_t at = place_of(key[i] >> a.k_bits);
+        const uint32_t prev = slot > 0 ? place_of(keys[slot - 1] >> a.k_bits) : 0u;
+        col = slot == 0 || owner[slot] != owner[slot - 1] || at >> 4 != prev >> 4;
+        piece = col || at != prev;
       }
-      if (tid == 0) { col_heads[chunks] = 0u; heads[chunks] = 0u; }
-      __syncthreads();
-      if (wave == 0) {
-        uint32_t sum = 0;
-        for (int k = 0; k <= chunks; k += 64) {
-          const uint32_t n = k + lane < chunks ? (uint32_t)__popcll(heads[k + lane]) << 16 | (uint32_t)__popcll(col_heads[k + lane]) : 0u;
-          uint32_t s = n;
-          for (int o = 1; o < 64; o <<= 1) {
-            const uint32_t below = __shfl_up(s, o, 64);
-            if (lane >= o) s += below;
-          }
-          if (k + lane <= chunks) before[k + lane] = sum + s - n;
-          sum += read_lane(s, 63);
+      const uint64_t col_votes = __ballot(col), votes = __ballot(piece);
+      if (lane == 0) { col_heads[chunk] = col_votes; heads[chunk] = votes; }
+    }
+    if (tid == 0) { col_heads[chunks] = 0u; heads[chunks] = 0u; }
+    __syncthreads();
+    if (wave == 0) {
+      uint32_t sum = 0;
+      for (int k = 0; k <= chunks; k += 64) {
+        const uint32_t n = k + lane < chunks ? (uint32_t)__popcll(heads[k + lane]) << 16 | (uint32_t)__popcll(col_heads[k + lane]) : 0u;
+        uint32_t s = n;
+        for (int o = 1; o < 64; o <<= 1) {
+          const uint32_t below = __shfl_up(s, o, 64);
+          if (lane >= o) s += below;
         }
+        if (k + lane <= chunks) before[k + lane] = sum + s - n;
+        sum += read_lane(s, 63);
       }
-      __syncthreads();
-      auto count = [&](int slot) {  // of heads below a slot: pieces << 16 | columns
-        const uint64_t below = (1ull << (slot & 63)) - 1ull;
-        return before[slot >> 6] + ((uint32_t)__popcll(heads[slot >> 6] & below) << 16 | (uint32_t)__popcll(col_heads[slot >> 6] & below));
-      };
-      part();
-      for (int p = p0 + tid; p < p1; p += kLiThreads)  // (of the owner's heads before its first slot)
-        singles[p] -= count((int)(slot0[p] - base));
-      __syncthreads();
+    }
+    __syncthreads();
+    auto count = [&](int slot) {  // of heads below a slot: pieces << 16 | columns
+      const uint64_t below = (1ull << (slot & 63)) - 1ull;
+      return before[slot >> 6] + ((uint32_t)__popcll(heads[slot >> 6] & below) << 16 | (uint32_t)__popcll(col_heads[slot >> 6] & below));
+    };
+    part();
+    for (int p = p0 + tid; p < p1; p += kLiThreads)  // (of the owner's heads before its first slot)
+      singles[p] -= count((int)(slot0[p] - base));
+    __syncthreads();
 #pragma unroll
-      for (int i = 0; i < kSortChunks; ++i) {
-        const int slot = 64 * (wave + i * kLiWaves) + lane;
-        if (slot < n_keys) {
-          const uint32_t p = owner[slot], list = first[p], n_list = first[p + 1] - list;
-          const int s1 = (int)(slot0[p + 1] - base);
-          const uint32_t at = n_list - (uint32_t)(s1 - slot);  // in the list
-          out[list + at] = make_uint2((key[i] >> a.k_bits) & pos_mask, key_values[slot]);
-          const uint64_t votes = heads[slot >> 6], bit = 1ull << lane;
-          if (votes & bit) {
-            const uint32_t k = singles[p] + count(slot);
-            if (col_heads[slot >> 6] & bit) cols[list + (k & 0xffffu)] = (key[i] >> (a.pos_bits + a.k_bits)) + 1u;
-            int chunk = slot >> 6;
-            uint64_t next = votes & ~bit & ~(bit - 1ull);
-            while (next == 0ull && chunk + 1 < chunks) next = heads[++chunk];
-            int end = next != 0ull ? 64 * chunk + __builtin_ctzll(next) : n_keys;  // (the next owner's first key is a head)
-            const bool last = end >= s1 || ((col_heads[end >> 6] >> (end & 63)) & 1ull);
-            const uint32_t size = (uint32_t)(end - slot);
-            pieces[list + (k >> 16)] = at | (n_list <= 64u * kLiChunks ? size << 12 : 0u) | (last ? kLast : 0u);
-            if (size > 1u) atomicMax(&longest[p], size);
-          }
+    for (int i = 0; i < kSortChunks; ++i) {
+      const int slot = 64 * (wave + i * kLiWaves) + lane;
+      if (slot < n_keys) {
+        const uint32_t p = owner[slot], list = first[p], n_list = first[p + 1] - list;
+        const int s1 = (int)(slot0[p + 1] - base);
+        const uint32_t at = n_list - (uint32_t)(s1 - slot);  // in the list
+        out[list + at] = make_uint2((key[i] >> a.k_bits) & pos_mask, key_values[slot]);
+        const uint64_t votes = heads[slot >> 6], bit = 1ull << lane;
+        if (votes & bit) {
+          const uint32_t k = singles[p] + count(slot);
+          if (col_heads[slot >> 6] & bit) cols[list + (k & 0xffffu)] = (key[i] >> (a.pos_bits + a.k_bits)) + 1u;
+          int chunk = slot >> 6;
+          uint64_t next = votes & ~bit & ~(bit - 1ull);
+          while (next == 0ull && chunk + 1 < chunks) next = heads[++chunk];
+          int end = next != 0ull ? 64 * chunk + __builtin_ctzll(next) : n_keys;  // (the next owner's first key is a head)
+          const bool last = end >= s1 || ((col_heads[end >> 6] >> (end & 63)) & 1ull);
+          const uint32_t size = (uint32_t)(end - slot);
+          pieces[list + (k >> 16)] = at | (n_list <= 64u * kLiChunks ? size << 12 : 0u) | (last ? kLast : 0u);
+          if (size > 1u) atomicMax(&longest[p], size);
         }
       }
-      __syncthreads();
-      for (int p = p0 + tid; p < p1; p += kLiThreads) {
-        const uint32_t k = singles[p] + count((int)(slot0[p + 1] - base));
-        uint32_t *rec = a.rec + ((int64_t)blockIdx.x * P + p) * kRecord;
-        rec[0] = first[p];
-        rec[1] = first[p + 1] - first[p];
-        rec[2] = k & 0xffffu;
-        rec[3] = k >> 16;
-        rec[4] = longest[p];
-      }
-    } else if (wave == 0) {  // one owner: the pairs from memory
-      const uint32_t list = first[p0], n_list = first[p0 + 1] - list;
-      uint32_t n = singles[p0] & 0xffffu, m = singles[p0] >> 16, prior = kNoEntry, open = 0;  // open: where the last piece begins
-      bool any = false;
-      for (uint32_t i = n_list - (uint32_t)n_keys; i < n_list; i += 64) {
-        const bool in = i + lane < n_list;
-        const uint32_t pair = in ? out[list + i + lane].x : 0u;
-        const uint32_t at = in ? place_of(pair) : kNoEntry - 16u;
-        const uint32_t prev = (uint32_t)__builtin_amdgcn_update_dpp((int)prior, (int)at, 0x138, 0xF, 0xF, false);  // wave_shr:1
-        prior = read_lane(at, 63);
-        const uint64_t col_votes = __ballot(at >> 4 != prev >> 4 && in), votes = __ballot(at != prev && in);
-        const uint64_t below = (1ull << lane) - 1ull;
-        if (in) {
-          out[list + i + lane].x = pair & pos_mask;
-          if ((col_votes >> lane) & 1ull) cols[list + n + __popcll(col_votes & below)] = (at >> 4) + 1u;
-          if ((votes >> lane) & 1ull) {
-            const uint64_t above = votes & ~below & ~(1ull << lane);
-            const bool last = above != 0ull && ((col_votes >> __builtin_ctzll(above)) & 1ull);
-            pieces[list + m + __popcll(votes & below)] = i + lane | (last ? kLast : 0u);
-          }
-        }
-        if (votes != 0ull) {  // the piece before: this chunk's last one waits for the next
-          if (any && lane == 0 && ((col_votes >> __builtin_ctzll(votes)) & 1ull)) pieces[list + m - 1u] = open | kLast;
-          open = i + 63u - (uint32_t)__builtin_clzll(votes);
-          any = true;
-        }
-        n += (uint32_t)__popcll(col_votes);
-        m += (uint32_t)__popcll(votes);
-      }
-      if (lane == 0) {
-        pieces[list + m - 1u] = open | kLast;
-        uint32_t *rec = a.rec + ((int64_t)blockIdx.x * P + p0) * kRecord;
-        rec[0] = list;
-        rec[1] = n_list;
-        rec[2] = n;
-        rec[3] = m;
-        rec[4] = 0u;  // (of no use in a list as long as that)
-      }
+    }
+    __syncthreads();
+    for (int p = p0 + tid; p < p1; p += kLiThreads) {
+      const uint32_t k = singles[p] + count((int)(slot0[p + 1] - base));
+      uint32_t *rec = a.rec + ((int64_t)blockIdx.x * P + p) * kRecord;
+      rec[0] = first[p];
+      rec[1] = first[p + 1] - first[p];
+      rec[2] = k & 0xffffu;
+      rec[3] = k >> 16;
+      rec[4] = longest[p];
     }
     __syncthreads();
     p0 = p1;
@@ -552,14 +487,30 @@ __global__ __launch_bounds__(256) void plan_margins_kernel(const int32_t *__rest
   if ((threadIdx.x & 15) == 0) plan[r].z = s;
 }
 
-__global__ __launch_bounds__(256) void longest_row_kernel(const int32_t *__restrict__ row_ptr, int64_t n,
-                                                          int32_t *__restrict__ out) {
-  int32_t most = 0;
-  for (int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x; r < n; r += (int64_t)gridDim.x * 256) {
-    const int32_t len = row_ptr[r + 1] - row_ptr[r];
-    most = len > most ? len : most;
+// out[0]: entries of the longest row; out[1]: the most entries of a row that belong to one owner.  A wavefront per row and turn.
+__global__ __launch_bounds__(256) void row_extents_kernel(const int32_t *__restrict__ row_ptr, const int32_t *__restrict__ col_idx,
+                                                          int64_t n, int32_t *__restrict__ out) {
+  __shared__ uint32_t entries[4][kOwners];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  uint32_t *mine = entries[wave];
+  for (int i = lane; i < kOwners; i += 64) mine[i] = 0u;
+  __syncthreads();
+  int32_t longest = 0, most = 0;
+  for (int64_t r = (int64_t)blockIdx.x * 4 + wave; r < n; r += (int64_t)gridDim.x * 4) {
+    const int32_t lo = row_ptr[r], hi = row_ptr[r + 1];
+    longest = hi - lo > longest ? hi - lo : longest;
+    for (int32_t e = lo + lane; e < hi; e += 64) most = max(most, (int32_t)atomicAdd(&mine[col_idx[e] & (kOwners - 1)], 1u) + 1);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    for (int32_t e = lo + lane; e < hi; e += 64) mine[col_idx[e] & (kOwners - 1)] = 0u;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
   }
-  atomicMax(out, most);
+  for (int o = 32; o > 0; o >>= 1) most = max(most, __shfl_xor(most, o, 64));
+  if (lane == 0) {
+    atomicMax(&out[0], longest);
+    atomicMax(&out[1], most);
+  }
 }
 
 // ---------------------------------------------------------------------------------------------------------------------
@@ -1392,16 +1343,16 @@ ListScratch lists_scratch(const lpc_ctx *c) {
 // Waits for `st`.
 hipError_t finish_lists(lpc_ctx *c, hipStream_t st) {
   const Shape s = shape_of(c);
-  int32_t longest = 0, *dev = reinterpret_cast<int32_t *>(c->s.li_state);
-  hipError_t e = launch_fill_u32(reinterpret_cast<uint32_t *>(dev), 0u, 1, st);
+  int32_t extents[2] = {0, 0}, *dev = reinterpret_cast<int32_t *>(c->s.li_state);
+  hipError_t e = launch_fill_u32(reinterpret_cast<uint32_t *>(dev), 0u, 2, st);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(longest_row_kernel, dim3((unsigned)(c->n < 256 * 1024 ? (c->n + 255) / 256 : 1024)), dim3(256), 0, st,
-                     c->prob.row_ptr, c->n, dev);
+  hipLaunchKernelGGL(row_extents_kernel, dim3((unsigned)(c->n < 4 * 2048 ? (c->n + 3) / 4 : 2048)), dim3(256), 0, st,
+                     c->prob.row_ptr, c->prob.col_idx, c->n, dev);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  e = hipMemcpyAsync(&longest, dev, sizeof(longest), hipMemcpyDeviceToHost, st);
+  e = hipMemcpyAsync(extents, dev, sizeof(extents), hipMemcpyDeviceToHost, st);
   if (e == hipSuccess) e = hipStreamSynchronize(st);
   if (e != hipSuccess) return e;
-  if (longest < 1) longest = 1;
+  const int32_t longest = extents[0] < 1 ? 1 : extents[0];
   const int lc_bits = bits_for(s.S), pos_bits = c->cfg.B > 1 ? bits_for(c->cfg.B) : 1, k_bits = bits_for(longest);
   c->list_pos_bits = pos_bits;
   c->list_k_bits = k_bits;
@@ -1409,7 +1360,9 @@ hipError_t finish_lists(lpc_ctx *c, hipStream_t st) {
   const int64_t lists = list_rows(c) / c->cfg.B;
   const int64_t fit = (int64_t)lists_scratch(c).entries / (lists * c->list_cap);
   c->list_iters = (int32_t)(fit < list_iters(c) ? fit : list_iters(c));
+  // (the builder sorts all of an owner's keys in LDS)
   c->lists_capable = lc_bits + pos_bits + k_bits <= 32 && lc_bits + pos_bits <= 30 &&
+                     (int64_t)c->cfg.B * extents[1] <= kKeyCap &&
                      c->list_iters >= (c->cfg.m < kLeastIters ? c->cfg.m : kLeastIters);
   return hipSuccess;
 }

@@ -265,7 +265,8 @@ def _one_bin(rng, r):  # columns of one owner, a quarter of its own
     (5001, 3, 512, lambda rng, r: list(range(10)) + [10 + r], dict(bits=4)),       # lists past five chunks
     (5003, 3, 200, lambda rng, r: rng.integers(0, 40, 30), dict(bits=6)),          # a row holds a column several times
     (60000, 2, 512, lambda rng, r: rng.choice(60000, 60, replace=False), {}),      # more keys than the builder holds at once
-    (262144, 2, 512, _one_bin, dict(m=2)),                                         # ... in one bin; lists past 128 columns
+    (262144, 2, 400, _one_bin, dict(m=2)),                                         # ... all in one bin; lists past 128 columns
+    (262144, 2, 512, _one_bin, dict(m=2)),                                         # more than it sorts: the separate launches
     (3000, 2, 4, _zipf(3000, 20), dict(m=131, n_full=700)),                        # a second launch; margins taken by the plan
     (3000, 15, 64, _zipf(3000, 20), dict(algo=lpco.ALGO_ALPC_SC, scheme=lpco.SCHEME_B, bits=4)),
     (2999, 7, 9, _zipf(2999, 6), dict(algo=lpco.ALGO_ALPC_GC, scheme=lpco.SCHEME_C, bits=7, n_full=900, clip_mode=1, clip=1.0))])
@@ -297,6 +298,34 @@ def test_csr_epochs_in_one_launch(d, N, B, rows, over):
         assert np.array_equal(got, separate)
         diff, scale = np.abs(got - w), np.abs(w).max()
         assert (diff > 1e-5 * scale).mean() <= max(2e-3, 2.0 / d) and diff.max() <= 0.05 * scale
+
+
+def _epoch_and_route(ctx, sp, epochs=1):
+    """x~, y and z after the epochs, and whether the inner loop was one launch."""
+    vec = [to_dev(sp.w0) for _ in range(3)]
+    ctx.profile_enable(True)
+    for s in range(epochs):
+        ctx.epoch(vec[0], s, vec[1], vec[2])
+    ctx.profile_enable(False)
+    counts = ctx.profile_read()
+    return np.stack([v.cpu().numpy() for v in vec]), counts["resident"][1] > 0 and counts["vr_rows"][1] == 0
+
+
+@pytest.mark.parametrize("B,one_launch", [(400, True), (401, False)])
+def test_csr_epochs_by_the_entries_of_one_owner(B, one_launch):
+    """The list builder sorts 6400 entries of an owner's columns; data whose batches may hold more take the separate launches."""
+    from paper_1901_08924_amd import lpc
+    sp = _csr_problem(262144, 2, B, _one_bin)     # sixteen of an owner's columns in a row: 6400 entries, and 6416
+    got = []
+    for form in (-1, 0):
+        ctx = gpu_context(sp, m=2, L=0.5, eta=0.4, bits=4)
+        if form == 0:
+            ctx.tune(lpc.TUNE_ITER_FORM, form)
+        vec, route = _epoch_and_route(ctx, sp)
+        assert route == (one_launch and form == -1) and ctx.take_device_flags() == 0
+        got.append(vec)
+        ctx.close()
+    assert np.array_equal(*got) and not np.array_equal(got[0][0], sp.w0)
 
 
 @pytest.mark.parametrize("over", [{}, dict(algo=lpco.ALGO_ALPC_GC, scheme=lpco.SCHEME_B)])
