@@ -1271,6 +1271,20 @@ constexpr int kListIters = 128;
 // drawn per row, N = 16, B = 256; N = 4, B = 32; d = 2^20, N = 16, B = 64; d = 4500, N = 4, B = 64): 128 iterations a launch 14.5, 8.6,
 // 11.1, 8.1, 16: 16.7, 10.8, 13.0, 10.6, 8: 21.1, 13.5, 16.2, 13.3, 5: 26.7, 16.7, 20.0, 16.6, 4: -, 19.4, 22.1, 18.5
 constexpr int kLeastIters = 4;
+// An epoch's own launches (plan, vectors to the owners and back) are about 50 us more.  Separate launches -> these, us per iteration,
+// by m: d = 4500, N = 4, B = 64, 31 entries a row: 22.9 -> 65.6 (1), 21.8 -> 22.6 (4), 21.0 -> 19.2 (5); d = 60000, N = 4, B = 32, 25:
+// 21.0 -> 22.5 (4), 22.4 -> 19.5 (5); d = 2^20, N = 16, 34: B = 64 60.6 -> 70.5 (1), 42.3 -> 39.9 (2); B = 256 104 -> 85 (1).
+// Below five iterations therefore only where they sample enough entries (35000 an iteration and 139000 in the last two).
+constexpr int64_t kFewIters = 4, kFewEntries = 50000;
+// A batch of E entries takes the builder about 7.5 ms (E / 200000)^2, since it walks the batch once for every 6400 entries, and the
+// lists of a launch's iterations are built 256 at a time; the separate launches' iteration is about 8 us per 1000 of E, 2.2 to
+// 4 where u^i stays sparse.  Separate launches -> these, us per iteration (16 vectors, iterations a launch in brackets), u^i dense:
+// d = 20000, B = 256, E = 102000 989 -> 197 [16], 205000 1848 -> 817 [10]; B = 512, E = 136000 1200 -> 743 [7], 200000 1630 ->
+// 1832 [4]; d = 2000, B = 512, E = 113000 923 -> 623 [7], 159000 1194 -> 1403 [4]; sparse: d = 2^20, B = 256, E = 65000 137 -> 93
+// [15], 79000 173 -> 138 [15], 118000 267 -> 291 [10].  By E over the iterations that are built at once that is a line each.  The
+// rows' length by itself does not matter: 800 entries, B = 64 547 -> 57.  More than 301000 entries (2122 -> 1952, 2 vectors) was
+// not measured.
+constexpr int64_t kBuiltDense = 35000, kBuiltSparse = 11000, kMostEntries = 300000;
 constexpr int kEntryBytes = 16;  // of a list's entry in `ent`, `cols` and `pieces`
 
 struct Shape {
@@ -1300,7 +1314,8 @@ int64_t list_budget(const lpc_ctx *c) {
 }
 
 // What does not depend on the rows' lengths; S = 0 where the kernel does not apply: a wavefront per vector, two rows per
-// wavefront at most, the slices must fit LDS, and the lists of kLeastIters iterations of mean rows what the workspace may grow by.
+// wavefront at most, the slices must fit LDS, the lists of kLeastIters iterations of mean rows what the workspace may grow by, and the
+// separate launches must not be the better ones.
 Shape shape_of(const lpc_ctx *c) {
   Shape s{};
   if (!c->csr || !c->quant || c->cfg.bits > 16 || c->cfg.N > kLiWaves || c->cfg.m < 1 || c->prob.nnz <= 0) return s;
@@ -1311,6 +1326,8 @@ Shape shape_of(const lpc_ctx *c) {
   if (c->cfg.B > kMaxBatch || rows > (int64_t)kLiRows * kLiWaves * P || S > 65535 || P > c->device_cus) return s;
   const int64_t least = c->cfg.m < kLeastIters ? c->cfg.m : kLeastIters;
   if (kEntryBytes * least * rows * list_mean(c) > list_budget(c)) return s;
+  if (c->cfg.m <= kFewIters && c->cfg.m * rows * list_mean(c) < kFewEntries) return s;
+  if (c->cfg.B * list_mean(c) > kMostEntries) return s;
   s.fields = 32 / c->cfg.bits;
   s.words = (c->cfg.N + s.fields - 1) / s.fields;
   s.lds = 4 * (size_t)S * ((alpc ? 6 : 2) + s.words + 1) + 12 * (size_t)((S + 31) / 32);
@@ -1360,10 +1377,12 @@ hipError_t finish_lists(lpc_ctx *c, hipStream_t st) {
   const int64_t lists = list_rows(c) / c->cfg.B;
   const int64_t fit = (int64_t)lists_scratch(c).entries / (lists * c->list_cap);
   c->list_iters = (int32_t)(fit < list_iters(c) ? fit : list_iters(c));
+  const int64_t turns = (lists * c->list_iters + kOwners - 1) / kOwners;
   // (the builder sorts all of an owner's keys in LDS)
   c->lists_capable = lc_bits + pos_bits + k_bits <= 32 && lc_bits + pos_bits <= 30 &&
                      (int64_t)c->cfg.B * extents[1] <= kKeyCap &&
-                     c->list_iters >= (c->cfg.m < kLeastIters ? c->cfg.m : kLeastIters);
+                     c->list_iters >= (c->cfg.m < kLeastIters ? c->cfg.m : kLeastIters) &&
+                     c->cfg.B * list_mean(c) * turns <= (c->csr_sparse ? kBuiltSparse : kBuiltDense) * c->list_iters;
   return hipSuccess;
 }
 

@@ -265,7 +265,7 @@ def _one_bin(rng, r):  # columns of one owner, a quarter of its own
     (5001, 3, 512, lambda rng, r: list(range(10)) + [10 + r], dict(bits=4)),       # lists past five chunks
     (5003, 3, 200, lambda rng, r: rng.integers(0, 40, 30), dict(bits=6)),          # a row holds a column several times
     (60000, 2, 512, lambda rng, r: rng.choice(60000, 60, replace=False), {}),      # more keys than the builder holds at once
-    (262144, 2, 400, _one_bin, dict(m=2)),                                         # ... all in one bin; lists past 128 columns
+    (262144, 2, 400, _one_bin, {}),                                                # ... all in one bin; lists past 128 columns
     (262144, 2, 512, _one_bin, dict(m=2)),                                         # more than it sorts: the separate launches
     (3000, 2, 4, _zipf(3000, 20), dict(m=131, n_full=700)),                        # a second launch; margins taken by the plan
     (3000, 15, 64, _zipf(3000, 20), dict(algo=lpco.ALGO_ALPC_SC, scheme=lpco.SCHEME_B, bits=4)),
@@ -311,14 +311,23 @@ def _epoch_and_route(ctx, sp, epochs=1):
     return np.stack([v.cpu().numpy() for v in vec]), counts["resident"][1] > 0 and counts["vr_rows"][1] == 0
 
 
-@pytest.mark.parametrize("B,one_launch", [(400, True), (401, False)])
-def test_csr_epochs_by_the_entries_of_one_owner(B, one_launch):
-    """The list builder sorts 6400 entries of an owner's columns; data whose batches may hold more take the separate launches."""
+def _spread(d, count):  # one column of each of `count` ranges
+    return lambda rng, r: np.arange(count) * (d // count) + rng.integers(0, d // count, count)
+
+
+@pytest.mark.parametrize("d,B,rows,m,one_launch", [
+    (262144, 400, _one_bin, 6, True), (262144, 401, _one_bin, 6, False),  # 6400 entries of one owner, and 6416: what the builder sorts
+    (3000, 50, _spread(3000, 20), 4, False), (3000, 50, _spread(3000, 20), 5, True),  # few iterations of few entries
+    (3000, 313, _spread(3000, 20), 4, True), (3000, 312, _spread(3000, 20), 4, False),  # ... of 12520 and 12480
+    (3000, 512, _spread(3000, 400), 5, False), (3000, 512, _spread(3000, 400), 6, True),  # 204800 in a batch: 40960 and 34133 each
+    (524288, 256, _spread(524288, 240), 5, False), (524288, 256, _spread(524288, 240), 6, True),  # u^i sparse: 12288, 10240
+    (4000, 512, _spread(4000, 588), 9, False)])                            # 301056 in a batch
+def test_csr_epochs_take_one_launch_where_it_pays(d, B, rows, m, one_launch):
     from paper_1901_08924_amd import lpc
-    sp = _csr_problem(262144, 2, B, _one_bin)     # sixteen of an owner's columns in a row: 6400 entries, and 6416
+    sp = _csr_problem(d, 2, B, rows)
     got = []
     for form in (-1, 0):
-        ctx = gpu_context(sp, m=2, L=0.5, eta=0.4, bits=4)
+        ctx = gpu_context(sp, m=m, L=0.5, eta=0.4, bits=4)
         if form == 0:
             ctx.tune(lpc.TUNE_ITER_FORM, form)
         vec, route = _epoch_and_route(ctx, sp)
