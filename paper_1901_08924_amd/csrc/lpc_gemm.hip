@@ -813,13 +813,13 @@ Plan plan_of(const GemmArgs &g) {
     return (int64_t)((rows + tm - 1) / tm) * ((g.N + tn - 1) / tn) * batch;
   };
   if ((int64_t)g.K * g.nseg <= kFewProducts) return {32, 32, 2};
-  if (g.ldc >= (1 << 22)) return {32, 32, 4, true};
   for (int s = 0; s < g.nseg; ++s)
     if (g.lda[s] >= (1 << 22) || g.ldb[s] >= (1 << 22)) return {32, 32, 4, true};
   const int64_t k = (int64_t)g.K * g.nseg, t128 = tiles(128, 128), t64 = tiles(64, 64);
   if (t128 >= 640) return {128, 128, 0};
   if (k <= 160 && tiles(128, 64) >= 200) return {128, 64, 0};
   if (t128 >= 150 || (t128 >= 60 && k <= 640 && !g.transA && g.transB)) return {128, 128, 1};
+  if (g.ldc >= (1 << 22)) return {32, 32, 4, true};  // (what the small kernel requests of C; the tile kernels' stores take any)
   if (k > 160 && t64 >= 100) return {64, 64, 8};
   const int64_t t32 = tiles(32, 32);
   return {32, 32, t32 <= 256 || k > 2048 ? 16 : t32 <= 512 ? 8 : 4};

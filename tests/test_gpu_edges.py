@@ -90,6 +90,24 @@ def test_small_products_through_the_options_of_a_store(M, N, K, ldc, relu, accum
     assert bool((C[:, N:] == 7.0).all())
 
 
+# the tile kernel and its eight-wavefront form
+@pytest.mark.parametrize("M,N,K", [(128, 12800, 160), (128, 19200, 200)])
+def test_products_do_not_depend_on_the_distance_of_their_rows(M, N, K):
+    """Only the small tiles' kernel reaches C by offsets of 32 bits: the others take rows any distance apart, with the same bits."""
+    import torch
+    from paper_1901_08924_amd import lpc
+    rng = np.random.default_rng(M + K)
+    A, B = (to_dev(rng.standard_normal(shape, dtype=np.float32)) for shape in ((M, K), (K, N)))
+    got = []
+    for ldc in (N, 1 << 22):
+        C = torch.empty((M, ldc), device="cuda")
+        rc = lpc.lib.lpc_debug_gemm(A.data_ptr(), B.data_ptr(), C.data_ptr(), M, N, K, K, N, ldc, 0, 0, 1.0, None, 0, 0,
+                                    torch.cuda.current_stream().cuda_stream)
+        assert rc == 0
+        got.append(C[:, :N].cpu().numpy())
+    assert np.array_equal(*got)
+
+
 @pytest.mark.parametrize("M,N,K", GEMMS[1:])
 @pytest.mark.parametrize("tA,tB", [(0, 0), (0, 1), (1, 0), (1, 1)])
 def test_products_of_infinite_and_of_the_largest_numbers(M, N, K, tA, tB):
