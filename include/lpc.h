@@ -170,7 +170,8 @@ lpc_status lpc_dequantize_shared(lpc_ctx *ctx, const uint32_t *packed, const flo
 /* Alg. 1 steps 7-8 in one call (quantization step + communication step 2, scheme (a)): statistics of
  * the N rows of U, eq. (3), quantize + pack into packed [N][W] with delta_out [N], and the receiver's
  * average u_avg (d floats) of eq. (4).  Same results, bit for bit, as lpc_vector_stats +
- * lpc_quantize_clip + lpc_dequantize_avg in LPC_CLIP_LAMBDA mode; for small d it runs as two launches. */
+ * lpc_quantize_clip + lpc_dequantize_avg in LPC_CLIP_LAMBDA mode, also where u_avg overwrites parts of U.  One launch for a few
+ * thousand coordinates in all, two up to d = 32768, three or four past that. */
 lpc_status lpc_exchange(lpc_ctx *ctx, const float *U, uint32_t epoch, uint32_t iter, uint32_t *packed,
                         float *delta_out, float *u_avg, void *stream);
 

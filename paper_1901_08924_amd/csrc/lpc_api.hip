@@ -684,11 +684,13 @@ lpc_status lpc_dequantize_shared(lpc_ctx *ctx, const uint32_t *packed, const flo
 namespace {
 lpc_status exchange_impl(const lpc_ctx *c, const float *U, StreamKey key, uint32_t *packed, float *delta_out, float *u_avg,
                          hipStream_t st) {
-  // (an average over parts of U that other workgroups still read: launches of their own)
-  const bool apart = u_avg + c->d <= U || U + (int64_t)c->cfg.N * c->d_pad <= u_avg;
-  if (exchange_at_once(c) && (apart || fused_exchange_supported(c))) {
+  // Where the average overwrites a part of U: the launch's workgroups read the coordinates that they write before they write them,
+  // so it may lie on one of the vectors, unless they read all of U for the statistics.  Else launches of their own.
+  const int64_t at = ((intptr_t)u_avg - (intptr_t)U) / (int64_t)sizeof(float);  // (both 16-byte aligned)
+  const bool apart = at <= -c->d || at >= (int64_t)c->cfg.N * c->d_pad, on_vector = at >= 0 && at % c->d_pad == 0;
+  if (exchange_at_once(c) && (apart || on_vector)) {
     int32_t slots = 0;
-    if (!own_statistics(c)) LPC_TRY_HIP(launch_vector_stats(c, U, c->d_pad, 0, c->cfg.N, nullptr, kStatsPartial, &slots, st));
+    if (!apart || !own_statistics(c)) LPC_TRY_HIP(launch_vector_stats(c, U, c->d_pad, 0, c->cfg.N, nullptr, kStatsPartial, &slots, st));
     return dev(launch_fused_exchange(c, U, slots, key, packed, delta_out, nullptr, 0.0f, nullptr, u_avg, st));
   }
   LPC_TRY_HIP(launch_quantize_vectors(c, U, key, packed, delta_out, st));

@@ -217,6 +217,28 @@ def test_exchange_takes_the_same_statistics_itself(d, N):
     ctx.close()
 
 
+# one launch with statistics of its own, two launches, and none of both
+@pytest.mark.parametrize("d,N", [(5, 1), (1003, 5), (1025, 4), (8192, 1), (2500, 7), (16384, 64), (20000, 3), (40000, 2)])
+def test_exchange_whose_average_overwrites_a_vector(d, N):
+    """On a vector, in the middle of one, and over the first one's beginning: what an average beside U gives."""
+    import torch
+    sp = lpc_synth.make("c1", n=64, d=d, N=N, B=1, bits=3, seed=3)
+    ctx = gpu_context(sp, bits=3, clip_mode=lpco.CLIP_CSIGMA, clip=1.5)
+    u = to_dev(lpc_synth.gaussian_u(N, d, seed=d + N)).view(-1)
+    outs = []
+    for at in (None, 0, (N - 1) * ctx.d_pad, (N // 2) * ctx.d_pad + 4, -4):
+        memory = torch.zeros(8 + u.numel() + d, device="cuda")
+        memory[8:8 + u.numel()] = u
+        U, packed = memory[8:8 + u.numel()].view(N, -1), torch.empty(N, ctx.W, dtype=torch.int32, device="cuda")
+        delta, avg = torch.empty(N, device="cuda"), torch.empty(d, device="cuda") if at is None else memory[8 + at:8 + at + d]
+        ctx.exchange(U, 1, 2, packed, delta, avg)
+        outs.append([t.cpu().numpy() for t in (packed, delta, avg)])
+    for other in outs[1:]:
+        for a, b in zip(outs[0], other):
+            assert np.array_equal(a, b)
+    ctx.close()
+
+
 # a workgroup of the entropy coder owns 255 segments of 32 coordinates
 @pytest.mark.parametrize("d,bits,scale", [(8159, 3, 1.0), (8160, 3, 1.0), (8161, 2, 1e-3), (16321, 4, 1.0), (24481, 5, 0.05),
                                           (40000, 9, 1.0)])
