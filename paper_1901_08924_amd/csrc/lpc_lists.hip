@@ -842,10 +842,10 @@ __global__ __launch_bounds__(kLiThreads) void list_epoch_kernel(ListArgs a) {
         }
         s = row16_sum(s);
         const float z = read_lane(s, 0);
-        // (x_0 of Alg. 1 is the snapshot: its differences are exactly zero; the builder left the snapshot's slope in row.z)
+        // (x_0 of Alg. 1 is the snapshot: zero, or NaN where the slope is; the builder left the snapshot's slope in row.z)
         const uint32_t label = row[q].z, snap = row[q].w;
         const float diff = loss_slope(a.loss, z, __builtin_bit_cast(float, label)) - __builtin_bit_cast(float, snap);
-        const float coef = ALPC || t > 0 ? diff * a.scale : 0.0f;
+        const float coef = diff * a.scale;
         if (lane == 0) st_word(a.slope + par * total_rows + slot[q], __builtin_bit_cast(uint32_t, coef), tag);
       }
     }

@@ -337,6 +337,41 @@ def test_csr_epochs_take_one_launch_where_it_pays(d, B, rows, m, one_launch):
     assert np.array_equal(*got) and not np.array_equal(got[0][0], sp.w0)
 
 
+@pytest.mark.parametrize("where", ["w", "value", "label", "largest"])
+@pytest.mark.parametrize("d,over", [(3000, {}), (50000, {}), (3000, dict(m=1, B=400)), (50000, dict(clip_mode=1, clip=2.0)),
+                                    (3000, dict(algo=lpco.ALGO_ALPC_GC)), (50000, dict(algo=lpco.ALGO_ALPC_GC, scheme=lpco.SCHEME_B)),
+                                    (3000, dict(scheme=lpco.SCHEME_C))])
+def test_csr_epochs_of_numbers_that_are_not_finite(d, over, where):
+    """Infinities and NaN in the iterate, in entries and labels, and entries whose margins and sums overflow: the numbers and the
+    flag of the separate launches."""
+    from paper_1901_08924_amd import lpc
+    over = dict(dict(m=6, N=5, B=64, L=0.5, eta=0.4, bits=4, tau2=0.5), **over)
+    sp = _csr_problem(d, over["N"], over["B"], _zipf(d, 20) if over["m"] > 1 else _spread(d, 40))
+    rng = np.random.default_rng(1)
+    some = rng.permutation(sp.n)[:12]
+    if where == "w":
+        sp.w0[[3, 700, 2900]] = np.inf, np.nan, -np.inf
+    elif where == "value":
+        sp.csr[2][sp.csr[0][some]] = np.resize([np.inf, np.nan, -np.inf], 12)
+    elif where == "label":
+        sp.y = sp.y.copy()
+        sp.y[some] = np.nan
+    else:
+        sp.csr[2][:] *= np.float32(2e38) / np.abs(sp.csr[2]).max()
+    got = []
+    for form in (-1, 0):
+        ctx = gpu_context(sp, **over)
+        if form == 0:
+            ctx.tune(lpc.TUNE_ITER_FORM, form)
+        vec, route = _epoch_and_route(ctx, sp, epochs=2 if over["m"] > 1 else 1)
+        assert route == (form == -1)
+        got.append((vec, ctx.take_device_flags()))
+        ctx.close()
+    # (one iteration of differences at x~: zeros while the margins are finite)
+    assert got[0][1] == got[1][1] == (0 if where == "largest" and over["m"] == 1 else lpc.ENONFINITE)
+    assert np.array_equal(got[0][0], got[1][0], equal_nan=True)
+
+
 @pytest.mark.parametrize("over", [{}, dict(algo=lpco.ALGO_ALPC_GC, scheme=lpco.SCHEME_B)])
 def test_csr_epoch_that_gives_up_or_is_refused(over):
     """The caller's vectors are the epoch's or what they were, whatever the waits are given; a launch that does not fit
