@@ -497,3 +497,47 @@ def test_epochs_of_two_threads_on_two_streams(d, N):
     for k in range(2):
         assert alone[k][1] == together[k][1] == 0
         assert np.array_equal(alone[k][0], together[k][0])
+
+
+@pytest.mark.parametrize("over", [{}, dict(algo=lpco.ALGO_ALPC_GC, scheme=lpco.SCHEME_B, tau2=0.5, L=0.5)])
+@pytest.mark.parametrize("beside", ["csr", "dense", "products"])
+def test_csr_epochs_beside_other_work(beside, over):
+    """The inner loop of CSR epochs wants all compute units at once.  Another thread's such loops, dense loops and a queue of
+    products on another stream hold them for a while: the epochs wait, and give what they give alone."""
+    import threading
+    import torch
+    problems = [lpc_synth.make("c3", n=4096, d=20000, nnz_mean=20, N=6, B=64, seed=2),
+                lpc_synth.make("c2", n=2048, d=4096, N=8, B=16, seed=2) if beside == "dense" else
+                lpc_synth.make("c3", n=4096, d=3001, nnz_mean=10, N=16, B=100, seed=3)]
+
+    def run(out, k, stream):
+        with torch.cuda.stream(stream):
+            ctx = gpu_context(problems[k], m=140, seed=k, **(over if k == 0 else {}))
+            vec = [to_dev(problems[k].w0) for _ in range(3)]
+            for s in range(8):
+                ctx.epoch(vec[0], s, vec[1], vec[2])
+            stream.synchronize()
+            out[k] = (np.stack([v.cpu().numpy() for v in vec]), ctx.take_device_flags())
+            ctx.close()
+
+    def products(out, k, stream):
+        with torch.cuda.stream(stream):
+            a = torch.ones(4096, 4096, device="cuda")
+            for _ in range(60):
+                a = (a @ a).clamp_(max=1.0)
+            stream.synchronize()
+            out[k] = (a.cpu().numpy(), 0)
+
+    other = products if beside == "products" else run
+    alone, together = {}, {}
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    run(alone, 0, streams[0])
+    other(alone, 1, streams[1])
+    threads = [threading.Thread(target=f, args=(together, k, streams[k])) for k, f in enumerate((run, other))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for k in range(2):
+        assert alone[k][1] == together[k][1] == 0
+        assert np.array_equal(alone[k][0], together[k][0])
