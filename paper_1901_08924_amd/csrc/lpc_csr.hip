@@ -545,10 +545,15 @@ __global__ __launch_bounds__(kSparseThreads) void csr_vr_ordered_kernel(CsrArgs 
         const int32_t len = cur.hi - cur.lo;
         *reinterpret_cast<float4 *>(&hot[grp][gl * 4]) = make_float4(0.f, 0.f, 0.f, 0.f);  // kHotCols = 4 * kGroup
         const int sh = lane & 48;  // this group's first lane in the wavefront
-        int32_t cls[4], rt[4], nt = 0;
+        int32_t cls[4], rt[4], nt = 0, before[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q)  // of the row's lane before (lane 0: of lane 15)
+          before[q] = __builtin_amdgcn_update_dpp(0, c[q], 0x121, 0xF, 0xF, false);
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-          cls[q] = q * kGroup + gl >= len ? 0 : c[q] < kHotCols ? 3 : c[q] < a.head ? 1 : 2;
+          // (`hot` has one place for a column that a row holds several times: the others are added like the head's)
+          const bool again = c[q] == (gl > 0 ? before[q] : q > 0 ? before[q - 1] : -1);
+          cls[q] = q * kGroup + gl >= len ? 0 : c[q] < kHotCols && !again ? 3 : c[q] < a.head ? 1 : 2;
           if (cls[q] == 3) hot[grp][c[q]] = coef * v[q];
           stage[0][grp][q * kGroup + gl] = make_int2(cls[q] == 1 ? c[q] : -1, __float_as_int(coef * v[q]));
           const uint32_t gt = (uint32_t)(__ballot(cls[q] == 2) >> sh) & 0xffffu;
@@ -854,10 +859,11 @@ hipError_t launch_csr_vr_grad(const lpc_ctx *c, const float *w, const float *w_s
 }
 
 // Sparse worker pass (all N workers).  s.U rows and the bitmap must be zero outside what this call adds.
-// workgroups per worker of the sparse worker pass: one round of rows each
+// Batch positions that a workgroup of it takes: one round of rows.
+int csr_sparse_block() { return kRowGroups; }
+// Workgroups per worker
 // (measured on n = d = 2^20, N = 16, B = 256: two rounds per workgroup, hence three planes per worker instead of
 // five, make this pass 7 us slower and the statistics pass 3.4 us faster)
-int csr_sparse_block() { return kRowGroups; }
 int csr_sparse_parts(int32_t B) { return (B + kRowGroups - 1) / kRowGroups; }
 
 // Leading columns the sparse inner iteration treats densely.  Twice the snapshot pass's head when d is large: the

@@ -300,6 +300,26 @@ def test_csr_epochs_in_one_launch(d, N, B, rows, over):
         assert (diff > 1e-5 * scale).mean() <= max(2e-3, 2.0 / d) and diff.max() <= 0.05 * scale
 
 
+@pytest.mark.parametrize("form", [-1, 0])
+@pytest.mark.parametrize("B", [20, 70])
+def test_sparse_epochs_of_rows_that_hold_a_column_several_times(B, form):
+    """Among the frequent columns that the sparse worker pass keeps a value per row of, up to a row's 64th entry, and among the
+    others."""
+    from paper_1901_08924_amd import lpc
+    sp = _csr_problem(70000, 4, B, lambda rng, r: np.concatenate([rng.integers(0, 70, 20 + r % 50), rng.integers(69990, 70000, 5)]))
+    over = dict(m=40, L=0.5, eta=0.4, bits=8)
+    ctx = gpu_context(sp, **over)
+    ctx.tune(lpc.TUNE_ITER_FORM, form)
+    vec, one_launch = _epoch_and_route(ctx, sp)
+    assert one_launch == (form == -1) and ctx.take_device_flags() == 0
+    ctx.close()
+    p, _k = oracle_problem(sp)
+    want = sp.w0.copy()
+    lpco.epoch(p, oracle_config(sp, **over), want, 0)
+    # a flipped rounding decision moves a coordinate by eta * delta / N, 2e-6 of the largest here; entries left out, by 5e-4
+    assert np.abs(vec[0] - want).max() <= 1e-5 * np.abs(want).max() and np.abs(want - sp.w0).max() >= 0.05 * np.abs(want).max()
+
+
 def _epoch_and_route(ctx, sp, epochs=1):
     """x~, y and z after the epochs, and whether the inner loop was one launch."""
     vec = [to_dev(sp.w0) for _ in range(3)]
