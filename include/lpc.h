@@ -57,7 +57,7 @@ typedef enum { LPC_SCHEME_A = 0, LPC_SCHEME_B = 1, LPC_SCHEME_C = 2 } lpc_scheme
 typedef enum { LPC_BATCH_WORKER = 1, LPC_BATCH_SHARED = 2 } lpc_batch_kind;
 
 /* The data of eq. (1).  Exactly one of X (dense row-major, leading dimension
- * ldx floats) or (row_ptr, col_idx, vals) (CSR, sorted int32 indices) is set.
+ * ldx floats) or (row_ptr, col_idx, vals) (CSR, sorted int32 indices; equal ones add up) is set.
  * Losses: logistic f_i = log(1+exp(-y_i x_i'w)), y_i = +-1; squared
  * f_i = (x_i'w - y_i)^2/2; MLP = ReLU multi-layer perceptron with softmax
  * cross-entropy, X = inputs [n][mlp_dims[0]], y = class ids stored as floats,
@@ -199,7 +199,7 @@ lpc_status lpc_prox_step(lpc_ctx *ctx, float *w, const float *u_avg, const float
  * snapshot gradient, m inner iterations, snapshot update.  w_snap: in x~^s, out
  * x~^(s+1).  y, z: ALPC-SVRG's auxiliary iterates, in/out (d floats each; start
  * them equal to x~^0).  epoch = s selects the random streams and Alg. 3's schedule.
- * On dense data the inner loop may be one launch whose workgroups wait for each other (LPC_TUNE_ITER_FORM), for a
+ * The inner loop may be one launch whose workgroups wait for each other (LPC_TUNE_ITER_FORM), for a
  * bounded time.  Should that run out (they have to be on the GPU together, and another process may hold part of it),
  * the epoch does not take place: w_snap, y and z keep what they held.  As this call only enqueues, the next ones that
  * answer to the host say so: lpc_objective, lpc_gradient_mapping, lpc_clip_sweep, lpc_epoch_report, and lpc_epoch_traced
@@ -231,10 +231,10 @@ lpc_status lpc_gradient_mapping(lpc_ctx *ctx, const float *w, float eta, double 
  * entropy coding (Sec. 6.1: the optimal prefix code of that message's own histogram; 32*d with
  * quantization off; add 32 bits for delta and Table 1's fan-out for a total as in Sec. 6.1's table of
  * communication costs); asking for it synchronises the stream once per message.  Each of the three may be
- * NULL; all NULL is lpc_epoch.  Where lpc_epoch takes one launch for the inner loop (dense data, see
- * LPC_TUNE_ITER_FORM), the traced epoch takes one per iteration and its iterates are the same bits.  Elsewhere it takes
- * the unfused launches (statistics, quantizer, receiver, prox as separate kernels): for Alg. 1 in LPC_CLIP_LAMBDA mode on
- * dense data its iterates equal lpc_epoch's bit for bit, else to rounding.
+ * NULL; all NULL is lpc_epoch.  Where lpc_epoch takes one launch for the inner loop of dense data (see
+ * LPC_TUNE_ITER_FORM), the traced epoch takes one per iteration and its iterates are the same bits.  Elsewhere, and on CSR
+ * data always, it takes the unfused launches (whole vectors, statistics, quantizer, receiver, prox as separate kernels): for
+ * Alg. 1 in LPC_CLIP_LAMBDA mode on dense data its iterates equal lpc_epoch's bit for bit, else to rounding.
  * Asynchronous unless coded_bits_host is given. */
 lpc_status lpc_epoch_traced(lpc_ctx *ctx, float *w_snap, float *y, float *z, uint32_t epoch, float *delta_trace,
                             uint32_t *nclip_trace, uint64_t *coded_bits_host, void *stream);
@@ -351,9 +351,12 @@ lpc_status lpc_debug_gemm(const float *A, const float *B, float *C, int32_t M, i
  *       one workgroup; every scheme, with or without quantization; not while the stream is being captured) all m inner
  *       iterations in one launch, cooperative with a workgroup per worker whose waits LPC_TUNE_SPIN_LIMIT bounds, or of one
  *       workgroup for all; on wide problems (d <= 24576, B <= 64, b <= 8 or quantization off, as far as the workers' column
- *       blocks fit the compute units) likewise with a group of workgroups per worker; on CSR data (b <= 16, N <= 16, B <= 512, at
- *       most 8192 sampled rows per iteration, 256 compute units) up to 128 inner iterations per launch, the same way, with the
- *       bits of the separate launches.  Such an epoch takes place as a whole or not at all (lpc_epoch).
+ *       blocks fit the compute units) likewise with a group of workgroups per worker; on quantized CSR data
+ *       (N <= 16, B <= 512, at most 8192 sampled rows per iteration, d up to about 2 million, 256 compute units) up to 128 inner
+ *       iterations per launch, the same way, where that pays: not for one to four iterations of few entries, batches of more
+ *       than 300000 entries, and rows so long, the longest one among them, that a launch holds too few iterations.  Its bits are
+ *       those of the separate launches with clipping by lambda and rows of at most 64 different columns, else they agree to
+ *       rounding.  Such an epoch takes place as a whole or not at all (lpc_epoch).
  *     0: three launches: the workers' rows (whole rows per workgroup, partial gradient rows out), their fold, the
  *       exchange.  CSR data: the separate launches of its sparse inner iteration.
  *     1: two launches: the workers' rows, then fold + exchange in one launch whose workgroups wait, for a bounded

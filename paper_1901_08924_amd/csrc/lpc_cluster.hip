@@ -79,8 +79,9 @@ __global__ __launch_bounds__(kClThreads) void cluster_epoch_kernel(ClusterArgs a
   constexpr int D = 64 * K, RG = (RW + 3) / 4;
   constexpr bool kWaveOwns = K <= 4;  // a wavefront holds a whole vector, four coordinates per lane
   int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  // What derives from these alone is else kept in registers for the whole loop, and takes others with it.  Where taking them afresh
-  // in every iteration pays: d = 90, N = 8, B = 64, 905 iterations 3784 -> 3616 us, fifteen drawn problems of these kernels 0.95 to
+  // What derives from these alone is else kept in registers for the whole loop, and takes others with it: this compiler's choice,
+  // to be looked at again with another one (K = 2 and 4: 98 -> 85, 108 -> 93 vector registers, 78 -> 62 scalar ones in memory).
+  // Where taking them afresh in every iteration pays: d = 90, N = 8, B = 64, 905 iterations 3784 -> 3616 us, fifteen drawn problems of these kernels 0.95 to
   // 1.006 times; the others of Alg. 1 the same, Alg. 2 and 3 up to 1.12 times.
   constexpr bool kAfresh = !ALPC && Q == kOwnScale && K >= 2 && K <= 4 && RW == 4;
   const int g = blockIdx.x / a.spread, v0 = g * a.nv;

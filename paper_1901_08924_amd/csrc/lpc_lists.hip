@@ -14,8 +14,10 @@
 // of an owner takes vector i's list: slope times value, sums, eq. (3), rules (1) and (2); the codes meet in LDS, a field per
 // vector and column, and a lane per touched column takes eq. (4) and the update.
 // Margins and sums are added up in the order of the separate launches (a column's entries in blocks of batch positions, the
-// blocks in order: a list is cut in pieces of one column and block), so an epoch's bits do not depend on the route.  A
-// segmented scan over the lanes would be 0.3 us per iteration less (16 vectors), and another rounding now and then.
+// blocks in order: a list is cut in pieces of one column and block), so an epoch's bits do not depend on the route, but for
+// three sums of another order: what a row holds past its 64th entry or a second time, which the sparse worker pass adds by
+// itself, and with clipping by c*sigma the sums over the coordinates.  A segmented scan over the lanes would be 0.3 us per
+// iteration less (16 vectors), and another rounding now and then.
 // Neighbouring columns belong to different owners because text-like data has its frequent columns side by side.
 // Reuse of words: a column's x word is kept once, written again when its owner has the slopes of every row that holds the
 // column, hence after those rows' wavefronts read it.  Slopes and statistics have two sets: set t is written again at t + 2 by
@@ -85,8 +87,8 @@ __device__ __forceinline__ auto buffer(const void *from, uint32_t bytes) {
 // and walked in that order: heads of columns and pieces are votes of 64 neighbours, and counts of votes place them.  No sum or
 // place depends on timing.
 // Entries go to memory by way of LDS: stored from where they are read, one line each, the address units were busy throughout
-// and lines left the L2 half full (0.77 GB written for 0.24).  Registers must not spill: 30 of them are as many bytes as the lists.
-// Bound by instructions (2370 of the vector units per wavefront and batch) and LDS.  Two workgroups to a CU: 80 KB for B = 256.
+// and lines left the L2 half full (0.77 GB written for 0.24; now 0.35).  Registers must not spill: 30 of them are as many bytes as the lists.
+// Bound by instructions (2360 of the vector units per wavefront and batch: these are busy 58 % of the time) and LDS (73 %).  Two workgroups to a CU: 80 KB for B = 256.
 // Measured on MI355X, lists of 128 iterations of n = d = 2^20, 16 vectors, B = 256, 40 entries a row: 214 us; 64 iterations of
 // d = 150001, 9 vectors, B = 100, 24 entries: 40 (each entry placed by itself, a wavefront per list to find heads: 362, 63).
 __global__ __launch_bounds__(kLiThreads, 8) void list_build_kernel(ListBuildArgs a) {

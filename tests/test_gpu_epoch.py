@@ -272,7 +272,8 @@ def _one_bin(rng, r):  # columns of one owner, a quarter of its own
     (2999, 7, 9, _zipf(2999, 6), dict(algo=lpco.ALGO_ALPC_GC, scheme=lpco.SCHEME_C, bits=7, n_full=900, clip_mode=1, clip=1.0))])
 def test_csr_epochs_in_one_launch(d, N, B, rows, over):
     """Workgroups by columns, lists of the sampled entries: agreement with the oracle's dense arithmetic up to a few flipped
-    rounding decisions (a flip moves a coordinate by eta*delta/N), and the bits of the separate launches."""
+    rounding decisions (a flip moves a coordinate by eta*delta/N), and the bits of the separate launches (with clipping by c*sigma
+    the sums over the coordinates have another order: their last bits reach no scale factor here)."""
     from paper_1901_08924_amd import lpc
     sp = _csr_problem(d, N, B, rows)
     over = dict(dict(m=6, L=0.5, eta=0.4, bits=2, sigma=1e-3, tau2=0.5), **over)
