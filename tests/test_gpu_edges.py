@@ -63,6 +63,34 @@ def test_products_are_no_less_exact_than_fp32_multiply_adds(M, N, K, tA, tB):
     assert np.linalg.norm(got - A @ B) <= np.linalg.norm(chain - A @ B)
 
 
+# whole and ragged tiles of 128 x 128 by eight and by four wavefronts, sums from the first length in fp16 parts on
+@pytest.mark.parametrize("M,N,K", [(2048, 1280, 512), (1921, 1300, 513), (3201, 3330, 545), (3328, 3200, 576)])
+@pytest.mark.parametrize("tA,tB", [(0, 0), (0, 1), (1, 0), (1, 1)])
+def test_products_whose_rows_grow_and_shrink_along_the_sum(M, N, K, tA, tB):
+    """The power of two that a row's fp16 parts are scaled by follows the row: zeros first, then growth by up to 2^60, from
+    numbers below 2^-126 on, at another place in every row; decay; single large numbers among small ones."""
+    rng = np.random.default_rng(M + N + K)
+    k = np.arange(K)
+    def operand(rows):
+        X = rng.standard_normal((rows, K))
+        begin, slope = rng.integers(0, 80, (rows, 1)), rng.integers(-2, 3, (rows, 1)) * rng.random((rows, 1))
+        X *= np.exp2(np.clip(slope * k * 60.0 / K, -30, 30) + rng.integers(-10, 10, (rows, 1)))
+        X[k[None] < begin * (np.arange(rows)[:, None] % 3 == 0)] = 0.0
+        X[np.arange(rows), rng.integers(0, K, rows)] *= np.exp2(rng.integers(0, 12, rows))
+        X[::7] *= 2.0 ** -100
+        return X.astype(np.float32)
+    A, B = operand(M), operand(N).T.copy()
+    A64, B64 = A.astype(np.float64), B.astype(np.float64)
+    got = _gemm(to_dev(A.T.copy() if tA else A), to_dev(B.T.copy() if tB else B), tA, tB)
+    # Two operands in 22 bits and, per sixteen k, four additions that round to 2^-23 if the instruction cuts off (one product
+    # often outweighs all others here, so their roundings do not cancel); an element below 2^-15 of its row's largest is off by
+    # up to 2^-37 of that; results below 2^-126.
+    most = (2 + 4 * ((K + 15) // 16)) * 2.0 ** -23
+    bound = (most * (np.abs(A64) @ np.abs(B64)) + 2.0 ** -149 +
+             2.0 ** -37 * (np.abs(A64).max(1)[:, None] * np.abs(B64).sum(0) + np.abs(A64).sum(1)[:, None] * np.abs(B64).max(0)))
+    assert (np.abs(got - A64 @ B64) <= bound).all()
+
+
 # 32 x 32 tiles by sixteen wavefronts with fewer, as many and more steps of K; 64 x 64 by eight; rows of C too far apart for
 # offsets within a tile; 32 x 32 by eight (272, 288 tiles) and four (528); 270 tiles with a long K
 @pytest.mark.parametrize("M,N,K,ldc", [(1, 3, 4, 3), (33, 31, 16, 40), (32, 33, 257, 33), (65, 64, 1030, 70), (640, 660, 161, 663),
