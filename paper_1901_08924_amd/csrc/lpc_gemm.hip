@@ -420,12 +420,12 @@ __device__ __forceinline__ void store_tile(const GemmArgs &g, const floatx16 (&a
 // wavefront, not in use by anyone else); slot `tile` of batch item bz receives them.  Contains a barrier.
 template <int NW = 4>
 __device__ __forceinline__ void tile_statistics(const GemmArgs &g, double *red, int tid, int64_t bz, int64_t tile,
-                                                float fmx, double ssum, double ssq, double sbad) {
+                                                float fmx, double ssum, double ssq, double sbad, bool keeps = true) {
   const int lane = tid & 63, wave = tid >> 6;
   const double a_w = (double)wave_max(fmx), s_w = wave_sum(ssum), q_w = wave_sum(ssq), b_w = wave_sum(sbad);
   if (lane == 0) { red[wave * 4 + 0] = a_w; red[wave * 4 + 1] = s_w; red[wave * 4 + 2] = q_w; red[wave * 4 + 3] = b_w; }
   __syncthreads();
-  if (tid == 0) {
+  if (tid == 0 && keeps) {
     double a_t = 0.0, s_t = 0.0, q_t = 0.0, b_t = 0.0;
     for (int k = 0; k < NW; ++k) { a_t = fmax(a_t, red[k * 4]); s_t += red[k * 4 + 1]; q_t += red[k * 4 + 2]; b_t += red[k * 4 + 3]; }
     double *p = g.stat_part + bz * g.stat_batch_stride + ((int64_t)g.stat_slot0 + tile) * 4;
@@ -877,15 +877,14 @@ __global__ __launch_bounds__(512, 1) void gemm_pair_kernel(GemmArgs g) {
 // over four alone: 240 products of 40 sizes (K 17 to 5821, transposed and not) 0.51 to 1.0 times the error, workers' vectors of 16
 // nets 0.67 to 0.95 times.
 // FAR: operands whose rows are too far apart for fetch8.
-template <bool TA, bool TB, int T, int NW, bool FAR = false>
-__global__ __launch_bounds__(64 * NW) void gemm_small_kernel(GemmArgs g) {
-  touch_kernel_arguments<(int)(sizeof(GemmArgs))>();
+// part: one 32 x 32 part of the tile at a time; tid: within the tile's wavefronts; keeps = false: a workgroup's spare wavefronts,
+// which take part in its barriers and store nothing.
+template <bool TA, bool TB, int T, int NW, bool FAR>
+__device__ __forceinline__ void small_tile(const GemmArgs &g, int bx, int by, int64_t bz, int tiles_n, int tid,
+                                           float (&part)[NW][32][32], double (&red)[4 * NW], bool keeps) {
   constexpr int I = T / 32, DEPTH = FAR ? 4 : 2;
-  __shared__ float part[NW][32][32];  // one 32 x 32 part of the tile at a time
-  __shared__ double red[4 * NW];
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int m0 = blockIdx.y * T, n0 = blockIdx.x * T;
-  const int64_t bz = blockIdx.z;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int m0 = by * T, n0 = bx * T;
   const int steps = (g.K + 15) / 16, total = steps * g.nseg;
   const int mn = lane & 31, kq = 8 * (lane >> 5);
   floatx16 acc[I][I];
@@ -981,7 +980,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_small_kernel(GemmArgs g) {
         float t = part[0][e >> 5][e & 31];
 #pragma unroll
         for (int w = 1; w < NW; ++w) t += part[w][e >> 5][e & 31];
-        if (row < g.M && col < g.N) {
+        if (keeps && row < g.M && col < g.N) {
           if (t == t) {
             float val;
             if constexpr (FAR) {
@@ -1006,7 +1005,15 @@ __global__ __launch_bounds__(64 * NW) void gemm_small_kernel(GemmArgs g) {
     count(skinny_store(g, g.C + bz * g.strideC, bz, row, col, plain_sum<TA, TB>(g, bz, row, col)));
   }
   if (g.stat_part)  // uniform
-    tile_statistics<NW>(g, red, tid, bz, (int64_t)blockIdx.y * gridDim.x + blockIdx.x, fmx, ssum, ssq, sbad);
+    tile_statistics<NW>(g, red, tid, bz, (int64_t)by * tiles_n + bx, fmx, ssum, ssq, sbad, keeps);
+}
+
+template <bool TA, bool TB, int T, int NW, bool FAR = false>
+__global__ __launch_bounds__(64 * NW) void gemm_small_kernel(GemmArgs g) {
+  touch_kernel_arguments<(int)(sizeof(GemmArgs))>();
+  __shared__ float part[NW][32][32];
+  __shared__ double red[4 * NW];
+  small_tile<TA, TB, T, NW, FAR>(g, blockIdx.x, blockIdx.y, blockIdx.z, gridDim.x, threadIdx.x, part, red, true);
 }
 
 // Sums of at most kFewProducts products (two classes; a batch of one row): there the five small parts and what is left
@@ -1252,12 +1259,11 @@ int gemm_skinny_short_slots(const GemmArgs &g) { return (g.M + 63) / 64; }
 // The same product when K <= 128 (a worker's rows of one batch): every row of A and B that the workgroup needs
 // is requested before anything is consumed, one round trip instead of one per operand and parameter set.
 // Rows are taken in the order of gemm_skinny_tn_kernel, so the sums are the same to the bit.
-__global__ __launch_bounds__(256) void gemm_skinny_tn_short_kernel(GemmArgs g) {
-  touch_kernel_arguments<(int)(sizeof(GemmArgs))>();
-  __shared__ __attribute__((aligned(16))) float Bs[2 * 128 * kSkinnyN];  // [segment][k][16], then [4][64][16]
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int64_t bz = blockIdx.y;
-  const int m = blockIdx.x * 64 + lane;
+// Bs: [segment][k][16], then [4][64][16]
+constexpr int kShortFloats = 2 * 128 * kSkinnyN;
+__device__ __forceinline__ void skinny_short(const GemmArgs &g, int bx, int64_t bz, int tid, float *Bs, double *stat_red, bool keeps) {
+  const int lane = tid & 63, wave = tid >> 6;
+  const int m = bx * 64 + lane;
   const int kn = g.K;
   float a[2][32];
 #pragma unroll
@@ -1315,8 +1321,8 @@ __global__ __launch_bounds__(256) void gemm_skinny_tn_short_kernel(GemmArgs g) {
   float fmx = 0.0f;
   double ssum = 0.0, ssq = 0.0, sbad = 0.0;
   for (int i = tid; i < 64 * kSkinnyN; i += 256) {
-    const int l = i >> 4, c = i & 15, row = blockIdx.x * 64 + l;
-    if (row < g.M && c < g.N) {
+    const int l = i >> 4, c = i & 15, row = bx * 64 + l;
+    if (keeps && row < g.M && c < g.N) {
       const float r = ((red[(0 * 64 + l) * kSkinnyN + c] + red[(1 * 64 + l) * kSkinnyN + c]) +
                        red[(2 * 64 + l) * kSkinnyN + c]) + red[(3 * 64 + l) * kSkinnyN + c];
       const float val = skinny_store(g, C, bz, row, c, r);
@@ -1327,10 +1333,174 @@ __global__ __launch_bounds__(256) void gemm_skinny_tn_short_kernel(GemmArgs g) {
       }
     }
   }
-  if (g.stat_part) {  // uniform
-    __shared__ double stat_red[16];
-    tile_statistics(g, stat_red, tid, bz, blockIdx.x, fmx, ssum, ssq, sbad);
+  if (g.stat_part) tile_statistics(g, stat_red, tid, bz, bx, fmx, ssum, ssq, sbad, keeps);  // uniform
+}
+__global__ __launch_bounds__(256) void gemm_skinny_tn_short_kernel(GemmArgs g) {
+  touch_kernel_arguments<(int)(sizeof(GemmArgs))>();
+  __shared__ __attribute__((aligned(16))) float Bs[kShortFloats];
+  __shared__ double stat_red[16];
+  skinny_short(g, blockIdx.x, blockIdx.y, threadIdx.x, Bs, stat_red, true);
+}
+
+// ---- what is left of a worker pass once every layer's deltas are there ---------------------------------------
+// Bias sums of every layer and the weight gradients that neither fill the chip nor need the sum of the two sets of deltas (the
+// first layer's) in one launch: each by itself is bound by its launch, its first loads and its last stores.  A workgroup of WT
+// threads is WT / 64 NW tiles of a product, or WT / 256 blocks of 64 rows of a short product or of 64 columns of the sums;
+// each computes what its own launch would, to the bit.
+// Epochs, us, launches of their own -> this: 777-391-129-33, N = 6, B = 50 2559 -> 2499; 735-640-487-2, N = 3, B = 32 2106 -> 1940;
+// 94-640-64-10, N = 10, B = 64 786 -> 724; 3072-1024-1024-10, N = 16, B = 128 (bias sums and last layer) 17821 -> 17682; fourteen nets
+// 1.005 to 1.085 times.  Larger products (64 x 64 tiles and more) keep launches of their own, which fill the chip.
+constexpr int kGroupMax = kGroupProducts;
+struct GroupArgs {
+  GemmArgs g[kGroupMax];
+  ColsumLayers cl;
+  // workgroups [first[i], first[i+1]) take product i, those from first[n] on the bias sums; waves[i]: 0 a short product; units:
+  // tiles (blocks) of a product and batch item, along N and in all
+  int first[kGroupMax + 1], waves[kGroupMax], tiles_n[kGroupMax], tiles[kGroupMax];
+  int n, sums, sum_blocks;
+};
+
+// out[b][c] = alpha * sum over the K rows of batch item b of (D0[row][c] + D1[row][c]); 64 columns; the four wavefronts take
+// interleaved rows and are combined in wavefront order.  sum_back: D0[row][c] also receives D0[row][c] + D1[row][c] (every
+// element is read by exactly one thread).
+__device__ __forceinline__ void bias_sums(const ColsumLayers &g, int x, int b, int tid, float (&red)[4][64], bool keeps) {
+  const int lane = tid & 63, wv = tid >> 6;
+  int l = 0;
+#pragma unroll
+  for (int k = 1; k < kColsumMaxLayers; ++k)
+    if (k < g.n && x >= g.first[k]) l = k;
+  // the layer's fields, selected without indexing the argument arrays by a run-time value
+  float *D0 = g.D0[0], *out = g.out[0];
+  const float *D1 = g.D1[0];
+  int cols = g.cols[0], first = g.first[0], sum_back = g.sum_back[0];
+#pragma unroll
+  for (int k = 1; k < kColsumMaxLayers; ++k)
+    if (k == l) { D0 = g.D0[k]; D1 = g.D1[k]; out = g.out[k]; cols = g.cols[k]; first = g.first[k]; sum_back = g.sum_back[k]; }
+  const int c = (x - first) * 64 + lane, K = g.K;
+  float s = 0.0f;
+  if (keeps && c < cols) {
+    float *p0 = D0 + (int64_t)b * K * cols + c;
+    const float *p1 = D1 + (int64_t)b * K * cols + c;
+    for (int k = wv; k < K; k += 32) {  // eight rows of each set in flight per step
+      float v0[8], v1[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const bool ok = k + 4 * j < K;
+        v0[j] = ok ? p0[(int64_t)(k + 4 * j) * cols] : 0.0f;
+        v1[j] = ok ? p1[(int64_t)(k + 4 * j) * cols] : 0.0f;
+      }
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const float t = v0[j] + v1[j];
+        s += t;
+        if (sum_back && k + 4 * j < K) p0[(int64_t)(k + 4 * j) * cols] = t;
+      }
+    }
   }
+  red[wv][lane] = s;
+  __syncthreads();
+  if (wv == 0 && keeps) {  // the whole wavefront
+    float val = 0.0f;
+    if (c < cols) {
+      val = g.alpha * (((red[0][lane] + red[1][lane]) + red[2][lane]) + red[3][lane]);
+      out[(int64_t)b * g.out_stride + c] = val;
+    }
+    if (g.stat_part) {  // uniform; a lane past the layer's columns holds 0, which adds nothing
+      const bool fin = isfinite(val);
+      const double a_w = (double)wave_max(fin ? fabsf(val) : 0.0f), s_w = wave_sum(fin ? (double)val : 0.0),
+                   q_w = wave_sum(fin ? (double)val * (double)val : 0.0), b_w = wave_sum(fin ? 0.0 : 1.0);
+      if (lane == 0) {
+        double *p = g.stat_part + (int64_t)b * g.stat_batch_stride + ((int64_t)g.stat_slot0 + x) * 4;
+        p[0] = a_w; p[1] = s_w; p[2] = q_w; p[3] = b_w;
+      }
+    }
+  }
+}
+
+template <int WT>
+__global__ __launch_bounds__(WT) void backward_group_kernel(GroupArgs a) {
+  touch_kernel_arguments<(int)(sizeof(GroupArgs))>();
+  constexpr int kSubs = WT / 256;
+  constexpr int kFloats = WT / 64 * 1024 > kSubs * kShortFloats ? WT / 64 * 1024 : kSubs * kShortFloats;
+  __shared__ __attribute__((aligned(16))) float lds[kFloats];
+  __shared__ double red[4 * (WT / 64)];
+  const int b = blockIdx.x, tid = threadIdx.x;
+  if (b >= a.first[a.n]) {  // (all conditions here are uniform over the workgroup)
+    const int sub = tid >> 8, at = (b - a.first[a.n]) * kSubs + sub, unit = at < a.sums ? at : a.sums - 1;
+    const int item = unit / a.sum_blocks;
+    bias_sums(a.cl, unit - item * a.sum_blocks, item, tid & 255, *reinterpret_cast<float(*)[4][64]>(lds + sub * 256), at < a.sums);
+    return;
+  }
+  int i = 0;
+#pragma unroll
+  for (int k = 1; k < kGroupMax; ++k)
+    if (k < a.n && b >= a.first[k]) i = k;
+  // the product's arguments, straight from the argument block: indexing the parameter by a run-time value would copy it
+  typedef const GroupArgs __attribute__((address_space(4))) *Block;
+  typedef const uint32_t __attribute__((address_space(4))) *Words;
+  struct Raw {
+    uint32_t w[sizeof(GemmArgs) / 4];
+  } raw;
+  Block block = (Block)__builtin_amdgcn_kernarg_segment_ptr();
+  const Words words = (Words)&block->g[i];
+#pragma unroll
+  for (size_t k = 0; k < sizeof(GemmArgs) / 4; ++k) raw.w[k] = words[k];
+  const GemmArgs g = __builtin_bit_cast(GemmArgs, raw);
+  const int waves = block->waves[i], tiles_n = block->tiles_n[i], tiles = block->tiles[i], at0 = b - block->first[i];
+  auto tile = [&](auto nw) {
+    constexpr int NW = decltype(nw)::value, kPer = WT / (64 * NW);
+    const int sub = __builtin_amdgcn_readfirstlane(tid / (64 * NW)), at = at0 * kPer + sub, all = tiles * g.batch;
+    const int unit = at < all ? at : all - 1, item = unit / tiles, t = unit - item * tiles, by = t / tiles_n;
+    small_tile<true, false, 32, NW, false>(g, t - by * tiles_n, by, item, tiles_n, tid - sub * 64 * NW,
+                                           *reinterpret_cast<float(*)[NW][32][32]>(lds + sub * NW * 1024),
+                                           *reinterpret_cast<double(*)[4 * NW]>(red + sub * 4 * NW), at < all);
+  };
+  if (waves == 0) {
+    const int sub = tid >> 8, at = at0 * kSubs + sub, all = tiles * g.batch, unit = at < all ? at : all - 1, item = unit / tiles;
+    skinny_short(g, unit - item * tiles, item, tid & 255, lds + sub * kShortFloats, red + sub * 16, at < all);
+  } else if (waves == 4) {
+    tile(std::integral_constant<int, 4>{});
+  } else if (waves == 8) {
+    if constexpr (WT >= 512) tile(std::integral_constant<int, 8>{});
+  } else {
+    if constexpr (WT >= 1024) tile(std::integral_constant<int, 16>{});
+  }
+}
+
+// whether a weight gradient (transA) may be part of such a launch
+bool gemm_groups(const GemmArgs &g) {
+  if (!g.transA || g.transB) return false;
+  if (!gemm_takes_matrix_cores(g)) return gemm_takes_skinny_short(g);
+  const Plan p = plan_of(g);
+  return p.tile_m == 32 && p.waves >= 4 && !p.far;
+}
+
+// The bias sums `cl` (of `blocks` blocks of 64 columns and nw batch items) and up to kGroupMax products that gemm_groups names.
+hipError_t launch_backward_group(const GemmArgs *g, int n, const ColsumLayers &cl, int blocks, int nw, hipStream_t st) {
+  if (n < 0 || n > kGroupMax || blocks < 1 || nw < 1) return hipErrorInvalidValue;
+  GroupArgs a{};
+  int wt = 256;
+  for (int i = 0; i < n; ++i) {
+    if (g[i].M <= 0 || g[i].N <= 0 || g[i].K <= 0 || g[i].nseg < 1 || g[i].nseg > 2 || g[i].batch < 1) return hipErrorInvalidValue;
+    a.g[i] = g[i];
+    if (!gemm_takes_matrix_cores(g[i])) {
+      a.waves[i] = 0; a.tiles_n[i] = 1; a.tiles[i] = gemm_skinny_short_slots(g[i]);
+    } else {
+      a.waves[i] = plan_of(g[i]).waves; a.tiles_n[i] = (g[i].N + 31) / 32; a.tiles[i] = gemm_tiles(g[i]);
+      if (64 * a.waves[i] > wt) wt = 64 * a.waves[i];
+    }
+  }
+  a.n = n;
+  for (int i = 0; i < n; ++i) {
+    const int per = a.waves[i] ? wt / (64 * a.waves[i]) : wt / 256;
+    a.first[i + 1] = a.first[i] + (a.tiles[i] * g[i].batch + per - 1) / per;
+  }
+  a.cl = cl; a.sum_blocks = blocks; a.sums = blocks * nw;
+  const dim3 grid((unsigned)(a.first[n] + (a.sums + wt / 256 - 1) / (wt / 256)));
+  if (wt == 256) hipLaunchKernelGGL(backward_group_kernel<256>, grid, dim3(256), 0, st, a);
+  else if (wt == 512) hipLaunchKernelGGL(backward_group_kernel<512>, grid, dim3(512), 0, st, a);
+  else hipLaunchKernelGGL(backward_group_kernel<1024>, grid, dim3(1024), 0, st, a);
+  return hipGetLastError();
 }
 
 // Validates shapes on the host (every access in the kernel is guarded by M, N, K).

@@ -60,6 +60,24 @@ struct GemmArgs {
   int32_t stat_slot0;
 };
 
+// The column sums of the deltas of every layer of a worker pass (bias gradients), part of launch_backward_group: blocks of 64
+// columns run over the layers, first[l] being layer l's first.
+constexpr int kColsumMaxLayers = 8;
+struct ColsumLayers {
+  float *D0[kColsumMaxLayers];
+  const float *D1[kColsumMaxLayers];
+  float *out[kColsumMaxLayers];
+  int cols[kColsumMaxLayers], first[kColsumMaxLayers + 1], sum_back[kColsumMaxLayers];
+  int n, K;
+  float alpha;
+  int64_t out_stride;
+  // not null: block x of batch item b also leaves the statistics of its 64 sums (Sec. 3.2 needs those of u^i) as
+  // slot stat_slot0 + x of the item's partials
+  double *stat_part;
+  int64_t stat_batch_stride;
+  int32_t stat_slot0;
+};
+
 // One sampled row of a CSR epoch, looked up ahead of the inner loop: its extent in col_idx/vals, its label and
 // its cached snapshot margin.
 struct RowPlan {
@@ -346,6 +364,9 @@ hipError_t launch_csr_vr_grad(const lpc_ctx *c, const float *w, const float *w_s
 
 // MLP instance (lpc_gemm.hip, lpc_mlp.hip)
 hipError_t launch_gemm(const GemmArgs &g, hipStream_t st);
+constexpr int kGroupProducts = 4;
+bool gemm_groups(const GemmArgs &g);
+hipError_t launch_backward_group(const GemmArgs *g, int n, const ColsumLayers &cl, int blocks, int nw, hipStream_t st);
 bool gemm_takes_matrix_cores(const GemmArgs &g);  // false: the vector-unit path (no statistic partials)
 int gemm_tiles(const GemmArgs &g);
 bool gemm_takes_skinny_short(const GemmArgs &g);
