@@ -208,6 +208,23 @@ struct Share {
   }
 };
 
+// Which tile of the launch a workgroup takes.  Workgroups go to the eight dies in turn (one in eight to each), and each die has an
+// L2 of its own: with tiles numbered along N a die would get every eighth of them, and read all of A and an eighth of B of every
+// batch item.  So a die takes an eighth of the tiles in one stretch.  (Only the speed depends on where a workgroup runs.)
+// us: 3072 x 1024 x 16384, A' 217 -> 203, a worker pass' A' 1024 x 1024 x 256, 16 items 60 -> 56; epochs of 3072-1024-1024-10 17744 -> 17052, of
+// 777-391-129-33 2543 -> 2511.  Not in the small kernels, whose launches are a tile or two per CU (13.0 -> 13.7, 4.9 -> 5.2).
+struct TilePlace {
+  int x, y;
+  int64_t z;
+};
+__device__ __forceinline__ TilePlace tile_place() {
+  const uint32_t gx = gridDim.x, gxy = gx * gridDim.y, total = gxy * gridDim.z;
+  const uint32_t at = blockIdx.x + gx * blockIdx.y + gxy * blockIdx.z, die = at & 7u, more = total & 7u;
+  const uint32_t t = die * (total >> 3) + (die < more ? die : more) + (at >> 3);
+  const uint32_t z = t / gxy, yx = t - z * gxy, y = yx / gx;
+  return {(int)(yx - y * gx), (int)y, (int64_t)z};
+}
+
 // Eight consecutive k of row / column mn of an operand, zero outside [0, MN) x [0, K).  k0 is the first k of the eight.
 //   TRANS == false: stored [mn][k] (k contiguous);  TRANS == true : stored [k][mn].
 // Plain addresses, for operands of any extent: loads outside are redirected inside and their values dropped.
@@ -657,8 +674,9 @@ __global__ __launch_bounds__(256, P == 2 ? 3 : 2) void gemm_tile_kernel(GemmArgs
   __shared__ Changes<P == 2 ? BM + TN : 1> changes;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = (wave >> 1) * 64, wn = (wave & 1) * (TN / 2);
-  const int m0 = blockIdx.y * BM, n0 = blockIdx.x * TN;
-  const int64_t bz = blockIdx.z;
+  const TilePlace at_tile = tile_place();
+  const int m0 = at_tile.y * BM, n0 = at_tile.x * TN;
+  const int64_t bz = at_tile.z;
   using MineA = Share<TA, BM, 256, P>;
   using MineB = Share<!TB, TN, 256, P>;
   const MineA ma(tid);
@@ -675,7 +693,7 @@ __global__ __launch_bounds__(256, P == 2 ? 3 : 2) void gemm_tile_kernel(GemmArgs
 
   const int nslab = (g.K + BK - 1) / BK, total = nslab * g.nseg;
   float ra[2][8], rb[NJ][8];
-  SlabWalk<TA, TB, TN, 256, P, FULL> walk(g, ma, mb, bz, m0, n0, g.rows_alike ? 0u : blockIdx.y);
+  SlabWalk<TA, TB, TN, 256, P, FULL> walk(g, ma, mb, bz, m0, n0, g.rows_alike ? 0u : (uint32_t)at_tile.y);
   walk.fetch(ra, rb);
   if constexpr (P == 2) {
     if (tid < BM + TN) changes.of[tid] = make_int2(-1, 0);
@@ -721,7 +739,7 @@ __global__ __launch_bounds__(256, P == 2 ? 3 : 2) void gemm_tile_kernel(GemmArgs
   store_tile<TA, TB, TN, FULL>(g, acc, m0, n0, bz, lane, wm, wn, fmx, ssum, ssq, sbad);
   if (g.stat_part) {
     __syncthreads();  // LDS has been read; the statistics may have it
-    tile_statistics(g, reinterpret_cast<double *>(&As[0][0]), tid, bz, (int64_t)blockIdx.y * gridDim.x + blockIdx.x,
+    tile_statistics(g, reinterpret_cast<double *>(&As[0][0]), tid, bz, (int64_t)at_tile.y * gridDim.x + at_tile.x,
                     fmx, ssum, ssq, sbad);
   }
 }
@@ -743,8 +761,9 @@ __global__ __launch_bounds__(512, 1) void gemm_pair_kernel(GemmArgs g) {
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int group = wave >> 2, w4 = wave & 3;
   const int wm = (w4 >> 1) * 64, wn = (w4 & 1) * 64;
-  const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BM;
-  const int64_t bz = blockIdx.z;
+  const TilePlace at_tile = tile_place();
+  const int m0 = at_tile.y * BM, n0 = at_tile.x * BM;
+  const int64_t bz = at_tile.z;
   using MineA = Share<TA, BM, 512, P>;
   using MineB = Share<!TB, BM, 512, P>;
   const MineA ma(tid);
@@ -761,7 +780,7 @@ __global__ __launch_bounds__(512, 1) void gemm_pair_kernel(GemmArgs g) {
 
   const int nslab = (g.K + BK - 1) / BK, total = nslab * g.nseg;
   float ra0[1][8], rb0[1][8], ra1[1][8], rb1[1][8];
-  SlabWalk<TA, TB, BM, 512, P, FULL> walk(g, ma, mb, bz, m0, n0, g.rows_alike ? 0u : blockIdx.y);
+  SlabWalk<TA, TB, BM, 512, P, FULL> walk(g, ma, mb, bz, m0, n0, g.rows_alike ? 0u : (uint32_t)at_tile.y);
   struct Operands {
     uint4 a[2][P], b[2][P];
     int changed;
@@ -856,7 +875,7 @@ __global__ __launch_bounds__(512, 1) void gemm_pair_kernel(GemmArgs g) {
   if (g.stat_part) {
     __syncthreads();
     tile_statistics<8>(g, reinterpret_cast<double *>(&smem[0][0][0][0]), tid, bz,
-                       (int64_t)blockIdx.y * gridDim.x + blockIdx.x, fmx, ssum, ssq, sbad);
+                       (int64_t)at_tile.y * gridDim.x + at_tile.x, fmx, ssum, ssq, sbad);
   }
 }
 
