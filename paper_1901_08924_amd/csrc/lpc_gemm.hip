@@ -246,6 +246,9 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const float *p, uint
 __device__ __forceinline__ float buffer_float(__amdgpu_buffer_rsrc_t rs, uint32_t offset, uint32_t scalar_offset = 0) {
   return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, offset, scalar_offset, 0));
 }
+__device__ __forceinline__ void buffer_put(__amdgpu_buffer_rsrc_t rs, uint32_t offset, uint32_t scalar_offset, float v) {
+  __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), rs, offset, scalar_offset, 0);
+}
 // eight floats at `offset`, two 16-byte loads (rows need not start on 16 bytes)
 __device__ __forceinline__ void buffer_float8(__amdgpu_buffer_rsrc_t rs, uint32_t offset, uint32_t scalar_offset,
                                               float (&r)[8]) {
@@ -328,41 +331,46 @@ __device__ __forceinline__ float plain_sum(const GemmArgs &g, int64_t bz, int ro
 // values (per thread in fp32 -- at most 64 terms --, in fp64 across threads).
 // Accumulator layout of the 32x32 MFMA: lane l holds column (l % 32); register v holds row
 // 8*(v/4) + 4*(l/32) + (v%4).
-// The options are compile-time so that the 32 stores of a thread are straight-line code: FULL = the tile lies
-// inside C (no row / column checks).  Rows are reached by pointer steps of ldc, not by a product per element.
+// The options are compile-time and no element branches, so that the 64 stores of a thread are straight-line code: FULL = the
+// tile lies inside C (no row / column checks); STAT = what is stored is finite (store_tile sees to it).  Rows are scalar
+// offsets (store_tile: less than 2^22 floats apart); what is read of C or the mask is requested sixteen at a time.  Short sums are as much epilogue as
+// sum; us, a branch per element and 64-bit lane addresses -> this, A' in a worker pass of 16 items: 3072 x 1024 x 128 98 -> 90,
+// 1024 x 1024 x 256 56 -> 50; 4096 x 1024 x 1024 B' with a mask, whose loads each waited for the store before, 54 -> 42.
 template <int TN, bool FULL, bool BIAS, bool RELU, bool MASK, bool ACC, bool STAT>
 __device__ __forceinline__ void store_tile_as(const GemmArgs &g, const floatx16 (&acc)[2][TN / 64], int m0, int n0,
                                               int64_t bz, int lane, int wm, int wn, float &fmx, float &ssum,
-                                              float &ssq, float &sbad) {
+                                              float &ssq) {
   constexpr int NJ = TN / 64;
-  const int64_t ldc = g.ldc;
+  const uint32_t row4 = (uint32_t)g.ldc * 4u;
+  const int rows = g.M - m0 - wm - 4 * (lane >> 5), cols = g.N - n0 - wn - (lane & 31);  // this lane's, from its first on
+  const uint32_t mine = (uint32_t)(4 * (lane >> 5)) * row4 + (uint32_t)(lane & 31) * 4u;
+  const int64_t tile0 = bz * g.strideC + (int64_t)(m0 + wm) * g.ldc + n0 + wn;
+  const __amdgpu_buffer_rsrc_t c = buffer_of(g.C + tile0, 0x7FFFFFFFu);
+  const __amdgpu_buffer_rsrc_t mask = buffer_of(MASK ? g.relu_mask + tile0 : g.C + tile0, 0x7FFFFFFFu);
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
-      const int col = n0 + wn + 32 * j + (lane & 31);
-      if (!FULL && col >= g.N) continue;
-      const float bias = BIAS ? g.bias[bz * g.strideBias + col] : 0.0f;
-      const int row0 = m0 + wm + 32 * i + 4 * (lane >> 5);
-      const int64_t off0 = bz * g.strideC + (int64_t)row0 * ldc + col;
-      float *crow = g.C + off0;
-      const float *mrow = MASK ? g.relu_mask + off0 : nullptr;
+      const bool col_in = FULL || 32 * j < cols;
+      const float bias = BIAS && col_in ? g.bias[bz * g.strideBias + n0 + wn + 32 * j + (lane & 31)] : 0.0f;
+      auto row_of = [&](int v) { return 32 * i + 8 * (v >> 2) + (v & 3); };
+      auto in = [&](int v) { return FULL || (col_in && row_of(v) < rows); };
+      auto at = [&](int v) { return (uint32_t)row_of(v) * row4 + 128u * j; };
+      float there[MASK || ACC ? 16 : 1];  // requested together, ahead of the stores
+      if constexpr (MASK || ACC) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) there[v] = in(v) ? buffer_float(MASK ? mask : c, mine, at(v)) : 0.0f;
+      }
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
-        const int dr = 8 * (v >> 2) + (v & 3);
-        if (!FULL && row0 + dr >= g.M) continue;
-        float *cp = crow + dr * ldc;
         float val = g.alpha * acc[i][j][v] + bias;
         if (RELU) val = relu(val);
-        if (MASK) val = mrow[dr * ldc] > 0.0f ? val : 0.0f;
-        if (ACC) val += *cp;
-        *cp = val;
+        if constexpr (MASK) val = there[v] > 0.0f ? val : 0.0f;
+        if constexpr (ACC) val += there[v];
+        if (in(v)) buffer_put(c, mine, at(v), val);
         if (STAT) {
-          if (isfinite(val)) {
-            fmx = fmaxf(fmx, fabsf(val)); ssum += val; ssq = fmaf(val, val, ssq);
-          } else {
-            sbad += 1.0f;
-          }
+          const float x = in(v) ? val : 0.0f;
+          fmx = fmaxf(fmx, fabsf(x)); ssum += x; ssq = fmaf(x, x, ssq);
         }
       }
     }
@@ -386,17 +394,25 @@ __device__ __forceinline__ void store_tile(const GemmArgs &g, const floatx16 (&a
     for (int j = 0; j < TN / 64; ++j)
 #pragma unroll
       for (int v = 0; v < 16; ++v) odd = fmaf(acc[i][j][v], 0.0f, odd);  // NaN where one is, or an infinity
-  if (__ballot(odd != odd) == 0ull) {
-    if (bias && relu_on && !mask && !accu && !stat)          // forward layer
-      return store_tile_as<TN, FULL, true, true, false, false, false>(g, acc, m0, n0, bz, lane, wm, wn, fmx, ssum, ssq, sbad);
-    if (!bias && !relu_on && mask && !accu && !stat)    // data gradient
-      return store_tile_as<TN, FULL, false, false, true, false, false>(g, acc, m0, n0, bz, lane, wm, wn, fmx, ssum, ssq, sbad);
-    if (!bias && !relu_on && !mask && !accu && stat)    // a worker's weight gradient, with its statistics
-      return store_tile_as<TN, FULL, false, false, false, false, true>(g, acc, m0, n0, bz, lane, wm, wn, fmx, ssum, ssq, sbad);
-    if (!bias && !relu_on && !mask && !stat && accu)    // snapshot weight gradient, accumulating
-      return store_tile_as<TN, FULL, false, false, false, true, false>(g, acc, m0, n0, bz, lane, wm, wn, fmx, ssum, ssq, sbad);
-    if (!bias && !relu_on && !mask && !stat)            // snapshot weight gradient, first chunk or block
-      return store_tile_as<TN, FULL, false, false, false, false, false>(g, acc, m0, n0, bz, lane, wm, wn, fmx, ssum, ssq, sbad);
+  // (|alpha| <= 1: what is finite stays it)
+  if (__ballot(odd != odd) == 0ull && g.ldc < (1 << 22) && (!stat || fabsf(g.alpha) <= 1.0f)) {
+    auto as = [&](auto inside) {
+      constexpr bool kIn = FULL || decltype(inside)::value;
+      if (bias && relu_on && !mask && !accu && !stat)          // forward layer
+        store_tile_as<TN, kIn, true, true, false, false, false>(g, acc, m0, n0, bz, lane, wm, wn, fmx, ssum, ssq);
+      else if (!bias && !relu_on && mask && !accu && !stat)    // data gradient
+        store_tile_as<TN, kIn, false, false, true, false, false>(g, acc, m0, n0, bz, lane, wm, wn, fmx, ssum, ssq);
+      else if (!bias && !relu_on && !mask && !accu && stat)    // a worker's weight gradient, with its statistics
+        store_tile_as<TN, kIn, false, false, false, false, true>(g, acc, m0, n0, bz, lane, wm, wn, fmx, ssum, ssq);
+      else if (!bias && !relu_on && !mask && !stat && accu)    // snapshot weight gradient, accumulating
+        store_tile_as<TN, kIn, false, false, false, true, false>(g, acc, m0, n0, bz, lane, wm, wn, fmx, ssum, ssq);
+      else if (!bias && !relu_on && !mask && !stat)            // snapshot weight gradient, first chunk or block
+        store_tile_as<TN, kIn, false, false, false, false, false>(g, acc, m0, n0, bz, lane, wm, wn, fmx, ssum, ssq);
+      else
+        return false;
+      return true;
+    };
+    if (FULL || (m0 + BM <= g.M && n0 + TN <= g.N) ? as(std::true_type{}) : as(std::false_type{})) return;
   }
   // general: every option decided per element
   constexpr int NJ = TN / 64;
