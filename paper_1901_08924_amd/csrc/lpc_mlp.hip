@@ -98,11 +98,14 @@ struct LastArgs {
   double *row_loss;     // set 0 only, or nullptr
 };
 
-template <int R>
+// Two columns of W are requested at a time, sixteen-byte reads without a branch per lane; WHOLE: K is a multiple of 256, so every lane
+// of a read has activations (otherwise those past K take zeros: a weight there may be an infinity).
+// Bound by the trips of its loads and by LDS; 2 x 2048 rows of K = 1024, C = 10: 21.2 -> 14.7 us (a branch, and a wait, for each read before).
+template <int R, bool WHOLE>
 __global__ __launch_bounds__(64 * kLastRows / R) void last_layer_kernel(LastArgs g) {
   touch_kernel_arguments<(int)(sizeof(LastArgs))>();
   constexpr int kThreadsLast = 64 * kLastRows / R;
-  extern __shared__ float Wt[];  // [C][K + 4], then bias [C]
+  extern __shared__ __attribute__((aligned(16))) float Wt[];  // [C][K + 4], then bias [C]
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int set = blockIdx.y;
   const int pitch = g.K + 4;
@@ -122,48 +125,62 @@ __global__ __launch_bounds__(64 * kLastRows / R) void last_layer_kernel(LastArgs
       av[r][q] = make_float4(0.f, 0.f, 0.f, 0.f);
       if (row0 + r < g.rows && k < g.K) av[r][q] = *reinterpret_cast<const float4 *>(a + (int64_t)(row0 + r) * g.lda + k);
     }
+  int label[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) label[r] = (int)g.labels[row0 + r < g.rows ? row0 + r : g.rows - 1];
   // W goes to LDS while the activations are on their way
   const uint32_t inv_c = (uint32_t)((0x100000000ull + (uint32_t)g.C - 1) / (uint32_t)g.C);
   constexpr int kStage = 20;  // elements in flight per thread
-  for (int i0 = tid; i0 < g.K * g.C; i0 += kStage * kThreadsLast) {
+  const int most = g.K * g.C - 1;
+  for (int i0 = tid; i0 <= most; i0 += kStage * kThreadsLast) {  // past the end: the last element again, to its own place
     float t[kStage];
+    auto at = [&](int j) { return i0 + j * kThreadsLast < most ? i0 + j * kThreadsLast : most; };
 #pragma unroll
-    for (int j = 0; j < kStage; ++j) t[j] = i0 + j * kThreadsLast < g.K * g.C ? W[i0 + j * kThreadsLast] : 0.0f;
+    for (int j = 0; j < kStage; ++j) t[j] = W[(uint32_t)at(j)];
 #pragma unroll
     for (int j = 0; j < kStage; ++j) {
       // i / C by a multiply: exact for i < 2^16 and C <= 16 with the rounded-up reciprocal 2^32 / C
-      const int i = i0 + j * kThreadsLast, k = (int)__umulhi((uint32_t)i, inv_c), c = i - k * g.C;
-      if (i < g.K * g.C) Wt[c * pitch + k] = t[j];
+      const int i = at(j), k = (int)__umulhi((uint32_t)i, inv_c), c = i - k * g.C;
+      Wt[c * pitch + k] = t[j];
     }
   }
   if (tid < g.C) bias[tid] = W[g.bias_off + tid];
   __syncthreads();
+  const int quads = g.K / 4;
+  auto weights = [&](int c, float4 (&w)[4]) {  // of class c, at this lane's activations
+    const float4 *row = reinterpret_cast<const float4 *>(Wt) + c * (quads + 1);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      w[q] = make_float4(0.f, 0.f, 0.f, 0.f);
+      const int k4 = 64 * q + lane;
+      if (64 * q < quads) {  // uniform
+        const float4 t = row[WHOLE || k4 < quads ? k4 : quads - 1];
+        if (WHOLE || k4 < quads) w[q] = t;
+      }
+    }
+  };
   // logits: one read of a column of W serves the wavefront's rows; lane (16j + c) keeps z[c] of each row
   float z[R];
 #pragma unroll
   for (int r = 0; r < R; ++r) z[r] = -INFINITY;
+  for (int c = 0; c < g.C; c += 2) {
+    const int c1 = c + 1 < g.C ? c + 1 : c;
+    float4 w0[4], w1[4];
+    weights(c, w0);
+    weights(c1, w1);
+    auto dot = [&](int r, const float4 (&w)[4]) {
+      float t = 0.0f;
 #pragma unroll
-  for (int c = 0; c < kLastMaxC; ++c) {
-    if (c < g.C) {  // uniform
-      float s[R];
+      for (int q = 0; q < 4; ++q)
+        t = fmaf(av[r][q].x, w[q].x, fmaf(av[r][q].y, w[q].y, fmaf(av[r][q].z, w[q].z, fmaf(av[r][q].w, w[q].w, t))));
+      return t;
+    };
+    const float b0 = bias[c], b1 = bias[c1];
 #pragma unroll
-      for (int r = 0; r < R; ++r) s[r] = 0.0f;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int k = 256 * q + 4 * lane;
-        if (k < g.K) {
-          const float4 w4 = *reinterpret_cast<const float4 *>(&Wt[c * pitch + k]);
-#pragma unroll
-          for (int r = 0; r < R; ++r)
-            s[r] = fmaf(av[r][q].x, w4.x, fmaf(av[r][q].y, w4.y, fmaf(av[r][q].z, w4.z, fmaf(av[r][q].w, w4.w, s[r]))));
-        }
-      }
-      const float bc = bias[c];
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        const float t = wave_sum(s[r]) + bc;
-        z[r] = lc == c ? t : z[r];
-      }
+    for (int r = 0; r < R; ++r) {
+      const float t0 = wave_sum(dot(r, w0)) + b0, t1 = wave_sum(dot(r, w1)) + b1;
+      z[r] = lc == c1 ? t1 : z[r];
+      z[r] = lc == c ? t0 : z[r];
     }
   }
   // softmax cross-entropy inside each row of 16 lanes (lanes c >= C hold -inf and contribute exp = 0)
@@ -174,40 +191,46 @@ __global__ __launch_bounds__(64 * kLastRows / R) void last_layer_kernel(LastArgs
     const float mx = row16_max(z[r]);
     const float e = lc < g.C ? expf(z[r] - mx) : 0.0f;
     const float sum = row16_sum(e);
-    const int label = (int)g.labels[row];
-    dl[r] = sign * (e * (1.0f / sum) - (lc == label ? 1.0f : 0.0f));
+    dl[r] = sign * (e * (1.0f / sum) - (lc == label[r] ? 1.0f : 0.0f));
     if (row0 + r < g.rows) {
       if (lane < g.C) g.delta[(int64_t)set * g.d_set_stride + (int64_t)row * g.C + lane] = dl[r];
       if (set == 0 && g.row_loss) {
-        const float zl = row16_sum(lc == label ? z[r] : 0.0f);  // uniform branch: whole rows of lanes are active
+        const float zl = row16_sum(lc == label[r] ? z[r] : 0.0f);  // uniform branch: whole rows of lanes are active
         if (lane == 0) g.row_loss[row] = (double)(logf(sum) + mx - zl);
       }
     }
   }
   if (g.delta_prev) {
+    float4 o[R][4];
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) o[r][q] = make_float4(0.f, 0.f, 0.f, 0.f);
+    auto add = [&](int c, const float4 (&w)[4]) {
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const float dc = read_lane(dl[r], c);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          o[r][q].x = fmaf(dc, w[q].x, o[r][q].x); o[r][q].y = fmaf(dc, w[q].y, o[r][q].y);
+          o[r][q].z = fmaf(dc, w[q].z, o[r][q].z); o[r][q].w = fmaf(dc, w[q].w, o[r][q].w);
+        }
+      }
+    };
+    for (int c = 0; c < g.C; c += 2) {
+      float4 w0[4], w1[4];
+      weights(c, w0);
+      weights(c + 1 < g.C ? c + 1 : c, w1);
+      add(c, w0);
+      if (c + 1 < g.C) add(c + 1, w1);
+    }
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const int k = 256 * q + 4 * lane;
-      float4 o[R];
-#pragma unroll
-      for (int r = 0; r < R; ++r) o[r] = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-      for (int c = 0; c < kLastMaxC; ++c) {
-        if (c < g.C) {
-          float4 w4 = make_float4(0.f, 0.f, 0.f, 0.f);
-          if (k < g.K) w4 = *reinterpret_cast<const float4 *>(&Wt[c * pitch + k]);
-#pragma unroll
-          for (int r = 0; r < R; ++r) {
-            const float dc = read_lane(dl[r], c);
-            o[r].x = fmaf(dc, w4.x, o[r].x); o[r].y = fmaf(dc, w4.y, o[r].y);
-            o[r].z = fmaf(dc, w4.z, o[r].z); o[r].w = fmaf(dc, w4.w, o[r].w);
-          }
-        }
-      }
 #pragma unroll
       for (int r = 0; r < R; ++r) {
         if (row0 + r >= g.rows || k >= g.K) continue;
-        float4 t = o[r];
+        float4 t = o[r][q];
         t.x = av[r][q].x > 0.0f ? t.x : 0.0f; t.y = av[r][q].y > 0.0f ? t.y : 0.0f;
         t.z = av[r][q].z > 0.0f ? t.z : 0.0f; t.w = av[r][q].w > 0.0f ? t.w : 0.0f;
         float *dp = g.delta_prev + (int64_t)set * g.dp_set_stride + (int64_t)(row0 + r) * g.K;
@@ -377,10 +400,10 @@ hipError_t backward_data(const Net &nn, const float *W, int64_t wstride, int nse
     g.delta_prev = l >= 1 ? nn.del(l, 0) : nullptr; g.dp_set_stride = nn.rows_cap * nn.dims[l];
     g.row_loss = row_loss;
     const size_t lds = ((size_t)classes * (g.K + 4) + classes) * sizeof(float);
-    constexpr int kRowsPerWave = 2;  // eight wavefronts per workgroup: 21.7 us per worker pass; four rows each 24.2, one row 29.6
-    hipLaunchKernelGGL(last_layer_kernel<kRowsPerWave>,
-                       dim3((unsigned)((rows + kLastRows - 1) / kLastRows), (unsigned)nsets),
-                       dim3(64 * kLastRows / kRowsPerWave), lds, st, g);
+    constexpr int kRowsPerWave = 2;  // eight wavefronts per workgroup; four rows each 1.12 times as long, one row 1.36 times
+    const dim3 grid((unsigned)((rows + kLastRows - 1) / kLastRows), (unsigned)nsets), threads(64 * kLastRows / kRowsPerWave);
+    if (g.K % 256 == 0) hipLaunchKernelGGL((last_layer_kernel<kRowsPerWave, true>), grid, threads, lds, st, g);
+    else hipLaunchKernelGGL((last_layer_kernel<kRowsPerWave, false>), grid, threads, lds, st, g);
     first = nn.L - 2;
   } else {
     hipLaunchKernelGGL(softmax_delta_kernel, dim3((unsigned)((rows + 3) / 4), (unsigned)nsets), dim3(256), 0, st,
