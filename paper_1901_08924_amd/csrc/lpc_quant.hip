@@ -426,9 +426,10 @@ __global__ __launch_bounds__(kThreads) void quantize_kernel(const float *__restr
 // Quantize + pack for the bit widths whose words hold whole groups of four codes (B = 2, 4, 8): one packed word per
 // thread.  A thread reads the 32/B consecutive coordinates of its word straight from memory (8/B loads of 16 bytes),
 // draws their 8/B Philox blocks and stores the word; a wavefront's stores are 256 contiguous bytes.  No LDS and no
-// barrier, so the registers alone bound the number of resident wavefronts.  The pass is bound by the vector unit:
-// one generator block (18 64-bit multiply-adds, 35 exclusive-ors) and about 45 other instructions per four
-// coordinates; with neither loads nor stores it runs 6 % faster.  Measured and dropped: workgroups that walk the
+// barrier, so the registers alone bound the number of resident wavefronts.  Bound by HBM (16 vectors of 4.2 M coordinates, 303 MB:
+// 44.9 us = 6.7 TB/s) and by the vector unit about alike: one generator block (18 64-bit multiply-adds, 35 exclusive-ors) and
+// about 45 other instructions per four coordinates; with neither loads nor stores it runs 6 % faster, with a fifth fewer
+// instructions (codes by integer additions in 2^-24ths, two words a thread) 2 %, and a whole exchange not at all.  Measured and dropped: workgroups that walk the
 // message with a grid stride and request their next word's coordinates ahead (8 to 10 % slower than a thread per
 // word: fresh workgroups cost less than the loop).  Codes, draws and bit layout are those of quantize_kernel.
 // grid = (words of a message / kThreads, N workers).
